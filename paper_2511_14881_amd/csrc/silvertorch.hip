@@ -193,6 +193,66 @@ int device_setup(int device)
     return ST_OK;
 }
 
+// Device memory of freed indexes.  A program that publishes builds a new index and frees the one it
+// replaces, over and over; handing hundreds of megabytes back to the driver and fetching them again
+// costs 0.3 ms a time, and 10 ms and more once the driver has no cleared pages left in stock.  The
+// block of the most recently freed index is therefore kept, one per device and at most kIndexKeepBytes,
+// for the next build of the same size.  It is given back when an index of another size is built or freed,
+// or when an allocation fails.  st_bloom_free has waited for the device before a block is kept (as hipFree
+// would have), so whoever takes it, on whatever stream, finds no work in flight on it.
+constexpr int64_t kIndexKeepBytes = 4ll << 30;
+struct KeptBlock {
+    void* ptr = nullptr;
+    int64_t bytes = 0;
+};
+KeptBlock g_kept[kMaxDevices];
+std::mutex g_kept_mu;
+
+KeptBlock take_kept(int device)
+{
+    std::lock_guard<std::mutex> lock(g_kept_mu);
+    KeptBlock k = g_kept[device];
+    g_kept[device] = KeptBlock{};
+    return k;
+}
+
+int index_alloc(int device, int64_t bytes, void** out)
+{
+    const KeptBlock k = take_kept(device);
+    if (k.ptr && k.bytes == bytes) {
+        *out = k.ptr;
+        return ST_OK;
+    }
+    if (k.ptr) ST_HIP(hipFree(k.ptr));
+    ST_HIP(hipMalloc(out, (size_t)bytes));
+    return ST_OK;
+}
+
+int index_free(int device, void* ptr, int64_t bytes)
+{
+    if (bytes > kIndexKeepBytes) {
+        ST_HIP(hipFree(ptr));
+        return ST_OK;
+    }
+    int current = 0;
+    ST_HIP(hipGetDevice(&current));
+    if (current != device) ST_HIP(hipSetDevice(device));
+    const hipError_t e = hipDeviceSynchronize();
+    if (current != device) ST_HIP(hipSetDevice(current));
+    if (e != hipSuccess) {
+        (void)hipFree(ptr);
+        ST_HIP(e);
+    }
+    KeptBlock old;
+    {
+        std::lock_guard<std::mutex> lock(g_kept_mu);
+        old = g_kept[device];
+        g_kept[device] = KeptBlock{ptr, bytes};
+    }
+    if (old.ptr) ST_HIP(hipFree(old.ptr));
+    return ST_OK;
+}
+
 bool is_device_pointer(const void* p)
 {
     hipPointerAttribute_t attr;
@@ -620,7 +680,10 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
         ST_HIP(hipGetDevice(&b->device));
         const int rc_setup = device_setup(b->device);
         if (rc_setup != ST_OK) return rc_setup;
-        if (b->bytes > 0) ST_HIP(hipMalloc((void**)&b->dev, (size_t)b->bytes));
+        if (b->bytes > 0) {
+            const int rc_mem = index_alloc(b->device, b->bytes, (void**)&b->dev);
+            if (rc_mem != ST_OK) return rc_mem;
+        }
         if (n_items == 0) return ST_OK;
         const int64_t* off = feat_offsets;
         const uint64_t* ids = feat_ids;
@@ -676,9 +739,9 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
 int st_bloom_free(st_bloom* bloom)
 {
     if (!bloom) return ST_OK;
-    if (bloom->dev) ST_HIP(hipFree(bloom->dev));
+    const int rc = bloom->dev ? index_free(bloom->device, bloom->dev, bloom->bytes) : (int)ST_OK;
     delete bloom;
-    return ST_OK;
+    return rc;
 }
 
 int64_t st_bloom_bytes(const st_bloom* bloom)
