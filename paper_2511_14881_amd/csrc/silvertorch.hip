@@ -760,9 +760,17 @@ int st_bloom_export_signatures(const st_bloom* bloom, uint64_t* dev_out, void* h
 {
     if (!bloom || !dev_out) return fail(ST_EINVAL, "null argument");
     if (bloom->n_items == 0) return ST_OK;
-    const unsigned grid = (unsigned)((bloom->n_items + 255) / 256);
-    hipLaunchKernelGGL(st::bloom_export_kernel, dim3(grid), dim3(256), 0, (hipStream_t)hip_stream,
-                       bloom->dev, bloom->n_items, bloom->m_bits, dev_out);
+    const int tiles_per = st::export_tiles_per(bloom->m_bits);
+    const int lds = st::export_lds_bytes(bloom->m_bits);
+    static std::atomic<bool> lds_set{false};  // (setting the attribute twice is harmless)
+    if (!lds_set.load(std::memory_order_acquire)) {
+        ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&st::bloom_export_kernel),
+                                   hipFuncAttributeMaxDynamicSharedMemorySize, st::export_lds_bytes(64)));  // (the largest)
+        lds_set.store(true, std::memory_order_release);
+    }
+    const unsigned grid = (unsigned)((bloom->n_tiles + tiles_per - 1) / tiles_per);
+    hipLaunchKernelGGL(st::bloom_export_kernel, dim3(grid), dim3(st::kExportThreads), lds, (hipStream_t)hip_stream,
+                       bloom->dev, bloom->n_items, bloom->m_bits, tiles_per, dev_out);
     ST_HIP(hipGetLastError());
     return ST_OK;
 }

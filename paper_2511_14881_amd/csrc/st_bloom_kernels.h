@@ -6,6 +6,8 @@
 // One row segment of a tile is 16 words = 128 bytes; a filter that sets r signature bits
 // touches r such lines per tile.
 #pragma once
+#include <type_traits>
+
 #include "st_device.h"
 
 namespace st {
@@ -54,25 +56,100 @@ __global__ __launch_bounds__(kBuildThreads) void bloom_build_kernel(const int64_
     }
 }
 
-// Item-major signatures for parity checks: out[item][word j] gathers bit `row` from 64 rows.
-__global__ __launch_bounds__(256) void bloom_export_kernel(const uint64_t* __restrict__ bloom,
-                                                           int64_t n_items, int32_t m_bits,
-                                                           uint64_t* __restrict__ out)
+// In-register transpose of a 32 x 32 bit matrix: bit j of a[i] and bit i of a[j] change places.
+// (The steps at distance 16 and 8 exchange whole bytes: one byte permute per word.)
+__device__ inline void transpose32(uint32_t (&a)[32])
 {
-    const int64_t item = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (item >= n_items) return;
-    const int64_t tile = item >> 10;
-    const int w = (int)((item & 1023) >> 6);
-    const int bit = (int)(item & 63);
-    const uint64_t* base = bloom + (tile * (int64_t)m_bits) * kTileWords + w;
-    const int n_slabs = (m_bits + 63) >> 6;
-    for (int slab = 0; slab < n_slabs; ++slab) {
-        uint64_t sig = 0;
-        for (int b = 0; b < 64; ++b) {
-            const int row = slab * 64 + b;
-            if (row < m_bits) sig |= ((base[(int64_t)row * kTileWords] >> bit) & 1ULL) << b;
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+        const uint32_t lo = a[k], hi = a[k + 16];
+        a[k] = __builtin_amdgcn_perm(hi, lo, 0x05040100u);
+        a[k + 16] = __builtin_amdgcn_perm(hi, lo, 0x07060302u);
+    }
+#pragma unroll
+    for (int k0 = 0; k0 < 32; k0 += 16)
+#pragma unroll
+        for (int k = k0; k < k0 + 8; ++k) {
+            const uint32_t lo = a[k], hi = a[k + 8];
+            a[k] = __builtin_amdgcn_perm(hi, lo, 0x06020400u);
+            a[k + 8] = __builtin_amdgcn_perm(hi, lo, 0x07030501u);
         }
-        out[item * n_slabs + slab] = sig;
+    auto step = [&](auto dist, uint32_t mask) {
+        constexpr int j = decltype(dist)::value;
+#pragma unroll
+        for (int k = 0; k < 32; ++k)
+            if ((k & j) == 0) {
+                const uint32_t t = ((a[k] >> j) ^ a[k + j]) & mask;
+                a[k + j] ^= t;
+                a[k] ^= t << j;
+            }
+    };
+    step(std::integral_constant<int, 4>{}, 0x0F0F0F0Fu);
+    step(std::integral_constant<int, 2>{}, 0x33333333u);
+    step(std::integral_constant<int, 1>{}, 0x55555555u);
+}
+
+// Item-major signatures: out[item][word j] gathers bit `item` of 64 rows, i.e. every tile is
+// transposed.  A thread takes a block of 32 rows x 32 items: it reads its 32-bit column of the 32
+// rows (32 neighbouring lanes cover a row's whole 128-byte line), transposes the block in registers
+// and leaves 32 row-bits per item in LDS, from where the items' words go out in order.  A workgroup
+// has 16 row blocks: 512 rows of one tile, or all rows of `tiles_per` tiles where a tile has fewer.
+// Bound by memory (the index read once, the signatures written once).  One thread per item, gathering
+// a bit from every row, took 4.77 ms for 10 M items x 512 bits (each word read 64 times, 64 shifts and
+// masks per output word); the transpose takes 0.24 ms, 5.3 TB/s.
+constexpr int kExportThreads = 512;
+constexpr int kExportBlocks = kExportThreads / 32;  // 32-row blocks of a workgroup
+// LDS words of one tile with `blocks` row blocks: the items of neighbouring lanes lie 32 * blocks words
+// apart, four words of padding per 32 items spread them over the banks
+constexpr int export_tile_words(int blocks) { return kTileItems * blocks + 32 * 4; }
+inline int export_tiles_per(int m_bits)
+{
+    const int blocks = 2 * ((m_bits + 63) / 64);
+    return blocks >= kExportBlocks ? 1 : kExportBlocks / blocks;
+}
+inline int export_lds_bytes(int m_bits)
+{
+    const int blocks = 2 * ((m_bits + 63) / 64);
+    return 4 * export_tiles_per(m_bits) * export_tile_words(blocks < kExportBlocks ? blocks : kExportBlocks);
+}
+
+__global__ __launch_bounds__(kExportThreads) void bloom_export_kernel(const uint64_t* __restrict__ bloom,
+                                                                      int64_t n_items, int32_t m_bits,
+                                                                      int32_t tiles_per, uint64_t* __restrict__ out)
+{
+    extern __shared__ __attribute__((aligned(16))) uint32_t s_out[];
+    const int tid = threadIdx.x;
+    const int n_slabs = (m_bits + 63) >> 6, all_blocks = 2 * n_slabs;
+    const int64_t tile0 = (int64_t)blockIdx.x * tiles_per;
+    const uint32_t* rows = reinterpret_cast<const uint32_t*>(bloom);
+    for (int c0 = 0; c0 < all_blocks; c0 += kExportBlocks) {
+        const int blocks = min(kExportBlocks, all_blocks - c0);  // (an even number)
+        const int unit = tid >> 5, w32 = tid & 31;
+        const int tl = unit / blocks, blk = unit - tl * blocks;
+        const int64_t item0 = (tile0 + tl) * kTileItems;
+        if (tl < tiles_per && item0 < n_items) {
+            const int row0 = (c0 + blk) * 32;
+            const uint32_t* src = rows + ((tile0 + tl) * (int64_t)m_bits + row0) * 32 + w32;
+            uint32_t a[32];
+#pragma unroll
+            for (int j = 0; j < 32; ++j) a[j] = row0 + j < m_bits ? src[j * 32] : 0u;
+            transpose32(a);
+            uint32_t* dst = s_out + tl * export_tile_words(blocks) + w32 * (32 * blocks + 4) + blk;
+#pragma unroll
+            for (int i = 0; i < 32; ++i) dst[i * blocks] = a[i];
+        }
+        __syncthreads();
+        const int words = blocks >> 1;  // 64-bit words per item in this pass
+        for (int t = 0; t < tiles_per; ++t) {
+            const int64_t first = (tile0 + t) * kTileItems;
+            const int n = first >= n_items ? 0 : (n_items - first < kTileItems ? (int)(n_items - first) : kTileItems);
+            for (int e = tid; e < n * words; e += kExportThreads) {
+                const int it = e / words, w = e - it * words;
+                const uint32_t* src = s_out + t * export_tile_words(blocks) + it * blocks + (it >> 5) * 4 + 2 * w;
+                out[(first + it) * n_slabs + (c0 >> 1) + w] = *reinterpret_cast<const uint64_t*>(src);
+            }
+        }
+        __syncthreads();
     }
 }
 
