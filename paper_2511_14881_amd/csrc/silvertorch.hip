@@ -708,16 +708,18 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
             ids = d_ids;
         }
         const size_t lds = (size_t)std::min<int32_t>(m_bits, st::kBuildSlabRows) * st::kTileWords * 8;
-        static std::atomic<bool> lds_set{false};
-        if (!lds_set.load(std::memory_order_acquire)) {
-            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&st::bloom_build_kernel),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, st::kBuildSlabRows * st::kTileWords * 8));
-            lds_set.store(true, std::memory_order_release);
+        const bool pow2 = (m_bits & (m_bits - 1)) == 0;
+        const auto kernel = pow2 ? &st::bloom_build_kernel<true> : &st::bloom_build_kernel<false>;
+        static std::atomic<bool> lds_set[2] = {{false}, {false}};  // (setting the attribute twice is harmless)
+        if (!lds_set[pow2].load(std::memory_order_acquire)) {
+            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       st::kBuildSlabRows * st::kTileWords * 8));
+            lds_set[pow2].store(true, std::memory_order_release);
         }
         {
             TimedLaunch t(0, stream);
-            hipLaunchKernelGGL(st::bloom_build_kernel, dim3((unsigned)b->n_tiles), dim3(st::kBuildThreads), lds, stream, off,
-                               ids, n_items, m_bits, k_hashes, b->dev);
+            hipLaunchKernelGGL(kernel, dim3((unsigned)b->n_tiles), dim3(st::kBuildThreads), lds, stream, off, ids, n_items,
+                               st::build_mod(m_bits), k_hashes, b->dev);
         }
         ST_HIP(hipGetLastError());
         ST_HIP(hipStreamSynchronize(stream));

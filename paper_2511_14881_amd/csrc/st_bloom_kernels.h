@@ -12,46 +12,98 @@
 
 namespace st {
 
-// One workgroup per 1024-item tile.  The tile's block of the index -- m rows of 128 bytes -- is
-// assembled in LDS (in slabs of kBuildSlabRows rows where m is larger): every thread hashes the
-// ids of its items once per slab (k positions each, Sec. 4.1), sets the item's bit in the rows the
-// positions name with LDS atomic ORs, and the finished rows go out as one contiguous, coalesced
+// Position of a hash modulo m <= 65536, for the build kernel's inner loop (the same value as
+// bloom_bit).  A power of two needs the low bits of the hash alone, so the second product of
+// splitmix64 is formed only as far as they reach; other sizes reduce the two halves of the hash with a
+// multiply-high by floor(2^32 / m), which is at most one short of the quotient.
+struct BuildMod {
+    uint32_t m, magic, two32;  // magic = floor(2^32 / m), two32 = 2^32 mod m
+};
+inline BuildMod build_mod(int32_t m_bits)
+{
+    BuildMod b;
+    b.m = (uint32_t)m_bits;
+    b.magic = m_bits > 1 ? (uint32_t)((1ULL << 32) / (uint64_t)m_bits) : 0u;
+    b.two32 = (uint32_t)((1ULL << 32) % (uint64_t)m_bits);
+    return b;
+}
+template <bool POW2>
+__device__ inline uint32_t build_pos(uint64_t x, const BuildMod& b)
+{
+    uint64_t z = x + 0x9E3779B97F4A7C15ULL;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ULL;
+    z ^= z >> 27;
+    constexpr uint32_t kLo = 0x133111EBu, kHi = 0x94D049BBu;
+    if (POW2) {
+        // bits 0 .. 15 of w ^ (w >> 31), w = z * (kHi:kLo): the cross products count from bit 32 on, and
+        // their low 15 bits depend on the low bits of the factors only (24-bit multiplies)
+        const uint64_t lo = (uint64_t)(uint32_t)z * kLo;
+        const uint32_t hi = (uint32_t)(lo >> 32) + __umul24((uint32_t)z & 0xFFFFFFu, kHi & 0xFFFFFFu) +
+                            __umul24((uint32_t)(z >> 32) & 0xFFFFFFu, kLo & 0xFFFFFFu);
+        return ((uint32_t)lo ^ (((uint32_t)lo >> 31) | (hi << 1))) & (b.m - 1u);
+    }
+    z *= ((uint64_t)kHi << 32) | kLo;
+    z ^= z >> 31;
+    auto mod = [&](uint32_t v) {
+        const uint32_t r = v - __umulhi(v, b.magic) * b.m;
+        return r >= b.m ? r - b.m : r;
+    };
+    return mod(mod((uint32_t)(z >> 32)) * b.two32 + mod((uint32_t)z));  // < m * m <= 2^32
+}
+
+// One workgroup per 1024-item tile, one item per thread.  The tile's block of the index -- m rows of
+// 128 bytes -- is assembled in LDS (in slabs of kBuildSlabRows rows where m is larger): every thread
+// hashes the ids of its item once per slab (k positions each, Sec. 4.1), sets the item's bit in the rows
+// the positions name with LDS atomic ORs, and the finished rows go out as one contiguous, coalesced
 // copy.  Hash work is therefore independent of m up to the slab size, and HBM sees the feature
 // lists once and the index once.
-constexpr int kBuildThreads = 256;
+constexpr int kBuildThreads = kTileItems;
 constexpr int kBuildSlabRows = 1024;  // 128 KB of LDS
+constexpr int kBuildIds = 8;          // ids of a list in flight per thread
 
-__global__ __launch_bounds__(kBuildThreads) void bloom_build_kernel(const int64_t* __restrict__ feat_offsets,
+// Word w32 (32 items) of LDS row r lies at w32 ^ (r & 31): the 64 lanes of a wavefront hold two words'
+// worth of items, and without the swizzle their updates of any rows would meet in two to four banks.
+__device__ inline int build_word(int r, int w32) { return r * 32 + (w32 ^ (r & 31)); }
+
+template <bool POW2>
+__global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int64_t* __restrict__ feat_offsets,
                                                                     const uint64_t* __restrict__ feat_ids,
-                                                                    int64_t n_items, int32_t m_bits,
+                                                                    int64_t n_items, BuildMod bm,
                                                                     int32_t k_hashes, uint64_t* __restrict__ bloom)
 {
     extern __shared__ __attribute__((aligned(16))) uint32_t s_bits[];  // [rows][32]: the 16 words of a row as 32-bit halves
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
-    const int64_t item0 = tile * kTileItems;
-    const bool pow2 = (m_bits & (m_bits - 1)) == 0;
+    const int64_t item = tile * kTileItems + tid;
+    const int m_bits = (int)bm.m;
+    const int64_t f_begin = item < n_items ? feat_offsets[item] : 0;
+    const int64_t f_end = item < n_items ? feat_offsets[item + 1] : 0;
+    const uint32_t bit = 1u << (tid & 31);
     for (int slab0 = 0; slab0 < m_bits; slab0 += kBuildSlabRows) {
         const int rows = min(kBuildSlabRows, m_bits - slab0);
         for (int i = tid; i < rows * 8; i += kBuildThreads) reinterpret_cast<int4*>(s_bits)[i] = make_int4(0, 0, 0, 0);
         __syncthreads();
-        for (int it = tid; it < kTileItems; it += kBuildThreads) {
-            const int64_t item = item0 + it;
-            if (item >= n_items) break;
-            const int64_t f_end = feat_offsets[item + 1];
-            const uint32_t bit = 1u << (it & 31);
-            for (int64_t e = feat_offsets[item]; e < f_end; ++e) {
-                const uint64_t f = feat_ids[e];
-                for (int j = 0; j < k_hashes; ++j) {
-                    const uint64_t h = splitmix64(f ^ (uint64_t)j);
-                    const int r = (int)(pow2 ? (h & (uint64_t)(m_bits - 1)) : (h % (uint64_t)m_bits)) - slab0;
-                    if (r >= 0 && r < rows) atomicOr(&s_bits[r * 32 + (it >> 5)], bit);
-                }
-            }
+        for (int64_t e = f_begin; e < f_end; e += kBuildIds) {
+            uint64_t f[kBuildIds];
+#pragma unroll
+            for (int u = 0; u < kBuildIds; ++u) f[u] = e + u < f_end ? feat_ids[e + u] : 0;
+#pragma unroll
+            for (int u = 0; u < kBuildIds; ++u)
+                if (e + u < f_end)
+                    for (int j = 0; j < k_hashes; ++j) {
+                        const int r = (int)build_pos<POW2>(f[u] ^ (uint64_t)j, bm) - slab0;
+                        if ((uint32_t)r < (uint32_t)rows) atomicOr(&s_bits[build_word(r, tid >> 5)], bit);
+                    }
         }
         __syncthreads();
         int4* dst = reinterpret_cast<int4*>(bloom + (tile * (int64_t)m_bits + slab0) * kTileWords);
-        for (int i = tid; i < rows * 8; i += kBuildThreads) dst[i] = reinterpret_cast<const int4*>(s_bits)[i];
+        for (int i = tid; i < rows * 8; i += kBuildThreads) {
+            const int r = i >> 3, c = i & 7;  // the four words of a piece lie in one piece, their order depends on the row
+            const int4 v = reinterpret_cast<const int4*>(s_bits)[r * 8 + (c ^ ((r >> 2) & 7))];
+            int4 o = (r & 1) ? make_int4(v.y, v.x, v.w, v.z) : v;
+            if (r & 2) o = make_int4(o.z, o.w, o.x, o.y);
+            dst[i] = o;
+        }
         __syncthreads();
     }
 }
