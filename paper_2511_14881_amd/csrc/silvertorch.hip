@@ -14,6 +14,7 @@
 #include <map>
 #include <mutex>
 #include <new>
+#include <thread>
 #include <vector>
 
 #include "st_stage_pool.h"
@@ -99,33 +100,70 @@ struct TimedLaunch {
 };
 
 // Pinned staging slots for the per-call tables (st_stage_pool.h): a call owns its slot from
-// stage_get() until the StageHold goes out of scope, by which time the event behind the work that
-// reads the slot has been recorded (or, on an error path after something was enqueued, the stream
-// has been waited for).
+// stage_get() until the StageHold goes out of scope, by which time a kernel behind the work that reads
+// the slot has been told to report there (or, on an error path after something was enqueued, the
+// stream has been waited for).
+//
+// The report is a number that the kernel stores into pinned host memory, a new one for every use of the
+// slot.  (An event recorded behind the reading kernel did the same with 6 us between that kernel and the
+// next one: its packet waits for everything before it and holds up everything after it.  The store
+// rides along in a kernel that is launched anyway.)
 st::StagePool g_pool;
 
-bool stage_event_done(void* e)
+struct StageMark {
+    uint64_t* seen = nullptr;      // pinned: number of the latest use known to be over, stored by the device
+    uint64_t* dev_view = nullptr;  // the same word as the device addresses it
+    uint64_t number = 0;           // of the current or latest use
+    int device = 0;
+    bool retired = false;          // used under stream capture: every replay of the graph reads the slot again
+};
+
+bool stage_mark_done(void* e)
 {
-    if (hipEventQuery((hipEvent_t)e) == hipSuccess) return true;
-    (void)hipGetLastError();  // "not ready" must not show up as the next launch's error
-    return false;
+    const StageMark* m = (const StageMark*)e;
+    return !m->retired && __atomic_load_n(m->seen, __ATOMIC_ACQUIRE) >= m->number;
 }
 
-int stage_event_wait(void* e) { return hipEventSynchronize((hipEvent_t)e) == hipSuccess ? 0 : (int)ST_EHIP; }
+int stage_mark_wait(void* e)
+{
+    StageMark* m = (StageMark*)e;
+    if (m->retired) return (int)ST_EHIP;
+    for (int i = 0; i < 2000; ++i) {  // (a millisecond or so: the slot's kernels are already enqueued)
+        if (stage_mark_done(e)) return 0;
+        std::this_thread::yield();
+    }
+    int current = 0;
+    if (hipGetDevice(&current) != hipSuccess) return (int)ST_EHIP;
+    if (current != m->device && hipSetDevice(m->device) != hipSuccess) return (int)ST_EHIP;
+    const hipError_t err = hipDeviceSynchronize();
+    if (current != m->device) (void)hipSetDevice(current);
+    return err == hipSuccess && stage_mark_done(e) ? 0 : (int)ST_EHIP;
+}
 
 struct StageHold {
     st::StageSlot* s = nullptr;
     hipStream_t stream = nullptr;
     bool enqueued = false;  // work that reads the slot is on the stream
-    bool recorded = false;  // ... and the slot's event behind it
+    bool recorded = false;  // ... and behind it a kernel that stores the number of this use
     void* host() const { return s->host; }
     void* dev_view() const { return s->dev_view; }
-    ~StageHold()
+    StageMark* mark() const { return (StageMark*)s->event; }
+    st::StageDone done() const { return st::StageDone{mark()->dev_view, mark()->number}; }
+    void reported()  // a kernel with done() has been enqueued
+    {
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
+        else if (st != hipStreamCaptureStatusNone) mark()->retired = true;
+        recorded = true;
+    }
+    void release()
     {
         if (!s) return;
         if (enqueued && !recorded) (void)hipStreamSynchronize(stream);
         g_pool.release(s, recorded);
+        s = nullptr;
     }
+    ~StageHold() { release(); }
 };
 
 // Set while st_search_static runs in the calling thread: nothing may be allocated then.
@@ -134,7 +172,7 @@ thread_local bool t_no_alloc = false;
 int stage_get(size_t bytes, hipStream_t stream, StageHold* h)
 {
     st::StageSlot* s = nullptr;
-    if (g_pool.acquire(stage_event_done, stage_event_wait, &s) != 0)
+    if (g_pool.acquire(stage_mark_done, stage_mark_wait, &s) != 0)
         return fail(ST_EHIP, "waiting for a staging slot failed");
     h->s = s;
     h->stream = stream;
@@ -142,10 +180,14 @@ int stage_get(size_t bytes, hipStream_t stream, StageHold* h)
         return fail(ST_EINVAL, "the tables of this batch (%zu bytes) exceed the pre-allocated staging slots (%zu bytes)",
                     bytes, s->bytes);
     if (!s->event) {
-        hipEvent_t ev;
-        ST_HIP(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-        s->event = ev;
+        StageMark m;
+        ST_HIP(hipHostMalloc((void**)&m.seen, 64, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
+        *m.seen = 0;
+        ST_HIP(hipHostGetDevicePointer((void**)&m.dev_view, m.seen, 0));
+        s->event = new StageMark(m);
     }
+    ++h->mark()->number;
+    ST_HIP(hipGetDevice(&h->mark()->device));
     if (s->bytes < bytes) {  // owned and not pending: nothing reads the old memory any more
         if (s->host) ST_HIP(hipHostFree(s->host));
         s->host = nullptr;
@@ -158,16 +200,9 @@ int stage_get(size_t bytes, hipStream_t stream, StageHold* h)
     return ST_OK;
 }
 
-int stage_record(StageHold* h)
-{
-    ST_HIP(hipEventRecord((hipEvent_t)h->s->event, h->stream));
-    h->recorded = true;
-    return ST_OK;
-}
-
 // Per-device set-up, run by st_bloom_build (which allocates anyway and precedes every search on
 // its device): the address of this device's copy of the static workspace, and, once per process,
-// pinned memory and an event for every staging slot, so that st_search_static finds all of it in
+// pinned memory for every staging slot and its mark, so that st_search_static finds all of it in
 // place.  In host code the array's name is only a handle for hipGetSymbolAddress; the address
 // kept here is what kernels and copies are given.
 constexpr int kMaxDevices = 64;
@@ -881,13 +916,15 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                        void* dev_workspace, int64_t workspace_bytes, void* hip_stream,
                        const Groups* expr_groups = nullptr, const uint64_t* expr_rows = nullptr,
                        int32_t expr_row_count = 0, bool allow_seed = true, int32_t min_cap = 64,
-                       int32_t* dry_out = nullptr)
+                       int32_t* dry_out = nullptr, StageHold* shared = nullptr, size_t shared_used = 0)
 {
     // dry_out: host part only (st_search_host_plan): no device pointer is looked at, nothing is
     // enqueued, and the summary of the schedule goes to dry_out[8]
     // allow_seed = false: no seed pass and no thresholds tighter than the K-th best so far (both
     // rest on a prefix of the corpus, which says nothing when the passing items sit in a few item
     // ranges, as after cluster probing)
+    // shared: the staging slot of work already enqueued for this call, which holds shared_used bytes (a
+    // multiple of 16) of it; the search puts its tables behind them and reports the use of both
     // expr_groups: the filters were evaluated beforehand into expr_row_count mask rows at
     // expr_rows, laid out like a Bloom index; each group then tests the one row it names
     if (!bloom) return fail(ST_EINVAL, "bloom is null");
@@ -1055,18 +1092,25 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
 
     char* ws = (char*)dev_workspace;
-    StageHold stage;
-    rc = stage_get(blob.bytes(), stream, &stage);
-    if (rc != ST_OK) return rc;
-    memcpy(stage.host(), blob.data.data(), blob.bytes());
+    StageHold own;
+    if (!shared) {
+        rc = stage_get(blob.bytes(), stream, &own);
+        if (rc != ST_OK) return rc;
+    }
+    StageHold& stage = shared ? *shared : own;
+    if (shared_used + blob.bytes() > stage.s->bytes) return fail(ST_EINVAL, "group tables exceed the staging slot");
+    memcpy((char*)stage.host() + shared_used, blob.data.data(), blob.bytes());
+    const char* staged = (const char*)stage.dev_view() + shared_used;  // the tables as the device sees them
     // A search that starts with the seed pass lets that kernel bring the tables over (it reads its
-    // own from the pinned copy); otherwise they are copied ahead of the first kernel.
+    // own from the pinned copy); otherwise a small kernel copies them ahead of the first one.  (A copy
+    // enqueued with hipMemcpyAsync is a kernel too, but with 6 us of waiting on either side of it.)
     const bool seed_uploads = plan.n_levels > 0 && plan.level[0].seed;
     if (!seed_uploads) {
         stage.enqueued = true;
-        ST_HIP(hipMemcpyAsync(ws + L.meta, stage.host(), blob.bytes(), hipMemcpyHostToDevice, stream));
-        rc = stage_record(&stage);
-        if (rc != ST_OK) return rc;
+        const int64_t pieces = (int64_t)blob.bytes() / 16;  // (the blob's tables are padded to 16 bytes)
+        hipLaunchKernelGGL(st::stage_upload_kernel, dim3((unsigned)((pieces + st::kUploadThreads - 1) / st::kUploadThreads)),
+                           dim3(st::kUploadThreads), 0, stream, (const int4*)staged, (int4*)(ws + L.meta), pieces);
+        ST_HIP(hipGetLastError());
     }
     auto tab = [&](size_t at) { return (const int32_t*)(ws + L.meta + at); };
 
@@ -1170,7 +1214,7 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
         if (L_.seed) {  // per-query scan + selection of the prefix in one launch
             TimedLaunch t(1, stream);
             st::SeedUpload up;
-            up.src = (const int32_t*)stage.dev_view();
+            up.src = (const int32_t*)staged;
             up.dst = (int32_t*)(ws + L.meta);
             up.words = (int32_t)(blob.bytes() / 4);
             up.img_q = nullptr;
@@ -1182,14 +1226,14 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                 up.img_q = mp.img_q;
                 up.img_sq = mp.img_sq;
                 up.img_qrow = mp.img_qrow;
-                up.blk_row = (const int32_t*)((const char*)stage.dev_view() + at_blk_row);
+                up.blk_row = (const int32_t*)(staged + at_blk_row);
                 up.n_blocks = mp.n_blocks;
                 up.q_split = mp.q_split;
                 up.rows_local = rows_local;
                 mfma_started = true;
             }
             st::SelectParams se_seed = se;  // the seed pass reads its tables from the pinned copy
-            auto host_tab = [&](size_t at) { return (const int32_t*)((const char*)stage.dev_view() + at); };
+            auto host_tab = [&](size_t at) { return (const int32_t*)(staged + at); };
             se_seed.q_prow = host_tab(at_qprow);
             se_seed.q2grp = host_tab(at_q2grp);
             se_seed.q_taupos = host_tab(at_taupos);
@@ -1198,8 +1242,6 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             seed_parts = st::seed_parts(batch, L.k_pad);
             stage.enqueued = true;
             ST_HIP(st::launch_seed(se_seed, L_.end, batch, seed_parts, up, stream));
-            rc = stage_record(&stage);
-            if (rc != ST_OK) return rc;
             continue;
         }
         for (st::ScanParams* q : {&sp_m, &sp_d}) {
@@ -1298,9 +1340,13 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                 lds_set.store(true, std::memory_order_release);
             }
             const size_t lds = std::max<size_t>((size_t)st::select_lds_bytes(se.lds_keys), se.big_sort == 1 ? big_bytes : (se.big_sort == 2 ? kBigSortMax : 0));
+            // the first selection comes behind everything that reads the pinned tables
+            const bool report = !stage.recorded;
+            se.done = report ? stage.done() : st::StageDone{nullptr, 0};
             hipLaunchKernelGGL(st::select_kernel, dim3(batch), dim3(st::kSelectThreads), lds, stream, se);
+            ST_HIP(hipGetLastError());
+            if (report) stage.reported();
         }
-        ST_HIP(hipGetLastError());
     }
     return ST_OK;
 }
@@ -1464,15 +1510,18 @@ int st_search_expr(const st_bloom* bloom, const int8_t* dev_items, const float* 
     uint64_t* mask_rows = (uint64_t*)(ws + st::round_up(base, 256));
     int32_t* d_tab = (int32_t*)((char*)mask_rows + n_tiles * batch * st::kTileWords * 8);
 
+    StageHold stage;
+    size_t staged_bytes = 0;
     if (n_tiles > 0) {
-        // tables through a pinned slot (asynchronous copy), then one launch evaluates every
+        // tables through a pinned slot, then one launch evaluates every
         // distinct program into its row of the mask index
         const size_t n_off = tab.prog_off.size(), n_code = tab.code.size(), n_rows = tab.leaf_rows.size();
         const size_t bytes = (n_off + n_code + n_rows) * 4;
         if (bytes > expr_table_bytes(batch, host_expr_offsets[batch], ST_MAX_K_HASHES))
             return fail(ST_EINVAL, "program tables exceed their workspace slot");
-        StageHold stage;
-        rc = stage_get(bytes, stream, &stage);
+        // (one slot for the whole call: the search's own tables go behind these)
+        staged_bytes = (size_t)st::round_up((int64_t)bytes, 16);
+        rc = stage_get(staged_bytes + st::meta_bound_bytes(batch), stream, &stage);
         if (rc != ST_OK) return rc;
         int32_t* h = (int32_t*)stage.host();
         memcpy(h, tab.prog_off.data(), n_off * 4);
@@ -1495,12 +1544,11 @@ int st_search_expr(const st_bloom* bloom, const int8_t* dev_items, const float* 
                                tab.n_exprs, mask_rows);
         }
         ST_HIP(hipGetLastError());
-        rc = stage_record(&stage);
-        if (rc != ST_OK) return rc;
     }
     return search_impl(bloom, dev_items, dev_item_scale, n_items, d, dev_queries, dev_query_scale, batch, n_tasks,
                        host_task_weight, nullptr, nullptr, K, dev_out_ids, dev_out_scores, dev_out_count,
-                       dev_workspace, base, hip_stream, &groups, mask_rows, tab.n_exprs);
+                       dev_workspace, base, hip_stream, &groups, mask_rows, tab.n_exprs, true, 64, nullptr,
+                       stage.s ? &stage : nullptr, staged_bytes);
     });
 }
 
@@ -1598,6 +1646,24 @@ int st_search_ivf(const st_bloom* bloom, const int8_t* dev_items, const float* d
         groups.q2grp.push_back(b);
     }
 
+    // The programs' tables go into a pinned slot, and the first workgroup of the first kernel brings
+    // them to the workspace and reports the slot free.
+    const size_t n_off = tab.prog_off.size(), n_code = tab.code.size(), n_rows = tab.leaf_rows.size();
+    StageHold stage;
+    if (n_tiles > 0) {
+        const size_t bytes = (size_t)st::round_up((int64_t)(n_off + n_code + n_rows) * 4, 16);
+        if (bytes > expr_table_bytes(batch, host_expr_offsets[batch], ST_MAX_K_HASHES))
+            return fail(ST_EINVAL, "program tables exceed their workspace slot");
+        rc = stage_get(bytes, stream, &stage);
+        if (rc != ST_OK) return rc;
+        int32_t* h = (int32_t*)stage.host();
+        memcpy(h, tab.prog_off.data(), n_off * 4);
+        if (n_code) memcpy(h + n_off, tab.code.data(), n_code * 4);
+        if (n_rows) memcpy(h + n_off + n_code, tab.leaf_rows.data(), n_rows * 4);
+        ip.tables = st::StageCopy{(const int4*)stage.dev_view(), (int4*)d_tab, (int32_t)(bytes / 16), stage.done()};
+        stage.enqueued = true;
+    }
+
     {   // phase 1: centroid scores and the n_probe best clusters of every query
         // Many centroids: several workgroups per query, each on a slice, then a merge.  The number of
         // parts is the largest that keeps a slice within the register-resident select and all parts'
@@ -1626,24 +1692,10 @@ int st_search_ivf(const st_bloom* bloom, const int8_t* dev_items, const float* d
         }
     }
     ST_HIP(hipGetLastError());
+    if (stage.s) stage.reported();
+    stage.release();  // (a call never holds one slot while it waits for another)
     if (n_tiles > 0) {
-        const size_t n_off = tab.prog_off.size(), n_code = tab.code.size(), n_rows = tab.leaf_rows.size();
-        const size_t bytes = (n_off + n_code + n_rows) * 4;
-        if (bytes > expr_table_bytes(batch, host_expr_offsets[batch], ST_MAX_K_HASHES))
-            return fail(ST_EINVAL, "program tables exceed their workspace slot");
-        StageHold stage;
-        rc = stage_get(bytes, stream, &stage);
-        if (rc != ST_OK) return rc;
-        int32_t* h = (int32_t*)stage.host();
-        memcpy(h, tab.prog_off.data(), n_off * 4);
-        if (n_code) memcpy(h + n_off, tab.code.data(), n_code * 4);
-        if (n_rows) memcpy(h + n_off + n_code, tab.leaf_rows.data(), n_rows * 4);
-        const int32_t* t_dev = (const int32_t*)stage.dev_view();
-        stage.enqueued = true;
-        if (bytes > 64 * 1024) {
-            ST_HIP(hipMemcpyAsync(d_tab, stage.host(), bytes, hipMemcpyHostToDevice, stream));
-            t_dev = d_tab;
-        }
+        const int32_t* t_dev = d_tab;
         if (per_query) {
             st::Plan plan1;
             if (cached_plan(n_items, K, 1, st::kMaxSegItems, batch, &plan1, 2048, kIvfCap) != 0)
@@ -1692,7 +1744,7 @@ int st_search_ivf(const st_bloom* bloom, const int8_t* dev_items, const float* d
                     hipLaunchKernelGGL(st::ivf_merge_kernel, dim3(batch), dim3(st::kQueryThreads), 0, stream, qp, parts);
             }
             ST_HIP(hipGetLastError());
-            return stage_record(&stage);
+            return ST_OK;
         }
         {   // phase 2: the filter over the probed ranges only, into zeroed mask rows
             TimedLaunch t(3, stream);
@@ -1704,8 +1756,6 @@ int st_search_ivf(const st_bloom* bloom, const int8_t* dev_items, const float* d
                                t_dev + n_off + n_code, mask_rows);
         }
         ST_HIP(hipGetLastError());
-        rc = stage_record(&stage);
-        if (rc != ST_OK) return rc;
     }
     // phases 3 and 4
     return search_impl(bloom, dev_items, dev_item_scale, n_items, d, dev_queries, dev_query_scale, batch, 1, nullptr,

@@ -30,6 +30,7 @@ struct IvfParams {
     uint64_t* keys;               // [batch][n_clusters]  scratch: centroid keys
     int32_t* probes;              // [batch][n_probe]     probed clusters in rank order, -1 = none
     int32_t* user_probes;         // the same for the caller, or null
+    StageCopy tables;             // the filter programs' tables, brought over by the first workgroup of phase 1
 };
 
 // Dynamic LDS: sorted keys [k_pad], histogram [256], misc [8], reduction [2 * waves].
@@ -43,6 +44,7 @@ __global__ __launch_bounds__(kProbeThreads) void ivf_probe_kernel(IvfParams p)
     uint32_t* s_hist = reinterpret_cast<uint32_t*>(s_red + 2 * (kProbeThreads / 64));  // [256]
     uint32_t* s_misc = s_hist + 256;                                      // [8]
     const int tid = threadIdx.x, b = blockIdx.x;
+    if (b == 0 && p.tables.src) stage_copy(p.tables);
     const float sq = p.qscale[b];
     uint64_t* keys = p.keys + (int64_t)b * p.n_clusters;
     int64_t qoff[kRowBlock];
@@ -83,6 +85,7 @@ __global__ __launch_bounds__(kProbeThreads) void ivf_probe_part_kernel(IvfParams
     __shared__ uint32_t s_hist[3 * 256], s_misc[8];
     __shared__ uint64_t s_red[32];
     const int tid = threadIdx.x, b = blockIdx.x, part = blockIdx.y;
+    if (b == 0 && part == 0 && p.tables.src) stage_copy(p.tables);
     const int c0 = part * chunk;
     int n = p.n_clusters - c0;
     n = n < 0 ? 0 : (n > chunk ? chunk : n);

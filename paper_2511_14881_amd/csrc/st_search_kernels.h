@@ -618,7 +618,55 @@ __device__ inline int lds_topk(uint64_t* keys, int n, int K, uint64_t* sorted, i
     return n_out;
 }
 
+// Report of a kernel behind the last reader of a pinned staging slot: `number` is stored into the
+// host's word (null: nothing to report).  Everything earlier on the stream has completed when a kernel
+// runs, so the store needs no order of its own.
+struct StageDone {
+    uint64_t* seen;
+    uint64_t number;
+};
+__device__ inline void stage_report(const StageDone& d)
+{
+    if (d.seen) __hip_atomic_store(d.seen, d.number, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The same by the first workgroup of a kernel that is launched anyway: copies `pieces` 16-byte pieces (eight
+// per thread in flight: the round trips over PCIe are what it costs) and reports the slot free.
+struct StageCopy {
+    const int4* src;  // null: nothing to copy
+    int4* dst;
+    int32_t pieces;
+    StageDone done;
+};
+__device__ inline void stage_copy(const StageCopy& c)
+{
+    constexpr int U = 8;
+    const int nt = blockDim.x;
+    for (int i0 = threadIdx.x; i0 < c.pieces; i0 += U * nt) {
+        int4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * nt < c.pieces) v[u] = c.src[i0 + u * nt];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (i0 + u * nt < c.pieces) c.dst[i0 + u * nt] = v[u];
+    }
+    __syncthreads();  // every load has returned: its store has been issued
+    if (threadIdx.x == 0) stage_report(c.done);
+}
+
+// Copy of a call's tables from the pinned slot to the workspace, one 16-byte piece per thread.  Bound by
+// one round trip over PCIe.
+constexpr int kUploadThreads = 256;
+__global__ __launch_bounds__(kUploadThreads) void stage_upload_kernel(const int4* __restrict__ src, int4* __restrict__ dst,
+                                                                      int64_t pieces)
+{
+    const int64_t i = (int64_t)blockIdx.x * kUploadThreads + threadIdx.x;
+    if (i < pieces) dst[i] = src[i];
+}
+
 struct SelectParams {
+    StageDone done;         // the staging slot of the call, whose readers have completed when this kernel starts
     const uint64_t* cand;   // [B][G][cap]
     const uint32_t* cnt;    // [B][G]
     int32_t cap, groups;
@@ -725,6 +773,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
     uint32_t* s_wsum = s_misc + 8;                                                 // [16]
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
     constexpr int NT = kSelectThreads;
+    if (q == 0 && tid == 0) stage_report(p.done);
     // counts are clamped to what the buffers can hold, whatever the memory says
     uint32_t n_prev = p.first ? 0u : p.topk_cnt[q];
     n_prev = n_prev < (uint32_t)p.K ? n_prev : (uint32_t)p.K;

@@ -1,7 +1,8 @@
 // Pool of pinned staging slots for the per-call table uploads of the search entry points.
 //
 // A call fills a slot with its tables on the host, enqueues the copy (or a kernel that reads the
-// slot directly) on its stream and records an event behind it.  A slot therefore goes through
+// slot directly) on its stream and arranges for an event behind it (whatever tells the host that the
+// work is over).  A slot therefore goes through
 // three states:
 //   free      nobody uses it; if `pending`, the event recorded behind its last use may not have
 //             completed yet and has to be waited for before the memory is written again

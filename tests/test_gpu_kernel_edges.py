@@ -6,6 +6,7 @@ import torch
 
 from oracle import st_oracle as O
 from paper_2511_14881_amd import binding as st
+from paper_2511_14881_amd import synth as S
 
 pytestmark = pytest.mark.gpu
 
@@ -26,3 +27,32 @@ def test_index_build_and_export_at_tile_edges(n, m):
     bloom = st.st_bloom_build(torch.from_numpy(off).cuda(), torch.from_numpy(ids).cuda(), n, m, 3)
     got = _u64(st.st_bloom_export_signatures(bloom))
     assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, 3))
+
+
+# The tables of a captured call are read again at every replay: eager calls in between (more than there are
+# staging slots) must not get the slot.  Once without a seed pass, once with it.
+@pytest.mark.parametrize("n", [20_000, 300_000])
+def test_captured_search_replays_beside_eager_calls(n):
+    print(f"[edges] graph n={n}", flush=True)
+    w = S.make_workload(S.scaled(S.CONFIGS["mid"], n, batch=9, top_k=20), "cuda")
+    cfg = w.cfg
+    bloom = st.st_bloom_build(w.feat_offsets, w.feat_ids, n, cfg.m_bits, cfg.k_hashes)
+
+    def call(fid, foff, buf):
+        return st.st_search(bloom, w.items, w.item_scale, w.queries, w.query_scale, fid, foff, cfg.top_k, buffers=buf)
+
+    buf, other = st.SearchBuffers(n, cfg.d, 9, 1, cfg.top_k), st.SearchBuffers(n, cfg.d, 9, 1, cfg.top_k)
+    want = [t.clone() for t in call(w.filt_ids, w.filt_offsets, buf)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(w.filt_ids, w.filt_offsets, buf)
+    no_filter = np.zeros(10, np.int64)
+    for _ in range(3):
+        for _ in range(20):
+            call(np.zeros(0, np.uint64), no_filter, other)
+        for t in (buf.ids, buf.scores, buf.count):
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((buf.ids, buf.scores, buf.count), want))
