@@ -1173,7 +1173,7 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     se.K = K;
     se.k_pad = L.k_pad;
     // more queries than compute units: a smaller key buffer lets two selection workgroups share one
-    se.lds_keys = batch > st::kComputeUnits ? st::kLdsKeysDense : st::kLdsKeys;
+    se.lds_keys = se.srt ? st::kLdsKeysBig : (batch > st::kComputeUnits ? st::kLdsKeysDense : st::kLdsKeys);
     se.tau = (uint64_t*)(ws + L.tau);
     se.ovf = sp.ovf;
     se.out_ids = dev_out_ids;
@@ -1329,21 +1329,21 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
         {
             TimedLaunch t(1, stream);
             // K above the LDS sort size: the final ordering of k_pad keys runs in LDS where they fit
-            const size_t big_bytes = (size_t)L.k_pad * 8;
-            constexpr size_t kBigSortMax = 128 * 1024;
-            se.big_sort = se.srt ? (big_bytes <= kBigSortMax ? 1 : 2) : 0;
-            static std::atomic<bool> lds_set{false};  // (setting the attribute twice is harmless)
-            if (!lds_set.load(std::memory_order_acquire)) {
-                ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&st::select_kernel),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)std::max<size_t>(st::kSelectLdsBytes, kBigSortMax)));
-                lds_set.store(true, std::memory_order_release);
+            constexpr int kBigSortMax = 16384;
+            static_assert(kBigSortMax <= st::kLdsKeysBig, "the keys are ordered in the key buffer");
+            se.big_sort = se.srt ? (L.k_pad <= kBigSortMax ? 1 : 2) : 0;
+            const auto kernel = se.srt ? &st::select_kernel<st::kSelectBigThreads, true> : &st::select_kernel<st::kSelectThreads, false>;
+            static std::atomic<bool> lds_set[2] = {{false}, {false}};  // (setting the attribute twice is harmless)
+            if (!lds_set[se.srt != nullptr].load(std::memory_order_acquire)) {
+                ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           st::select_lds_bytes(se.srt ? st::kLdsKeysBig : st::kLdsKeys)));
+                lds_set[se.srt != nullptr].store(true, std::memory_order_release);
             }
-            const size_t lds = std::max<size_t>((size_t)st::select_lds_bytes(se.lds_keys), se.big_sort == 1 ? big_bytes : (se.big_sort == 2 ? kBigSortMax : 0));
             // the first selection comes behind everything that reads the pinned tables
             const bool report = !stage.recorded;
             se.done = report ? stage.done() : st::StageDone{nullptr, 0};
-            hipLaunchKernelGGL(st::select_kernel, dim3(batch), dim3(st::kSelectThreads), lds, stream, se);
+            hipLaunchKernelGGL(kernel, dim3(batch), dim3(se.srt ? st::kSelectBigThreads : st::kSelectThreads),
+                               (size_t)st::select_lds_bytes(se.lds_keys), stream, se);
             ST_HIP(hipGetLastError());
             if (report) stage.reported();
         }

@@ -618,6 +618,137 @@ __device__ inline int lds_topk(uint64_t* keys, int n, int K, uint64_t* sorted, i
     return n_out;
 }
 
+// Ordering of the best `want` keys of a set by buckets of the score, for the whole workgroup.  The
+// score range is cut into kOrderBins equal steps (in the order-preserving integer form of the score), the
+// keys are counted per step, the steps from the top down to the want-th key are given consecutive places
+// in s_out, the keys are dropped there, and a key's rank is its step's first place plus the number of
+// larger keys in the step.  Three passes over the keys and a few reads per key, where a radix selection
+// with a bitonic network took 4 + 105 passes (64 queries, K = 10,000 of 18 k candidates each: final
+// selection 502 -> 34 us).  Bound by the latency of a pass over the candidates, not by the ranking.
+//
+// More keys than s_out holds go in rounds, from the top.  A range whose steps come out too full (a few
+// scores far above the rest, or keys below the want-th one spread much wider) is cut again from the
+// lowest step wanted upwards.  False: too many keys share a score (they rank by id, which the steps do
+// not split), nothing the caller needs has been changed and it takes the general way.
+//
+// each(f) calls f(key) for this thread's share of the keys, the same ones on every call; emit(rank, key)
+// is called once for every rank below `want` and for some ranks above (the caller drops them).
+// The set must hold `want` keys at least, all distinct; want >= 1.
+constexpr int kOrderBins = 4096;
+constexpr uint32_t kOrderStepKeys = 512;  // keys of one step ranked against each other, at most
+
+template <int NT, class Each, class Emit>
+__device__ inline bool bucket_order(Each&& each, uint32_t want, uint32_t room, uint64_t* s_out, uint32_t* s_bins,
+                                    uint32_t* s_misc /*[4]*/, uint64_t* s_red /*[NT / 64]*/, uint32_t* s_wsum /*[NT / 64]*/,
+                                    Emit&& emit)
+{
+    constexpr int NW = NT / 64, kPer = kOrderBins / NT;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    uint32_t lo = ~0u, hi = 0u;
+    each([&](uint64_t key) {
+        const uint32_t s = (uint32_t)(key >> 32);
+        lo = s < lo ? s : lo;
+        hi = s > hi ? s : hi;
+    });
+    lo = ~wave_max_u32(~lo);  // (both in lane 63)
+    hi = wave_max_u32(hi);
+    if (lane == 63) s_red[wv] = ((uint64_t)lo << 32) | hi;
+    __syncthreads();
+    for (int w = 0; w < NW; ++w) {
+        const uint64_t r = s_red[w];
+        lo = min(lo, (uint32_t)(r >> 32));
+        hi = max(hi, (uint32_t)r);
+    }
+    uint32_t base = lo, done = 0;
+    // rounds and cuts: every round takes what fits, so that two in a row fill s_out once, up to the cuts
+    for (int turns = 16 + (int)(4 * (want / room)); turns > 0; --turns) {
+        const uint64_t width = (uint64_t)hi - base + 1;
+        const uint32_t mult = width > kOrderBins ? (uint32_t)(((uint64_t)kOrderBins << 32) / width) : 0u;
+        auto step_of = [&](uint32_t s) { return mult ? __umulhi(s - base, mult) : s - base; };
+        auto first_of = [&](uint32_t b) {  // lowest score of step b
+            return (uint64_t)base + (mult ? (((uint64_t)b << 32) + mult - 1) / mult : (uint64_t)b);
+        };
+        for (int i = tid; i < kOrderBins; i += NT) s_bins[i] = 0;
+        if (tid < 3) s_misc[tid] = 0;
+        __syncthreads();
+        each([&](uint64_t key) {
+            const uint32_t s = (uint32_t)(key >> 32);
+            if (s >= base && s <= hi) atomicAdd(&s_bins[step_of(s)], 1u);
+        });
+        __syncthreads();
+        // thread t owns steps kOrderBins - 1 - kPer * t and the ones below (descending)
+        uint32_t h[kPer], sum = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) { h[j] = s_bins[kOrderBins - 1 - kPer * tid - j]; sum += h[j]; }
+        const uint32_t incl = wave_scan_add(sum);
+        if (lane == 63) s_wsum[wv] = incl;
+        __syncthreads();
+        uint32_t before = incl - sum;
+        for (int w = 0; w < wv; ++w) before += s_wsum[w];
+        // a step is taken if a wanted key may lie in it and everything down to it has room
+        uint32_t n_steps = 0, n_keys = 0, fullest = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            s_bins[kOrderBins - 1 - kPer * tid - j] = before;
+            if (before < want - done && before + h[j] <= room) {
+                n_steps = (uint32_t)(kPer * tid + j + 1);
+                n_keys = before + h[j];
+                fullest = max(fullest, h[j]);
+            }
+            before += h[j];
+        }
+        n_steps = wave_max_u32(n_steps);
+        n_keys = wave_max_u32(n_keys);
+        fullest = wave_max_u32(fullest);
+        if (lane == 63) {
+            atomicMax(&s_misc[0], n_steps);
+            atomicMax(&s_misc[1], n_keys);
+            atomicMax(&s_misc[2], fullest);
+        }
+        __syncthreads();
+        n_steps = s_misc[0];
+        n_keys = s_misc[1];
+        fullest = s_misc[2];
+        const uint32_t b0 = kOrderBins - n_steps;  // lowest step taken
+        if (n_keys == 0 || fullest > kOrderStepKeys) {
+            const uint64_t cut = first_of(n_keys ? b0 : b0 - 1);  // (no key taken: the next step down is too full)
+            if (cut <= base) return false;
+            base = (uint32_t)cut;
+            __syncthreads();
+            continue;
+        }
+        each([&](uint64_t key) {
+            const uint32_t s = (uint32_t)(key >> 32);
+            if (s >= base && s <= hi) {
+                const uint32_t b = step_of(s);
+                if (b >= b0) s_out[atomicAdd(&s_bins[b], 1u)] = key;
+            }
+        });
+        __syncthreads();
+        // s_bins[b] is now the place behind step b's last key, where step b - 1 begins
+        for (uint32_t i = tid; i < n_keys; i += NT) {
+            const uint64_t key = s_out[i];
+            const uint32_t b = step_of((uint32_t)(key >> 32));
+            const uint32_t p0 = b + 1 < (uint32_t)kOrderBins ? s_bins[b + 1] : 0u, p1 = s_bins[b];
+            uint32_t rank = p0;
+            for (uint32_t j0 = p0; j0 < p1; j0 += 4) {
+                uint64_t o[4];
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) o[u] = s_out[min(j0 + u, p1 - 1)];
+#pragma unroll
+                for (uint32_t u = 0; u < 4; ++u) rank += (j0 + u < p1 && o[u] > key) ? 1u : 0u;
+            }
+            emit(done + rank, key);
+        }
+        done += n_keys;
+        if (done >= want) return true;
+        hi = (uint32_t)(first_of(b0) - 1);  // (keys are left, so some score lies below)
+        base = lo;
+        __syncthreads();
+    }
+    return false;
+}
+
 // Report of a kernel behind the last reader of a pinned staging slot: `number` is stored into the
 // host's word (null: nothing to report).  Everything earlier on the stream has completed when a kernel
 // runs, so the store needs no order of its own.
@@ -699,6 +830,7 @@ struct SelectParams {
 };
 
 constexpr int kSelectThreads = 512;
+constexpr int kSelectBigThreads = 1024;  // K above the LDS sort size
 constexpr int kLdsKeys = kSelectLdsKeys;  // candidates per query gathered in LDS; more go through global memory
 
 // Slow exact path for a query whose candidate region overflowed in some level: rescans the whole
@@ -758,9 +890,16 @@ constexpr int kSelectLdsBytes = kLdsKeys * 8 + kLdsSortMax * 8 + 3 * 256 * 4 + 6
 // Key capacity for batches that need more than one workgroup per compute unit: two selection
 // workgroups then fit the 160 KB of LDS side by side.
 constexpr int kLdsKeysDense = 7168;
+// K above the LDS sort size: the key buffer takes what LDS there is (the final ordering by buckets has its
+// keys there and its counters in the sort buffer).
+constexpr int kLdsKeysBig = 17408;
 inline int select_lds_bytes(int lds_keys) { return kSelectLdsBytes - (kLdsKeys - lds_keys) * 8; }
+static_assert(kOrderBins * 4 <= kLdsSortMax * 8, "the counters of the final ordering borrow the sort buffer");
+static_assert(kSelectLdsBytes + (kLdsKeysBig - kLdsKeys) * 8 <= 160 * 1024, "LDS of a compute unit");
 
-__global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
+// BIG: K above the LDS sort size (p.srt is there).
+template <int NT, bool BIG>
+__global__ __launch_bounds__(NT) void select_kernel(SelectParams p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char sel_lds[];
     const int lds_keys = p.lds_keys;
@@ -772,7 +911,6 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
     uint32_t* s_misc = s_hist + 3 * 256;                                           // [8]
     uint32_t* s_wsum = s_misc + 8;                                                 // [16]
     const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
-    constexpr int NT = kSelectThreads;
     if (q == 0 && tid == 0) stage_report(p.done);
     // counts are clamped to what the buffers can hold, whatever the memory says
     uint32_t n_prev = p.first ? 0u : p.topk_cnt[q];
@@ -797,7 +935,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
     // of keys as a rule, so this is one memory round trip instead of two (what lies beyond the
     // count is stale workspace and is dropped).
     constexpr int kHead = 8;
-    const bool spec = per <= 2 && gridDim.x <= 512;  // (larger batches fill the chip several times over: latency is hidden, bytes are not)
+    const bool spec = per <= 2 && gridDim.x <= 512 && !(BIG && p.last);  // (larger batches fill the chip several times over: latency is hidden, bytes are not)
     uint32_t hc[2] = {0u, 0u};
     int4 hv[2][kHead / 2];
     if (spec) {
@@ -846,10 +984,61 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
         rescue_query(p, q, s_sorted, s_hist, s_misc, s_red, s_mask, &s_misc[4]);
         return;
     }
+    if constexpr (BIG) {
+        if (p.last) {
+            // f(key) for every candidate, 16 lanes to a region: their counts are fetched once, the keys of
+            // eight regions are requested together
+            constexpr int kSweeps = kScanGroups / (NT / 16);
+            const int sub = tid & 15;
+            uint32_t c[kSweeps], c_max = 0;
+#pragma unroll
+            for (int j = 0; j < kSweeps; ++j) {
+                const int w = j * (NT / 16) + (tid >> 4);
+                c[j] = w < R ? min(cq[w], (uint32_t)p.cap) : 0u;
+            }
+#pragma unroll
+            for (int j = 0; j < kSweeps; ++j) c_max = max(c_max, c[j]);
+            const uint64_t* region = p.cand + ((int64_t)q * p.groups + (tid >> 4)) * p.cap;
+            auto each = [&](auto&& f) {
+                for (uint32_t i = sub; ballot(i < c_max) != 0; i += 16)
+#pragma unroll
+                    for (int j0 = 0; j0 < kSweeps; j0 += 8) {
+                        uint64_t v[8];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (i < c[j0 + u]) v[u] = region[(int64_t)(j0 + u) * (NT / 16) * p.cap + i];
+#pragma unroll
+                        for (int u = 0; u < 8; ++u)
+                            if (i < c[j0 + u]) f(v[u]);
+                    }
+                for (int i = tid; i < (int)n_prev; i += NT) f(p.topk_keys[(int64_t)q * p.K + i]);
+            };
+            const uint32_t want = total < (uint32_t)p.K ? total : (uint32_t)p.K;
+            int64_t* ids = p.out_ids + (int64_t)q * p.K;
+            float* scores = p.out_scores + (int64_t)q * p.K;
+            const bool ordered = want == 0 ||
+                bucket_order<NT>(each, want, (uint32_t)lds_keys, s_keys, reinterpret_cast<uint32_t*>(s_sorted), s_misc, s_red,
+                                 s_wsum, [&](uint32_t rank, uint64_t key) {
+                                     if (rank < want) {
+                                         ids[rank] = (int64_t)key_item(key);
+                                         scores[rank] = key_score(key);
+                                     }
+                                 });
+            if (ordered) {
+                for (int i = (int)want + tid; i < p.K; i += NT) {
+                    ids[i] = -1;
+                    scores[i] = -__builtin_inff();
+                }
+                if (tid == 0) p.out_count[q] = (int32_t)want;
+                return;
+            }
+            __syncthreads();
+        }
+    }
     const bool in_lds = total <= (uint32_t)lds_keys;
     // More candidates than LDS holds, result sorted in LDS: the candidates are narrowed down where
     // they lie (below), not copied.
-    const bool narrow = !in_lds && !p.srt;
+    const bool narrow = !BIG && !in_lds;
     uint64_t* gkeys = p.gath + (int64_t)q * p.gath_cap;
     // f(key) for every candidate of the query: each thread walks its own regions (loads independent
     // of each other), then the running top-K
@@ -934,7 +1123,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
     }
     __syncthreads();
 
-    uint64_t* sorted = p.srt ? p.srt + (int64_t)q * p.k_pad : s_sorted;
+    uint64_t* sorted = BIG ? p.srt + (int64_t)q * p.k_pad : s_sorted;
     int n_out;
     uint64_t kth = 0;  // K-th best key so far (0: fewer than K candidates yet)
     if (narrow) {
@@ -1004,9 +1193,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
         __syncthreads();
         keep = keep < (uint32_t)lds_keys ? keep : (uint32_t)lds_keys;  // keys are distinct: never cut
         n_out = lds_topk(s_keys, (int)keep, p.keep, s_sorted, p.k_pad, s_hist, s_misc, s_red, p.last != 0, kth);
-    } else if (in_lds && !p.srt) {
+    } else if (!BIG) {
         n_out = lds_topk(s_keys, (int)total, p.keep, s_sorted, p.k_pad, s_hist, s_misc, s_red, p.last != 0, kth);
-    } else if (p.big_sort) {
+    } else {
         // Large K: the set is carried from level to level unordered (only its K-th key is needed);
         // the last level orders it in LDS, which holds all k_pad keys once the selection's own
         // buffers are no longer in use.
@@ -1049,9 +1238,6 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectParams p)
             }
             sorted = big;
         }
-    } else {
-        n_out = wg_topk(in_lds ? s_keys : gkeys, (int64_t)total, p.keep, sorted, p.k_pad, s_hist, s_misc, s_red);
-        kth = n_out == p.keep ? sorted[p.keep - 1] : 0ULL;
     }
     if (!p.last) {
         for (int i = tid; i < n_out; i += NT) p.topk_keys[(int64_t)q * p.K + i] = sorted[i];

@@ -7,6 +7,7 @@ import torch
 from oracle import st_oracle as O
 from paper_2511_14881_amd import binding as st
 from paper_2511_14881_amd import synth as S
+from tests.test_gpu_parity import check_search, ragged_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -56,3 +57,25 @@ def test_captured_search_replays_beside_eager_calls(n):
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(a, b) for a, b in zip((buf.ids, buf.scores, buf.count), want))
+
+
+# The final ordering of K > 2048 cuts the score range into steps: scores of one size, a few far above the rest
+# (cut again), spread over many powers of two, infinite ones, hundreds of keys to a score (general path), fewer
+# passing items than K; one round of the key buffer and several.
+@pytest.mark.parametrize("K", [2049, 16384, 17409, 40_000])
+@pytest.mark.parametrize("kind", ["plain", "outliers", "spread", "ties", "few"])
+def test_ordering_of_large_results(K, kind):
+    n, B = 60_000, 3
+    w = ragged_workload(900 + K, n, 16, B, 10, 3, 64, 2)
+    w.filt_ids, w.filt_offsets = np.array([3], np.uint64), np.array([0, 1, 1, 1], np.int64)
+    if kind == "outliers":
+        w.item_scale[5::n // 7] *= 1e30
+        w.item_scale[77] = float("inf")
+    elif kind == "spread":
+        w.item_scale = torch.from_numpy(np.exp2(np.random.default_rng(K).uniform(-60, 60, n)).astype(np.float32))
+    elif kind == "ties":
+        w.items = w.items[:60].repeat(n // 60, 1).contiguous()
+        w.item_scale = w.item_scale[:60].repeat(n // 60).contiguous()
+    elif kind == "few":
+        w.filt_ids, w.filt_offsets = np.arange(9, dtype=np.uint64), np.array([0, 3, 6, 9], np.int64)
+    check_search(w, K, label=f"ordering {kind}")
