@@ -7,6 +7,7 @@
 
 #include <algorithm>
 #include <atomic>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -115,22 +116,25 @@ struct StageMark {
     uint64_t* dev_view = nullptr;  // the same word as the device addresses it
     uint64_t number = 0;           // of the current or latest use
     int device = 0;
-    bool retired = false;          // used under stream capture: every replay of the graph reads the slot again
 };
 
 bool stage_mark_done(void* e)
 {
     const StageMark* m = (const StageMark*)e;
-    return !m->retired && __atomic_load_n(m->seen, __ATOMIC_ACQUIRE) >= m->number;
+    return __atomic_load_n(m->seen, __ATOMIC_ACQUIRE) >= m->number;
 }
 
 int stage_mark_wait(void* e)
 {
     StageMark* m = (StageMark*)e;
-    if (m->retired) return (int)ST_EHIP;
-    for (int i = 0; i < 2000; ++i) {  // (a millisecond or so: the slot's kernels are already enqueued)
+    // The slot's kernels are enqueued already, so this ends by itself.  (Waiting for the device would do as
+    // well, but not while another thread captures a graph; it is left for a device that has failed.)
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int i = 1;; ++i) {
         if (stage_mark_done(e)) return 0;
-        std::this_thread::yield();
+        if (i <= 2000) std::this_thread::yield();
+        else std::this_thread::sleep_for(std::chrono::microseconds(20));
+        if (i % 2000 == 0 && std::chrono::steady_clock::now() - t0 > std::chrono::seconds(10)) break;
     }
     int current = 0;
     if (hipGetDevice(&current) != hipSuccess) return (int)ST_EHIP;
@@ -145,6 +149,7 @@ struct StageHold {
     hipStream_t stream = nullptr;
     bool enqueued = false;  // work that reads the slot is on the stream
     bool recorded = false;  // ... and behind it a kernel that stores the number of this use
+    bool captured = false;  // ... in a graph: every replay reads the slot again
     void* host() const { return s->host; }
     void* dev_view() const { return s->dev_view; }
     StageMark* mark() const { return (StageMark*)s->event; }
@@ -153,14 +158,15 @@ struct StageHold {
     {
         hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
         if (hipStreamIsCapturing(stream, &st) != hipSuccess) (void)hipGetLastError();
-        else if (st != hipStreamCaptureStatusNone) mark()->retired = true;
+        else if (st != hipStreamCaptureStatusNone) captured = true;
         recorded = true;
     }
     void release()
     {
         if (!s) return;
         if (enqueued && !recorded) (void)hipStreamSynchronize(stream);
-        g_pool.release(s, recorded);
+        if (captured) g_pool.keep(s);
+        else g_pool.release(s, recorded);
         s = nullptr;
     }
     ~StageHold() { release(); }
@@ -169,22 +175,63 @@ struct StageHold {
 // Set while st_search_static runs in the calling thread: nothing may be allocated then.
 thread_local bool t_no_alloc = false;
 
+int stage_mark_new(void** event)
+{
+    StageMark m;
+    ST_HIP(hipHostMalloc((void**)&m.seen, 64, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
+    *m.seen = 0;
+    ST_HIP(hipHostGetDevicePointer((void**)&m.dev_view, m.seen, 0));
+    *event = new StageMark(m);
+    return ST_OK;
+}
+
+constexpr size_t kStageBytes = 64 * 1024;  // of a slot, at least
+
+// The slot that a captured call used gets other memory, at the next call that may allocate; what it had
+// stays with the graph, which may be replayed for as long as the program runs.
+void stage_refill(hipStream_t stream)
+{
+    if (t_no_alloc) return;
+    st::StageSlot* s = g_pool.take_kept();
+    if (!s) return;
+    st::StageSlot fresh;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    bool ok = hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another thread may be capturing)
+    if (ok && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
+        ok = stage_mark_new(&fresh.event) == ST_OK && hipHostMalloc(&fresh.host, kStageBytes, hipHostMallocDefault) == hipSuccess &&
+             hipHostGetDevicePointer(&fresh.dev_view, fresh.host, 0) == hipSuccess;
+        (void)hipThreadExchangeStreamCaptureMode(&mode);
+    } else {
+        ok = false;
+    }
+    if (!ok) {
+        (void)hipGetLastError();
+        g_pool.keep(s);
+        return;
+    }
+    s->host = fresh.host;
+    s->dev_view = fresh.dev_view;
+    s->event = fresh.event;
+    s->bytes = kStageBytes;
+    g_pool.release(s, false);
+}
+
 int stage_get(size_t bytes, hipStream_t stream, StageHold* h)
 {
     st::StageSlot* s = nullptr;
-    if (g_pool.acquire(stage_mark_done, stage_mark_wait, &s) != 0)
-        return fail(ST_EHIP, "waiting for a staging slot failed");
+    stage_refill(stream);
+    const int got = g_pool.acquire(stage_mark_done, stage_mark_wait, &s);
+    if (got == st::StagePool::kNoSlot) return fail(ST_EHIP, "captured graphs hold every staging slot");
+    if (got != 0) return fail(ST_EHIP, "waiting for a staging slot failed");
     h->s = s;
     h->stream = stream;
     if (t_no_alloc && (!s->event || s->bytes < bytes))
         return fail(ST_EINVAL, "the tables of this batch (%zu bytes) exceed the pre-allocated staging slots (%zu bytes)",
                     bytes, s->bytes);
     if (!s->event) {
-        StageMark m;
-        ST_HIP(hipHostMalloc((void**)&m.seen, 64, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent));
-        *m.seen = 0;
-        ST_HIP(hipHostGetDevicePointer((void**)&m.dev_view, m.seen, 0));
-        s->event = new StageMark(m);
+        const int rc = stage_mark_new(&s->event);
+        if (rc != ST_OK) return rc;
     }
     ++h->mark()->number;
     ST_HIP(hipGetDevice(&h->mark()->device));
@@ -192,7 +239,7 @@ int stage_get(size_t bytes, hipStream_t stream, StageHold* h)
         if (s->host) ST_HIP(hipHostFree(s->host));
         s->host = nullptr;
         s->bytes = 0;
-        const size_t want = std::max<size_t>(bytes, 64 * 1024);
+        const size_t want = std::max<size_t>(bytes, kStageBytes);
         ST_HIP(hipHostMalloc(&s->host, want, hipHostMallocDefault));
         s->bytes = want;
         ST_HIP(hipHostGetDevicePointer(&s->dev_view, s->host, 0));
@@ -222,7 +269,7 @@ int device_setup(int device)
     for (int i = 0; i < st::kStageSlots; ++i) {
         // slots nobody has used yet (a slot in use has its memory and event already)
         StageHold h;
-        const int rc = stage_get(64 * 1024, nullptr, &h);
+        const int rc = stage_get(kStageBytes, nullptr, &h);
         if (rc != ST_OK) return rc;
     }
     return ST_OK;

@@ -59,6 +59,37 @@ def test_captured_search_replays_beside_eager_calls(n):
         assert all(torch.equal(a, b) for a, b in zip((buf.ids, buf.scores, buf.count), want))
 
 
+# More captured calls than there are staging slots, all kept for replay, and queues of eager calls between them.
+def test_more_graphs_than_staging_slots():
+    n = 20_000
+    w = S.make_workload(S.scaled(S.CONFIGS["mid"], n, batch=9, top_k=20), "cuda")
+    cfg = w.cfg
+    bloom = st.st_bloom_build(w.feat_offsets, w.feat_ids, n, cfg.m_bits, cfg.k_hashes)
+
+    def call(buf):
+        return st.st_search(bloom, w.items, w.item_scale, w.queries, w.query_scale, w.filt_ids, w.filt_offsets, cfg.top_k,
+                            buffers=buf)
+
+    bufs = [st.SearchBuffers(n, cfg.d, 9, 1, cfg.top_k) for _ in range(19)]
+    want = [t.clone() for t in call(bufs[18])]
+    torch.cuda.synchronize()
+    graphs = []
+    for i in range(18):
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[i]):
+            call(bufs[i])
+        for _ in range(40):
+            call(bufs[18])
+    for _ in range(2):
+        for g, b in zip(graphs, bufs):
+            for t in (b.ids, b.scores, b.count):
+                t.zero_()
+            g.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(a, c) for a, c in zip((b.ids, b.scores, b.count), want))
+            call(bufs[18])
+
+
 # The final ordering of K > 2048 cuts the score range into steps: scores of one size, a few far above the rest
 # (cut again), spread over many powers of two, infinite ones, hundreds of keys to a score (general path), fewer
 # passing items than K; one round of the key buffer and several.
