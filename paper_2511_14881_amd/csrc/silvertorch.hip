@@ -1769,26 +1769,24 @@ int st_search_ivf(const st_bloom* bloom, const int8_t* dev_items, const float* d
             qp.out_count = dev_out_count;
             qp.ovf = (uint32_t*)(ws + L.ovf);
             qp.part_cnt = q_parts;
-            // Workgroups per query: enough to occupy the chip, as long as every part's share of the
-            // key buffer holds a round beside the K keys it keeps, the parts' survivors fit the final
-            // selection in LDS together, and the result is sorted in LDS.
+            // Workgroups per query: as many as occupy the chip (one to a compute unit: the LDS), while each has
+            // a wavefront's words at least and its share of the key buffer holds some rounds beside the K
+            // keys it keeps.
+            const int64_t scratch = L.k_pad > st::kLdsSortMax ? L.k_pad : 0;
+            auto fits = [&](int pp) { return pp <= st::kQueryParts && L.gath_cap / pp - scratch >= 2 * (int64_t)K + 64 * 64; };
+            const int64_t words = (int64_t)n_probe * (n_items / std::max(n_clusters, 1) / 64 + 1);
             int parts = 1;
-            if (!qp.srt) {
-                auto fits = [&](int pp) {
-                    return pp <= st::kQueryParts && (int64_t)pp * K <= (int64_t)st::kTopkRegs * st::kQueryThreads &&
-                           L.gath_cap / pp >= 2 * (int64_t)K + 64 * st::kQueryThreads;
-                };
-                while (fits(parts * 2) && batch * parts * 2 <= st::kComputeUnits) parts *= 2;
-                // a large batch fills the chip by itself, but queries with many probed words still gain
-                // from parts (the longest query sets the kernel's duration): two rounds per part at least
-                const int64_t words = (int64_t)n_probe * (n_items / std::max(n_clusters, 1) / 64 + 1);
-                while (fits(parts * 2) && words / parts > 2 * st::kQueryThreads) parts *= 2;
-            }
+            while (fits(parts * 2) && batch * parts * 2 <= st::kComputeUnits && words / (parts * 2) >= 64) parts *= 2;
+            // a large batch fills the chip by itself, but queries with many probed words still gain
+            // from parts (the longest query sets the kernel's duration): two rounds per part at least
+            while (fits(parts * 2) && words / parts > 2 * st::kQueryThreads) parts *= 2;
+            qp.part_cap = L.gath_cap / parts;
+            qp.part_keys = qp.part_cap - (parts > 1 ? scratch : 0);
+            qp.part_keep = std::max(K, st::kMergeKeys / parts);
             {
                 TimedLaunch t(0, stream);
                 hipLaunchKernelGGL(st::ivf_query_kernel, dim3(batch, parts), dim3(st::kQueryThreads), 0, stream, qp);
-                if (parts > 1)
-                    hipLaunchKernelGGL(st::ivf_merge_kernel, dim3(batch), dim3(st::kQueryThreads), 0, stream, qp, parts);
+                hipLaunchKernelGGL(st::ivf_merge_kernel, dim3(batch), dim3(st::kMergeThreads), 0, stream, qp, parts);
             }
             ST_HIP(hipGetLastError());
             return ST_OK;

@@ -4,8 +4,8 @@
 // Phase 1 (ivf_probe_kernel): one workgroup per query scores every centroid like an item
 // (int8 dot, two fp32 multiplies), and an exact top-n_p by (score descending, cluster id
 // ascending) gives the probed clusters.
-// Phases 2-4, up to kQueryProbes probes (ivf_query_kernel): one workgroup per query filters and
-// scores the items of its probed ranges alone and selects the top K.
+// Phases 2-4, up to kQueryProbes probes (ivf_query_kernel): the workgroups of a query filter and
+// score the items of its probed ranges alone, ivf_merge_kernel selects and orders the top K.
 // Phase 2, any number of probes (ivf_mask_kernel): 32 threads per (query, probed cluster) run the
 // query's filter program only over the words of that cluster's range and OR the result into the
 // query's row of a bit-sliced mask index (zeroed beforehand), laid out like the Bloom index; phases
@@ -189,16 +189,21 @@ __global__ __launch_bounds__(256) void ivf_mask_kernel(const uint64_t* __restric
 }
 
 // ------------------------------------------------------------------------------------------
-// Phases 2-4 in one kernel, for up to kQueryProbes probes: one workgroup per query walks the
-// words of its probed clusters (all of them laid end to end, one word per thread and round), runs
-// the filter program on each word, scores the items that pass itself (one v_dot4 row product per
-// set bit), appends their keys to the query's buffer and prunes the buffer to the best K whenever
-// it cannot take another round; the final selection writes the result rows.  The work is
-// proportional to the probed items, nothing is written for the rest of the corpus, and no
-// candidate can be lost (no regions, no thresholds from elsewhere).
+// Phases 2-4 for up to kQueryProbes probes: the workgroups of a query (its parts) walk the words of
+// its probed clusters (all of them laid end to end, one word per thread and round, the parts taking
+// rounds in turn), run the filter program on each word, score the items that pass themselves (one
+// v_dot4 row product per set bit) and append their keys to their share of the query's buffer,
+// which is pruned to the best K whenever it cannot take another round.  A merge kernel selects and orders what
+// the parts kept.  The work is proportional to the probed items, nothing is written for the rest of
+// the corpus, and no candidate can be lost (no regions, no thresholds from elsewhere).
+//
+// Bound by chains of memory round trips (program leaves, then item rows), so it wants many short
+// parts with all wavefronts scoring: 20 M x 128, 16 queries, K = 2048, 32 of 4096 clusters probed take
+// 88 us a call with 16 parts a query, against 162 us with 4 (what a merge in LDS had room for) and a
+// list of passing items per wavefront.
 constexpr int kQueryThreads = 512;
 constexpr int kQueryProbes = 512;   // one probe per thread when the ranges are laid out
-constexpr int kQueryParts = 8;      // workgroups per query, at most
+constexpr int kQueryParts = 16;     // workgroups per query, at most (powers of two)
 
 struct IvfQueryParams {
     IvfParams ivf;
@@ -209,14 +214,15 @@ struct IvfQueryParams {
     const int32_t *prog_off, *code, *leaf_rows;
     uint64_t* gath;            // [batch][gath_cap] key buffer
     int64_t gath_cap;
-    uint64_t* srt;             // [batch][k_pad] when k_pad > kLdsSortMax, else null
+    int64_t part_cap;          // keys of one part's share of the buffer
+    int64_t part_keys;         // ... of which keys are gathered in; the rest (several parts, k_pad above the LDS sort size) is the prune's scratch
+    int32_t part_keep;         // a part hands on all its keys if they are no more than this (>= K), else its best K
+    uint64_t* srt;             // [batch][k_pad] when k_pad > kLdsSortMax, else null (merge's general way, prune of a lone part)
     int32_t K, k_pad;
     int64_t* out_ids;
     float* out_scores;
     int32_t* out_count;
     uint32_t* ovf;             // [batch] "took the slow exact path" flags of the workspace: reset (this path has none)
-    // several workgroups per query (grid.y = parts <= kQueryParts): each takes every parts-th round
-    // with its own share of the key buffer and keeps its best K; ivf_merge_kernel merges them
     uint32_t* part_cnt;        // [batch][kQueryParts] keys each part kept
 };
 
@@ -233,7 +239,9 @@ __global__ __launch_bounds__(kQueryThreads) void ivf_query_kernel(IvfQueryParams
     __shared__ int64_t s_word[kQueryThreads];  // first item of the word each thread evaluated this round
     const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, b = blockIdx.x;
     const IvfParams& v = p.ivf;
-    static_assert(sizeof(s_stack) >= (size_t)kTopkRegs * kQueryThreads * 8, "the stack doubles as the final key buffer");
+    static_assert(sizeof(s_stack) >= (size_t)kTopkRegs * kQueryThreads * 8, "the stack doubles as a key buffer");
+    static_assert(sizeof(s_stack) >= (size_t)kQueryThreads * 64 * 2, "... and as the list of a round's passing items");
+    static_assert(kQueryThreads * 64 <= 65536, "an entry of that list has 16 bits");
 
     // the program, and the item ranges of the probed clusters (clipped to the corpus)
     const int i0 = p.prog_off[b], n_ops = p.prog_off[b + 1] - i0;
@@ -273,9 +281,9 @@ __global__ __launch_bounds__(kQueryThreads) void ivf_query_kernel(IvfQueryParams
     __syncthreads();
 
     const int part = blockIdx.y, parts = gridDim.y;
-    const int64_t cap = p.gath_cap / parts;  // this workgroup's share of the query's key buffer
-    uint64_t* buf = p.gath + (int64_t)b * p.gath_cap + part * cap;
-    uint64_t* sorted = p.srt ? p.srt + (int64_t)b * p.k_pad : s_sorted;
+    const int64_t cap = p.part_keys;
+    uint64_t* buf = p.gath + (int64_t)b * p.gath_cap + part * p.part_cap;
+    uint64_t* sorted = p.k_pad <= kLdsSortMax ? s_sorted : parts > 1 ? buf + cap : p.srt + (int64_t)b * p.k_pad;
     uint32_t* s_n = &s_misc[4];
     int64_t qoff[kRowBlock];
 #pragma unroll
@@ -316,100 +324,143 @@ __global__ __launch_bounds__(kQueryThreads) void ivf_query_kernel(IvfQueryParams
             const uint64_t* wbase = p.bloom + ((gw >> 4) * (int64_t)p.m_bits) * kTileWords + (gw & 15);
             m = expr_eval_word(s_code, s_rows, n_ops, p.k_hashes, wbase, s_stack, tid) & in;
         }
-        // The wavefront's passing items, dealt out evenly over its lanes: every lane lists its set
-        // bits as (lane, bit) pairs in the wavefront's own columns of the stack (free once the words
-        // are evaluated; 16 rows x 64 columns x 8 bytes = 4096 pairs, the most 64 words can hold).
+        // The round's passing items, dealt out evenly over the workgroup's threads: every thread lists
+        // its set bits as (thread, bit) pairs in the stack's memory, which is free once all words are
+        // evaluated.  (A part with few words has them in its first wavefronts alone; a list per
+        // wavefront left the others without items to score.)
         s_word[tid] = first;
-        const int cnt = __popcll(m);
-        int inc = cnt;
-        inc = (int)wave_scan_add((uint32_t)inc);
-        const int wave_total = (int)lane_value((uint32_t)inc, 63);
-        auto pair_at = [&](int e) -> uint16_t* {
-            return reinterpret_cast<uint16_t*>(&s_stack[e >> 8][wv * 64]) + (e & 255);
-        };
-        {
-            int e = inc - cnt;
-            uint64_t mm = m;
-            while (mm) {
-                const int bit = __ffsll((long long)mm) - 1;
-                mm &= mm - 1;
-                *pair_at(e++) = (uint16_t)((lane << 6) | bit);
-            }
-        }
+        const uint32_t cnt = (uint32_t)__popcll(m);
+        const uint32_t inc = wave_scan_add(cnt);
+        if (lane == 63) s_wsum[wv] = inc;
         __syncthreads();
-        for (int k = lane; k < wave_total; k += 64) {
-            const int pr = *pair_at(k);
-            const int64_t item = s_word[wv * 64 + (pr >> 6)] + (pr & 63);
+        uint32_t at = inc - cnt, n_pairs = 0;
+        for (int w = 0; w < kQueryThreads / 64; ++w) {
+            const uint32_t t = s_wsum[w];
+            if (w < wv) at += t;
+            n_pairs += t;
+        }
+        uint16_t* pairs = reinterpret_cast<uint16_t*>(&s_stack[0][0]);
+        while (m) {
+            const int bit = __ffsll((long long)m) - 1;
+            m &= m - 1;
+            pairs[at++] = (uint16_t)((tid << 6) | bit);
+        }
+        const uint32_t n_before = *s_n;
+        __syncthreads();
+        for (uint32_t k = tid; k < n_pairs; k += kQueryThreads) {
+            const uint32_t pr = pairs[k];
+            const int64_t item = s_word[pr >> 6] + (pr & 63);
             // (query chunks through the scalar cache, item chunks four loads at a time)
             int acc[kRowBlock] = {0, 0, 0, 0, 0, 0, 0, 0};
             dot_block<1>(reinterpret_cast<const int4*>(p.items + item * v.d), v.queries, qoff, v.d >> 4, acc);
             const float sc = rescale(acc[0], sq, p.iscale[item]);
             const uint64_t key = make_key(sc, (uint32_t)item);
-            if (key >= tau) buf[atomicAdd(s_n, 1u)] = key;
+            // (without a threshold every key stays: its place is known)
+            if (tau == 0) buf[n_before + k] = key;
+            else if (key >= tau) buf[atomicAdd(s_n, 1u)] = key;
         }
+        if (tau == 0 && tid == 0) *s_n = n_before + n_pairs;
         __syncthreads();
     }
     uint32_t n_keys = *s_n;
-    if (parts > 1) {
+    if (n_keys > (uint32_t)p.part_keep) {
         // keep this part's best K (unordered) at the head of its share
-        if (n_keys > (uint32_t)p.K) {
-            uint64_t kth;
-            int kept;
-            if (n_keys <= (uint32_t)(kTopkRegs * kQueryThreads)) {  // register-resident select on a copy in LDS
-                uint64_t* s_keys = &s_stack[0][0];
-                __syncthreads();
-                for (uint32_t i = tid; i < n_keys; i += kQueryThreads) s_keys[i] = buf[i];
-                __syncthreads();
-                kept = lds_topk(s_keys, (int)n_keys, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, false, kth);
-                __syncthreads();
-            } else {
-                kept = wg_topk(buf, (int64_t)n_keys, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, false, &kth);
-            }
-            for (int i = tid; i < kept; i += kQueryThreads) buf[i] = s_sorted[i];
-            n_keys = (uint32_t)kept;
-        }
-        // the merge is a kernel of its own (ivf_merge_kernel): a device-wide fence here, for a
-        // last-finisher merge in this kernel, measured 30 us per workgroup
-        if (tid == 0) p.part_cnt[b * kQueryParts + part] = n_keys;
-        return;
-    }
-    // final selection: in LDS (the stack is free now) when the keys and the result fit there
-    int n_out;
-    if (!p.srt && n_keys <= (uint32_t)(kTopkRegs * kQueryThreads)) {
-        uint64_t* s_keys = &s_stack[0][0];
-        __syncthreads();
-        for (uint32_t i = tid; i < n_keys; i += kQueryThreads) s_keys[i] = buf[i];
-        __syncthreads();
         uint64_t kth;
-        n_out = lds_topk(s_keys, (int)n_keys, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, true, kth);
-    } else {
-        n_out = wg_topk(buf, (int64_t)n_keys, p.K, sorted, p.k_pad, s_hist, s_misc, s_red);
+        int kept;
+        if (p.k_pad <= kLdsSortMax && n_keys <= (uint32_t)(kTopkRegs * kQueryThreads)) {  // register-resident select on a copy in LDS
+            uint64_t* s_keys = &s_stack[0][0];
+            for (uint32_t i = tid; i < n_keys; i += kQueryThreads) s_keys[i] = buf[i];
+            __syncthreads();
+            kept = lds_topk(s_keys, (int)n_keys, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, false, kth);
+            __syncthreads();
+        } else {
+            kept = wg_topk(buf, (int64_t)n_keys, p.K, sorted, p.k_pad, s_hist, s_misc, s_red, false, &kth);
+        }
+        for (int i = tid; i < kept; i += kQueryThreads) buf[i] = sorted[i];
+        n_keys = (uint32_t)kept;
     }
-    write_result(sorted, n_out, p.K, p.out_ids + (int64_t)b * p.K, p.out_scores + (int64_t)b * p.K, p.out_count + b);
+    // the merge is a kernel of its own (ivf_merge_kernel): a device-wide fence here, for a
+    // last-finisher merge in this kernel, measured 30 us per workgroup
+    if (tid == 0) p.part_cnt[b * kQueryParts + part] = n_keys;
 }
 
-// Merge of the parts' survivors (at most kTopkRegs * kQueryThreads keys per query: the host chooses
-// the number of parts accordingly): one workgroup per query, selection and sort in LDS.
-__global__ __launch_bounds__(kQueryThreads) void ivf_merge_kernel(IvfQueryParams p, int parts)
+// Keys the parts of a query hand on together, as a target (each at least K): the merge reads them three times.
+constexpr int kMergeKeys = 16384;
+
+// Selection and order of what the parts of a query handed on: one workgroup per query, by buckets of the
+// score over the keys where they lie, a share of the wavefronts to each part.  Bound by the latency of three
+// passes over the keys (figures above).
+constexpr int kMergeThreads = 1024;
+constexpr int kMergeRoom = 8192;
+static_assert(kOrderBins * 4 >= kLdsSortMax * 8, "the general way's result borrows the counters");
+__global__ __launch_bounds__(kMergeThreads) void ivf_merge_kernel(IvfQueryParams p, int parts)
 {
-    __shared__ uint64_t s_keys[kTopkRegs * kQueryThreads];
-    __shared__ uint64_t s_sorted[kLdsSortMax];
-    __shared__ uint32_t s_hist[3 * 256], s_misc[8];
+    __shared__ uint64_t s_keys[kMergeRoom];
+    __shared__ uint64_t s_bins[kOrderBins / 2];
+    __shared__ uint32_t s_hist[256], s_misc[8], s_wsum[kMergeThreads / 64];
     __shared__ uint64_t s_red[32];
-    const int tid = threadIdx.x, b = blockIdx.x;
-    const int64_t cap = p.gath_cap / parts;
-    uint32_t at = 0;
+    constexpr int NW = kMergeThreads / 64;
+    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, b = blockIdx.x;
+    uint64_t* keys = p.gath + (int64_t)b * p.gath_cap;
+    auto held = [&](int pp) {  // (a part hands on no more than its share holds, whatever the memory says)
+        const uint32_t c = p.part_cnt[b * kQueryParts + pp];
+        return c < (uint32_t)p.part_keys ? c : (uint32_t)p.part_keys;
+    };
+    static_assert(kQueryParts <= NW, "every part has a wavefront of its own");
+    uint32_t total = 0;
+    for (int pp = 0; pp < parts; ++pp) total += held(pp);
+    const int per = NW / parts, mine = wv / per;  // (parts is a power of two)
+    const uint32_t n_mine = held(mine);
+    const uint64_t* src = keys + mine * p.part_cap;
+    const uint32_t first = (uint32_t)((wv % per) * 64 + lane), step = (uint32_t)per * 64;
+    auto each = [&](auto&& f) {
+        for (uint32_t i0 = first; ballot(i0 < n_mine) != 0; i0 += 8 * step) {
+            uint64_t v[8];
+#pragma unroll
+            for (uint32_t u = 0; u < 8; ++u)
+                if (i0 + u * step < n_mine) v[u] = src[i0 + u * step];
+#pragma unroll
+            for (uint32_t u = 0; u < 8; ++u)
+                if (i0 + u * step < n_mine) f(v[u]);
+        }
+    };
+    const uint32_t want = total < (uint32_t)p.K ? total : (uint32_t)p.K;
+    int64_t* ids = p.out_ids + (int64_t)b * p.K;
+    float* scores = p.out_scores + (int64_t)b * p.K;
+    const bool ordered = want == 0 ||
+        bucket_order<kMergeThreads>(each, want, (uint32_t)kMergeRoom, s_keys, reinterpret_cast<uint32_t*>(s_bins), s_misc, s_red,
+                                    s_wsum, [&](uint32_t rank, uint64_t key) {
+                                        if (rank < want) {
+                                            ids[rank] = (int64_t)key_item(key);
+                                            scores[rank] = key_score(key);
+                                        }
+                                    });
+    if (ordered) {
+        for (int i = (int)want + tid; i < p.K; i += kMergeThreads) {
+            ids[i] = -1;
+            scores[i] = -__builtin_inff();
+        }
+        if (tid == 0) p.out_count[b] = (int32_t)want;
+        return;
+    }
+    // many equal scores: the general way over the keys moved together (a step's keys are read before any of
+    // them is written; they only move down)
+    int64_t at = 0;
     for (int pp = 0; pp < parts; ++pp) {
-        uint32_t c = p.part_cnt[b * kQueryParts + pp];
-        c = c < (uint32_t)p.K ? c : (uint32_t)p.K;  // (a part keeps at most K, whatever the memory says)
-        const uint64_t* src = p.gath + (int64_t)b * p.gath_cap + pp * cap;
-        for (uint32_t i = tid; i < c; i += kQueryThreads) s_keys[at + i] = src[i];
+        const uint32_t c = held(pp);
+        for (uint32_t i0 = 0; i0 < c; i0 += kMergeThreads) {
+            __syncthreads();
+            const uint64_t k = i0 + tid < c ? keys[pp * p.part_cap + i0 + tid] : 0ULL;
+            __syncthreads();
+            if (i0 + tid < c) keys[at + i0 + tid] = k;
+        }
         at += c;
     }
+    __threadfence_block();
     __syncthreads();
-    uint64_t kth;
-    const int n_fin = lds_topk(s_keys, (int)at, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, true, kth);
-    write_result(s_sorted, n_fin, p.K, p.out_ids + (int64_t)b * p.K, p.out_scores + (int64_t)b * p.K, p.out_count + b);
+    uint64_t* sorted = p.srt ? p.srt + (int64_t)b * p.k_pad : s_bins;
+    const int n_out = wg_topk(keys, at, p.K, sorted, p.k_pad, s_hist, s_misc, s_red);
+    write_result(sorted, n_out, p.K, ids, scores, p.out_count + b);
 }
 
 __global__ __launch_bounds__(256) void fill_zero_kernel(uint64_t* __restrict__ dst, int64_t n)

@@ -633,7 +633,7 @@ __device__ inline int lds_topk(uint64_t* keys, int n, int K, uint64_t* sorted, i
 //
 // each(f) calls f(key) for this thread's share of the keys, the same ones on every call; emit(rank, key)
 // is called once for every rank below `want` and for some ranks above (the caller drops them).
-// The set must hold `want` keys at least, all distinct; want >= 1.
+// The set must hold `want` keys at least; want >= 1.  (A key that occurs twice takes two ranks.)
 constexpr int kOrderBins = 4096;
 constexpr uint32_t kOrderStepKeys = 512;  // keys of one step ranked against each other, at most
 
@@ -736,7 +736,7 @@ __device__ inline bool bucket_order(Each&& each, uint32_t want, uint32_t room, u
 #pragma unroll
                 for (uint32_t u = 0; u < 4; ++u) o[u] = s_out[min(j0 + u, p1 - 1)];
 #pragma unroll
-                for (uint32_t u = 0; u < 4; ++u) rank += (j0 + u < p1 && o[u] > key) ? 1u : 0u;
+                for (uint32_t u = 0; u < 4; ++u) rank += (j0 + u < p1 && (o[u] > key || (o[u] == key && j0 + u < i))) ? 1u : 0u;
             }
             emit(done + rank, key);
         }
