@@ -22,6 +22,7 @@
 #include "st_bloom_kernels.h"
 #include "st_mfma_kernels.h"
 #include "st_ivf_kernels.h"
+#include "st_own_kernels.h"
 #include "st_quant_kernels.h"
 #include "st_vm_kernels.h"
 #include "st_plan.h"
@@ -1249,6 +1250,12 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
     bool mfma_started = false;  // the first MFMA launch builds the resident-query image
     bool density_on = false;    // the first level counts the pairs it admits (chooses the later levels' form of the scan)
+    // Batches that hardly share filters: from the second level on all pairs are multiplied, see st_own_kernels.h.
+    // (One task, no weights; with fewer than 16 queries more than half of the products would be padding.)
+    const auto own_scan = g_scoring_path == 0 && n_tasks == 1 && !weighted && set_dot.q_list.size() >= 16 && sp_d.m_bits <= st::kOwnRows &&
+                                  set_dot.rows.size() <= (size_t)st::kOwnRowRefs
+                              ? st::own_kernel(d)
+                              : nullptr;
     int seed_parts = 1;         // slices per query of the seed pass (one threshold each)
     for (int lv = 0; lv < plan.n_levels; ++lv) {
         const st::Level& L_ = plan.level[lv];
@@ -1365,7 +1372,23 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             TimedLaunch t(0, stream);
             ST_HIP(st::launch_scan_mfma(sp_m, mp, gx, stream));
         }
-        if (set_dot.n) {
+        if (set_dot.n && own_scan && lv > 0 && L_.end - L_.begin >= st::kOwnMinItems && L_.begin % st::kOwnSeg == 0) {
+            st::ScanParams sp_o = sp_d;
+            const int64_t n_own = (L_.end - L_.begin + st::kOwnSeg - 1) / st::kOwnSeg;
+            sp_o.seg_items = st::kOwnSeg;
+            sp_o.seg_per_visit = (int32_t)std::max<int64_t>(1, std::min<int64_t>(4, n_own / plan.groups));
+            const size_t lds = st::own_lds_bytes((int)set_dot.q_list.size(), d, sp_o.m_bits);
+            static std::atomic<bool> lds_set[9] = {};  // (setting the attribute twice is harmless)
+            if (!lds_set[d / 32].load(std::memory_order_acquire)) {
+                ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(own_scan), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           160 * 1024));
+                lds_set[d / 32].store(true, std::memory_order_release);
+            }
+            TimedLaunch t(0, stream);
+            hipLaunchKernelGGL(own_scan, dim3(std::min(plan.groups, st::kComputeUnits), (set_dot.q_list.size() + st::kOwnCols - 1) / st::kOwnCols),
+                               dim3(st::kOwnThreads), lds, stream, sp_o, (int)set_dot.rows.size());
+            ST_HIP(hipGetLastError());
+        } else if (set_dot.n) {
             TimedLaunch t(0, stream);
             hipLaunchKernelGGL(st::scan_wavedot_kernel, dim3(plan.groups), dim3(st::kScanThreads),
                                (size_t)((batch + 1) & ~1) * 4 + (size_t)batch * 8, stream, sp_d);

@@ -90,6 +90,28 @@ def test_more_graphs_than_staging_slots():
             call(bufs[18])
 
 
+# Batches whose queries hardly share filters (the products of all pairs, or of the passing ones where a wavefront has
+# few): row lengths of every variant, one query block and several, two rows of the grid, ragged last segment
+# and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores.
+@pytest.mark.parametrize("n,d,B,m,kind", [(600_001, 64, 16, 64, "mixed"), (530_049, 96, 33, 100, "mixed"),
+                                          (400_003, 128, 130, 512, "mixed"), (524_288 + 31, 192, 40, 257, "mixed"),
+                                          (420_000, 256, 300, 128, "mixed"), (600_000, 64, 64, 512, "rare"),
+                                          (350_000, 128, 140, 512, "rare"), (400_001, 64, 150, 128, "ties")])
+def test_own_filters(n, d, B, m, kind):
+    w = ragged_workload(n, n, d, B, 40, 8, m, 3)
+    filters = []
+    for b in range(B):
+        one = [(b // 3) % 40]
+        two = [b % 40, (7 * b + b // 40 + 1) % 40]
+        filters.append([] if b == 0 else [999] if b == 1 else one if b % 3 == 0 and kind != "rare" else two + [(b * 11 + 3) % 40] * (b % 2))
+    w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
+    w.filt_offsets = np.concatenate([[0], np.cumsum([len(f) for f in filters])]).astype(np.int64)
+    if kind == "ties":
+        w.items = w.items[:997].repeat(n // 997 + 1, 1)[:n].contiguous()
+        w.item_scale = w.item_scale[:997].repeat(n // 997 + 1)[:n].contiguous()
+    check_search(w, 60, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, max(1, B // 12))}), label=f"own filters {kind}")
+
+
 # The final ordering of K > 2048 cuts the score range into steps: scores of one size, a few far above the rest
 # (cut again), spread over many powers of two, infinite ones, hundreds of keys to a score (general path), fewer
 # passing items than K; one round of the key buffer and several.
