@@ -29,6 +29,14 @@ def test_quantisation_matches_oracle(n, d):
     check(x, "normal")
 
 
+# Around the edges of a workgroup's chunk (4096 values) and of the last chunk's lanes, the extreme value last.
+@pytest.mark.parametrize("n", [3, 4, 4095, 4096, 4097, 4099, 8191, 3 * 4096 + 1029, 4096 * 4097 + 5])
+def test_chunk_edges(n):
+    x = np.random.default_rng(n).standard_normal((n, 1)).astype(np.float32)
+    x[-1, 0] = -40.0
+    check(x, "chunk edges")
+
+
 def test_special_tables():
     check(np.zeros((5, 16), np.float32), "all zero")
     check(np.zeros((0, 16), np.float32), "empty")
