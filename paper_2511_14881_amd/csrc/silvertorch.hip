@@ -188,8 +188,19 @@ int stage_mark_new(void** event)
 
 constexpr size_t kStageBytes = 64 * 1024;  // of a slot, at least
 
-// The slot that a captured call used gets other memory, at the next call that may allocate; what it had
-// stays with the graph, which may be replayed for as long as the program runs.
+// While one exists, this thread may allocate although a stream is being captured, by itself or by another
+// thread: pinned memory is no part of a graph.
+struct RelaxedCapture {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    bool ok = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    ~RelaxedCapture()
+    {
+        if (ok) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    }
+};
+
+// The slot that a captured call used gets other memory of the same size, at the next call that may allocate; what
+// it had stays with the graph, which may be replayed for as long as the program runs.
 void stage_refill(hipStream_t stream)
 {
     if (t_no_alloc) return;
@@ -198,13 +209,12 @@ void stage_refill(hipStream_t stream)
     st::StageSlot fresh;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     bool ok = hipStreamIsCapturing(stream, &cap) == hipSuccess && cap == hipStreamCaptureStatusNone;
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;  // (another thread may be capturing)
-    if (ok && hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess) {
-        ok = stage_mark_new(&fresh.event) == ST_OK && hipHostMalloc(&fresh.host, kStageBytes, hipHostMallocDefault) == hipSuccess &&
+    fresh.bytes = std::max(s->bytes, kStageBytes);
+    if (ok) {
+        RelaxedCapture relaxed;
+        ok = relaxed.ok && stage_mark_new(&fresh.event) == ST_OK &&
+             hipHostMalloc(&fresh.host, fresh.bytes, hipHostMallocDefault) == hipSuccess &&
              hipHostGetDevicePointer(&fresh.dev_view, fresh.host, 0) == hipSuccess;
-        (void)hipThreadExchangeStreamCaptureMode(&mode);
-    } else {
-        ok = false;
     }
     if (!ok) {
         (void)hipGetLastError();
@@ -214,7 +224,7 @@ void stage_refill(hipStream_t stream)
     s->host = fresh.host;
     s->dev_view = fresh.dev_view;
     s->event = fresh.event;
-    s->bytes = kStageBytes;
+    s->bytes = fresh.bytes;
     g_pool.release(s, false);
 }
 
@@ -237,6 +247,7 @@ int stage_get(size_t bytes, hipStream_t stream, StageHold* h)
     ++h->mark()->number;
     ST_HIP(hipGetDevice(&h->mark()->device));
     if (s->bytes < bytes) {  // owned and not pending: nothing reads the old memory any more
+        RelaxedCapture relaxed;
         if (s->host) ST_HIP(hipHostFree(s->host));
         s->host = nullptr;
         s->bytes = 0;
@@ -956,6 +967,43 @@ int64_t st_search_overflow_flags_offset(int64_t n_items, int32_t d, int32_t batc
 
 static int32_t plan_groups_per_row(int32_t q_split) { return st::scan_groups() / std::max(q_split, 1); }
 
+// The filter programs of an expression search: one launch evaluates every distinct one into its row of the
+// mask index, ahead of the search's own kernels.
+struct ProgramPass {
+    const st_bloom* bloom;
+    const ExprTables* tab;
+    int64_t n_words;      // of a mask row: whole tiles, the pad words become 0
+    int32_t* d_tab;       // room for the tables in the workspace
+    uint64_t* mask_rows;
+    size_t table_bytes() const { return (tab->prog_off.size() + tab->code.size() + tab->leaf_rows.size()) * 4; }
+    size_t bytes() const { return (size_t)st::round_up((int64_t)table_bytes(), 16); }  // of the staging slot
+    int enqueue(StageHold* stage) const
+    {
+        const size_t n_off = tab->prog_off.size(), n_code = tab->code.size(), n_rows = tab->leaf_rows.size();
+        int32_t* h = (int32_t*)stage->host();
+        memcpy(h, tab->prog_off.data(), n_off * 4);
+        if (n_code) memcpy(h + n_off, tab->code.data(), n_code * 4);
+        if (n_rows) memcpy(h + n_off + n_code, tab->leaf_rows.data(), n_rows * 4);
+        // small tables are read by the kernel straight from the pinned slot (each workgroup fetches
+        // its program once); larger ones are copied to the workspace first
+        const int32_t* t_dev = (const int32_t*)stage->dev_view();
+        stage->enqueued = true;
+        if (table_bytes() > 64 * 1024) {
+            ST_HIP(hipMemcpyAsync(d_tab, stage->host(), table_bytes(), hipMemcpyHostToDevice, stage->stream));
+            t_dev = d_tab;
+        }
+        dim3 grid((unsigned)((n_words + 255) / 256), (unsigned)tab->n_exprs);
+        {
+            TimedLaunch t(3, stage->stream);
+            hipLaunchKernelGGL(st::bloom_expr_kernel, grid, dim3(256), 0, stage->stream, bloom->dev, bloom->m_bits,
+                               bloom->k_hashes, bloom->n_items, n_words, t_dev, t_dev + n_off, t_dev + n_off + n_code,
+                               tab->n_exprs, mask_rows);
+        }
+        ST_HIP(hipGetLastError());
+        return ST_OK;
+    }
+};
+
 static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const float* dev_item_scale,
                        int64_t n_items, int32_t d, const int8_t* dev_queries, const float* dev_query_scale,
                        int32_t batch, int32_t n_tasks, const float* host_task_weight,
@@ -964,15 +1012,14 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                        void* dev_workspace, int64_t workspace_bytes, void* hip_stream,
                        const Groups* expr_groups = nullptr, const uint64_t* expr_rows = nullptr,
                        int32_t expr_row_count = 0, bool allow_seed = true, int32_t min_cap = 64,
-                       int32_t* dry_out = nullptr, StageHold* shared = nullptr, size_t shared_used = 0)
+                       int32_t* dry_out = nullptr, const ProgramPass* programs = nullptr)
 {
     // dry_out: host part only (st_search_host_plan): no device pointer is looked at, nothing is
     // enqueued, and the summary of the schedule goes to dry_out[8]
     // allow_seed = false: no seed pass and no thresholds tighter than the K-th best so far (both
     // rest on a prefix of the corpus, which says nothing when the passing items sit in a few item
     // ranges, as after cluster probing)
-    // shared: the staging slot of work already enqueued for this call, which holds shared_used bytes (a
-    // multiple of 16) of it; the search puts its tables behind them and reports the use of both
+    // programs: evaluates them ahead of the search; its tables share the search's staging slot
     // expr_groups: the filters were evaluated beforehand into expr_row_count mask rows at
     // expr_rows, laid out like a Bloom index; each group then tests the one row it names
     if (!bloom) return fail(ST_EINVAL, "bloom is null");
@@ -1140,15 +1187,19 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
 
     char* ws = (char*)dev_workspace;
-    StageHold own;
-    if (!shared) {
-        rc = stage_get(blob.bytes(), stream, &own);
+    // One slot for the whole call, of the bytes it holds: programs' tables, then the search's own.  (A call that
+    // is captured finds a slot of that size after any call of its shape; a bound on the bytes would have every slot
+    // grow once, some of them within captures.)
+    const size_t ahead = programs ? programs->bytes() : 0;
+    StageHold stage;
+    rc = stage_get(ahead + blob.bytes(), stream, &stage);
+    if (rc != ST_OK) return rc;
+    memcpy((char*)stage.host() + ahead, blob.data.data(), blob.bytes());
+    const char* staged = (const char*)stage.dev_view() + ahead;  // the tables as the device sees them
+    if (programs) {
+        rc = programs->enqueue(&stage);
         if (rc != ST_OK) return rc;
     }
-    StageHold& stage = shared ? *shared : own;
-    if (shared_used + blob.bytes() > stage.s->bytes) return fail(ST_EINVAL, "group tables exceed the staging slot");
-    memcpy((char*)stage.host() + shared_used, blob.data.data(), blob.bytes());
-    const char* staged = (const char*)stage.dev_view() + shared_used;  // the tables as the device sees them
     // A search that starts with the seed pass lets that kernel bring the tables over (it reads its
     // own from the pinned copy); otherwise a small kernel copies them ahead of the first one.  (A copy
     // enqueued with hipMemcpyAsync is a kernel too, but with 6 us of waiting on either side of it.)
@@ -1580,45 +1631,13 @@ int st_search_expr(const st_bloom* bloom, const int8_t* dev_items, const float* 
     uint64_t* mask_rows = (uint64_t*)(ws + st::round_up(base, 256));
     int32_t* d_tab = (int32_t*)((char*)mask_rows + n_tiles * batch * st::kTileWords * 8);
 
-    StageHold stage;
-    size_t staged_bytes = 0;
-    if (n_tiles > 0) {
-        // tables through a pinned slot, then one launch evaluates every
-        // distinct program into its row of the mask index
-        const size_t n_off = tab.prog_off.size(), n_code = tab.code.size(), n_rows = tab.leaf_rows.size();
-        const size_t bytes = (n_off + n_code + n_rows) * 4;
-        if (bytes > expr_table_bytes(batch, host_expr_offsets[batch], ST_MAX_K_HASHES))
-            return fail(ST_EINVAL, "program tables exceed their workspace slot");
-        // (one slot for the whole call: the search's own tables go behind these)
-        staged_bytes = (size_t)st::round_up((int64_t)bytes, 16);
-        rc = stage_get(staged_bytes + st::meta_bound_bytes(batch), stream, &stage);
-        if (rc != ST_OK) return rc;
-        int32_t* h = (int32_t*)stage.host();
-        memcpy(h, tab.prog_off.data(), n_off * 4);
-        if (n_code) memcpy(h + n_off, tab.code.data(), n_code * 4);
-        if (n_rows) memcpy(h + n_off + n_code, tab.leaf_rows.data(), n_rows * 4);
-        // small tables are read by the kernel straight from the pinned slot (each workgroup fetches
-        // its program once); larger ones are copied to the workspace first
-        const int32_t* t_dev = (const int32_t*)stage.dev_view();
-        stage.enqueued = true;
-        if (bytes > 64 * 1024) {
-            ST_HIP(hipMemcpyAsync(d_tab, stage.host(), bytes, hipMemcpyHostToDevice, stream));
-            t_dev = d_tab;
-        }
-        const int64_t n_words = n_tiles * st::kTileWords;  // whole tiles: the pad words become 0
-        dim3 grid((unsigned)((n_words + 255) / 256), (unsigned)tab.n_exprs);
-        {
-            TimedLaunch t(3, stream);
-            hipLaunchKernelGGL(st::bloom_expr_kernel, grid, dim3(256), 0, stream, bloom->dev, bloom->m_bits,
-                               bloom->k_hashes, n_items, n_words, t_dev, t_dev + n_off, t_dev + n_off + n_code,
-                               tab.n_exprs, mask_rows);
-        }
-        ST_HIP(hipGetLastError());
-    }
+    const ProgramPass programs{bloom, &tab, n_tiles * st::kTileWords, d_tab, mask_rows};
+    if (programs.bytes() > expr_table_bytes(batch, host_expr_offsets[batch], ST_MAX_K_HASHES))
+        return fail(ST_EINVAL, "program tables exceed their workspace slot");
     return search_impl(bloom, dev_items, dev_item_scale, n_items, d, dev_queries, dev_query_scale, batch, n_tasks,
                        host_task_weight, nullptr, nullptr, K, dev_out_ids, dev_out_scores, dev_out_count,
                        dev_workspace, base, hip_stream, &groups, mask_rows, tab.n_exprs, true, 64, nullptr,
-                       stage.s ? &stage : nullptr, staged_bytes);
+                       n_tiles > 0 ? &programs : nullptr);
     });
 }
 

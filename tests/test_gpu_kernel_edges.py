@@ -7,6 +7,7 @@ import torch
 from oracle import st_oracle as O
 from paper_2511_14881_amd import binding as st
 from paper_2511_14881_amd import synth as S
+from tests.test_gpu_expr import pack
 from tests.test_gpu_parity import check_search, ragged_workload
 
 pytestmark = pytest.mark.gpu
@@ -52,6 +53,90 @@ def test_captured_search_replays_beside_eager_calls(n):
     for _ in range(3):
         for _ in range(20):
             call(np.zeros(0, np.uint64), no_filter, other)
+        for t in (buf.ids, buf.scores, buf.count):
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((buf.ids, buf.scores, buf.count), want))
+
+
+def _programs(rng, B, vocab):
+    """One filter program per query (none for some): a AND NOT b, a OR b, or a alone."""
+    out = []
+    for b in range(B):
+        x, y = (int(v) for v in rng.integers(0, vocab, 2))
+        out.append([([], []), ([O.LEAF, O.LEAF, O.NOT, O.AND], [x, y, 0, 0]), ([O.LEAF, O.LEAF, O.OR], [x, y, 0]),
+                    ([O.LEAF], [x])][int(rng.integers(0, 4)) if b else 0])
+    return pack(out)
+
+
+def _replays_like_eager(call, buf, others):
+    """call(buf): one search into buf.  Once eagerly, once captured, then replays beside eager calls of others(); every
+    replay has to give what the eager call gave."""
+    want = [t.clone() for t in call(buf)]
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(buf)
+    for _ in range(3):
+        for _ in range(20):
+            others()
+        for t in (buf.ids, buf.scores, buf.count):
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip((buf.ids, buf.scores, buf.count), want))
+
+
+# A captured call finds a staging slot of its size after one eager call of its shape (200 programs: their
+# tables and the search's fit a slot as it comes, a bound on the tables' size does not).  With and without a seed
+# pass; probing per query and through mask rows.
+@pytest.mark.parametrize("kind,n,B,probes", [("expr", 20_000, 200, 0), ("expr", 300_000, 100, 0), ("ivf", 20_000, 200, 9),
+                                             ("ivf", 20_000, 40, 600)])
+def test_captured_programs_and_probing(kind, n, B, probes):
+    print(f"[edges] graph {kind} n={n} B={B} probes={probes}", flush=True)
+    w = ragged_workload(n + B, n, 32, B, 24, 6, 128, 3)
+    ops, ids, off = _programs(np.random.default_rng(n + B), B, 24)
+    items, iscale, foff, fids, q, qs = [t.cuda() for t in (w.items, w.item_scale, w.feat_offsets, w.feat_ids, w.queries,
+                                                           w.query_scale)]
+    bloom = st.st_bloom_build(foff, fids, n, 128, 3)
+    if kind == "expr":
+        bufs = [st.SearchBuffers(n, 32, B, 1, 20, n_expr_entries=int(off[-1])) for _ in range(2)]
+
+        def call(buf):
+            return st.st_search_expr(bloom, items, iscale, q, qs, ops, ids, off, 20, buffers=buf)
+    else:
+        cent, cs, coff = (t.cuda() for t in S.gen_clusters(w.cfg, 1000))
+        bufs = [st.IvfBuffers(n, 32, B, 20, 1000, probes, int(off[-1])) for _ in range(2)]
+
+        def call(buf):
+            return st.st_search_ivf(bloom, items, iscale, cent, cs, coff, probes, q, qs, ops, ids, off, 20, buffers=buf)[:3]
+
+    _replays_like_eager(call, bufs[0], lambda: call(bufs[1]))
+
+
+# The first call with larger tables than any slot holds may itself be captured: its slot grows within the capture.
+def test_staging_slot_grows_within_a_capture():
+    n, B = 5_000, 2000
+    w = ragged_workload(5, n, 16, B, 400, 6, 256, 3)
+    w.filt_ids = np.random.default_rng(1).integers(0, 400, 2 * B).astype(np.uint64)
+    w.filt_offsets = np.arange(0, 2 * B + 1, 2).astype(np.int64)
+    assert st.st_search_host_plan(n, 16, B, 1, 5, 256, 3, w.filt_ids, w.filt_offsets)["table_bytes"] > 200_000
+    items, iscale, foff, fids, q, qs = [t.cuda() for t in (w.items, w.item_scale, w.feat_offsets, w.feat_ids, w.queries,
+                                                           w.query_scale)]
+    bloom = st.st_bloom_build(foff, fids, n, 256, 3)
+
+    def call(buf, b):
+        return st.st_search(bloom, items, iscale, q[:b], qs[:b], w.filt_ids[:2 * b], w.filt_offsets[:b + 1], 5, buffers=buf)
+
+    small, buf, eager = (st.SearchBuffers(n, 16, b, 1, 5) for b in (300, B, B))
+    call(small, 300)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(buf, B)
+    want = call(eager, B)
+    for _ in range(2):
         for t in (buf.ids, buf.scores, buf.count):
             t.zero_()
         graph.replay()
