@@ -100,8 +100,15 @@ typedef struct st_bloom st_bloom;
 int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_t n_items,
                    int32_t m_bits, int32_t k_hashes, void* hip_stream, st_bloom** out);
 
-/* Frees the handle and its device memory (NULL is allowed). */
+/* Frees the handle (NULL is allowed); on an error the handle stays valid.  Its device memory goes back to the
+ * driver at once when it is the last index of its device or larger than 1 GiB.  Otherwise the library may keep the
+ * block -- one per device -- for the next st_bloom_build of the same size (a program that publishes replaces
+ * one index by another), until that device's last index is freed, an index of another size is built or another one
+ * freed, an allocation of the library fails, or st_bloom_trim is called. */
 int st_bloom_free(st_bloom* bloom);
+
+/* Gives back what st_bloom_free has kept, on every device. */
+int st_bloom_trim(void);
 
 /* Device bytes of the index: n_items*m_bits/8 rounded up to whole 1024-item tiles (the
  * paper's N*M/8 accounting, Sec. 6.2.2).  st_bloom_layout_bytes is the same figure from

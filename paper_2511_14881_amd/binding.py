@@ -17,7 +17,7 @@ _lib = None
 ST_OK, ST_EINVAL, ST_ENOMEM, ST_EHIP, ST_EWORKSPACE = 0, -1, -2, -3, -4
 
 EXPORTS = [
-    "st_last_error", "st_version", "st_bloom_build", "st_bloom_free", "st_bloom_bytes",
+    "st_last_error", "st_version", "st_bloom_build", "st_bloom_free", "st_bloom_trim", "st_bloom_bytes",
     "st_bloom_layout_bytes", "st_bloom_n_items", "st_bloom_export_signatures", "st_bloom_mask",
     "st_search_workspace_bytes", "st_search", "st_search_multitask", "st_score_pairs",
     "st_search_plan", "st_set_scoring_path", "st_timing_begin", "st_timing_end",
@@ -50,6 +50,8 @@ def lib() -> C.CDLL:
         L.st_bloom_build.argtypes = [p, p, i64, i32, i32, p, C.POINTER(p)]
         L.st_bloom_free.restype = C.c_int
         L.st_bloom_free.argtypes = [p]
+        L.st_bloom_trim.restype = C.c_int
+        L.st_bloom_trim.argtypes = []
         L.st_bloom_bytes.restype = i64
         L.st_bloom_bytes.argtypes = [p]
         L.st_bloom_layout_bytes.restype = i64
@@ -187,6 +189,11 @@ def st_bloom_build(feat_offsets, feat_ids, n_items: int, m_bits: int, k_hashes: 
     _check(lib().st_bloom_build(ptr(feat_offsets, np.int64), ptr(feat_ids, np.uint64), n_items, m_bits,
                                 k_hashes, _stream(stream), C.byref(out)))
     return BloomIndex(out.value, n_items, m_bits, k_hashes)
+
+
+def st_bloom_trim() -> None:
+    """Gives the memory that freed indexes left with the library back to the driver."""
+    _check(lib().st_bloom_trim())
 
 
 def st_bloom_layout_bytes(n_items: int, m_bits: int) -> int:

@@ -18,6 +18,7 @@
 #include <thread>
 #include <vector>
 
+#include "st_block_keep.h"
 #include "st_stage_pool.h"
 #include "st_bloom_kernels.h"
 #include "st_mfma_kernels.h"
@@ -287,63 +288,43 @@ int device_setup(int device)
     return ST_OK;
 }
 
-// Device memory of freed indexes.  A program that publishes builds a new index and frees the one it
-// replaces, over and over; handing hundreds of megabytes back to the driver and fetching them again
-// costs 0.3 ms a time, and 10 ms and more once the driver has no cleared pages left in stock.  The
-// block of the most recently freed index is therefore kept, one per device and at most kIndexKeepBytes,
-// for the next build of the same size.  It is given back when an index of another size is built or freed,
-// or when an allocation fails.  st_bloom_free has waited for the device before a block is kept (as hipFree
-// would have), so whoever takes it, on whatever stream, finds no work in flight on it.
-constexpr int64_t kIndexKeepBytes = 4ll << 30;
-struct KeptBlock {
-    void* ptr = nullptr;
-    int64_t bytes = 0;
-};
-KeptBlock g_kept[kMaxDevices];
-std::mutex g_kept_mu;
+// Device memory of the library: the indexes' and what a call needs for its own duration.  See st_block_keep.h for
+// what is kept of a freed index, and for how long.
+st::BlockKeep g_blocks;
+static_assert(st::kKeepDevices == kMaxDevices, "one entry per device");
 
-KeptBlock take_kept(int device)
+int block_alloc(void** out, int64_t bytes)
 {
-    std::lock_guard<std::mutex> lock(g_kept_mu);
-    KeptBlock k = g_kept[device];
-    g_kept[device] = KeptBlock{};
-    return k;
+    const hipError_t e = hipMalloc(out, (size_t)bytes);
+    if (e != hipSuccess) (void)hipGetLastError();  // (reported here, not by the next launch)
+    return (int)e;
 }
+int block_free(void* ptr) { return (int)hipFree(ptr); }
+int block_idle() { return (int)hipDeviceSynchronize(); }
 
-int index_alloc(int device, int64_t bytes, void** out)
+// (null on failure, so that a caller's clean-up can free whatever it holds)
+int call_alloc(int64_t bytes, void** out)
 {
-    const KeptBlock k = take_kept(device);
-    if (k.ptr && k.bytes == bytes) {
-        *out = k.ptr;
-        return ST_OK;
-    }
-    if (k.ptr) ST_HIP(hipFree(k.ptr));
-    ST_HIP(hipMalloc(out, (size_t)bytes));
+    *out = nullptr;
+    int device = 0;
+    ST_HIP(hipGetDevice(&device));
+    void* p = nullptr;
+    if (device < 0 || device >= kMaxDevices) ST_HIP((hipError_t)block_alloc(&p, bytes));
+    else ST_HIP((hipError_t)g_blocks.get(device, bytes, block_alloc, block_free, &p));
+    *out = p;
     return ST_OK;
 }
 
+// On success the index is gone; an error leaves it as it was.  (A kept block waits for the device here, as hipFree
+// does, so whoever takes it, on whatever stream, finds no work in flight on it.)
 int index_free(int device, void* ptr, int64_t bytes)
 {
-    if (bytes > kIndexKeepBytes) {
-        ST_HIP(hipFree(ptr));
-        return ST_OK;
-    }
     int current = 0;
     ST_HIP(hipGetDevice(&current));
     if (current != device) ST_HIP(hipSetDevice(device));
-    const hipError_t e = hipDeviceSynchronize();
-    if (current != device) ST_HIP(hipSetDevice(current));
-    if (e != hipSuccess) {
-        (void)hipFree(ptr);
-        ST_HIP(e);
-    }
-    KeptBlock old;
-    {
-        std::lock_guard<std::mutex> lock(g_kept_mu);
-        old = g_kept[device];
-        g_kept[device] = KeptBlock{ptr, bytes};
-    }
-    if (old.ptr) ST_HIP(hipFree(old.ptr));
+    const int e = g_blocks.put_index(device, ptr, bytes, block_free, block_idle);
+    if (current != device) (void)hipSetDevice(current);
+    ST_HIP((hipError_t)e);
     return ST_OK;
 }
 
@@ -775,8 +756,9 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
         const int rc_setup = device_setup(b->device);
         if (rc_setup != ST_OK) return rc_setup;
         if (b->bytes > 0) {
-            const int rc_mem = index_alloc(b->device, b->bytes, (void**)&b->dev);
-            if (rc_mem != ST_OK) return rc_mem;
+            void* mem = nullptr;
+            ST_HIP((hipError_t)g_blocks.get_index(b->device, b->bytes, block_alloc, block_free, &mem));
+            b->dev = (uint64_t*)mem;
         }
         if (n_items == 0) return ST_OK;
         const int64_t* off = feat_offsets;
@@ -790,14 +772,16 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
             for (int64_t i = 0; i < n_items; ++i)
                 if (feat_offsets[i + 1] < feat_offsets[i]) return fail(ST_EINVAL, "feat_offsets decrease at item %lld", (long long)i);
             nnz = feat_offsets[n_items];
-            ST_HIP(hipMalloc((void**)&d_off, (size_t)(n_items + 1) * 8));
+            const int rc_mem = call_alloc((n_items + 1) * 8, (void**)&d_off);
+            if (rc_mem != ST_OK) return rc_mem;
             ST_HIP(hipMemcpyAsync(d_off, feat_offsets, (size_t)(n_items + 1) * 8, hipMemcpyHostToDevice, stream));
             off = d_off;
         }
         if (nnz < 0) return fail(ST_EINVAL, "negative feature count");
         if (nnz > 0 && !feat_ids) return fail(ST_EINVAL, "feat_ids is null");
         if (nnz > 0 && !is_device_pointer(feat_ids)) {
-            ST_HIP(hipMalloc((void**)&d_ids, (size_t)nnz * 8));
+            const int rc_mem = call_alloc(nnz * 8, (void**)&d_ids);
+            if (rc_mem != ST_OK) return rc_mem;
             ST_HIP(hipMemcpyAsync(d_ids, feat_ids, (size_t)nnz * 8, hipMemcpyHostToDevice, stream));
             ids = d_ids;
         }
@@ -823,7 +807,7 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
     if (d_off) (void)hipFree(d_off);
     if (d_ids) (void)hipFree(d_ids);
     if (rc != ST_OK) {
-        if (b->dev) (void)hipFree(b->dev);
+        if (b->dev) (void)g_blocks.put_index(b->device, b->dev, b->bytes, block_free, block_idle);
         delete b;
         return rc;
     }
@@ -835,9 +819,18 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
 int st_bloom_free(st_bloom* bloom)
 {
     if (!bloom) return ST_OK;
-    const int rc = bloom->dev ? index_free(bloom->device, bloom->dev, bloom->bytes) : (int)ST_OK;
+    if (bloom->dev) {
+        const int rc = index_free(bloom->device, bloom->dev, bloom->bytes);
+        if (rc != ST_OK) return rc;  // (the handle stays what it was)
+    }
     delete bloom;
-    return rc;
+    return ST_OK;
+}
+
+int st_bloom_trim(void)
+{
+    for (int device = 0; device < kMaxDevices; ++device) ST_HIP((hipError_t)g_blocks.release(device, block_free));
+    return ST_OK;
 }
 
 int64_t st_bloom_bytes(const st_bloom* bloom)
@@ -896,8 +889,8 @@ int st_bloom_mask(const st_bloom* bloom, const uint64_t* host_filt_ids, const in
     rows.push_back(0);
     int32_t* d_tab = nullptr;
     const size_t n_int = row_off.size() + rows.size();
-    ST_HIP(hipMalloc((void**)&d_tab, n_int * 4));
-    int rc = ST_OK;
+    int rc = call_alloc((int64_t)n_int * 4, (void**)&d_tab);
+    if (rc != ST_OK) return rc;
     auto body = [&]() -> int {
         ST_HIP(hipMemcpyAsync(d_tab, row_off.data(), row_off.size() * 4, hipMemcpyHostToDevice, stream));
         ST_HIP(hipMemcpyAsync(d_tab + row_off.size(), rows.data(), rows.size() * 4, hipMemcpyHostToDevice, stream));
@@ -1562,7 +1555,8 @@ int st_bloom_mask_expr(const st_bloom* bloom, const int32_t* host_expr_ops, cons
     tab.leaf_rows.push_back(0);
     int32_t* d_tab = nullptr;
     const size_t n_off = tab.prog_off.size(), n_code = tab.code.size(), n_rows = tab.leaf_rows.size();
-    ST_HIP(hipMalloc((void**)&d_tab, (n_off + n_code + n_rows) * 4));
+    rc = call_alloc((int64_t)(n_off + n_code + n_rows) * 4, (void**)&d_tab);
+    if (rc != ST_OK) return rc;
     auto body = [&]() -> int {
         ST_HIP(hipMemcpyAsync(d_tab, tab.prog_off.data(), n_off * 4, hipMemcpyHostToDevice, stream));
         ST_HIP(hipMemcpyAsync(d_tab + n_off, tab.code.data(), n_code * 4, hipMemcpyHostToDevice, stream));
@@ -1625,7 +1619,6 @@ int st_search_expr(const st_bloom* bloom, const int8_t* dev_items, const float* 
     if (need < 0) return (int)need;
     if (workspace_bytes < need)
         return fail(ST_EWORKSPACE, "workspace has %lld bytes, %lld needed", (long long)workspace_bytes, (long long)need);
-    hipStream_t stream = (hipStream_t)hip_stream;
     const int64_t n_tiles = (n_items + st::kTileItems - 1) / st::kTileItems;
     char* ws = (char*)dev_workspace;
     uint64_t* mask_rows = (uint64_t*)(ws + st::round_up(base, 256));

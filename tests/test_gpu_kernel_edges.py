@@ -1,5 +1,7 @@
 """Kernels at the sizes where their tiling can go wrong, against the CPU oracle: edges of tiles,
 remainders, the smallest and largest shapes of a variant.  Bit-exact like every result of the library."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -173,6 +175,34 @@ def test_more_graphs_than_staging_slots():
             torch.cuda.synchronize()
             assert all(torch.equal(a, c) for a, c in zip((b.ids, b.scores, b.count), want))
             call(bufs[18])
+
+
+# Freed index memory is the program's again: at once when the last index is freed, and on request while another one
+# lives (128 MB each).
+def test_freed_index_memory_goes_back_to_the_driver():
+    n, m, mb = 1 << 20, 1024, 128 << 20
+    gc.collect()
+    off, ids = torch.zeros(n + 1, dtype=torch.int64, device="cuda"), torch.zeros(1, dtype=torch.int64, device="cuda")
+    st.st_bloom_build(off, ids, n, 64, 1).free()
+    st.st_bloom_trim()
+
+    def free_bytes():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0]
+
+    start = free_bytes()
+    first = st.st_bloom_build(off, ids, n, m, 1)
+    assert free_bytes() < start - mb + mb // 4
+    first.free()
+    assert free_bytes() > start - mb // 2
+    first, second = (st.st_bloom_build(off, ids, n, m, 1) for _ in range(2))
+    first.free()
+    st.st_bloom_trim()
+    assert start - 2 * mb < free_bytes() < start - mb + mb // 4
+    third = st.st_bloom_build(off, ids, n, m, 1)
+    second.free()
+    third.free()
+    assert free_bytes() > start - mb // 2
 
 
 # Batches whose queries hardly share filters (the products of all pairs, or of the passing ones where a wavefront has
