@@ -10,7 +10,7 @@ from oracle import st_oracle as O
 from paper_2511_14881_amd import binding as st
 from paper_2511_14881_amd import synth as S
 from tests.test_gpu_expr import pack
-from tests.test_gpu_parity import check_search, ragged_workload
+from tests.test_gpu_parity import check_search, oracle_index, ragged_workload
 
 pytestmark = pytest.mark.gpu
 
@@ -207,11 +207,16 @@ def test_freed_index_memory_goes_back_to_the_driver():
 
 # Batches whose queries hardly share filters (the products of all pairs, or of the passing ones where a wavefront has
 # few): row lengths of every variant, one query block and several, two rows of the grid, ragged last segment
-# and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores.
+# and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores; a corpus whose
+# filters pass everything in some stretches and nothing in others (wavefronts change between the two forms), and
+# no filter at all (no signature row is named).  The last selection would make good for lost candidates, so no
+# query that passes enough items may have needed that.
 @pytest.mark.parametrize("n,d,B,m,kind", [(600_001, 64, 16, 64, "mixed"), (530_049, 96, 33, 100, "mixed"),
                                           (400_003, 128, 130, 512, "mixed"), (524_288 + 31, 192, 40, 257, "mixed"),
                                           (420_000, 256, 300, 128, "mixed"), (600_000, 64, 64, 512, "rare"),
-                                          (350_000, 128, 140, 512, "rare"), (400_001, 64, 150, 128, "ties")])
+                                          (350_000, 128, 140, 512, "rare"), (400_001, 64, 150, 128, "ties"),
+                                          (430_013, 256, 48, 300, "stretches"), (330_077, 96, 260, 64, "stretches"),
+                                          (300_011, 96, 20, 257, "none")])
 def test_own_filters(n, d, B, m, kind):
     w = ragged_workload(n, n, d, B, 40, 8, m, 3)
     filters = []
@@ -219,12 +224,26 @@ def test_own_filters(n, d, B, m, kind):
         one = [(b // 3) % 40]
         two = [b % 40, (7 * b + b // 40 + 1) % 40]
         filters.append([] if b == 0 else [999] if b == 1 else one if b % 3 == 0 and kind != "rare" else two + [(b * 11 + 3) % 40] * (b % 2))
+    if kind == "none":
+        filters = [[] for _ in range(B)]
     w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
     w.filt_offsets = np.concatenate([[0], np.cumsum([len(f) for f in filters])]).astype(np.int64)
     if kind == "ties":
         w.items = w.items[:997].repeat(n // 997 + 1, 1)[:n].contiguous()
         w.item_scale = w.item_scale[:997].repeat(n // 997 + 1)[:n].contiguous()
-    check_search(w, 60, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, max(1, B // 12))}), label=f"own filters {kind}")
+    elif kind == "stretches":  # all 40 features, none, or two of them, for 700 items each (in no order)
+        turn = np.random.default_rng(d).integers(0, 3, n // 700 + 1).repeat(700)[:n]
+        lens = np.array([0, 40, 2])[turn]
+        off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
+        ids = (np.arange(off[-1]) - off[:-1].repeat(lens) + (np.arange(n) * (turn == 2)).repeat(lens)) % 40
+        w.feat_offsets, w.feat_ids = torch.from_numpy(off), torch.from_numpy(ids.astype(np.int64))
+    K = 60
+    sigs = oracle_index(w)
+    passing = [int(np.unpackbits(O.bloom_mask(sigs, m, 3, np.array(f, np.uint64)).view(np.uint8)).sum()) for f in filters]
+    fast = [b for b in range(B) if passing[b] >= 40 * K] if kind != "ties" else []
+    assert kind == "ties" or len(fast) > B // 2
+    check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, max(1, B // 12))}), slow_path=([], fast),
+                 label=f"own filters {kind}")
 
 
 # The final ordering of K > 2048 cuts the score range into steps: scores of one size, a few far above the rest
