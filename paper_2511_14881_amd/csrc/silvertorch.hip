@@ -1416,7 +1416,8 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             TimedLaunch t(0, stream);
             ST_HIP(st::launch_scan_mfma(sp_m, mp, gx, stream));
         }
-        if (set_dot.n && own_scan && lv > 0 && L_.end - L_.begin >= st::kOwnMinItems && L_.begin % st::kOwnSeg == 0) {
+        if (set_dot.n && own_scan && lv > 0 && L_.end - L_.begin >= st::kOwnMinItems && L_.begin % st::kOwnSeg == 0 &&
+            st::level_takes_segments(L_, st::kOwnSeg)) {
             st::ScanParams sp_o = sp_d;
             const int64_t n_own = (L_.end - L_.begin + st::kOwnSeg - 1) / st::kOwnSeg;
             sp_o.seg_items = st::kOwnSeg;

@@ -37,8 +37,8 @@ constexpr int kOwnSeg = 512;            // items of a segment
 constexpr int kOwnWords = kOwnSeg / 64; // one mask word per wavefront
 constexpr int kOwnCols = 256;           // queries resident at a time (one row of the grid)
 constexpr int kOwnRows = 512;           // signature rows of the index, at most
-// Items of a level, at least: a segment's admissions of one query go to one region, and a level admits up to some
-// 8000 per query, which 512 segments spread over regions of 64 entries with room for four times as many.
+// Items of a level, at least: two segments to each of the workgroups that are resident.  (Whether the candidate
+// regions have room for segments of this size is the plan's to say: level_takes_segments.)
 constexpr int64_t kOwnMinItems = 512 * kOwnSeg;
 constexpr int kOwnAllRows = 64;         // an index of no more rows is staged whole
 constexpr int kOwnRowRefs = 6144;       // rows all filters name together, at most

@@ -35,6 +35,8 @@ struct Level {
     int32_t seg_per_visit;   // consecutive segments a workgroup takes before striding on
     int32_t seed;            // 1: this prefix is handled by the per-query seed kernel
     int32_t keep;            // keys per query the selection after this level keeps (K on the last level)
+    int64_t min_segs;        // segments the level is to be cut into at least: a segment's candidates go to one region,
+                             // which then has room for four times what is expected
 };
 
 struct Plan {
@@ -114,9 +116,9 @@ inline int make_levels_sized(int64_t n_items, int32_t K, int32_t cap, int32_t g_
     const int32_t seg0 = cap < seg_cap ? cap : seg_cap;
     if (seed_items > 0) {
         n0 = seed_items < n_items ? seed_items : n_items;
-        p.level[p.n_levels++] = Level{0, n0, 0, 0, 1, K};
+        p.level[p.n_levels++] = Level{0, n0, 0, 0, 1, K, 0};
     } else {
-        p.level[p.n_levels++] = Level{0, n0, seg0, cap / seg0, 0, K};
+        p.level[p.n_levels++] = Level{0, n0, seg0, cap / seg0, 0, K, 0};
     }
     // keys kept after the level just planned = what the next level's threshold admits per growth
     auto keep_after = [&](int64_t prefix) -> int32_t {
@@ -158,10 +160,10 @@ inline int make_levels_sized(int64_t n_items, int32_t K, int32_t cap, int32_t g_
         // expected in the level: sizes that leave fewer segments than four times that many over
         // the region capacity are passed over (down to the smallest size).
         int32_t seg = seg_cap;
+        const double admitted = (double)keep * ((double)nxt / (double)(cur > 0 ? cur : 1) - 1.0);
+        const int64_t min_seg_count = (int64_t)(4.0 * admitted / (double)cap) + 1;
         {
             const int64_t span = nxt - next_begin;
-            const double admitted = (double)keep * ((double)nxt / (double)(cur > 0 ? cur : 1) - 1.0);
-            const int64_t min_seg_count = (int64_t)(4.0 * admitted / (double)cap) + 1;
             int64_t best = -1;
             for (int32_t c = seg_cap; c >= 64; c >>= 1) {
                 const int64_t n_seg = (span + c - 1) / c;
@@ -174,12 +176,18 @@ inline int make_levels_sized(int64_t n_items, int32_t K, int32_t cap, int32_t g_
             }
         }
         keep = keep_after(nxt);
-        p.level[p.n_levels++] = Level{next_begin, nxt, seg, 4, 0, keep};  // one segment per wavefront of the workgroup
+        p.level[p.n_levels++] = Level{next_begin, nxt, seg, 4, 0, keep, min_seg_count};  // one segment per wavefront of the workgroup
         cur = nxt;
         next_begin = nxt;
     }
     *out = p;
     return 0;
+}
+
+// Whether a scan may take a level in segments of another size than the planned one.
+inline bool level_takes_segments(const Level& l, int32_t seg_items)
+{
+    return (l.end - l.begin + seg_items - 1) / seg_items >= l.min_segs;
 }
 
 // A first level of half the size costs less itself (fewer candidates for its selection to read, a

@@ -238,3 +238,27 @@ def test_first_level_is_halved_only_where_the_last_selection_stays_small(tmp_pat
         if small and levels == 2 and end0 == 32768:
             keep = int(subprocess.run([exe, str(K), str(end0), str(n)], capture_output=True, text=True, check=True).stdout)
             assert K + keep * (n / end0 - 1) <= 3500
+
+
+def test_a_level_is_not_taken_in_larger_segments_than_its_regions_have_room_for(tmp_path):
+    # A scan with segments of its own size (512 items) leaves the planner's margin as it is: a region has room for four
+    # times the candidates expected of a segment.  Large K plans 256-item segments for that.
+    import shutil
+    import subprocess
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    exe = str(tmp_path / "plan_segments")
+    src = os.path.join(ROOT, "tests", "plan_keep_host_test.cpp")
+    inc = os.path.join(ROOT, "paper_2511_14881_amd", "csrc")
+    subprocess.run([cxx, "-std=c++17", "-O1", "-I", inc, src, "-o", exe], check=True)
+    cases = [(400_000, 20_000), (400_000, 40_000), (2_000_000, 40_000), (10_000_000, 500), (330_000, 60), (777_777, 77),
+             (20_000_000, 2048), (1_000_000, 10_000), (700_000, 5000)]
+    out = subprocess.run([exe, "segments"] + [str(x) for n, K in cases for x in (n, K, 512)], capture_output=True, text=True, check=True)
+    rows = [line.split() for line in out.stdout.splitlines()]
+    assert len(rows) == len(cases)
+    for (n, K), (admitted, cap, segs, planned, ok) in zip(cases, rows):
+        room = int(segs) * int(cap) >= 4 * float(admitted)
+        assert (ok == "1") == room, (n, K, admitted, cap, segs, planned)
+    took = [r[4] for r in rows]
+    assert took[:2] == ["0", "0"] and took[3:7] == ["1"] * 4
