@@ -9,7 +9,7 @@ import torch
 from oracle import st_oracle as O
 from paper_2511_14881_amd import binding as st
 from paper_2511_14881_amd import synth as S
-from tests.test_gpu_expr import pack
+from tests.test_gpu_expr import check_ivf, pack
 from tests.test_gpu_parity import check_search, oracle_index, ragged_workload
 
 pytestmark = pytest.mark.gpu
@@ -69,7 +69,7 @@ def _programs(rng, B, vocab):
         x, y = (int(v) for v in rng.integers(0, vocab, 2))
         out.append([([], []), ([O.LEAF, O.LEAF, O.NOT, O.AND], [x, y, 0, 0]), ([O.LEAF, O.LEAF, O.OR], [x, y, 0]),
                     ([O.LEAF], [x])][int(rng.integers(0, 4)) if b else 0])
-    return pack(out)
+    return out
 
 
 def _replays_like_eager(call, buf, others):
@@ -98,7 +98,7 @@ def _replays_like_eager(call, buf, others):
 def test_captured_programs_and_probing(kind, n, B, probes):
     print(f"[edges] graph {kind} n={n} B={B} probes={probes}", flush=True)
     w = ragged_workload(n + B, n, 32, B, 24, 6, 128, 3)
-    ops, ids, off = _programs(np.random.default_rng(n + B), B, 24)
+    ops, ids, off = pack(_programs(np.random.default_rng(n + B), B, 24))
     items, iscale, foff, fids, q, qs = [t.cuda() for t in (w.items, w.item_scale, w.feat_offsets, w.feat_ids, w.queries,
                                                            w.query_scale)]
     bloom = st.st_bloom_build(foff, fids, n, 128, 3)
@@ -266,3 +266,44 @@ def test_ordering_of_large_results(K, kind):
     elif kind == "few":
         w.filt_ids, w.filt_offsets = np.arange(9, dtype=np.uint64), np.array([0, 3, 6, 9], np.int64)
     check_search(w, K, label=f"ordering {kind}")
+
+
+def _parts(n, B, n_c, n_p, K):
+    """(workgroups to a query, keys of a workgroup's share, keys it hands on unpruned) by the host's rule."""
+    k_pad = 1 << (K - 1).bit_length()
+    room, scratch, words = K + 1024 * 512, k_pad if k_pad > 2048 else 0, n_p * (n // n_c // 64 + 1)
+    parts = 1
+
+    def fits(p):
+        return p <= 16 and room // p - scratch >= 2 * K + 4096
+
+    while fits(2 * parts) and 2 * B * parts <= 256 and words // (2 * parts) >= 64:
+        parts *= 2
+    while fits(2 * parts) and words // parts > 1024:
+        parts *= 2
+    return parts, room // parts - (scratch if parts > 1 else 0), max(K, 16384 // parts)
+
+
+# What the workgroups of a probing query hand on, and its merge.  All clusters are probed and the first query has no
+# filter, so that its n items go through: more than a workgroup hands on (pruned in LDS or in memory), more than its
+# share of the key buffer holds (pruned on the way), one workgroup and 16, more results than a round of the merge holds,
+# hundreds of keys to a score (the merge's general way), with the result ordered in LDS and in memory.
+@pytest.mark.parametrize("n,B,K,kind,parts,pruned", [
+    (100_000, 3, 1500, "plain", 16, "end"), (200_000, 3, 1500, "plain", 16, "end"), (200_000, 3, 3000, "plain", 16, "end"),
+    (700_000, 2, 3000, "plain", 16, "round"), (700_000, 2, 10_000, "plain", 8, "round"), (60_000, 130, 3000, "plain", 1, "end"),
+    (60_000, 130, 100, "plain", 1, "end"), (20_000, 3, 10_000, "plain", 4, "no"), (100_000, 3, 1500, "ties", 16, "end"),
+    (200_000, 3, 3000, "ties", 16, "end"), (30_000, 20, 700, "ties", 4, "end"), (700_000, 2, 10_000, "ties", 8, "round"),
+    (200_000, 3, 9000, "outliers", 8, "end")])
+def test_probing_parts_and_merge(n, B, K, kind, parts, pruned):
+    n_c = 50
+    got, share, keep = _parts(n, B, n_c, n_c, K)
+    mine = n // got
+    assert got == parts and ("round" if mine > share else "end" if mine > keep else "no") == pruned, (got, share, keep, mine)
+    w = ragged_workload(n + K, n, 16, B, 24, 4, 64, 2)
+    if kind == "ties":
+        w.items = w.items[:60].repeat(n // 60 + 1, 1)[:n].contiguous()
+        w.item_scale = w.item_scale[:60].repeat(n // 60 + 1)[:n].contiguous()
+    elif kind == "outliers":
+        w.item_scale[5::n // 7] *= 1e30
+    check_ivf(w, _programs(np.random.default_rng(n + B), B, 24), n_c, n_c, K, queries=sorted({0, 1, B - 1}), label=f"parts {kind}",
+              fast_path_only=True)
