@@ -629,7 +629,10 @@ __device__ inline int lds_topk(uint64_t* keys, int n, int K, uint64_t* sorted, i
 // More keys than s_out holds go in rounds, from the top.  A range whose steps come out too full (a few
 // scores far above the rest, or keys below the want-th one spread much wider) is cut again from the
 // lowest step wanted upwards.  False: too many keys share a score (they rank by id, which the steps do
-// not split), nothing the caller needs has been changed and it takes the general way.
+// not split), or the lowest step of the range is wanted and too full (every key is wanted, and one lies far above the
+// others), which no cut from below mends; nothing the caller needs has been changed and it takes the general way.  (64
+// queries whose 10,000 passing items are all wanted, some with scores 1e30 above the rest: 270 us a call, 512 with
+// the radix selection.)
 //
 // each(f) calls f(key) for this thread's share of the keys, the same ones on every call; emit(rank, key)
 // is called once for every rank below `want` and for some ranks above (the caller drops them).
@@ -853,9 +856,11 @@ __device__ inline void rescue_query(const SelectParams& r, int q, uint64_t* s_so
     if (tid == 0) *s_n = 0;
     __syncthreads();
     // A thread owns one 64-item word per round and scores the items it admits itself: rounds of up to
-    // blockDim.x words, as many as the buffer is sure to hold beside the K keys kept (one tile at least).
+    // blockDim.x words, half of what the buffer is sure to hold beside the K keys kept (one tile at least).  (With
+    // rounds of all of it, 1024 words of 1024 threads, every round behind the first K keys prunes: 64 queries of tied
+    // scores on 1 M items, K = 10,000, 6.8 ms against 1.2.)
     const int64_t n_words = (p.n_items + 63) >> 6;
-    int64_t wpr = (r.gath_cap - r.K) / 64;
+    int64_t wpr = (r.gath_cap - r.K) / 128;
     wpr = wpr > nt ? nt : (wpr < kTileWords ? kTileWords : wpr);
     (void)s_mask;
     for (int64_t w0 = 0; w0 < n_words; w0 += wpr) {

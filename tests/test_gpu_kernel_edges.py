@@ -268,6 +268,17 @@ def test_ordering_of_large_results(K, kind):
     check_search(w, K, label=f"ordering {kind}")
 
 
+# Tied scores that overflow the regions: the slow exact path over several rounds of its buffer, with results above and
+# below the LDS sort size (rounds of the large selection's 1024 threads and of the small one's 512).
+@pytest.mark.parametrize("n,K", [(200_000, 3000), (300_001, 10_000), (200_000, 2048)])
+def test_ties_on_the_slow_exact_path_over_several_rounds(n, K):
+    w = ragged_workload(n + K, n, 16, 3, 10, 3, 64, 2)
+    w.filt_ids, w.filt_offsets = np.array([3], np.uint64), np.array([0, 0, 1, 1], np.int64)
+    w.items = w.items[:20].repeat(n // 20 + 1, 1)[:n].contiguous()
+    w.item_scale = torch.full((n,), 0.01)
+    check_search(w, K, slow_path=([0, 2], []), label="ties, slow path")
+
+
 def _parts(n, B, n_c, n_p, K):
     """(workgroups to a query, keys of a workgroup's share, keys it hands on unpruned) by the host's rule."""
     k_pad = 1 << (K - 1).bit_length()
