@@ -1819,10 +1819,12 @@ int st_search_ivf(const st_bloom* bloom, const int8_t* dev_items, const float* d
             qp.part_cap = L.gath_cap / parts;
             qp.part_keys = qp.part_cap - (parts > 1 ? scratch : 0);
             qp.part_keep = std::max(K, st::kMergeKeys / parts);
+            qp.finish = parts == 1 && L.k_pad <= st::kLdsSortMax && words <= st::kQueryFewWords ? 1 : 0;
             {
                 TimedLaunch t(0, stream);
                 hipLaunchKernelGGL(st::ivf_query_kernel, dim3(batch, parts), dim3(st::kQueryThreads), 0, stream, qp);
-                hipLaunchKernelGGL(st::ivf_merge_kernel, dim3(batch), dim3(st::kMergeThreads), 0, stream, qp, parts);
+                if (!qp.finish)
+                    hipLaunchKernelGGL(st::ivf_merge_kernel, dim3(batch), dim3(st::kMergeThreads), 0, stream, qp, parts);
             }
             ST_HIP(hipGetLastError());
             return ST_OK;

@@ -5,7 +5,8 @@
 // (int8 dot, two fp32 multiplies), and an exact top-n_p by (score descending, cluster id
 // ascending) gives the probed clusters.
 // Phases 2-4, up to kQueryProbes probes (ivf_query_kernel): the workgroups of a query filter and
-// score the items of its probed ranges alone, ivf_merge_kernel selects and orders the top K.
+// score the items of its probed ranges alone, ivf_merge_kernel selects and orders the top K (or a lone
+// workgroup itself, where it has few words).
 // Phase 2, any number of probes (ivf_mask_kernel): 32 threads per (query, probed cluster) run the
 // query's filter program only over the words of that cluster's range and OR the result into the
 // query's row of a bit-sliced mask index (zeroed beforehand), laid out like the Bloom index; phases
@@ -203,6 +204,10 @@ __global__ __launch_bounds__(256) void ivf_mask_kernel(const uint64_t* __restric
 // list of passing items per wavefront.
 constexpr int kQueryThreads = 512;
 constexpr int kQueryProbes = 512;   // one probe per thread when the ranges are laid out
+// A lone workgroup with no more words to walk than this (by the average cluster) orders its keys itself: as a rule fewer than
+// 4096, which its own LDS selection takes.  (256 queries, 20,000 items, K = 500, 64 of 1024 clusters, 64 words: 43 us a call,
+// 46 to 48 with the merge; 1024 queries, 100,000 items, 128 words: 150 against 135.)
+constexpr int kQueryFewWords = 64;
 constexpr int kQueryParts = 16;     // workgroups per query, at most (powers of two)
 
 struct IvfQueryParams {
@@ -216,6 +221,7 @@ struct IvfQueryParams {
     int64_t gath_cap;
     int64_t part_cap;          // keys of one part's share of the buffer
     int64_t part_keys;         // ... of which keys are gathered in; the rest (several parts, k_pad above the LDS sort size) is the prune's scratch
+    int32_t finish;            // 1: a lone part writes the result rows itself (k_pad within the LDS sort size), no merge follows
     int32_t part_keep;         // a part hands on all its keys if they are no more than this (>= K), else its best K
     uint64_t* srt;             // [batch][k_pad] when k_pad > kLdsSortMax, else null (merge's general way, prune of a lone part)
     int32_t K, k_pad;
@@ -363,6 +369,20 @@ __global__ __launch_bounds__(kQueryThreads) void ivf_query_kernel(IvfQueryParams
         __syncthreads();
     }
     uint32_t n_keys = *s_n;
+    if (p.finish) {
+        uint64_t kth;
+        int n_out;
+        if (n_keys <= (uint32_t)(kTopkRegs * kQueryThreads)) {
+            uint64_t* s_keys = &s_stack[0][0];
+            for (uint32_t i = tid; i < n_keys; i += kQueryThreads) s_keys[i] = buf[i];
+            __syncthreads();
+            n_out = lds_topk(s_keys, (int)n_keys, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, true, kth);
+        } else {
+            n_out = wg_topk(buf, (int64_t)n_keys, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red);
+        }
+        write_result(s_sorted, n_out, p.K, p.out_ids + (int64_t)b * p.K, p.out_scores + (int64_t)b * p.K, p.out_count + b);
+        return;
+    }
     if (n_keys > (uint32_t)p.part_keep) {
         // keep this part's best K (unordered) at the head of its share
         uint64_t kth;

@@ -318,3 +318,34 @@ def test_probing_parts_and_merge(n, B, K, kind, parts, pruned):
         w.item_scale[5::n // 7] *= 1e30
     check_ivf(w, _programs(np.random.default_rng(n + B), B, 24), n_c, n_c, K, queries=sorted({0, 1, B - 1}), label=f"parts {kind}",
               fast_path_only=True)
+
+
+# A lone workgroup with few words orders its query's keys itself, by the average cluster: here most items lie in one
+# cluster that every query probes, or in clusters that none does.
+@pytest.mark.parametrize("n,big,K", [(20_000, 0, 500), (20_000, 19_000, 500), (20_000, 7000, 2048), (300, 200, 512), (20_000, 19_999, 1),
+                                     (40_000, 39_000, 2048)])
+def test_probing_batch_with_few_words_to_a_query(n, big, K):
+    B, n_c, n_p, d = 140, 400, 3, 16
+    assert n_p * (n // n_c // 64 + 1) <= 64 and B > 128
+    w = ragged_workload(n + big + K, n, d, B, 24, 4, 64, 2)
+    programs = _programs(np.random.default_rng(n + B), B, 24)
+    ops, ids, off = pack(programs)
+    cent, cs, coff = S.gen_clusters(w.cfg, n_c)
+    if big:  # cluster 7 wins every query (all queries' first value is positive); the others share the rest
+        w.queries[:, 0] = 100
+        cent[7] = 0
+        cent[7, 0], cs[7] = 127, 1e6
+        coff = torch.cat([torch.arange(8) * 0, torch.linspace(big, n, n_c - 7).long()]).contiguous()
+    items, iscale, foff, fids, q, qs = [t.cuda() for t in (w.items, w.item_scale, w.feat_offsets, w.feat_ids, w.queries,
+                                                           w.query_scale)]
+    bloom = st.st_bloom_build(foff, fids, n, 64, 2)
+    got = st.st_search_ivf(bloom, items, iscale, cent.cuda(), cs.cuda(), coff.cuda(), n_p, q, qs, ops, ids, off, K)
+    got = [t.cpu().numpy() for t in got]
+    sel = [0, 1, 2, 3, B - 1]
+    want = O.search_ivf(oracle_index(w), 64, 2, w.items.numpy(), w.item_scale.numpy(), cent.numpy(), cs.numpy(), coff.numpy(), n_p,
+                        w.queries.numpy()[sel], w.query_scale.numpy()[sel], *pack([programs[b] for b in sel]), K)
+    if big:
+        assert (got[3][:, 0] == 7).all() and got[2][0] >= min(K, big)
+    for g, x in zip(got, want):
+        x = np.asarray(x)
+        assert np.array_equal(g[sel].view(np.uint32) if g.dtype == np.float32 else g[sel], x.view(np.uint32) if x.dtype == np.float32 else x)
