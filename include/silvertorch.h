@@ -117,7 +117,7 @@ int64_t st_bloom_bytes(const st_bloom* bloom);
 int64_t st_bloom_layout_bytes(int64_t n_items, int32_t m_bits);
 int64_t st_bloom_n_items(const st_bloom* bloom);
 
-/* Parity/debug export, not on the timed path: item-major signatures,
+/* Export of the signatures, item-major (to be stored beside the corpus, and for parity checks):
  * dev_out[n_items][ceil(m_bits/64)], bit b of item i in word b/64 at position b%64. */
 int st_bloom_export_signatures(const st_bloom* bloom, uint64_t* dev_out, void* hip_stream);
 

@@ -409,7 +409,7 @@ constexpr int kMergeKeys = 16384;
 
 // Selection and order of what the parts of a query handed on: one workgroup per query, by buckets of the
 // score over the keys where they lie, a share of the wavefronts to each part.  Bound by the latency of its
-// passes over the keys (28 us for 16 x 1000 keys).
+// passes over the keys (27 us for 16 x 1000 keys).
 constexpr int kMergeThreads = 1024;
 constexpr int kMergeRoom = 8192;
 static_assert(kOrderBins * 4 >= kLdsSortMax * 8, "the general way's result borrows the counters");

@@ -624,7 +624,7 @@ __device__ inline int lds_topk(uint64_t* keys, int n, int K, uint64_t* sorted, i
 // in s_out, the keys are dropped there, and a key's rank is its step's first place plus the number of
 // larger keys in the step.  Three passes over the keys and a few reads per key, where a radix selection
 // with a bitonic network took 4 + 105 passes (64 queries, K = 10,000 of 18 k candidates each: final
-// selection 502 -> 34 us).  Bound by the latency of a pass over the candidates, not by the ranking.
+// selection 502 -> 37 us).  Bound by the latency of a pass over the candidates, not by the ranking.
 //
 // More keys than s_out holds go in rounds, from the top.  A range whose steps come out too full (a few
 // scores far above the rest, or keys below the want-th one spread much wider) is cut again from the
