@@ -21,3 +21,12 @@ def pytest_collection_modifyitems(config, items):
     for it in items:
         if "gpu" in it.keywords:
             it.add_marker(skip)
+
+
+@pytest.fixture(autouse=True, scope="module")
+def _collect_garbage():
+    # Tensors that only a reference cycle holds (a caught exception's frames) go before the next module starts: a later
+    # test that watches the allocator would see them go in its midst.
+    import gc
+    yield
+    gc.collect()

@@ -9,8 +9,9 @@ import torch
 from oracle import st_oracle as O
 from paper_2511_14881_amd import binding as st
 from paper_2511_14881_amd import synth as S
-from tests.test_gpu_expr import check_ivf, pack
+from tests.test_gpu_expr import check_expr_search, check_ivf, pack
 from tests.test_gpu_parity import check_search, oracle_index, ragged_workload
+from tests.test_oracle_expr_pins import postfix
 
 pytestmark = pytest.mark.gpu
 
@@ -244,6 +245,24 @@ def test_own_filters(n, d, B, m, kind):
     assert kind == "ties" or len(fast) > B // 2
     check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, max(1, B // 12))}), slow_path=([], fast),
                  label=f"own filters {kind}")
+
+
+# The same scan over rows of evaluated programs: few of them (all rows are staged) and more than 64 (the named ones are).
+@pytest.mark.parametrize("n,B", [(300_011, 37), (270_400, 100), (400_000, 140)])
+def test_own_programs(n, B):
+    w = ragged_workload(n, n, 96, B, 24, 6, 128, 3)
+    programs = [postfix(("and", ("leaf", b % 24), ("not", ("leaf", (b * 7 + 1 + b // 24) % 24)))) if b % 2 else
+                postfix(("or", ("leaf", b % 24), ("leaf", (b // 24 + b + 3) % 24))) for b in range(B)]
+    programs[3] = ([], [])
+    check_expr_search(w, programs, 60, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, 9)}), label="own programs", fast_path_only=True)
+
+
+# ... and behind cluster probing through mask rows, where most items pass for no query.
+@pytest.mark.parametrize("n,d,B,n_c,n_p", [(800_003, 64, 17, 4000, 600), (900_000, 96, 70, 700, 520)])
+def test_own_scan_behind_probing(n, d, B, n_c, n_p):
+    w = ragged_workload(n, n, d, B, 24, 4, 64, 2)
+    check_ivf(w, _programs(np.random.default_rng(n), B, 24), n_c, n_p, 50, queries=sorted({0, 1, 2, B - 1, *range(0, B, 12)}),
+              label="own scan behind probing")
 
 
 # The final ordering of K > 2048 cuts the score range into steps: scores of one size, a few far above the rest
