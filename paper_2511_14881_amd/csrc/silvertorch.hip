@@ -1407,7 +1407,8 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                     density_on = admit_all;
                     mp.density_acc = admit_all ? (unsigned long long*)(ws + L.density) : nullptr;
                     // pairs of the level if every filter passed kDenseItems items per 512-item segment
-                    mp.density_limit = (unsigned long long)((L_.end - L_.begin) * (int64_t)batch / 512 * st::kDenseItems);
+                    mp.density_pairs = (L_.end - L_.begin) * (int64_t)batch;
+                    mp.density_limit = (unsigned long long)(mp.density_pairs / 512 * st::kDenseItems);
                 } else if (!density_on) {
                     mp.density_acc = nullptr;
                 }

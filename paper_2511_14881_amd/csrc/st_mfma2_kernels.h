@@ -15,8 +15,9 @@
 //     F <= 2^P with P = 16 - log2 d keep dot * F within 2^30.
 //   * An item's scale is loaded with its row (one 4-byte load per lane and unit), so nothing is
 //     staged or reduced per segment.
+// The kernel that holds it also holds the form by units (st_tile_kernels.h) and the first one, and picks.
 #pragma once
-#include "st_mfma_kernels.h"
+#include "st_tile_kernels.h"
 
 namespace st {
 
@@ -703,14 +704,17 @@ __device__ __forceinline__ void scan_mfma2_body(const ScanParams& p, const MfmaP
     }
 }
 
-// Few passing items per filter and segment: units would be mostly padding, the carrying form
-// wins; many: the first form's cheaper unit set-up wins (the cross-over lies near a dozen items
-// per filter and 512-item segment).  The count comes from the first level of the same search.
+// Which form a level takes is decided by how many items the filters pass, which the first level of the same search has
+// counted.  Where a wavefront fills units of 64 items over the level, the form by units; else, with few passing items
+// per filter and segment (units of 16 would be mostly padding), the carrying form, and with more the first form's
+// cheaper unit set-up (the cross-over between those two lies near a dozen items per filter and 512-item segment).
 template <int KS, int TT, bool WEIGHTED>
-__global__ __launch_bounds__(512, 2) void scan_mfma2_kernel(ScanParams p, MfmaParams mp)
+__global__ __launch_bounds__(512, 2) void scan_mfma2_kernel(ScanParams p, MfmaParams mp, TileLds tile)
 {
-    const bool sparse = mp.density_acc != nullptr && *mp.density_acc < mp.density_limit;
-    if (sparse)
+    const unsigned long long pairs = mp.density_acc ? *mp.density_acc : 0ULL;
+    if (tile.total > 0 && pairs >= tile.min_pairs)
+        scan_tile_body<KS, TT, WEIGHTED>(p, mp, tile);
+    else if (mp.density_acc != nullptr && pairs < mp.density_limit)
         scan_mfma2_body<KS, TT, WEIGHTED>(p, mp);
     else
         scan_mfma_body<KS, TT, WEIGHTED, true, 8, false>(p, mp);
@@ -720,18 +724,20 @@ template <int KS, int TT, bool WEIGHTED>
 inline hipError_t launch_scan_mfma2_t(const ScanParams& sp, const MfmaParams& mp, int gx, hipStream_t stream)
 {
     static std::atomic<int> max_set{0};
-    if (mp.lds_total > max_set.load(std::memory_order_acquire)) {
+    TileLds tile;
+    const int lds = scan_tile_applies(sp, mp, gx, &tile) && tile.total > mp.lds_total ? tile.total : mp.lds_total;
+    if (lds > max_set.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&scan_mfma2_kernel<KS, TT, WEIGHTED>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, mp.lds_total);
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, lds);
         if (e != hipSuccess) return e;
-        max_set.store(mp.lds_total, std::memory_order_release);
+        max_set.store(lds, std::memory_order_release);
     }
     const dim3 grid((unsigned)gx, (unsigned)mp.q_split);
-    hipLaunchKernelGGL((scan_mfma2_kernel<KS, TT, WEIGHTED>), grid, dim3(512), (size_t)mp.lds_total, stream, sp, mp);
+    hipLaunchKernelGGL((scan_mfma2_kernel<KS, TT, WEIGHTED>), grid, dim3(512), (size_t)lds, stream, sp, mp, tile);
     return hipGetLastError();
 }
 
-// Whether a launch with these parameters is served by the second form.
+// Whether a launch with these parameters is served by the forms of this file.
 inline bool scan_mfma2_applies(const ScanParams& sp, const MfmaParams& mp)
 {
     const bool admit = !sp.use_tau && sp.seg_per_visit == 1 && sp.seg_items <= sp.cap;

@@ -80,6 +80,7 @@ struct MfmaParams {
     // it with density_limit to choose between the two forms of the scan (null: none of this).
     unsigned long long* density_acc;
     unsigned long long density_limit;
+    long long density_pairs;     // pairs of the first level, whether they pass or not
     // dynamic LDS layout (byte offsets)
     int32_t lds_sq, lds_tauf, lds_tau64, lds_qrow, lds_cnt, lds_list, lds_queue, lds_prow, lds_blkoff, lds_rowoff, lds_tq, lds_thr, lds_scl, lds_total;
 };

@@ -368,3 +368,47 @@ def test_probing_batch_with_few_words_to_a_query(n, big, K):
     for g, x in zip(got, want):
         x = np.asarray(x)
         assert np.array_equal(g[sel].view(np.uint32) if g.dtype == np.float32 else g[sel], x.view(np.uint32) if x.dtype == np.float32 else x)
+
+
+# The scan by units of passing items (levels behind the first, one workgroup to a compute unit, filters broad enough that
+# every wavefront fills units): each row length and number of tasks, filters with an odd number of 16-row blocks, up to
+# 32 filters and more, no filter, one that nothing passes, ragged last segment and word, few and many passing items
+# (lists by lane and by word), more than 8 and 16 signature rows, scales of many sizes, scores that are all negative
+# (no bound), tied scores, queries split over rows of workgroups.  "rare" and "many": the other forms of the same level.
+@pytest.mark.parametrize("n,d,B,T,groups,m,k,kind", [
+    (700_001, 64, 900, 0, 5, 128, 2, "plain"), (800_049, 128, 500, 0, 8, 128, 2, "plain"), (900_000, 256, 240, 0, 7, 256, 3, "plain"),
+    (690_031, 128, 1000, 0, 2, 64, 1, "dense"), (900_000, 256, 600, 0, 20, 512, 4, "plain"), (680_000, 64, 1100, 0, 31, 256, 3, "plain"),
+    (950_017, 128, 420, 0, 4, 1024, 7, "long"), (700_011, 256, 250, 0, 4, 1024, 7, "long"), (710_000, 128, 450, 0, 6, 128, 2, "scales"),
+    (700_000, 256, 260, 0, 4, 128, 2, "negative"), (700_000, 128, 400, 0, 3, 64, 2, "ties"), (600_000, 256, 250, 0, 8, 512, 4, "rare"),
+    (760_000, 64, 200, 4, 7, 128, 2, "plain"), (800_007, 128, 128, 4, 8, 128, 2, "plain"), (470_000, 256, 110, 2, 5, 128, 2, "plain"),
+    (780_001, 128, 420, 1, 3, 128, 2, "plain"), (860_000, 128, 130, 4, 12, 256, 3, "negative"), (300_000, 64, 1000, 0, 40, 256, 3, "many")])
+def test_scan_by_units(n, d, B, T, groups, m, k, kind):
+    rng = np.random.default_rng(n + d)
+    vocab, feats = (40, 4) if kind == "rare" else (40, 30) if kind == "many" else (12, 12)
+    w = ragged_workload(n + d, n, d, B, vocab, feats, m, k, T=T)
+    pool = [[] if g == 1 and kind != "rare" else [999] if g == 2 else [g % vocab] if g % 3 == 0 or kind == "dense" else
+            [g % vocab, *(int(x) for x in rng.choice(vocab, 2 if kind == "long" else 1))] for g in range(groups)]
+    pick = np.concatenate([np.arange(groups), rng.integers(0, groups, B - groups)])
+    filters = [pool[g] for g in pick]
+    w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
+    w.filt_offsets = np.concatenate([[0], np.cumsum([len(f) for f in filters])]).astype(np.int64)
+    if kind == "scales":
+        w.item_scale = torch.from_numpy(np.exp2(rng.uniform(-20, 20, n)).astype(np.float32))
+    elif kind == "negative":  # every score is below zero
+        w.items = w.items.abs().clamp(1, 127).to(torch.int8)
+        w.queries = (-w.queries.abs().clamp(1, 127).to(torch.int16)).to(torch.int8)
+    elif kind == "ties":
+        w.items = w.items[:997].repeat(n // 997 + 1, 1)[:n].contiguous()
+        w.item_scale = w.item_scale[:997].repeat(n // 997 + 1)[:n].contiguous()
+    K = 50
+    plan = st.st_search_host_plan(n, d, B, max(T, 1), K, m, k, w.filt_ids, w.filt_offsets)
+    assert plan["waves"] == 8 and plan["levels"] >= 2, plan
+    sigs = oracle_index(w)
+    passing = {g: int(np.unpackbits(O.bloom_mask(sigs, m, k, np.array(pool[g], np.uint64)).view(np.uint8)).sum()) for g in range(groups)}
+    # a wavefront's share of what an average query's filter passes decides for this form
+    share = np.mean([passing[g] for g in pick]) / (2048 / plan["q_split"])
+    assert kind in ("rare", "many") or share >= (64 if d <= 128 else 110), share
+    fast = [b for b in range(B) if passing[pick[b]] >= 40 * K] if kind not in ("ties", "scales") else []
+    assert kind in ("ties", "scales") or len(fast) > B // 2
+    check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, B - 1, *range(0, B, max(1, B // 14))}), slow_path=([], fast),
+                 label=f"units {kind}")
