@@ -7,15 +7,21 @@
 // wavefront whose filters pass few pairs (own_pairs) gathers after all, and one that did so requests the next
 // items' rows only when their masks are known.
 //
-// Eight wavefronts take a segment of 512 items.  Its part of the index (the rows that some filter names, 64 bytes each,
-// m <= kOwnRows) is brought to LDS with loads requested a segment ahead, and the mask words of all filters are formed
-// there (a filter's rows fetched one by one from memory took longer than the products).  A mask word is what one
-// wavefront needs for one query: lane l of the product's result holds query l % 32, and 16 of its items.
+// Eight wavefronts take a segment of 512 items, 64 items each; up to the reports of a region they share the queries
+// and the tables in LDS and nothing else, so that one forms masks or waits for rows while another multiplies.  A wavefront's
+// words of the index (the rows that some filter names, m <= kOwnRows) come to LDS with loads requested a segment
+// ahead, and its mask words of all filters are formed there (a filter's rows fetched one by one from memory took
+// longer than the products).  A mask word is what it needs for one query: lane l of the product's result holds query l % 32,
+// and 16 of its items.  The items go in two halves of 32; the first half of the next ones is requested behind the
+// products of the first half, into the same registers.  A pair is tested by one multiply-add (the item's scale in fixed point,
+// the query's bound) whose sign goes to the bit of the pair's item; lanes with a bit left under the mask are
+// queued with their 16 dot products, and the exact score, key and threshold test run where the queue is emptied.
 // The queries stay in LDS, padded by 16 bytes a row (an odd number of 16-byte pieces: no bank conflicts).
 // 10 M x 256 bytes, 256 queries with filters of their own (5 % each), K = 500: the level after the first takes
-// 1.33 ms, where gathering took 4.5 (the call 4.93 -> 1.65 ms); 778 k x 96 with 37 filter programs: 38 us.  Bound by
-// the tests of the scores (six vector instructions to a pair, 2.6 G pairs) beside the products; two wavefronts to a SIMD
-// leave part of the row loads uncovered.
+// 1.09 ms, where gathering took 4.5 (1.26 with exact tests of all scores and two barriers to a segment); 778 k x 96
+// with 37 filter programs: 35.5 us (38).  Bound by round trips to LDS (operands, masks, queue: 55 % of a wavefront's
+// time) with two wavefronts to a SIMD; the products alone keep the matrix units busy a fifth of the time, the
+// rows of all items once are 0.5 ms of memory.
 //
 // It takes the place of the gathering scan whatever the filters pass, which the host cannot know.  Calls on 3 M
 // items, m = 512, K = 100, every query with a filter of its own, gathering -> this scan, in us (d = 256 unless
@@ -41,6 +47,7 @@ constexpr int kOwnRows = 512;           // signature rows of the index, at most
 // regions have room for segments of this size is the plan's to say: level_takes_segments.)
 constexpr int64_t kOwnMinItems = 512 * kOwnSeg;
 constexpr int kOwnAllRows = 64;         // an index of no more rows is staged whole
+constexpr int kOwnQueue = 16;           // lanes of a wavefront that wait for the exact test
 constexpr int kOwnRowRefs = 6144;       // rows all filters name together, at most
 static_assert(kOwnWords == kOwnThreads / 64, "a word per wavefront");
 
@@ -53,15 +60,16 @@ constexpr int own_pairs(int cols) { return cols < 64 ? 64 : cols; }
 constexpr size_t own_lds_bytes(int n_q, int d, int m_bits)
 {
     const size_t c = own_cols(n_q);
-    return c * (d + 16) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnRowRefs * 2 + c * (8 + 4 * 5) +
-           own_pairs((int)c) * (kOwnThreads / 64) * 2 + kOwnRows * 2 + kOwnRows / 8;
+    return c * (d + 16) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnRowRefs * 2 + c * (8 + 4 * 6) +
+           own_pairs((int)c) * (kOwnThreads / 64) * 2 + kOwnRows * 2 + kOwnRows / 8 +
+           (size_t)kOwnWords * (64 * 4 + kOwnQueue * (16 * 4 + 8));
 }
 static_assert(own_lds_bytes(kOwnCols, 256, kOwnRows) <= 160 * 1024, "LDS of a compute unit");
 
 typedef int own_i4 __attribute__((ext_vector_type(4)));
 typedef int own_i16 __attribute__((ext_vector_type(16)));
 
-// LDS exchange without waiting for the global loads in flight (they go to registers of their own).
+// LDS exchange of the workgroup's set-up.
 __device__ inline void own_barrier()
 {
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
@@ -77,13 +85,15 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char own_lds[];
     constexpr int D = 32 * KS, DP = D + 16;
-    const int tid = threadIdx.x, lane = tid & 63, wv = tid >> 6, half = lane >> 5;
+    constexpr int P = KS <= 2 ? 10 : (KS <= 4 ? 9 : 8);   // bits of a scale in fixed point: |dot| <= 2^14 d, the product at most 2^30
+    constexpr int kPass = (1 << 30) - 1, kNever = -(1 << 30) - 1;  // bounds that every pair reaches, and none
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     const int n_q = p.grp_q_off[p.n_groups];
     const int cols = own_cols(n_q), c0 = (int)blockIdx.y * kOwnCols, n_c = min(n_q - c0, cols);
     unsigned char* at = own_lds;
     int8_t* s_q = reinterpret_cast<int8_t*>(at);                  at += (size_t)cols * DP;          // [cols][DP]
-    uint64_t* s_mask = reinterpret_cast<uint64_t*>(at);           at += (size_t)cols * kOwnWords * 8;
-    uint64_t* s_idx = reinterpret_cast<uint64_t*>(at);            at += (size_t)p.m_bits * kOwnWords * 8;  // [m_bits][kOwnWords]
+    uint64_t* s_mask = reinterpret_cast<uint64_t*>(at) + (size_t)wv * cols;      at += (size_t)cols * kOwnWords * 8;
+    uint64_t* s_idx = reinterpret_cast<uint64_t*>(at) + (size_t)wv * p.m_bits;   at += (size_t)p.m_bits * kOwnWords * 8;
     uint64_t* s_tau = reinterpret_cast<uint64_t*>(at);            at += (size_t)cols * 8;
     float* s_sq = reinterpret_cast<float*>(at);                   at += (size_t)cols * 4;
     int32_t* s_query = reinterpret_cast<int32_t*>(at);            at += (size_t)cols * 4;
@@ -94,7 +104,11 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
     uint16_t* s_pairs = reinterpret_cast<uint16_t*>(at) + (size_t)wv * few;  at += (size_t)few * (kOwnThreads / 64) * 2;
     uint16_t* s_refs = reinterpret_cast<uint16_t*>(at);           at += (size_t)kOwnRowRefs * 2;
     uint16_t* s_named = reinterpret_cast<uint16_t*>(at);          at += (size_t)kOwnRows * 2;
-    uint32_t* s_bits = reinterpret_cast<uint32_t*>(at);           // [kOwnRows / 32]
+    uint32_t* s_bits = reinterpret_cast<uint32_t*>(at);           at += kOwnRows / 8;               // [kOwnRows / 32]
+    uint32_t* q_val = reinterpret_cast<uint32_t*>(at) + (size_t)wv * kOwnQueue * 16;  at += (size_t)kOwnWords * kOwnQueue * 64;
+    uint2* q_code = reinterpret_cast<uint2*>(at) + (size_t)wv * kOwnQueue;  at += (size_t)kOwnWords * kOwnQueue * 8;
+    float* s_si = reinterpret_cast<float*>(at) + (size_t)wv * 64; at += (size_t)kOwnWords * 64 * 4;  // scales of the wavefront's items
+    int32_t* s_neg = reinterpret_cast<int32_t*>(at);              // [cols] bounds, for the largest exponent so far
 
     if (tid < kOwnRows / 32) s_bits[tid] = 0;
     for (int c = tid; c < cols; c += kOwnThreads) {
@@ -106,6 +120,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
         s_tau[c] = t;
         s_sq[c] = q >= 0 ? p.qscale[q] : 0.0f;
         s_cnt[c] = 0;
+        s_neg[c] = kNever;
     }
     for (int g = tid; g < p.n_groups; g += kOwnThreads) {
         const int r0 = p.grp_row_off[g], rn = p.grp_row_off[g + 1] - r0;
@@ -151,8 +166,8 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
         if (s_bits[tid >> 5] >> (tid & 31) & 1) s_named[named_before(tid)] = (uint16_t)tid;
         for (int i = tid; i < n_refs; i += kOwnThreads) s_refs[i] = (uint16_t)named_before(s_refs[i]);
         n_named = named_before(kOwnRows);
-        own_barrier();
     }
+    own_barrier();  // the last one: from here on every wavefront works by itself, up to the reports
 
     const int64_t n_seg = (p.item_end - p.item_begin + kOwnSeg - 1) / kOwnSeg;
     const int64_t n_visit = (n_seg + p.seg_per_visit - 1) / p.seg_per_visit;
@@ -187,27 +202,63 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
         }
         __syncthreads();
     };
-    // its index block: 4 pieces of 16 bytes to a named row, kOwnRows * 4 / kOwnThreads to a thread
-    constexpr int kIdx = kOwnRows * 4 / kOwnThreads;
-    const int n_idx = n_named * 4;
-    own_i4 idx[kIdx];
+    // index words of the wavefront's 64 items: one to a named row
+    constexpr int kIdx = kOwnRows / 64;
+    uint64_t idx[kIdx];
     int idx_at[kIdx];
 #pragma unroll
     for (int u = 0; u < kIdx; ++u) {
-        const int x = min(tid + u * kOwnThreads, n_idx - 1);  // (the last piece again: an unconditional load)
-        idx_at[u] = x < 0 ? 0 : (p.m_bits <= kOwnAllRows ? x >> 2 : (int)s_named[x >> 2]) * (kTileWords / 2) + (x & 3);
+        const int x = max(min(lane + u * 64, n_named - 1), 0);  // (the last row again: an unconditional load)
+        idx_at[u] = (p.m_bits <= kOwnAllRows ? min(x, p.m_bits - 1) : n_named > 0 ? (int)s_named[x] : 0) * kTileWords;
     }
     auto fetch = [&](int64_t sg) __attribute__((always_inline)) {
-        const int64_t w0 = (p.item_begin + sg * kOwnSeg) >> 6;
-        const own_i4* src = reinterpret_cast<const own_i4*>(p.bloom + (w0 >> 4) * (int64_t)p.m_bits * kTileWords) + ((w0 & 15) >> 1);
+        const int64_t w0 = ((p.item_begin + sg * kOwnSeg) >> 6) + wv;
+        const uint64_t* src = p.bloom + (w0 >> 4) * (int64_t)p.m_bits * kTileWords + (w0 & 15);
 #pragma unroll
-        for (int u = 0; u < kIdx; ++u) idx[u] = src[idx_at[u]];
+        for (int u = 0; u < kIdx; ++u)
+            if (u * 64 < n_named) idx[u] = src[idx_at[u]];
     };
-    uint32_t last = ~0u;  // pairs that passed among this wavefront's last items; if it multiplied those, the next items' rows are requested before their masks are known
+    // This wavefront's item rows (past the end the last row is repeated: no mask names it), 32 items to a half, and the
+    // scales of the items this lane holds results of.  If the wavefront multiplied its last items, the first half of the
+    // next ones is requested behind the products of the first half, into the same registers, and the second half
+    // at the top of the segment; both before the masks are known.  Otherwise they are requested behind the masks: where
+    // the filters pass little they are never read.
+    own_i4 a[2][KS];
+    float4 si[2][4];
+    bool have0 = false;
+    // (In two forms: whole words of items with vector loads of the scales, and any, for the words that are late.)
+    auto rows = [&](auto whole, int s, int64_t my0) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole)::value;
+        int64_t it = my0 + s * 32 + (lane & 31);
+        if (!kWhole) it = min(it, p.n_items - 1);
+        const own_i4* row = reinterpret_cast<const own_i4*>(p.items + it * D) + half;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) a[s][k] = row[2 * k];
+        int64_t it0 = my0 + 4 * half + s * 32;
+        if (!kWhole) asm volatile("" : "+v"(it0));  // (16 offsets, kept in registers all the time otherwise)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (kWhole) {
+                si[s][j] = *reinterpret_cast<const float4*>(p.iscale + it0 + j * 8);
+            } else {
+                float v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = p.iscale[min(it0 + j * 8 + i, p.n_items - 1)];
+                si[s][j] = make_float4(v[0], v[1], v[2], v[3]);
+            }
+        }
+    };
+    int cur_E = -1000;        // every scale that this wavefront's factors cover is below 2^cur_E (none yet)
+    float fix_scale = 0.0f;   // 2^(P - cur_E)
     const int first_region = region;
     settle();
     seg = vs * p.seg_per_visit;
-    if (region < p.groups) fetch(seg);
+    if (region < p.groups) {
+        fetch(seg);
+        const int64_t my0 = p.item_begin + seg * kOwnSeg + wv * 64;
+        have0 = my0 + 64 <= p.n_items;
+        if (have0) rows(std::true_type{}, 0, my0);
+    }
     int filling = first_region;  // the region that the counters belong to
     while (region < p.groups) {
         if (region != filling) {
@@ -218,86 +269,48 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
         const int64_t item0 = p.item_begin + seg * kOwnSeg, my0 = item0 + wv * 64;
         auto stage = [&]() __attribute__((always_inline)) {
 #pragma unroll
-            for (int u = 0; u < kIdx; ++u) {
-                const int x = tid + u * kOwnThreads;
-                if (x < n_idx) reinterpret_cast<own_i4*>(s_idx)[x] = idx[u];
-            }
-        };
-        // This wavefront's item rows (past the end the last row is repeated: no mask names it), and the scales of the
-        // items this lane holds results of.  They are requested before the masks are known if the wavefront
-        // multiplied its last items, and behind them otherwise: where the filters pass little they are never read.
-        own_i4 a[2][KS];
-        float si[2][16];
-        // (In two forms: whole words of items with vector loads of the scales, and any, for the words that are late.)
-        auto rows = [&](auto whole) __attribute__((always_inline)) {
-            constexpr bool kWhole = decltype(whole)::value;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                int64_t it = my0 + s * 32 + (lane & 31);
-                if (!kWhole) it = min(it, p.n_items - 1);
-                const own_i4* row = reinterpret_cast<const own_i4*>(p.items + it * D) + half;
-#pragma unroll
-                for (int k = 0; k < KS; ++k) a[s][k] = row[2 * k];
-            }
-            int64_t it0 = my0 + 4 * half;
-            if (!kWhole) asm volatile("" : "+v"(it0));  // (32 offsets, kept in registers all the time otherwise)
-#pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    if (kWhole) {
-                        const float4 v = *reinterpret_cast<const float4*>(p.iscale + it0 + s * 32 + j * 8);
-                        si[s][4 * j] = v.x;
-                        si[s][4 * j + 1] = v.y;
-                        si[s][4 * j + 2] = v.z;
-                        si[s][4 * j + 3] = v.w;
-                    } else {
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) si[s][4 * j + i] = p.iscale[min(it0 + s * 32 + j * 8 + i, p.n_items - 1)];
-                    }
-                }
+            for (int u = 0; u < kIdx; ++u)
+                if (lane + u * 64 < n_named) s_idx[lane + u * 64] = idx[u];
         };
         // (the index block is stored in either branch: behind one where the rows may or may not have been
         // requested, the wait for the block is one for the rows as well)
-        const bool early = last > (uint32_t)few && my0 + 64 <= p.n_items;
+        const bool early = have0;  // this wavefront multiplied its last items, and the first half of these rows is requested
         if (early) {
-            rows(std::true_type{});
             stage();
+            rows(std::true_type{}, 1, my0);
         } else {
             stage();
         }
-        own_barrier();
+        have0 = false;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
         advance();
         if (region < p.groups) fetch(seg);
-        for (int i = tid; i < cols * kOwnWords; i += kOwnThreads) {
-            const int c = i / kOwnWords, w = i % kOwnWords;
+        const int64_t left = item_lim - my0;
+        const uint64_t all = left >= 64 ? ~0ULL : left > 0 ? ((1ULL << left) - 1ULL) : 0ULL;
+        uint32_t n_pass = 0;  // pairs that pass, over all queries
+        for (int c = lane; c < cols; c += 64) {
             uint64_t m = 0;
             if (c < n_c) {
-                const int64_t left = item_lim - (item0 + w * 64);
-                m = left >= 64 ? ~0ULL : left > 0 ? ((1ULL << left) - 1ULL) : 0ULL;
+                m = all;
                 const uint16_t* refs = s_refs + s_r0[c];
                 const int rn = s_rn[c];
                 int r = 0;
                 for (; r + 4 <= rn; r += 4) {
-                    const uint64_t m0 = s_idx[refs[r] * kOwnWords + w], m1 = s_idx[refs[r + 1] * kOwnWords + w];
-                    const uint64_t m2 = s_idx[refs[r + 2] * kOwnWords + w], m3 = s_idx[refs[r + 3] * kOwnWords + w];
+                    const uint64_t m0 = s_idx[refs[r]], m1 = s_idx[refs[r + 1]], m2 = s_idx[refs[r + 2]], m3 = s_idx[refs[r + 3]];
                     m &= (m0 & m1) & (m2 & m3);
                 }
-                for (; r < rn; ++r) m &= s_idx[refs[r] * kOwnWords + w];
+                for (; r < rn; ++r) m &= s_idx[refs[r]];
             }
-            s_mask[c * kOwnWords + w] = m;
+            s_mask[c] = m;
+            n_pass += (uint32_t)__popcll(m);
         }
-        own_barrier();
-        // pairs that pass, over all queries
-        uint32_t n_pass = 0;
-        for (int c = lane; c < cols; c += 64) n_pass += (uint32_t)__popcll(s_mask[c * kOwnWords + wv]);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
         const uint32_t incl = wave_scan_add(n_pass);
         const uint32_t total = lane_value(incl, 63);
         if (total <= (uint32_t)few) {
-            last = total;
             uint32_t pos = incl - n_pass;
             for (int c = lane; c < cols; c += 64) {
-                uint64_t m = s_mask[c * kOwnWords + wv];
+                uint64_t m = s_mask[c];
                 while (m) {
                     const int bit = __ffsll((long long)m) - 1;
                     m &= m - 1;
@@ -324,57 +337,116 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
             }
             continue;
         }
-        if (!early) rows(std::false_type{});
-        last = total;
-        for (int b = 0; b < cols; b += 32) {
-            const int c = b + (lane & 31);
-            const uint64_t word = s_mask[c * kOwnWords + wv];
-            if (ballot(word != 0) == 0) continue;
-            own_i16 acc[2];
+        if (!early) {
+            rows(std::false_type{}, 0, my0);
+            rows(std::false_type{}, 1, my0);
+        }
+        // Lanes in which an admission is possible, emptied four lanes to an entry: the exact test of their pairs.
+        int qn = 0;
+        auto drain = [&]() __attribute__((always_inline)) {
+            const int e = lane >> 2, h = lane & 3;
+            if (e < qn) {
+                const uint2 code = q_code[e];  // (admissible results, where the lane was: column, half, set)
+                const int4 v4 = reinterpret_cast<const int4*>(q_val + e * 16)[h];
+                const int c = (int)(code.y & 255u), bit0 = (int)(code.y >> 9) * 32 + 8 * h + 4 * (int)((code.y >> 8) & 1u);
+                const float4 si4 = *reinterpret_cast<const float4*>(s_si + bit0);
+                const float sq = s_sq[c];
+                const uint64_t tau = s_tau[c];
+                const int v[4] = {v4.x, v4.y, v4.z, v4.w};
+                const float sv[4] = {si4.x, si4.y, si4.z, si4.w};
 #pragma unroll
-            for (int s = 0; s < 2; ++s)
-#pragma unroll
-                for (int i = 0; i < 16; ++i) acc[s][i] = 0;
-            const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)c * DP) + half;
-#pragma unroll
-            for (int k = 0; k < KS; ++k) {
-                const own_i4 bq = qr[2 * k];
-                acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[0][k], bq, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[1][k], bq, acc[1], 0, 0, 0);
-            }
-            const float sq = s_sq[c];
-            const uint64_t tau = s_tau[c];
-            // A score below the threshold's cannot be admitted; the others (also where a NaN is involved) are
-            // compared as keys.
-            const float bound = tau ? bits_score((uint32_t)(tau >> 32)) : -__builtin_inff();
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                // result i of set s is item 32 s + 8 (i / 4) + 4 half + i % 4
-                uint32_t over = 0;
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const float sc = rescale(acc[s][i], sq, si[s][i]);
-                    over |= !(sc < bound) ? 1u << (8 * (i >> 2) + (i & 3)) : 0u;
-                }
-                over &= (uint32_t)(word >> (32 * s)) >> (4 * half);
-                if (ballot(over != 0) != 0) {
-                    uint32_t it0 = (uint32_t)my0 + 32u * s + 4u * half;
-                    asm volatile("" : "+v"(it0));  // (16 ids to a set, kept in registers all the time otherwise)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int bit = 8 * (i >> 2) + (i & 3);
-                        if (over >> bit & 1) {
-                            const float sc = rescale(acc[s][i], sq, si[s][i]);
-                            const uint64_t key = make_key(sc, it0 + bit);
-                            if (key >= tau) {
-                                const uint32_t slot = atomicAdd(&s_cnt[c], 1u);
-                                if (slot < (uint32_t)p.cap) p.cand[((int64_t)s_query[c] * p.groups + at_region) * p.cap + slot] = key;
-                            }
-                        }
+                for (int i = 0; i < 4; ++i) {
+                    const uint64_t key = make_key(rescale(v[i], sq, sv[i]), (uint32_t)my0 + (uint32_t)(bit0 + i));
+                    if ((code.x >> (8 * h + i) & 1u) && key >= tau) {
+                        const uint32_t slot = atomicAdd(&s_cnt[c], 1u);
+                        if (slot < (uint32_t)p.cap) p.cand[((int64_t)s_query[c] * p.groups + at_region) * p.cap + slot] = key;
                     }
                 }
             }
+            qn = 0;
+        };
+        const int64_t next0 = p.item_begin + seg * kOwnSeg + wv * 64;  // (the segment advanced above)
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            // The scales: exact ones for the tests, and fixed-point factors against a power of two above the scales met
+            // so far.  A pair can only be admitted if dot * factor reaches its query's bound (rounded down by more than all
+            // roundings involved).
+            const float sv[16] = {si[s][0].x, si[s][0].y, si[s][0].z, si[s][0].w, si[s][1].x, si[s][1].y, si[s][1].z, si[s][1].w,
+                                  si[s][2].x, si[s][2].y, si[s][2].z, si[s][2].w, si[s][3].x, si[s][3].y, si[s][3].z, si[s][3].w};
+            if ((lane & 31) == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) *reinterpret_cast<float4*>(s_si + 32 * s + 8 * j + 4 * half) = si[s][j];
+            }
+            uint32_t top = 0;  // (scales are positive, so their bit patterns order as they do; others switch the bound off)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) top = max(top, __float_as_uint(sv[i]));
+            const float smax = __uint_as_float(max(lane_value(top, 0), lane_value(top, 32)));
+            const bool cull = smax > 0x1p-90f && smax < 0x1p90f;
+            const int E = (int)(__float_as_uint(smax) >> 23) - 126;  // 2^E > smax
+            if (cull && E > cur_E) {  // (a handful of times to a launch; a bound for a larger exponent lets more pairs through)
+                cur_E = E;
+                fix_scale = __uint_as_float((uint32_t)(P - E + 127) << 23);
+                for (int c = lane; c < cols; c += 64) {
+                    const uint64_t tau = s_tau[c];
+                    const float tf = key_score(tau);
+                    const float tq = tf / s_sq[c];
+                    int neg = kPass;
+                    if (tau != 0 && tf > 0.0f && tq > 0.0f && tq < __builtin_inff())
+                        neg = -min(__float2int_rd(fminf(tq * (fix_scale * 0.99999618530273f), 1.2e9f)), (1 << 30) + 1);  // (1 - 2^-18)
+                    atomicMax(&s_neg[c], neg);
+                }
+            }
+            int fix[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) fix[i] = cull ? max(__float2int_ru(sv[i] * fix_scale), 1) : 0;
+            for (int b = 0; b < cols; b += 32) {
+                const int c = b + (lane & 31);
+                const uint32_t word = (uint32_t)(s_mask[c] >> (32 * s)) >> (4 * half);
+                own_i16 acc;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[i] = 0;
+                const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)c * DP) + half;
+#pragma unroll
+                for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][k], qr[2 * k], acc, 0, 0, 0);
+                const int neg = cull ? s_neg[c] : kPass;
+                // result i is item 32 s + 8 (i / 4) + 4 half + i % 4; the signs of the tests go to the bits of the mask word
+                uint32_t below = 0;
+#pragma unroll
+                for (int j = 3; j >= 0; --j) {
+                    if (j < 3) below <<= 4;
+#pragma unroll
+                    for (int i = 4 * j + 3; i >= 4 * j; --i)
+                        below = __builtin_amdgcn_alignbit(below, (uint32_t)(__mul24(acc[i], fix[i]) + neg), 31);
+                }
+                const uint32_t over = word & ~below & 0x0F0F0F0Fu;
+                const uint64_t hits = ballot(over != 0);
+                if (hits == 0) continue;
+                uint64_t m = hits;
+                for (;;) {  // (more lanes than the queue holds go in rounds)
+                    const int n = __popcll(m);
+                    if (qn > 0 && qn + n > kOwnQueue) drain();
+                    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+                    const bool mine = ((m >> lane) & 1ULL) && rank < kOwnQueue;
+                    if (mine) {
+                        int4* dst = reinterpret_cast<int4*>(q_val + (qn + rank) * 16);
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) dst[j] = make_int4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
+                        q_code[qn + rank] = make_uint2(over, (uint32_t)(c | (half << 8) | (s << 9)));
+                    }
+                    if (n <= kOwnQueue) {
+                        qn = __builtin_amdgcn_readfirstlane(qn + n);
+                        break;
+                    }
+                    qn = kOwnQueue;
+                    m &= ~ballot(mine);
+                }
+            }
+            if (s == 0) {
+                have0 = region < p.groups && next0 + 64 <= p.n_items;
+                if (have0) rows(std::true_type{}, 0, next0);
+            }
         }
+        if (qn > 0) drain();
     }
     report(filling, p.groups);
 }
