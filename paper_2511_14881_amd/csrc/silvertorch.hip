@@ -1434,6 +1434,14 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             hipLaunchKernelGGL(own_scan, dim3(std::min(plan.groups, st::kComputeUnits), (set_dot.q_list.size() + st::kOwnCols - 1) / st::kOwnCols),
                                dim3(st::kOwnThreads), lds, stream, sp_o, (int)set_dot.rows.size());
             ST_HIP(hipGetLastError());
+        } else if (set_dot.n && own_scan && lv == 0 && L_.end > L_.begin && plan.cap == 64 && plan.groups % (st::kOwnThreads / 64) == 0) {
+            // the first level: 64 consecutive items to a region, every passing pair is admitted
+            static_assert(st::own_first_lds_bytes(256) <= 64 * 1024, "no larger dynamic LDS to be asked for");
+            TimedLaunch t(0, stream);
+            hipLaunchKernelGGL(st::own_first_kernel(d),
+                               dim3(plan.groups / (st::kOwnThreads / 64), (set_dot.q_list.size() + st::kOwnFirstCols - 1) / st::kOwnFirstCols),
+                               dim3(st::kOwnThreads), st::own_first_lds_bytes(d), stream, sp_d);
+            ST_HIP(hipGetLastError());
         } else if (set_dot.n) {
             TimedLaunch t(0, stream);
             hipLaunchKernelGGL(st::scan_wavedot_kernel, dim3(plan.groups), dim3(st::kScanThreads),

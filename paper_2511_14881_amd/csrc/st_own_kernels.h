@@ -451,6 +451,114 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
     report(filling, p.groups);
 }
 
+// The first level of such a search, which admits every passing pair: the same products, 64 items (a region) to a
+// wavefront.  An item's place among a filter's passing ones is its place in the region, so there are no counters; the
+// number of bits of the mask word is the region's count.  Masks are formed from the index in memory (a wavefront has one
+// segment: staging would not pay).  Grid (regions / 8, ceil(queries / kOwnFirstCols)): half the queries to a workgroup, so that 256 of
+// them fill the chip.  Bound by its round trips and the scattered stores of the keys: 65,536 items, 213 queries with filters
+// of their own (5 %), d = 256: 190 us by gathering a row per pair, now 27 (the call 1.48 -> 1.31 ms; 800,000 x 64, 256 queries: 320 -> 175).
+constexpr int kOwnFirstCols = 128;
+constexpr size_t own_first_lds_bytes(int d) { return (size_t)kOwnFirstCols * (d + 16 + 8 * 8 + 2 * 4); }
+
+template <int KS>
+__global__ __launch_bounds__(kOwnThreads) void scan_own_first_kernel(ScanParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char own_lds[];
+    constexpr int D = 32 * KS, DP = D + 16;
+    const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
+    const int n_q = p.grp_q_off[p.n_groups], c0 = (int)blockIdx.y * kOwnFirstCols, n_c = min(n_q - c0, kOwnFirstCols);
+    int8_t* s_q = reinterpret_cast<int8_t*>(own_lds);                                              // [cols][DP]
+    uint64_t* s_mask = reinterpret_cast<uint64_t*>(s_q + (size_t)kOwnFirstCols * DP) + (size_t)wv * kOwnFirstCols;
+    float* s_sq = reinterpret_cast<float*>(s_q + (size_t)kOwnFirstCols * (DP + 64));               // [cols]
+    int32_t* s_query = reinterpret_cast<int32_t*>(s_sq + kOwnFirstCols);                           // [cols]
+    const int region = (int)blockIdx.x * (kOwnThreads / 64) + wv;
+    const int64_t my0 = p.item_begin + (int64_t)region * 64;
+    const int64_t lim = p.item_end < p.n_items ? p.item_end : p.n_items, left = lim - my0;
+    const uint64_t all = left >= 64 ? ~0ULL : left > 0 ? ((1ULL << left) - 1ULL) : 0ULL;
+
+    // item rows and scales (past the end the last item is repeated: no mask names it)
+    own_i4 a[2][KS];
+    float si[2][16];
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+        const int64_t it = min(my0 + s * 32 + (lane & 31), p.n_items - 1);
+        const own_i4* row = reinterpret_cast<const own_i4*>(p.items + it * D) + half;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) a[s][k] = row[2 * k];
+#pragma unroll
+        for (int i = 0; i < 16; ++i) si[s][i] = p.iscale[min(my0 + s * 32 + 8 * (i >> 2) + 4 * half + (i & 3), p.n_items - 1)];
+    }
+    for (int i = tid; i < kOwnFirstCols * (D / 16); i += kOwnThreads) {
+        const int c = i / (D / 16), x = i - c * (D / 16);
+        int4 v = make_int4(0, 0, 0, 0);
+        if (c < n_c) v = reinterpret_cast<const int4*>(p.queries + (int64_t)p.grp_q[c0 + c] * D)[x];
+        *reinterpret_cast<int4*>(s_q + (size_t)c * DP + x * 16) = v;
+    }
+    if (tid < kOwnFirstCols) {
+        const int q = tid < n_c ? p.grp_q[c0 + tid] : -1;
+        s_query[tid] = q;
+        s_sq[tid] = q >= 0 ? p.qscale[q] : 0.0f;
+    }
+    // mask words: a filter of mine at a time, for its queries among these columns
+    const int64_t w0 = my0 >> 6;
+    const uint64_t* base = p.bloom + (w0 >> 4) * (int64_t)p.m_bits * kTileWords + (w0 & 15);
+    for (int c = lane; c < kOwnFirstCols; c += 64) s_mask[c] = 0;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    for (int g = lane; g < p.n_groups; g += 64) {
+        const int q0 = max(p.grp_q_off[g] - c0, 0), q1 = min(p.grp_q_off[g + 1] - c0, n_c);
+        if (q0 >= q1) continue;
+        uint64_t m = all;
+        const int r1 = p.grp_row_off[g + 1];
+        if (m)
+            for (int r = p.grp_row_off[g]; r < r1; r += 8) {  // eight rows are requested together (the last one again)
+                uint64_t v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = base[(int64_t)p.grp_rows[min(r + u, r1 - 1)] * kTileWords];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) m &= v[u];
+            }
+        for (int c = q0; c < q1; ++c) {
+            s_mask[c] = m;
+            p.cnt[(int64_t)p.grp_q[c0 + c] * p.groups + region] = (uint32_t)__popcll(m);
+        }
+    }
+    __syncthreads();
+    for (int b = 0; b < n_c; b += 32) {
+        const int c = b + (lane & 31);
+        const uint64_t word = s_mask[c];
+        if (ballot(word != 0) == 0) continue;
+        const float sq = s_sq[c];
+        uint64_t* dst = p.cand + ((int64_t)max(s_query[c], 0) * p.groups + region) * p.cap;
+        const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)c * DP) + half;
+        own_i16 acc[2];
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[s][i] = 0;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) {
+            const own_i4 bq = qr[2 * k];
+            acc[0] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[0][k], bq, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[1][k], bq, acc[1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                // results 4 j .. 4 j + 3 are the items from bit0 on
+                const int bit0 = 32 * s + 8 * j + 4 * half;
+                const uint32_t four = (uint32_t)(word >> bit0) & 15u;
+                if (ballot(four != 0) == 0) continue;
+                const int at = __popcll(word & ((1ULL << bit0) - 1ULL));
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (four >> i & 1u)
+                        dst[at + __popc(four & ((1u << i) - 1u))] =
+                            make_key(rescale(acc[s][4 * j + i], sq, si[s][4 * j + i]), (uint32_t)my0 + (uint32_t)(bit0 + i));
+            }
+    }
+}
+
 // The kernel for rows of d bytes, or null.  (One copy of the kernel to a length: the lengths the MFMA scan has, as far as
 // a workgroup's registers hold the rows of 64 items, and 96 and 192 between them; others go to the gathering scan.)
 inline auto own_kernel(int d) -> decltype(&scan_own_kernel<8>)
@@ -461,6 +569,17 @@ inline auto own_kernel(int d) -> decltype(&scan_own_kernel<8>)
     case 128: return &scan_own_kernel<4>;
     case 192: return &scan_own_kernel<6>;
     case 256: return &scan_own_kernel<8>;
+    default: return nullptr;
+    }
+}
+inline auto own_first_kernel(int d) -> decltype(&scan_own_first_kernel<8>)
+{
+    switch (d) {
+    case 64: return &scan_own_first_kernel<2>;
+    case 96: return &scan_own_first_kernel<3>;
+    case 128: return &scan_own_first_kernel<4>;
+    case 192: return &scan_own_first_kernel<6>;
+    case 256: return &scan_own_first_kernel<8>;
     default: return nullptr;
     }
 }
