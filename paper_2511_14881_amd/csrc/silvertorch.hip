@@ -1197,7 +1197,10 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     // own from the pinned copy); otherwise a small kernel copies them ahead of the first one.  (A copy
     // enqueued with hipMemcpyAsync is a kernel too, but with 6 us of waiting on either side of it.)
     const bool seed_uploads = plan.n_levels > 0 && plan.level[0].seed;
-    if (!seed_uploads) {
+    // Small corpora: the whole search in one kernel.
+    const bool direct = g_scoring_path == 0 && allow_seed && n_items > 0 && n_items <= st::kDirectItems && batch <= st::kDirectBatch &&
+                        n_items * d * n_tasks <= st::direct_bytes(d) && L.k_pad <= st::kLdsSortMax;
+    if (!seed_uploads && !(direct && batch == 1)) {
         stage.enqueued = true;
         const int64_t pieces = (int64_t)blob.bytes() / 16;  // (the blob's tables are padded to 16 bytes)
         hipLaunchKernelGGL(st::stage_upload_kernel, dim3((unsigned)((pieces + st::kUploadThreads - 1) / st::kUploadThreads)),
@@ -1277,6 +1280,29 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     se.tau_img = set_mfma.n ? mp.img_tau : nullptr;
     se.q_taupos = tab(at_taupos);
     se.q_prow = tab(at_qprow);
+    if (direct) {
+        auto host_tab = [&](size_t at) { return (const int32_t*)(staged + at); };
+        if (batch == 1) {
+            se.q_prow = host_tab(at_qprow);
+            se.q2grp = host_tab(at_q2grp);
+            se.scan.grp_row_off = host_tab(at_all_row_off);
+            se.scan.grp_rows = host_tab(at_all_rows);
+        }
+        se.lds_keys = st::direct_lds_keys(n_items);
+        se.done = stage.done();
+        static std::atomic<bool> lds_set{false};  // (setting the attribute twice is harmless)
+        if (!lds_set.load(std::memory_order_acquire)) {
+            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(&st::direct_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)st::direct_lds_bytes(st::kDirectItems)));
+            lds_set.store(true, std::memory_order_release);
+        }
+        TimedLaunch t(0, stream);
+        stage.enqueued = true;
+        hipLaunchKernelGGL(st::direct_kernel, dim3(batch), dim3(st::kDirectThreads), st::direct_lds_bytes(n_items), stream, se);
+        ST_HIP(hipGetLastError());
+        stage.reported();
+        return ST_OK;
+    }
     // Sample mode: the first level of a search that the 8-wavefront MFMA scan serves alone scans
     // its G * cap items as segments spread evenly over the corpus instead of a prefix, and the
     // second level scans the whole corpus without them.  The threshold the first selection

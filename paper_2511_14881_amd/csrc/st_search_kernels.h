@@ -1623,6 +1623,91 @@ inline hipError_t launch_seed(const SelectParams& se, int64_t seed_items, int ba
     }
 }
 
+// A whole search over a small corpus: one workgroup per query tests every word, lists the passing items, scores them (one to
+// a thread) and orders its keys in LDS.  Bound by its chain of round trips (rows, words, items) and the selection; the
+// levels take three kernels with as many chains each.  A lone query reads its tables from the pinned copy itself and
+// reports the slot free.  Calls, levels -> this kernel, in us, for filters that pass little and for none:
+//   10,000 x 64    1 query, K = 10: 20.3 -> 12.8, 44.6 -> 26.9;  256 queries, K = 500: 41 -> 24.5, 81 -> 40
+//   12,288 x 32    1 query: 20.7 -> 12.5, 44.8 -> 24.6;          256 queries: 70 -> 26, 206 -> 39
+//    8,000 x 128   1 query: 20.5 -> 14.2, 31.5 -> 42.4;          256 queries: 47 -> 27, 105 -> 56
+// One compute unit reads a query's rows here: where they may be a megabyte and rows are long, a small batch under broad
+// filters is better off with all of them (the last line), so the corpus is limited by its bytes.
+constexpr int kDirectThreads = 1024;
+constexpr int kDirectItems = 12288;  // the keys and the list of passing items fit the LDS
+constexpr int kDirectBatch = 256;    // a workgroup to a compute unit
+constexpr int64_t direct_bytes(int d) { return d <= 64 ? 800'000 : 400'000; }  // of all rows and tasks, at most
+inline int direct_lds_keys(int64_t n_items) { return (int)(n_items < 1024 ? 1024 : (n_items + 63) / 64 * 64); }
+inline size_t direct_lds_bytes(int64_t n_items) { return (size_t)direct_lds_keys(n_items) * 10 + kLdsSortMax * 8 + 32 * 8 + 3 * 256 * 4 + 32 * 4; }
+static_assert(kDirectItems <= kTopkRegs * kDirectThreads, "the selection holds every key in registers");
+
+__global__ __launch_bounds__(kDirectThreads) void direct_kernel(SelectParams p)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char sel_lds[];
+    constexpr int NT = kDirectThreads;
+    const ScanParams& sp = p.scan;
+    uint64_t* s_keys = reinterpret_cast<uint64_t*>(sel_lds);                   // [lds_keys]
+    uint64_t* s_sorted = s_keys + p.lds_keys;                                  // [kLdsSortMax]
+    uint64_t* s_red = s_sorted + kLdsSortMax;                                  // [32]
+    uint32_t* s_hist = reinterpret_cast<uint32_t*>(s_red + 32);                // [3][256]
+    uint32_t* s_misc = s_hist + 3 * 256;                                       // [8]
+    uint32_t* s_wsum = s_misc + 8;                                             // [16]
+    uint16_t* s_list = reinterpret_cast<uint16_t*>(s_misc + 32);               // [lds_keys]
+    const int q = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wv = tid >> 6;
+    // Bloom test: thread w owns word w (the first signature rows from the per-query table, as in the seed pass)
+    uint64_t m = 0;
+    const int64_t left = sp.n_items - (int64_t)tid * 64;
+    if (left > 0) {
+        m = left >= 64 ? ~0ULL : ((1ULL << left) - 1ULL);
+        const uint64_t* base = sp.bloom + (tid >> 4) * (int64_t)sp.m_bits * kTileWords + (tid & 15);
+        const int* qr = p.q_prow + q * (kSeedRows + 1);
+        const int nr = qr[kSeedRows];
+#pragma unroll
+        for (int r = 0; r < kSeedRows; ++r) {
+            const int row = qr[r];
+            if (row >= 0) m &= base[(int64_t)row * kTileWords];
+        }
+        if (nr > kSeedRows) {
+            const int r0 = sp.grp_row_off[p.q2grp[q]];
+            for (int r = kSeedRows; r < nr; ++r) m &= base[(int64_t)sp.grp_rows[r0 + r] * kTileWords];
+        }
+    }
+    const uint32_t mine = (uint32_t)__popcll(m);
+    const uint32_t incl = wave_scan_add(mine);
+    if (lane == 63) s_wsum[wv] = incl;
+    __syncthreads();  // (every read of the tables has returned)
+    if (q == 0 && tid == 0) stage_report(p.done);
+    uint32_t at = incl - mine, total = 0;
+    for (int w = 0; w < NT / 64; ++w) {
+        const uint32_t v = s_wsum[w];
+        if (w < wv) at += v;
+        total += v;
+    }
+    for (; m; m &= m - 1) s_list[at++] = (uint16_t)(tid * 64 + __ffsll((long long)m) - 1);
+    __syncthreads();
+    const int T = sp.weighted ? sp.n_tasks : 1;
+    for (uint32_t e = tid; e < total; e += NT) {
+        const int64_t item = s_list[e];
+        const int4* row = reinterpret_cast<const int4*>(sp.items + item * sp.d);
+        const float s_i = sp.iscale[item];
+        float sc = 0.0f;
+        for (int t = 0; t < T; ++t) {
+            int64_t qoff[kRowBlock];
+#pragma unroll
+            for (int r = 0; r < kRowBlock; ++r) qoff[r] = ((int64_t)q * T + t) * sp.d;
+            int acc[kRowBlock] = {0, 0, 0, 0, 0, 0, 0, 0};
+            dot_block<1>(row, sp.queries, qoff, sp.d >> 4, acc);
+            const float st = rescale(acc[0], sp.qscale[(int64_t)q * T + t], s_i);
+            sc = sp.weighted ? __fmaf_rn(sp.w[t], st, sc) : st;
+        }
+        s_keys[e] = make_key(sc, (uint32_t)item);
+    }
+    __syncthreads();
+    uint64_t kth;
+    const int n_out = lds_topk(s_keys, (int)total, p.K, s_sorted, p.k_pad, s_hist, s_misc, s_red, true, kth);
+    write_result(s_sorted, n_out, p.K, p.out_ids + (int64_t)q * p.K, p.out_scores + (int64_t)q * p.K, p.out_count + q);
+    if (tid == 0) p.ovf[q] = 0u;
+}
+
 // Parity export of the scoring arithmetic for chosen pairs.
 __global__ __launch_bounds__(256) void score_pairs_kernel(const int8_t* __restrict__ items,
                                                           const float* __restrict__ iscale, int32_t d,

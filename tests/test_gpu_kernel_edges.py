@@ -412,3 +412,42 @@ def test_scan_by_units(n, d, B, T, groups, m, k, kind):
     assert kind in ("ties", "scales") or len(fast) > B // 2
     check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, B - 1, *range(0, B, max(1, B // 14))}), slow_path=([], fast),
                  label=f"units {kind}")
+
+
+# Small corpora take one kernel for the whole search: the smallest and largest of its range (and one item or query more), a
+# lone query (it reads the pinned tables), several tasks, more than eight signature rows, fewer passing items than K, none,
+# all, ties, results of one key and as many as LDS orders.
+@pytest.mark.parametrize("n,d,B,T,m,k,K,kind", [
+    (1, 16, 1, 0, 64, 2, 5, "plain"), (63, 64, 3, 0, 64, 2, 70, "plain"), (64, 32, 1, 0, 64, 2, 64, "all"), (1025, 48, 2, 3, 100, 3, 20, "plain"),
+    (12_288, 64, 256, 0, 128, 2, 10, "plain"), (12_288, 32, 257, 0, 128, 2, 10, "plain"), (12_289, 64, 2, 0, 128, 2, 10, "plain"),
+    (12_288, 64, 1, 0, 128, 2, 2048, "all"), (12_288, 64, 5, 0, 128, 2, 2048, "ties"), (10_000, 64, 1, 0, 1024, 7, 1, "long"),
+    (3_125, 128, 9, 0, 256, 3, 300, "plain"), (3_126, 128, 9, 0, 256, 3, 300, "plain"), (1_500, 256, 4, 0, 256, 3, 1500, "plain"),
+    (2_000, 64, 7, 4, 256, 3, 100, "long"), (5_000, 64, 20, 0, 512, 4, 2049, "plain")])
+def test_small_corpora(n, d, B, T, m, k, K, kind):
+    w = ragged_workload(n + d + B, n, d, B, 12, 6, m, k, T=T)
+    if kind == "all":
+        w.filt_ids, w.filt_offsets = np.zeros(0, np.uint64), np.zeros(B + 1, np.int64)
+    elif kind == "long":
+        w.filt_ids, w.filt_offsets = np.tile(np.arange(3, dtype=np.uint64), B), np.arange(0, 3 * B + 1, 3).astype(np.int64)
+    elif kind == "ties":
+        w.items = w.items[:20].repeat(n // 20 + 1, 1)[:n].contiguous()
+        w.item_scale = torch.full((n,), 0.01)
+    if B > 2 and kind == "plain":  # nothing passes for one query
+        w.filt_ids = np.concatenate([w.filt_ids, np.array([999_999], np.uint64)])
+        w.filt_offsets[B] += 1
+    check_search(w, K, label=f"small {kind}")
+
+
+# ... also within a graph: a lone query's kernel reads the pinned tables at every replay.
+@pytest.mark.parametrize("B", [1, 9])
+def test_captured_search_over_a_small_corpus(B):
+    n = 9000
+    w = S.make_workload(S.scaled(S.CONFIGS["tiny"], n, batch=B, top_k=20), "cuda")
+    cfg = w.cfg
+    bloom = st.st_bloom_build(w.feat_offsets, w.feat_ids, n, cfg.m_bits, cfg.k_hashes)
+    buf, other = st.SearchBuffers(n, cfg.d, B, 1, 20), st.SearchBuffers(n, cfg.d, B, 1, 20)
+
+    def call(b, ids=w.filt_ids):
+        return st.st_search(bloom, w.items, w.item_scale, w.queries, w.query_scale, ids, w.filt_offsets, 20, buffers=b)
+
+    _replays_like_eager(call, buf, lambda: call(other, w.filt_ids + np.uint64(1)))
