@@ -708,24 +708,46 @@ __device__ __forceinline__ void scan_mfma2_body(const ScanParams& p, const MfmaP
 // counted.  Where a wavefront fills units of 64 items over the level, the form by units; else, with few passing items
 // per filter and segment (units of 16 would be mostly padding), the carrying form, and with more the first form's
 // cheaper unit set-up (the cross-over between those two lies near a dozen items per filter and 512-item segment).
-template <int KS, int TT, bool WEIGHTED>
-__global__ __launch_bounds__(512, 2) void scan_mfma2_kernel(ScanParams p, MfmaParams mp, TileLds tile)
+struct Mfma2Args {
+    ScanParams p;
+    MfmaParams mp;
+    TileLds tile;
+};
+// Each form reads the arguments behind its branch: what the compiler knows of them it moves before the branches
+// otherwise, for all three forms at once (a level of 0.2 M items x 156 queries under filters of 1 %: 53.0 us so, 55.2
+// without, 52.8 for the last two forms without the first).  Not where weights are among them: those it then keeps in
+// scratch memory.
+template <bool WEIGHTED>
+__device__ __forceinline__ const Mfma2Args& mfma2_args(const Mfma2Args& args)
 {
-    const unsigned long long pairs = mp.density_acc ? *mp.density_acc : 0ULL;
-    if (tile.total > 0 && pairs >= tile.min_pairs)
-        scan_tile_body<KS, TT, WEIGHTED>(p, mp, tile);
-    else if (mp.density_acc != nullptr && pairs < mp.density_limit)
-        scan_mfma2_body<KS, TT, WEIGHTED>(p, mp);
-    else
-        scan_mfma_body<KS, TT, WEIGHTED, true, 8, false>(p, mp);
+    if constexpr (WEIGHTED) return args;
+    typedef const Mfma2Args __attribute__((address_space(4))) * Args;
+    Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(a));
+    return *(const Mfma2Args*)a;
+}
+template <int KS, int TT, bool WEIGHTED>
+__global__ __launch_bounds__(512, 2) void scan_mfma2_kernel(Mfma2Args args)
+{
+    const unsigned long long pairs = args.mp.density_acc ? *args.mp.density_acc : 0ULL;
+    if (args.tile.total > 0 && pairs >= args.tile.min_pairs) {
+        const Mfma2Args& a = mfma2_args<WEIGHTED>(args);
+        scan_tile_body<KS, TT, WEIGHTED>(a.p, a.mp, a.tile);
+    } else if (args.mp.density_acc != nullptr && pairs < args.mp.density_limit) {
+        const Mfma2Args& a = mfma2_args<WEIGHTED>(args);
+        scan_mfma2_body<KS, TT, WEIGHTED>(a.p, a.mp);
+    } else {
+        const Mfma2Args& a = mfma2_args<WEIGHTED>(args);
+        scan_mfma_body<KS, TT, WEIGHTED, true, 8, false>(a.p, a.mp);
+    }
 }
 
 template <int KS, int TT, bool WEIGHTED>
 inline hipError_t launch_scan_mfma2_t(const ScanParams& sp, const MfmaParams& mp, int gx, hipStream_t stream)
 {
     static std::atomic<int> max_set{0};
-    TileLds tile;
-    const int lds = scan_tile_applies(sp, mp, gx, &tile) && tile.total > mp.lds_total ? tile.total : mp.lds_total;
+    Mfma2Args args{sp, mp, {}};
+    const int lds = scan_tile_applies(sp, mp, gx, &args.tile) && args.tile.total > mp.lds_total ? args.tile.total : mp.lds_total;
     if (lds > max_set.load(std::memory_order_acquire)) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&scan_mfma2_kernel<KS, TT, WEIGHTED>),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, lds);
@@ -733,7 +755,7 @@ inline hipError_t launch_scan_mfma2_t(const ScanParams& sp, const MfmaParams& mp
         max_set.store(lds, std::memory_order_release);
     }
     const dim3 grid((unsigned)gx, (unsigned)mp.q_split);
-    hipLaunchKernelGGL((scan_mfma2_kernel<KS, TT, WEIGHTED>), grid, dim3(512), (size_t)lds, stream, sp, mp, tile);
+    hipLaunchKernelGGL((scan_mfma2_kernel<KS, TT, WEIGHTED>), grid, dim3(512), (size_t)lds, stream, args);
     return hipGetLastError();
 }
 
