@@ -434,16 +434,8 @@ __global__ __launch_bounds__(kMergeThreads) void ivf_merge_kernel(IvfQueryParams
     const uint32_t n_mine = held(mine);
     const uint64_t* src = keys + mine * p.part_cap;
     const uint32_t first = (uint32_t)((wv % per) * 64 + lane), step = (uint32_t)per * 64;
-    // The wavefront's keys stay in registers for all passes, as far as they fit (0: none; no key is 0).
-    uint64_t kr[kMergeRegs];
-    const uint32_t held_regs = (uint32_t)__builtin_amdgcn_readfirstlane((int)min((n_mine + step - 1) / step, (uint32_t)kMergeRegs));
-#pragma unroll
-    for (uint32_t u = 0; u < kMergeRegs; ++u) kr[u] = first + u * step < n_mine ? src[first + u * step] : 0ULL;
-    auto each = [&](auto&& f) {
-#pragma unroll
-        for (uint32_t u = 0; u < kMergeRegs; ++u)
-            if (u < held_regs && kr[u]) f(kr[u]);
-        for (uint32_t i0 = first + kMergeRegs * step; ballot(i0 < n_mine) != 0; i0 += 8 * step) {
+    auto each_from = [&](uint32_t i0, auto&& f) {
+        for (; ballot(i0 < n_mine) != 0; i0 += 8 * step) {
             uint64_t v[8];
 #pragma unroll
             for (uint32_t u = 0; u < 8; ++u)
@@ -456,14 +448,33 @@ __global__ __launch_bounds__(kMergeThreads) void ivf_merge_kernel(IvfQueryParams
     const uint32_t want = total < (uint32_t)p.K ? total : (uint32_t)p.K;
     int64_t* ids = p.out_ids + (int64_t)b * p.K;
     float* scores = p.out_scores + (int64_t)b * p.K;
-    const bool ordered = want == 0 ||
-        bucket_order<kMergeThreads>(each, want, (uint32_t)kMergeRoom, s_keys, reinterpret_cast<uint32_t*>(s_bins), s_misc, s_red,
-                                    s_wsum, [&](uint32_t rank, uint64_t key) {
-                                        if (rank < want) {
-                                            ids[rank] = (int64_t)key_item(key);
-                                            scores[rank] = key_score(key);
-                                        }
-                                    });
+    auto order = [&](auto&& each) {
+        return bucket_order<kMergeThreads>(each, want, (uint32_t)kMergeRoom, s_keys, reinterpret_cast<uint32_t*>(s_bins), s_misc,
+                                           s_red, s_wsum, [&](uint32_t rank, uint64_t key) {
+                                               if (rank < want) {
+                                                   ids[rank] = (int64_t)key_item(key);
+                                                   scores[rank] = key_score(key);
+                                               }
+                                           });
+    };
+    // With more keys than one round of loads takes, a thread's first 16 stay in registers for all passes (0: none; no key
+    // is 0).  With fewer a pass is one round trip as it is and the unrolled code costs more than it saves (2 queries x 2
+    // parts of 21 keys: 7.5 us with registers, 6.6 without).
+    bool ordered = want == 0;
+    if (total > 8 * kMergeThreads) {
+        uint64_t kr[kMergeRegs];
+        const uint32_t held_regs = (uint32_t)__builtin_amdgcn_readfirstlane((int)min((n_mine + step - 1) / step, (uint32_t)kMergeRegs));
+#pragma unroll
+        for (uint32_t u = 0; u < kMergeRegs; ++u) kr[u] = first + u * step < n_mine ? src[first + u * step] : 0ULL;
+        ordered = order([&](auto&& f) {
+#pragma unroll
+            for (uint32_t u = 0; u < kMergeRegs; ++u)
+                if (u < held_regs && kr[u]) f(kr[u]);
+            each_from(first + kMergeRegs * step, f);
+        });
+    } else if (!ordered) {
+        ordered = order([&](auto&& f) { each_from(first, f); });
+    }
     if (ordered) {
         for (int i = (int)want + tid; i < p.K; i += kMergeThreads) {
             ids[i] = -1;
