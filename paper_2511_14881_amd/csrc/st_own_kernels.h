@@ -31,6 +31,8 @@
 //     64      244 -> 124    353 -> 129   464 -> 182   527 -> 253   734 -> 269
 //    256      909 -> 341   1458 -> 401  1909 -> 620  2127 -> 733  2222 -> 747
 //     16, 64 bytes  99 -> 88   129 -> 95   128 -> 88   131 -> 103   200 -> 130
+// (with two barriers to a segment and the first level gathered; without them and with scan_own_first_kernel, 256 queries,
+// same card: 349 -> 272, 396 -> 300, 621 -> 427, 711 -> 496, 700 -> 485; 16 queries on 0.8 to 3 M items 0.93 to 1.04 of the time)
 // one filter for 64 queries, 10 M x 192: 447 -> 176 at 0.02 %, 807 -> 339 at 0.5 %, 825 -> 543 at 5 %; behind cluster probing
 // (600 of 4096 clusters, 3 M x 128, 32 queries) 326 -> 243.
 #pragma once
