@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "st_bound.h"
+
 namespace st {
 
 constexpr int kTileItems = 1024;            // items per Bloom tile block

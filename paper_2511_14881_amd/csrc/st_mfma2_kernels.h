@@ -54,12 +54,8 @@ __device__ __forceinline__ void scan_mfma2_body(const ScanParams& p, const MfmaP
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int S = mp.q_split, y = blockIdx.y;
     const int l16 = lane & 15, kg = lane >> 4;
-    auto tq_of = [](float tf, float sq) -> float {  // tau / s_q; +inf: padding row, -inf: no bound
-        const float inf = __builtin_inff();
-        if (tf == inf) return inf;
-        if (!(tf > 0.0f)) return -inf;
-        const float tq = tf / sq;
-        return (tq > 0.0f && tq < inf) ? tq : -inf;
+    auto tq_of = [](int row, float tf, float sq) -> float {  // tau / s_q; +inf: padding row, -inf: no bound
+        return row < 0 ? __builtin_inff() : bound_quotient(tf, sq);
     };
     // wave-private state
     uint8_t* s_list = reinterpret_cast<uint8_t*>(lds + mp.lds_list) + wave * FB * seg_stride;     // [FB][seg] this segment's passing items
@@ -218,7 +214,7 @@ __device__ __forceinline__ void scan_mfma2_body(const ScanParams& p, const MfmaP
             s_sq[tid] = v_sq;
             const float tf = v_qrow >= 0 ? (v_tau ? key_score(v_tau) : -__builtin_inff()) : __builtin_inff();
             s_tauf[tid] = tf;
-            s_tq[tid] = tq_of(tf, v_sq);
+            s_tq[tid] = tq_of(v_qrow, tf, v_sq);
             if ((tid % TT) == 0) s_tau64[tid / TT] = v_tau;
         }
     }
@@ -245,7 +241,7 @@ __device__ __forceinline__ void scan_mfma2_body(const ScanParams& p, const MfmaP
             t64 = min(t64, mp.img_tau[(int64_t)(y * (mp.rows_local / TT) + lr / TT) * kTauParts + pp]);
         const float tf = grow >= 0 ? (t64 ? key_score(t64) : -__builtin_inff()) : __builtin_inff();
         s_tauf[lr] = tf;
-        s_tq[lr] = tq_of(tf, sq);
+        s_tq[lr] = tq_of(grow, tf, sq);
         if ((lr % TT) == 0) s_tau64[lr / TT] = t64;
     }
     lds_barrier();

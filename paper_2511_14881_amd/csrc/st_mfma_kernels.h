@@ -154,15 +154,8 @@ __device__ __forceinline__ void scan_mfma_body(const ScanParams& p, const MfmaPa
     const int S = mp.q_split, y = blockIdx.y;
     const int l16 = lane & 15, kg = lane >> 4;
     // Plain search: tau / s_q per row, so that a pair can only be admitted if dot * s_i reaches it.
-    // +inf marks padding rows (never admitted), -inf rows that cannot be culled (no threshold yet,
-    // tau <= 0, or a quotient outside the range the bound is valid for).
-    auto tq_of = [](float tf, float sq) -> float {
-        const float inf = __builtin_inff();
-        if (tf == inf) return inf;
-        if (!(tf > 0.0f)) return -inf;
-        const float tq = tf / sq;
-        return (tq > 0.0f && tq < inf) ? tq : -inf;
-    };
+    // +inf marks padding rows (never admitted), -inf rows that cannot be culled (see bound_quotient).
+    auto tq_of = [](int row, float tf, float sq) -> float { return row < 0 ? __builtin_inff() : bound_quotient(tf, sq); };
     // Passing items of each filter, in item order, as the low 8 bits of their place in the segment:
     // entries of the upper half of a 512-item segment follow those of the lower half, so the
     // number of lower-half entries per filter restores the ninth bit.
@@ -351,7 +344,7 @@ __device__ __forceinline__ void scan_mfma_body(const ScanParams& p, const MfmaPa
             s_sq[tid] = v_sq;
             const float tf = v_qrow >= 0 ? (v_tau ? key_score(v_tau) : -__builtin_inff()) : __builtin_inff();
             s_tauf[tid] = tf;
-            if (!WEIGHTED) s_tq[tid] = tq_of(tf, v_sq);
+            if (!WEIGHTED) s_tq[tid] = tq_of(v_qrow, tf, v_sq);
             if ((tid % TT) == 0) s_tau64[tid / TT] = v_tau;
         }
     }
@@ -402,7 +395,7 @@ __device__ __forceinline__ void scan_mfma_body(const ScanParams& p, const MfmaPa
                 s_sq[lr] = sq;
                 const float tf = grow >= 0 ? (t64 ? key_score(t64) : -__builtin_inff()) : __builtin_inff();
                 s_tauf[lr] = tf;
-                if (!WEIGHTED) s_tq[lr] = tq_of(tf, sq);
+                if (!WEIGHTED) s_tq[lr] = tq_of(grow, tf, sq);
                 if ((lr % TT) == 0) s_tau64[lr / TT] = t64;
             }
 #pragma unroll
@@ -436,7 +429,7 @@ __device__ __forceinline__ void scan_mfma_body(const ScanParams& p, const MfmaPa
                 t64 = min(t64, mp.img_tau[(int64_t)(y * (mp.rows_local / TT) + lr / TT) * kTauParts + pp]);
             const float tf = grow >= 0 ? (t64 ? key_score(t64) : -__builtin_inff()) : __builtin_inff();
             s_tauf[lr] = tf;
-            if (!WEIGHTED) s_tq[lr] = tq_of(tf, sq);
+            if (!WEIGHTED) s_tq[lr] = tq_of(grow, tf, sq);
             if ((lr % TT) == 0) s_tau64[lr / TT] = t64;
         }
         lds_barrier();

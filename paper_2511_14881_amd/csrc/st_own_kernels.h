@@ -62,7 +62,7 @@ constexpr int own_pairs(int cols) { return cols < 64 ? 64 : cols; }
 constexpr size_t own_lds_bytes(int n_q, int d, int m_bits)
 {
     const size_t c = own_cols(n_q);
-    return c * (d + 16) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnRowRefs * 2 + c * (8 + 4 * 6) +
+    return c * (d + 16) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnRowRefs * 2 + c * (8 + 4 * 7) +
            own_pairs((int)c) * (kOwnThreads / 64) * 2 + kOwnRows * 2 + kOwnRows / 8 +
            (size_t)kOwnWords * (64 * 4 + kOwnQueue * (16 * 4 + 8));
 }
@@ -110,7 +110,8 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
     uint32_t* q_val = reinterpret_cast<uint32_t*>(at) + (size_t)wv * kOwnQueue * 16;  at += (size_t)kOwnWords * kOwnQueue * 64;
     uint2* q_code = reinterpret_cast<uint2*>(at) + (size_t)wv * kOwnQueue;  at += (size_t)kOwnWords * kOwnQueue * 8;
     float* s_si = reinterpret_cast<float*>(at) + (size_t)wv * 64; at += (size_t)kOwnWords * 64 * 4;  // scales of the wavefront's items
-    int32_t* s_neg = reinterpret_cast<int32_t*>(at);              // [cols] bounds, for the largest exponent so far
+    int32_t* s_neg = reinterpret_cast<int32_t*>(at);              at += (size_t)cols * 4;  // bounds, for the largest exponent so far
+    float* s_tq = reinterpret_cast<float*>(at);                   // [cols] tau / s_q (see bound_quotient)
 
     if (tid < kOwnRows / 32) s_bits[tid] = 0;
     for (int c = tid; c < cols; c += kOwnThreads) {
@@ -120,7 +121,9 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
             for (int pp = 0; pp < p.tau_parts; ++pp) t = min(t, p.tau[(int64_t)q * kTauParts + pp]);
         s_query[c] = q;
         s_tau[c] = t;
-        s_sq[c] = q >= 0 ? p.qscale[q] : 0.0f;
+        const float sq = q >= 0 ? p.qscale[q] : 0.0f;
+        s_sq[c] = sq;
+        s_tq[c] = t ? bound_quotient(key_score(t), sq) : -__builtin_inff();
         s_cnt[c] = 0;
         s_neg[c] = kNever;
     }
@@ -389,11 +392,9 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
                 cur_E = E;
                 fix_scale = __uint_as_float((uint32_t)(P - E + 127) << 23);
                 for (int c = lane; c < cols; c += 64) {
-                    const uint64_t tau = s_tau[c];
-                    const float tf = key_score(tau);
-                    const float tq = tf / s_sq[c];
+                    const float tq = s_tq[c];
                     int neg = kPass;
-                    if (tau != 0 && tf > 0.0f && tq > 0.0f && tq < __builtin_inff())
+                    if (tq > 0.0f)
                         neg = -min(__float2int_rd(fminf(tq * (fix_scale * 0.99999618530273f), 1.2e9f)), (1 << 30) + 1);  // (1 - 2^-18)
                     atomicMax(&s_neg[c], neg);
                 }

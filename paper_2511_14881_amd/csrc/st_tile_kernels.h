@@ -99,7 +99,7 @@ __device__ __forceinline__ void scan_tile_body(const ScanParams& p, const MfmaPa
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int seg_stride = mp.seg_stride;
     int8_t* s_q = reinterpret_cast<int8_t*>(lds);
-    float* s_bound = reinterpret_cast<float*>(lds + L.bound);  // [rows] plain: tau / s_q; weighted: tau's score
+    float* s_bound = reinterpret_cast<float*>(lds + L.bound);  // [rows] tau's score (-inf: none; padding: +inf)
     float* s_sq = reinterpret_cast<float*>(lds + L.sq);
     uint64_t* s_tau64 = reinterpret_cast<uint64_t*>(lds + L.tau64);  // [rows / TT] (padding: above every key)
     int* s_qrow = reinterpret_cast<int*>(lds + L.qrow);
@@ -166,18 +166,9 @@ __device__ __forceinline__ void scan_tile_body(const ScanParams& p, const MfmaPa
         return t64;
     };
     auto row_store = [&](int lr, int qrow, float sq, uint64_t t64) {
-        const float inf = __builtin_inff();
-        float bound = inf;  // padding row
-        if (qrow >= 0) {
-            bound = t64 ? key_score(t64) : -inf;  // -inf: no bound
-            if (!WEIGHTED) {
-                const float tq = bound / sq;
-                bound = (bound > 0.0f && tq > 0.0f && tq < inf) ? tq : -inf;
-            }
-        }
         s_qrow[lr] = qrow;
         s_sq[lr] = sq;
-        s_bound[lr] = bound;
+        s_bound[lr] = qrow < 0 ? __builtin_inff() : t64 ? key_score(t64) : -__builtin_inff();
         if ((lr % TT) == 0) s_tau64[lr / TT] = qrow >= 0 ? t64 : ~0ULL;
         if (!WEIGHTED) s_thr[lr] = 0x7FFFFFFF;
     };
@@ -506,8 +497,9 @@ __device__ __forceinline__ void scan_tile_body(const ScanParams& p, const MfmaPa
                 fix_scale = __uint_as_float((uint32_t)(P - E + 127) << 23);
                 const float thr_scale = fix_scale * 0.99999618530273f;  // (1 - 2^-18) * 2^(P-E)
                 for (int row = lane; row < mp.rows_local; row += 64)
-                    // (infinite for padding and for rows without a bound)
-                    atomicMin(&s_thr[row], (int)__builtin_amdgcn_fmed3f(__builtin_floorf(s_bound[row] * thr_scale), -2147483648.0f, 2147483520.0f));
+                    if (s_qrow[row] >= 0)  // (not for padding)
+                        atomicMin(&s_thr[row], (int)__builtin_amdgcn_fmed3f(__builtin_floorf(bound_quotient(s_bound[row], s_sq[row]) * thr_scale),
+                                                                            -2147483648.0f, 2147483520.0f));
             }
             // (at least 1: the product of a tiny scale may round to zero, its ceiling does not)
             if (NS == 2 || half == 0) s_fix[lane] = cull ? max(__float2int_ru(si * fix_scale), 1) : 0;

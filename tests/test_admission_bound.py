@@ -1,0 +1,96 @@
+"""The integer tests that the scans put in front of a pair's score, on the host: whatever the scales (finite and > 0),
+a pair whose score reaches the threshold's must pass.  The arithmetic of the kernels is repeated here around the
+library's own bound_quotient."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2511_14881_amd", "csrc")
+
+_PROGRAM = r"""
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <cstdio>
+#include <random>
+#include "st_bound.h"
+
+static float score(int dot, float sq, float si)
+{
+    volatile float a = (float)dot * sq;
+    volatile float b = a * si;
+    return b;
+}
+// dot * factor against the threshold's bound, the factor of P bits (scan_own, scan_tile, scan_mfma2)
+static bool passes(int dot, float tq, float si, int E, int P)
+{
+    const float fix = std::ldexp(1.0f, P - E);
+    const int f = std::max((int)std::ceil(si * fix), 1);
+    const int thr = std::min((int)std::floor(std::fmin(tq * (fix * 0.99999618530273f), 1.2e9f)), (1 << 30) + 1);
+    return (int64_t)dot * f >= thr;
+}
+// the high half of dot * factor (scan_mfma)
+static bool passes_high(int dot, float tq, float si, int E)
+{
+    const int64_t f = (int64_t)std::ceil(si * std::ldexp(1.0f, 31 - E));
+    const int thr = (int)std::floor(std::fmin(tq * std::ldexp(0.99999618530273f, -(E + 1)), 2.0e9f));
+    return (int)(((int64_t)dot * f) >> 32) >= thr;
+}
+int main()
+{
+    std::mt19937_64 rng(5);
+    auto uni = [&](double a, double b) { return a + (b - a) * (double)(rng() >> 11) * 0x1p-53; };
+    const int dims[4] = {64, 128, 256, 512};
+    long tested = 0, bounded = 0, cut = 0;
+    for (long it = 0; it < 4000000; ++it) {
+        const int d = dims[it & 3], P = d == 64 ? 10 : d == 128 ? 9 : 8, top = 127 * 127 * d;
+        // the threshold's pair, then another one with a score near it
+        const double es = uni(-148, 127);
+        const float sq = std::fmin((float)std::exp2(es), 3.4e38f);
+        double ei = uni(-100, 100);
+        if (it & 4) ei = uni(-149.5, -95) - es;  // its score near or below the smallest normal number
+        else if (it & 8) ei = uni(80, 127) - es; // ... near or above the largest
+        const float si = (float)std::exp2(std::min(std::max(ei, -148.0), 126.9));
+        const int dot = (int)std::exp2(uni(0, std::log2((double)top)));
+        const float tau = score(dot, sq, si);
+        float si2 = si * (it & 16 ? 1.0f : (float)std::exp2(uni(-12, 12)));
+        if (!(si2 > 0.0f) || std::isinf(si2)) si2 = si;
+        int dot2 = (int)std::min((double)top, std::max(1.0, (double)dot * si / si2 * uni(0.9999, 1.0001) - (it & 32 ? 1 : 0)));
+        if (it % 7 == 0) dot2 = (int)std::exp2(uni(0, std::log2((double)top)));
+        const float sc2 = score(dot2, sq, si2);
+        const float tq = st::bound_quotient(tau, sq);
+        const float smax = std::max(si, si2);
+        if (!(smax > 0x1p-90f && smax < 0x1p90f)) continue;  // (no integer test then)
+        ++tested;
+        if (!(tq > 0.0f)) continue;
+        ++bounded;
+        const int E = std::ilogb(smax) + 1 + (it % 3 == 0 ? (int)uni(0, 8) : 0);  // a wavefront may have met larger scales
+        if (E >= 90) continue;
+        const bool p = d <= 256 ? passes(dot2, tq, si2, E, P) : true, h = passes_high(dot2, tq, si2, E);
+        cut += !p;
+        if (sc2 >= tau && !(p && h)) {
+            std::printf("cut: d=%d dot=%d dot2=%d sq=%a si=%a si2=%a tau=%a score=%a\n", d, dot, dot2, sq, si, si2, tau, sc2);
+            return 1;
+        }
+    }
+    std::printf("ok %ld %ld %ld\n", tested, bounded, cut);
+    return 0;
+}
+"""
+
+
+def test_integer_bounds_never_cut_a_pair_that_reaches_the_threshold(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    src, exe = tmp_path / "bound.cpp", str(tmp_path / "bound")
+    src.write_text(_PROGRAM)
+    built = subprocess.run([cxx, "-std=c++17", "-O1", "-ffp-contract=off", "-I", CSRC, str(src), "-o", exe], capture_output=True, text=True)
+    assert built.returncode == 0, built.stderr
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=240)
+    assert run.returncode == 0, run.stdout + run.stderr
+    ok, tested, bounded, cut = run.stdout.split()
+    # ordinary scales keep their bound, and the bound does cut
+    assert ok == "ok" and int(bounded) > 0.3 * int(tested) and int(cut) > 0.03 * int(tested), run.stdout

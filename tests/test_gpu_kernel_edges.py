@@ -247,6 +247,47 @@ def test_own_filters(n, d, B, m, kind):
                  label=f"own filters {kind}")
 
 
+# Scales (finite and > 0) whose scores leave the normal range, in every form of the scans that tests pairs by an
+# integer bound first.  "tiny": scores of two or three units of 2^-149, so that dots up to half a unit away round to the
+# score of the threshold and, with the lower id, come before it.  "huge": dot * s_q overflows for the largest dots, so
+# that items of small scales score infinity beside thresholds that are finite.
+def _extreme_scales(w, kind):
+    n, B = w.items.shape[0], w.queries.shape[0]
+    rng = np.random.default_rng(n + B)
+    top = (w.items[:4000].double() @ w.queries.double().T).amax(0).numpy()  # about the 4000th part of the best
+    if kind == "tiny":
+        w.item_scale = torch.full((n,), 2.0 ** -85)
+        w.query_scale = torch.from_numpy((rng.uniform(1.5, 4, B) * 2.0 ** -64 / top).astype(np.float32))
+    else:
+        w.item_scale = torch.from_numpy(np.exp2(rng.uniform(-80, -60, n)).astype(np.float32))
+        w.query_scale = torch.from_numpy((2.0 ** 128 / top).astype(np.float32))
+
+
+# form: the scan for filters of their own behind a seed pass and behind a first level of its own; the MFMA scan of four
+# wavefronts; of eight: rows of 512, few items to a filter, more filters than the form by units takes, and that form.
+@pytest.mark.parametrize("kind", ["tiny", "huge"])
+@pytest.mark.parametrize("form,n,d,B,groups,vocab,plan", [
+    ("own, seed", 300_000, 64, 128, 128, 40, dict(mfma_groups=0, seed_pass=1)),
+    ("own", 400_000, 256, 160, 160, 40, dict(mfma_groups=0, seed_pass=0)),
+    ("four", 300_000, 128, 64, 8, 12, dict(dot_groups=0, waves=4)),
+    ("rows of 512", 400_000, 512, 140, 4, 12, dict(dot_groups=0, waves=8)),
+    ("few", 600_000, 256, 250, 8, 60, dict(dot_groups=0, waves=8)),
+    ("many", 500_000, 64, 1000, 40, 40, dict(dot_groups=0)),
+    ("units", 700_000, 128, 400, 4, 12, dict(dot_groups=0, waves=8))])
+def test_scores_outside_the_normal_range(form, n, d, B, groups, vocab, plan, kind):
+    w = ragged_workload(n + B, n, d, B, vocab, 30 if "own" in form else 12, 256, 1)
+    pool = [[g % vocab] if form in ("four", "units", "many", "rows of 512") else [g % vocab, (g * 7 + 1 + g // vocab) % vocab]
+            for g in range(groups)]
+    filters = [pool[b % groups] for b in range(B)]
+    w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
+    w.filt_offsets = np.concatenate([[0], np.cumsum([len(f) for f in filters])]).astype(np.int64)
+    _extreme_scales(w, kind)
+    K = 20
+    got = st.st_search_host_plan(n, d, B, 1, K, 256, 1, w.filt_ids, w.filt_offsets)
+    assert all(got[key] == v for key, v in plan.items()), got
+    check_search(w, K, queries=range(0, B, max(1, B // 20)), label=f"{kind} scores, {form}")
+
+
 # The same scan over rows of evaluated programs: few of them (all rows are staged) and more than 64 (the named ones are).
 @pytest.mark.parametrize("n,B", [(300_011, 37), (270_400, 100), (400_000, 140)])
 def test_own_programs(n, B):
