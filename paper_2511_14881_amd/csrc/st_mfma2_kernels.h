@@ -710,13 +710,13 @@ struct Mfma2Args {
     TileLds tile;
 };
 // Each form reads the arguments behind its branch: what the compiler knows of them it moves before the branches
-// otherwise, for all three forms at once (a level of 0.2 M items x 156 queries under filters of 1 %: 53.0 us so, 55.2
-// without, 52.8 for the last two forms without the first).  Not where weights are among them: those it then keeps in
-// scratch memory.
-template <bool WEIGHTED>
-__device__ __forceinline__ const Mfma2Args& mfma2_args(const Mfma2Args& args)
+// otherwise, for all three forms at once, and spills it (d = 128, scalar registers spilled at 1 / 2 / 4 weighted tasks:
+// 213 / 240 / 181, so 87 / 60 / 54; d = 256: 215 / 218 / 227, so 37 / 26 / 32).  A level of 0.2 M items x 156 queries under
+// filters of 1 %: 53.0 us so, 55.2 without, 52.8 for the last two forms without the first.  Calls with several tasks and
+// sparse filters: 1 M x 128, 250 queries x 2 tasks, 0.1 %: 69.8 us so, 73.2 without, 70.2 for the two forms; 1 M x 256, 60 x 4,
+// 1 %: 57.3, 60.5, 57.2.
+__device__ __forceinline__ const Mfma2Args& mfma2_args()
 {
-    if constexpr (WEIGHTED) return args;
     typedef const Mfma2Args __attribute__((address_space(4))) * Args;
     Args a = (Args)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(a));
@@ -727,13 +727,13 @@ __global__ __launch_bounds__(512, 2) void scan_mfma2_kernel(Mfma2Args args)
 {
     const unsigned long long pairs = args.mp.density_acc ? *args.mp.density_acc : 0ULL;
     if (args.tile.total > 0 && pairs >= args.tile.min_pairs) {
-        const Mfma2Args& a = mfma2_args<WEIGHTED>(args);
+        const Mfma2Args& a = mfma2_args();
         scan_tile_body<KS, TT, WEIGHTED>(a.p, a.mp, a.tile);
     } else if (args.mp.density_acc != nullptr && pairs < args.mp.density_limit) {
-        const Mfma2Args& a = mfma2_args<WEIGHTED>(args);
+        const Mfma2Args& a = mfma2_args();
         scan_mfma2_body<KS, TT, WEIGHTED>(a.p, a.mp);
     } else {
-        const Mfma2Args& a = mfma2_args<WEIGHTED>(args);
+        const Mfma2Args& a = mfma2_args();
         scan_mfma_body<KS, TT, WEIGHTED, true, 8, false>(a.p, a.mp);
     }
 }
