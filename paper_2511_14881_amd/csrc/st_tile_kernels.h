@@ -36,11 +36,30 @@ constexpr int kTileWaves = 8;    // wavefronts of a workgroup
 constexpr int kTileGroups = 32;  // filters of a launch, at most
 constexpr int kTileQueue = 64;   // queued lanes of a wavefront
 constexpr int tile_unit(int d) { return d <= 128 ? 64 : 32; }  // items contracted at a time (their rows are held twice over, in registers)
-// Items that a filter hands a wavefront over the level, at least: with fewer, units go out partly filled at the end and
-// cost more than they save.  (Calls against the other forms: 4 M x 256, 500 queries with 8 filters at 1 %, 39 items:
-// 158 us against 147; 1 M x 256, 200 queries at 10 %, 49 items: 103 against 98; 10 M x 256, 256 queries at 5 %, 244 items:
-// 339 against 353; 5 M x 128, 500 queries with one filter at 20 %, 488 items: 241 against 298.)
+// Items that a filter hands a wavefront over the level, at least (an average over the batch): with fewer, units go out
+// partly filled at the end and cost more than they save.
 constexpr int tile_min_items(int d) { return d <= 128 ? 48 : 100; }
+// Items of the level to a wavefront, whether they pass or not, at least.  The form costs a level some 5 us more than the
+// others (set-up, the flush of every filter's last unit), and saves by the items: most where one query row tile comes by
+// for many rows of a filter, and less where scores are exact from the start (weighted) or the products of a unit are few (d = 256,
+// two 16-row blocks to a filter and row of workgroups).  Both thresholds from 860 calls of this shape, 0.3 to 16 M items, 1 to 24
+// filters of 2 to 26 %, each timed with this form wherever it fits and without it.  Calls without -> with it, in us:
+//   plain, d <= 128:          8 M x 128, 500 queries, one filter at 10 %   297 -> 227;  0.6 M x 128, 500, 4 at 17 %  158 -> 149
+//   weighted, d <= 128:       1 M x 128, 250 x 2 tasks, 3 at 19 %   123 -> 131;  2 M, 3 at 19 %  162 -> 164;  4 M, 4 at 9 %  174 -> 165
+//   d = 256, 2 blocks:        3.4 M, 256 queries, 8 at 11 %   218 -> 225;  6.9 M, 200, 8 at 8 %  282 -> 292;  8.8 M, 256, 8 at 4 %  242 -> 237
+//            ... 4 tasks and more than 8 filters:  2.7 M, 60 queries, 14 at 9 %   237 -> 227  (2 tasks, 6.7 M, 15 at 7 %: 350 -> 365)
+//   d = 256, up to 8 blocks:  1.1 M, 200 queries, 4 at 17 %   130 -> 132;  2 M, 200, 2 at 22 %  141 -> 136
+//   d = 256, more:            1.1 M, 256 queries, one at 18 %   131 -> 122
+//   d = 256, weighted, T = 1: 2 M, 300 queries, 3 at 19 %   196 -> 202;  4.7 M, 2 at 8 %  202 -> 184
+//                      T = 2: 1 M, 250 queries, 4 at 17 %   134 -> 136;  2 M, 4 at 9 %  149 -> 144
+//                      T = 4: 0.7 M, 130 queries, 2 at 22 %  127 -> 121
+constexpr int tile_min_span(int d, bool weighted, int n_tasks, int n_blocks, int n_groups, int q_split)
+{
+    if (d <= 128) return !weighted ? 0 : n_tasks == 4 ? 950 : 1000;
+    if (n_blocks <= 2 * n_groups * q_split) return n_tasks == 4 && n_groups > kMfmaFilterBatch ? 1000 : 3500;
+    if (!weighted) return n_blocks <= 8 * n_groups * q_split ? 700 : 0;
+    return n_tasks == 1 ? 1500 : n_tasks == 2 ? 1400 : 0;
+}
 constexpr int kTileRing = 8;     // units whose items are remembered for the queue
 
 // Byte offsets of the workgroup's LDS (the resident queries are at 0, rows of d + 16 bytes: an odd number of 16-byte
@@ -621,6 +640,7 @@ inline bool scan_tile_applies(const ScanParams& sp, const MfmaParams& mp, int gx
     lds->total = 0;
     if (!mp.density_acc || sp.n_groups > kTileGroups) return false;
     const double items = (double)(sp.item_end - sp.item_begin) / ((double)gx * kTileWaves);  // of a wavefront
+    if (items < tile_min_span(sp.d, sp.weighted != 0, sp.n_tasks, mp.n_blocks, sp.n_groups, mp.q_split)) return false;
     const double pairs = (double)mp.density_pairs * tile_min_items(sp.d) / (items > 1.0 ? items : 1.0);
     for (int lists = sp.n_groups < kMfmaFilterBatch ? sp.n_groups : kMfmaFilterBatch;; lists = (lists + 1) / 2) {
         *lds = tile_lds(mp.rows_local, sp.d, sp.n_tasks, sp.weighted != 0, sp.n_groups, mp.region_slots, mp.seg_stride, lists);
