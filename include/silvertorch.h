@@ -345,6 +345,13 @@ int st_search_host_plan(int64_t n_items, int32_t d, int32_t batch, int32_t n_tas
                         int32_t m_bits, int32_t k_hashes, const uint64_t* host_filt_ids,
                         const int64_t* host_filt_offsets, int32_t* host_out_summary);
 
+/* Diagnostic, host part alone like st_search_host_plan: whether the last level of such a search (weighted: of
+ * st_search_multitask) may be scanned by units of passing items.  That is decided on the device, by the passing pairs that the first level counts:
+ * host_out_units[2] receives {the count from which on it is (-1: never), the pairs of the first level}. */
+int st_search_host_units(int64_t n_items, int32_t d, int32_t batch, int32_t n_tasks, int32_t weighted,
+                         int32_t K, int32_t m_bits, int32_t k_hashes, const uint64_t* host_filt_ids,
+                         const int64_t* host_filt_offsets, int64_t* host_out_units);
+
 /* Search scheduling knob for tests: path = 0 auto, 1 force the wavefront dot-product scorer,
  * 2 force the int8 MFMA scorer where it applies.  The setting belongs to the calling thread
  * (searches of other threads are not affected).  Returns the thread's old value. */

@@ -23,7 +23,7 @@ EXPORTS = [
     "st_search_plan", "st_set_scoring_path", "st_timing_begin", "st_timing_end",
     "st_search_overflow_flags_offset", "st_bloom_mask_expr", "st_search_expr_workspace_bytes",
     "st_search_expr", "st_search_ivf_workspace_bytes", "st_search_ivf", "st_quantize_global", "st_value_model",
-    "st_search_host_plan", "st_stream_read", "st_search_static",
+    "st_search_host_plan", "st_search_host_units", "st_stream_read", "st_search_static",
 ]
 
 ST_OP_LEAF, ST_OP_AND, ST_OP_OR, ST_OP_NOT = 0, 1, 2, 3  # operations of a filter program
@@ -98,6 +98,8 @@ def lib() -> C.CDLL:
         L.st_value_model.argtypes = [p, i64, i32, p, p, i32, p, p]
         L.st_search_host_plan.restype = C.c_int
         L.st_search_host_plan.argtypes = [i64, i32, i32, i32, i32, i32, i32, p, p, p]
+        L.st_search_host_units.restype = C.c_int
+        L.st_search_host_units.argtypes = [i64, i32, i32, i32, i32, i32, i32, i32, p, p, p]
         L.st_stream_read.restype = C.c_int
         L.st_stream_read.argtypes = [p, i64, p, i32, p]
         L.st_quantize_global.restype = C.c_int
@@ -240,6 +242,16 @@ def st_search_host_plan(n_items: int, d: int, batch: int, n_tasks: int, K: int, 
                                      _hptr(out)))
     keys = ("distinct_filters", "mfma_groups", "dot_groups", "q_split", "waves", "levels", "table_bytes", "seed_pass")
     return {k: int(v) for k, v in zip(keys, out)}
+
+
+def st_search_host_units(n_items: int, d: int, batch: int, n_tasks: int, weighted: bool, K: int, m_bits: int, k_hashes: int,
+                         filt_ids, filt_offsets) -> tuple[int, int]:
+    """(passing pairs of the first level from which on the last one is scanned by units, -1: never; all its pairs)."""
+    ids, off = _filters(filt_ids, filt_offsets, batch)
+    out = np.zeros(2, dtype=np.int64)
+    _check(lib().st_search_host_units(n_items, d, batch, n_tasks, int(weighted), K, m_bits, k_hashes, _hptr(ids), _hptr(off),
+                                      _hptr(out)))
+    return int(out[0]), int(out[1])
 
 
 def st_set_scoring_path(path: int) -> int:

@@ -21,7 +21,7 @@
 #include "st_block_keep.h"
 #include "st_stage_pool.h"
 #include "st_bloom_kernels.h"
-#include "st_mfma_kernels.h"
+#include "st_mfma2_kernels.h"
 #include "st_ivf_kernels.h"
 #include "st_own_kernels.h"
 #include "st_quant_kernels.h"
@@ -1005,10 +1005,11 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                        void* dev_workspace, int64_t workspace_bytes, void* hip_stream,
                        const Groups* expr_groups = nullptr, const uint64_t* expr_rows = nullptr,
                        int32_t expr_row_count = 0, bool allow_seed = true, int32_t min_cap = 64,
-                       int32_t* dry_out = nullptr, const ProgramPass* programs = nullptr)
+                       int32_t* dry_out = nullptr, const ProgramPass* programs = nullptr,
+                       int64_t* dry_units = nullptr)
 {
     // dry_out: host part only (st_search_host_plan): no device pointer is looked at, nothing is
-    // enqueued, and the summary of the schedule goes to dry_out[8]
+    // enqueued, and the summary of the schedule goes to dry_out[8]; dry_units[2]: see st_search_host_units
     // allow_seed = false: no seed pass and no thresholds tighter than the K-th best so far (both
     // rest on a prefix of the corpus, which says nothing when the passing items sit in a few item
     // ranges, as after cluster probing)
@@ -1167,6 +1168,117 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
     const size_t at_qprow = blob.add(q_prow);
     if (blob.bytes() > L.meta_bytes) return fail(ST_EINVAL, "group tables exceed their workspace slot");
+    // Sample mode: the first level of a search that the 8-wavefront MFMA scan serves alone scans
+    // its G * cap items as segments spread evenly over the corpus instead of a prefix, and the
+    // second level scans the whole corpus without them.  The threshold the first selection
+    // publishes rests on the assumption that the order of the corpus says nothing about a query's
+    // scores; a strided sample keeps that true for corpora ordered along some trend (by age, by
+    // popularity, by category), where a prefix would not.
+    int64_t samp_stride = 0;
+    if (plan.n_levels >= 2 && !plan.level[0].seed && allow_seed && set_mfma.n && !set_dot.n && mp.waves == 8) {
+        const st::Level& L0 = plan.level[0];
+        const int64_t segs = (L0.end - L0.begin) / L0.seg_items;
+        if (L0.begin == 0 && segs > 0 && (L0.end - L0.begin) % L0.seg_items == 0 && L0.seg_items % 64 == 0) {
+            const int64_t stride = n_items / segs / 64 * 64;
+            if (stride >= 2 * (int64_t)L0.seg_items) samp_stride = stride;
+        }
+    }
+    const int seed_parts = st::seed_parts(batch, L.k_pad);  // slices per query of the seed pass (one threshold each)
+    bool density_on = false;  // the first level counts the pairs it admits (chooses the later levels' form of the scan)
+    // Sizes of a level's scans: item ranges and visits of the two scorers' parameters, the MFMA launch's regions and LDS;
+    // returns its workgroups per row of the grid.  (Levels in order: the first one decides on the count.)
+    auto level_sizes = [&](int lv, st::ScanParams& m, st::ScanParams& dot, unsigned long long* counter, int32_t* regions) -> int32_t {
+        const st::Level& L_ = plan.level[lv];
+        for (st::ScanParams* q : {&m, &dot}) {
+            q->item_begin = (samp_stride && lv == 1) ? 0 : L_.begin;
+            q->item_end = L_.end;
+            q->samp_role = samp_stride ? (lv == 0 ? 1 : 2) : 0;
+            q->samp_stride_items = samp_stride;
+            q->samp_segs = samp_stride ? (int32_t)((plan.level[0].end - plan.level[0].begin) / plan.level[0].seg_items) : 0;
+            q->samp_seg_items = samp_stride ? plan.level[0].seg_items : 0;
+            q->seg_items = L_.seg_items;
+            q->seg_per_visit = L_.seg_per_visit;
+            q->use_tau = lv > 0;
+            q->tau_parts = (lv == 1 && plan.level[0].seed) ? seed_parts : 1;
+        }
+        const int64_t n_seg = (L_.end - m.item_begin + L_.seg_items - 1) / L_.seg_items;
+        // workgroups of the MFMA scan that are resident at once, per row of the grid
+        const int32_t resident = std::max(1, st::pow2_ceil(st::kComputeUnits * mfma_wgs / mp.q_split + 1) / 2);
+        // Past the first level a visit is one segment per wavefront of the workgroup; a level with
+        // fewer segments than that gives every resident workgroup takes shorter visits instead, so
+        // that all of them (and with them all of their candidate regions) take part.
+        if (lv > 0 && mp.waves > L_.seg_per_visit) {
+            m.seg_per_visit = mp.waves;
+            // (with the second scorer in the same search every region has its own workgroup)
+            const int64_t wgs = set_dot.n ? plan.groups / mp.q_split : resident;
+            if (set_mfma.n && n_seg < wgs * mp.waves)
+                m.seg_per_visit = (int32_t)std::max<int64_t>(1, (n_seg + wgs - 1) / wgs);
+        }
+        // the same for the wavefront-dot scorer, whose workgroups take a visit's segments in turn
+        if (lv > 0 && n_seg < (int64_t)plan.groups * L_.seg_per_visit)
+            dot.seg_per_visit = (int32_t)std::max<int64_t>(1, (n_seg + plan.groups - 1) / plan.groups);
+        // workgroups with work: one visit (seg_per_visit segments) per step; launching no more
+        // keeps idle workgroups from staging queries, and the selection reads only their regions
+        const int64_t n_visit = (n_seg + m.seg_per_visit - 1) / m.seg_per_visit;
+        int32_t gx = 0;
+        *regions = plan.groups;
+        if (set_mfma.n) {
+            const int32_t per_row = plan.groups / mp.q_split;  // regions of one row of the grid
+            gx = per_row;
+            mp.region_slots = 1;
+            if (!set_dot.n) {
+                // only as many workgroups as are resident at once; each takes several regions
+                if (resident < gx) gx = resident;
+                if (n_visit < gx) gx = (int32_t)std::max<int64_t>(n_visit, 1);
+                // the first level needs exactly one visit per region; later levels spread each
+                // workgroup's candidates, segment by segment, over the regions the layout leaves it
+                // (as many as the LDS budget of the chosen configuration was sized for)
+                const int64_t want = lv == 0 ? std::min<int64_t>(per_row / gx, (n_visit + gx - 1) / gx)
+                                             : std::min<int64_t>(per_row / gx, st::mfma_region_slots(mfma_wgs));
+                mp.region_slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(want, st::kMaxRegionSlots));
+                // the first level needs a region per visit (no region can then overflow)
+                if (lv == 0 && (int64_t)gx * mp.region_slots < n_visit) {
+                    gx = (int32_t)std::min<int64_t>(per_row, std::max<int64_t>(n_visit, 1));
+                    mp.region_slots = 1;
+                }
+            }
+            *regions = set_dot.n ? plan.groups : gx * mp.region_slots * mp.q_split;
+            st::mfma_lds_layout(&mp, d, n_tasks, set_mfma.n, mp.waves);
+            // A first level that admits every pair also counts them: the later levels choose the
+            // form of the scan by how many items a filter passes per segment.
+            if (lv == 0) {
+                density_on = mp.waves == 8 && !set_dot.n && m.seg_per_visit == 1 && m.seg_items <= m.cap;
+                // pairs of the level if every filter passed kDenseItems items per 512-item segment
+                mp.density_pairs = (L_.end - L_.begin) * (int64_t)batch;
+                mp.density_limit = (unsigned long long)(mp.density_pairs / 512 * st::kDenseItems);
+            }
+            mp.density_acc = density_on ? counter : nullptr;
+        }
+        return gx;
+    };
+    if (dry_units) {  // whether the last level's scan may take the form by units, and from which count of the first one's pairs on
+        dry_units[0] = -1;
+        dry_units[1] = 0;
+        st::ScanParams m, dot;
+        memset(&m, 0, sizeof(m));
+        m.n_items = n_items;
+        m.d = d;
+        m.n_tasks = n_tasks;
+        m.weighted = weighted ? 1 : 0;
+        m.cap = plan.cap;
+        m.n_groups = set_mfma.n;
+        dot = m;
+        unsigned long long counter;
+        int32_t regions, gx = 0;
+        for (int lv = 0; lv < plan.n_levels; ++lv)
+            if (!plan.level[lv].seed) gx = level_sizes(lv, m, dot, &counter, &regions);
+        st::TileLds lds;
+        if (set_mfma.n && density_on && plan.n_levels > 1 && st::scan_mfma2_applies(m, mp) && st::scan_tile_applies(m, mp, gx, &lds)) {
+            dry_units[0] = (int64_t)lds.min_pairs;
+            dry_units[1] = mp.density_pairs;
+        }
+        return ST_OK;
+    }
     if (dry_out) {
         dry_out[0] = groups.n_groups;
         dry_out[1] = set_mfma.n;
@@ -1303,30 +1415,13 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
         stage.reported();
         return ST_OK;
     }
-    // Sample mode: the first level of a search that the 8-wavefront MFMA scan serves alone scans
-    // its G * cap items as segments spread evenly over the corpus instead of a prefix, and the
-    // second level scans the whole corpus without them.  The threshold the first selection
-    // publishes rests on the assumption that the order of the corpus says nothing about a query's
-    // scores; a strided sample keeps that true for corpora ordered along some trend (by age, by
-    // popularity, by category), where a prefix would not.
-    int64_t samp_stride = 0;
-    if (plan.n_levels >= 2 && !plan.level[0].seed && allow_seed && set_mfma.n && !set_dot.n && mp.waves == 8) {
-        const st::Level& L0 = plan.level[0];
-        const int64_t segs = (L0.end - L0.begin) / L0.seg_items;
-        if (L0.begin == 0 && segs > 0 && (L0.end - L0.begin) % L0.seg_items == 0 && L0.seg_items % 64 == 0) {
-            const int64_t stride = n_items / segs / 64 * 64;
-            if (stride >= 2 * (int64_t)L0.seg_items) samp_stride = stride;
-        }
-    }
     bool mfma_started = false;  // the first MFMA launch builds the resident-query image
-    bool density_on = false;    // the first level counts the pairs it admits (chooses the later levels' form of the scan)
     // Batches that hardly share filters: from the second level on all pairs are multiplied, see st_own_kernels.h.
     // (One task, no weights; with fewer than 16 queries more than half of the products would be padding.)
     const auto own_scan = g_scoring_path == 0 && n_tasks == 1 && !weighted && set_dot.q_list.size() >= 16 && sp_d.m_bits <= st::kOwnRows &&
                                   set_dot.rows.size() <= (size_t)st::kOwnRowRefs
                               ? st::own_kernel(d)
                               : nullptr;
-    int seed_parts = 1;         // slices per query of the seed pass (one threshold each)
     for (int lv = 0; lv < plan.n_levels; ++lv) {
         const st::Level& L_ = plan.level[lv];
         se.first = lv == 0 || (lv == 1 && plan.level[0].seed);  // no candidate list from before
@@ -1363,82 +1458,14 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             se_seed.q_taupos = host_tab(at_taupos);
             se_seed.scan.grp_row_off = host_tab(at_all_row_off);
             se_seed.scan.grp_rows = host_tab(at_all_rows);
-            seed_parts = st::seed_parts(batch, L.k_pad);
             stage.enqueued = true;
             ST_HIP(st::launch_seed(se_seed, L_.end, batch, seed_parts, up, stream));
             continue;
         }
-        for (st::ScanParams* q : {&sp_m, &sp_d}) {
-            q->item_begin = (samp_stride && lv == 1) ? 0 : L_.begin;
-            q->item_end = L_.end;
-            q->samp_role = samp_stride ? (lv == 0 ? 1 : 2) : 0;
-            q->samp_stride_items = samp_stride;
-            q->samp_segs = samp_stride ? (int32_t)((plan.level[0].end - plan.level[0].begin) / plan.level[0].seg_items) : 0;
-            q->samp_seg_items = samp_stride ? plan.level[0].seg_items : 0;
-            q->seg_items = L_.seg_items;
-            q->seg_per_visit = L_.seg_per_visit;
-            q->use_tau = lv > 0;
-            q->tau_parts = (lv == 1 && plan.level[0].seed) ? seed_parts : 1;
-        }
-        const int64_t n_seg = (L_.end - sp_m.item_begin + L_.seg_items - 1) / L_.seg_items;
-        // workgroups of the MFMA scan that are resident at once, per row of the grid
-        const int32_t resident = std::max(1, st::pow2_ceil(st::kComputeUnits * mfma_wgs / mp.q_split + 1) / 2);
-        // Past the first level a visit is one segment per wavefront of the workgroup; a level with
-        // fewer segments than that gives every resident workgroup takes shorter visits instead, so
-        // that all of them (and with them all of their candidate regions) take part.
-        if (lv > 0 && mp.waves > L_.seg_per_visit) {
-            sp_m.seg_per_visit = mp.waves;
-            // (with the second scorer in the same search every region has its own workgroup)
-            const int64_t wgs = set_dot.n ? plan.groups / mp.q_split : resident;
-            if (set_mfma.n && n_seg < wgs * mp.waves)
-                sp_m.seg_per_visit = (int32_t)std::max<int64_t>(1, (n_seg + wgs - 1) / wgs);
-        }
-        // the same for the wavefront-dot scorer, whose workgroups take a visit's segments in turn
-        if (lv > 0 && n_seg < (int64_t)plan.groups * L_.seg_per_visit)
-            sp_d.seg_per_visit = (int32_t)std::max<int64_t>(1, (n_seg + plan.groups - 1) / plan.groups);
-        // workgroups with work: one visit (seg_per_visit segments) per step; launching no more
-        // keeps idle workgroups from staging queries, and the selection reads only their regions
-        const int64_t n_visit = (n_seg + sp_m.seg_per_visit - 1) / sp_m.seg_per_visit;
-        int32_t regions = plan.groups;
+        int32_t regions;
+        const int32_t gx = level_sizes(lv, sp_m, sp_d, (unsigned long long*)(ws + L.density), &regions);
         if (set_mfma.n) {
-            const int32_t per_row = plan.groups / mp.q_split;  // regions of one row of the grid
-            int32_t gx = per_row;
-            mp.region_slots = 1;
-            if (!set_dot.n) {
-                // only as many workgroups as are resident at once; each takes several regions
-                if (resident < gx) gx = resident;
-                if (n_visit < gx) gx = (int32_t)std::max<int64_t>(n_visit, 1);
-                // the first level needs exactly one visit per region; later levels spread each
-                // workgroup's candidates, segment by segment, over the regions the layout leaves it
-                // (as many as the LDS budget of the chosen configuration was sized for)
-                const int64_t want = lv == 0 ? std::min<int64_t>(per_row / gx, (n_visit + gx - 1) / gx)
-                                             : std::min<int64_t>(per_row / gx, st::mfma_region_slots(mfma_wgs));
-                mp.region_slots = (int32_t)std::max<int64_t>(1, std::min<int64_t>(want, st::kMaxRegionSlots));
-                // the first level needs a region per visit (no region can then overflow)
-                if (lv == 0 && (int64_t)gx * mp.region_slots < n_visit) {
-                    gx = (int32_t)std::min<int64_t>(per_row, std::max<int64_t>(n_visit, 1));
-                    mp.region_slots = 1;
-                }
-            }
-            regions = set_dot.n ? plan.groups : gx * mp.region_slots * mp.q_split;
-            st::mfma_lds_layout(&mp, d, n_tasks, set_mfma.n, mp.waves);
             mp.first_level = mfma_started ? 0 : 1;
-            // A first level that admits every pair also counts them: the later levels choose the
-            // form of the scan by how many items a filter passes per segment.
-            {
-                st::ScanParams probe = sp_m;
-                probe.use_tau = lv > 0;
-                const bool admit_all = lv == 0 && mp.waves == 8 && !set_dot.n && probe.seg_per_visit == 1 && probe.seg_items <= probe.cap;
-                if (lv == 0) {
-                    density_on = admit_all;
-                    mp.density_acc = admit_all ? (unsigned long long*)(ws + L.density) : nullptr;
-                    // pairs of the level if every filter passed kDenseItems items per 512-item segment
-                    mp.density_pairs = (L_.end - L_.begin) * (int64_t)batch;
-                    mp.density_limit = (unsigned long long)(mp.density_pairs / 512 * st::kDenseItems);
-                } else if (!density_on) {
-                    mp.density_acc = nullptr;
-                }
-            }
             mfma_started = true;
             TimedLaunch t(0, stream);
             ST_HIP(st::launch_scan_mfma(sp_m, mp, gx, stream));
@@ -1572,6 +1599,27 @@ int st_search_host_plan(int64_t n_items, int32_t d, int32_t batch, int32_t n_tas
         return search_impl(&desc, nullptr, nullptr, n_items, d, nullptr, nullptr, batch, n_tasks,
                            n_tasks > 1 ? unit_weights : nullptr, host_filt_ids, host_filt_offsets, K, nullptr, nullptr,
                            nullptr, nullptr, 0, nullptr, nullptr, nullptr, 0, true, 64, host_out_summary);
+    });
+}
+
+int st_search_host_units(int64_t n_items, int32_t d, int32_t batch, int32_t n_tasks, int32_t weighted, int32_t K,
+                         int32_t m_bits, int32_t k_hashes, const uint64_t* host_filt_ids, const int64_t* host_filt_offsets,
+                         int64_t* host_out_units)
+{
+    return guarded([&]() -> int {
+        if (!host_out_units) return fail(ST_EINVAL, "host_out_units is null");
+        if (!weighted && n_tasks != 1) return fail(ST_EINVAL, "several tasks are weighted");
+        if (m_bits < 1 || m_bits > ST_MAX_M_BITS) return fail(ST_EINVAL, "m_bits=%d out of range", m_bits);
+        if (k_hashes < 1 || k_hashes > ST_MAX_K_HASHES) return fail(ST_EINVAL, "k_hashes=%d out of range", k_hashes);
+        int32_t unused = 0;  // (the summary is not asked for)
+        st_bloom desc;  // sizes only: the dry run reads no device memory
+        desc.n_items = n_items;
+        desc.m_bits = m_bits;
+        desc.k_hashes = k_hashes;
+        const float unit_weights[ST_MAX_TASKS] = {1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f, 1.f};
+        return search_impl(&desc, nullptr, nullptr, n_items, d, nullptr, nullptr, batch, n_tasks,
+                           weighted ? unit_weights : nullptr, host_filt_ids, host_filt_offsets, K, nullptr, nullptr,
+                           nullptr, nullptr, 0, nullptr, nullptr, nullptr, 0, true, 64, &unused, nullptr, host_out_units);
     });
 }
 

@@ -210,14 +210,18 @@ def test_freed_index_memory_goes_back_to_the_driver():
 # few): row lengths of every variant, one query block and several, two rows of the grid, ragged last segment
 # and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores; a corpus whose
 # filters pass everything in some stretches and nothing in others (wavefronts change between the two forms), and
-# no filter at all (no signature row is named).  The last selection would make good for lost candidates, so no
+# no filter at all (no signature row is named); scales of many sizes (a wavefront's bounds move as it meets larger ones), some
+# words of items beyond those that a bound is formed for, scores that are all negative (no bound).  The last selection would make good for lost candidates, so no
 # query that passes enough items may have needed that.
 @pytest.mark.parametrize("n,d,B,m,kind", [(600_001, 64, 16, 64, "mixed"), (530_049, 96, 33, 100, "mixed"),
                                           (400_003, 128, 130, 512, "mixed"), (524_288 + 31, 192, 40, 257, "mixed"),
                                           (420_000, 256, 300, 128, "mixed"), (600_000, 64, 64, 512, "rare"),
                                           (350_000, 128, 140, 512, "rare"), (400_001, 64, 150, 128, "ties"),
                                           (430_013, 256, 48, 300, "stretches"), (330_077, 96, 260, 64, "stretches"),
-                                          (300_011, 96, 20, 257, "none")])
+                                          (300_011, 96, 20, 257, "none"), (380_001, 128, 130, 256, "scales"),
+                                          (300_031, 64, 40, 64, "scales"), (350_000, 192, 70, 512, "beyond"),
+                                          (400_007, 64, 150, 100, "beyond"), (330_000, 256, 100, 300, "negative"),
+                                          (420_000, 96, 200, 64, "negative")])
 def test_own_filters(n, d, B, m, kind):
     w = ragged_workload(n, n, d, B, 40, 8, m, 3)
     filters = []
@@ -238,11 +242,20 @@ def test_own_filters(n, d, B, m, kind):
         off = np.concatenate([[0], np.cumsum(lens)]).astype(np.int64)
         ids = (np.arange(off[-1]) - off[:-1].repeat(lens) + (np.arange(n) * (turn == 2)).repeat(lens)) % 40
         w.feat_offsets, w.feat_ids = torch.from_numpy(off), torch.from_numpy(ids.astype(np.int64))
+    elif kind == "scales":
+        w.item_scale = torch.from_numpy(np.exp2(np.random.default_rng(n).uniform(-20, 20, n)).astype(np.float32))
+    elif kind == "beyond":  # word by word: up to 2^110, ordinary ones, all below 2^-90
+        rng = np.random.default_rng(n)
+        lo, hi = np.array([(-110, 110), (-3, 3), (-110, -95)])[rng.integers(0, 3, n // 64 + 1).repeat(64)[:n]].T
+        w.item_scale = torch.from_numpy(np.exp2(rng.uniform(lo, hi)).astype(np.float32))
+    elif kind == "negative":
+        w.items = w.items.abs().clamp(1, 127).to(torch.int8)
+        w.queries = (-w.queries.abs().clamp(1, 127).to(torch.int16)).to(torch.int8)
     K = 60
     sigs = oracle_index(w)
     passing = [int(np.unpackbits(O.bloom_mask(sigs, m, 3, np.array(f, np.uint64)).view(np.uint8)).sum()) for f in filters]
-    fast = [b for b in range(B) if passing[b] >= 40 * K] if kind != "ties" else []
-    assert kind == "ties" or len(fast) > B // 2
+    fast = [b for b in range(B) if passing[b] >= 40 * K] if kind not in ("ties", "beyond") else []
+    assert kind in ("ties", "beyond") or len(fast) > B // 2
     check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, max(1, B // 12))}), slow_path=([], fast),
                  label=f"own filters {kind}")
 
@@ -413,22 +426,40 @@ def test_probing_batch_with_few_words_to_a_query(n, big, K):
 
 # The scan by units of passing items (levels behind the first, one workgroup to a compute unit, filters broad enough that
 # every wavefront fills units): each row length and number of tasks, filters with an odd number of 16-row blocks, up to
-# 32 filters and more, no filter, one that nothing passes, ragged last segment and word, few and many passing items
-# (lists by lane and by word), more than 8 and 16 signature rows, scales of many sizes, scores that are all negative
-# (no bound), tied scores, queries split over rows of workgroups.  "rare" and "many": the other forms of the same level.
-@pytest.mark.parametrize("n,d,B,T,groups,m,k,kind", [
-    (700_001, 64, 900, 0, 5, 128, 2, "plain"), (800_049, 128, 500, 0, 8, 128, 2, "plain"), (900_000, 256, 240, 0, 7, 256, 3, "plain"),
-    (690_031, 128, 1000, 0, 2, 64, 1, "dense"), (900_000, 256, 600, 0, 20, 512, 4, "plain"), (680_000, 64, 1100, 0, 31, 256, 3, "plain"),
-    (950_017, 128, 420, 0, 4, 1024, 7, "long"), (700_011, 256, 250, 0, 4, 1024, 7, "long"), (710_000, 128, 450, 0, 6, 128, 2, "scales"),
-    (700_000, 256, 260, 0, 4, 128, 2, "negative"), (700_000, 128, 400, 0, 3, 64, 2, "ties"), (600_000, 256, 250, 0, 8, 512, 4, "rare"),
-    (760_000, 64, 200, 4, 7, 128, 2, "plain"), (800_007, 128, 128, 4, 8, 128, 2, "plain"), (470_000, 256, 110, 2, 5, 128, 2, "plain"),
-    (780_001, 128, 420, 1, 3, 128, 2, "plain"), (860_000, 128, 130, 4, 12, 256, 3, "negative"), (300_000, 64, 1000, 0, 40, 256, 3, "many")])
-def test_scan_by_units(n, d, B, T, groups, m, k, kind):
+# 20 filters (several batches of eight), no filter, one that nothing passes, ragged last segment and word, few and many passing
+# items (lists by lane and by word), more than 8 and 16 signature rows, scales of many sizes, scores that are all negative
+# (no bound), tied scores, queries split over rows of workgroups.  units: whether the last level takes that form -- the
+# host says whether it may, and from which count of passing pairs on; the others take it by another form: queries that do
+# not fit its LDS, too few items for it, filters that pass little ("rare"), more filters than it takes ("many").
+@pytest.mark.parametrize("n,d,B,T,groups,m,k,kind,units", [
+    (700_001, 64, 700, 0, 5, 128, 2, "plain", True), (700_001, 64, 560, 0, 12, 256, 2, "plain", True),
+    (800_049, 128, 420, 0, 8, 128, 2, "plain", True), (800_049, 128, 330, 0, 12, 256, 2, "plain", True),
+    (1_450_003, 256, 240, 0, 7, 256, 3, "plain", True), (800_001, 256, 480, 0, 5, 128, 2, "plain", True),
+    (690_031, 128, 1000, 0, 2, 64, 1, "dense", True), (950_017, 128, 420, 0, 4, 1024, 7, "long", True),
+    (1_450_003, 256, 230, 0, 4, 1024, 7, "long", True), (710_000, 128, 450, 0, 6, 128, 2, "scales", True),
+    (800_001, 256, 500, 0, 4, 128, 2, "negative", True), (700_000, 128, 400, 0, 3, 64, 2, "ties", True),
+    (1_000_000, 64, 400, 4, 5, 128, 2, "plain", True), (1_050_003, 64, 360, 4, 13, 256, 2, "plain", True),
+    (1_050_003, 128, 220, 4, 8, 128, 2, "plain", True), (800_001, 256, 130, 4, 5, 128, 2, "plain", True),
+    (800_001, 256, 75, 4, 10, 256, 2, "plain", True), (1_050_003, 64, 700, 2, 6, 128, 2, "plain", True),
+    (1_450_003, 256, 250, 2, 4, 128, 2, "plain", True), (1_050_003, 128, 800, 1, 5, 128, 2, "plain", True),
+    (1_050_003, 128, 200, 4, 20, 256, 2, "negative", True),
+    (700_001, 64, 900, 0, 5, 128, 2, "plain", False), (800_049, 128, 500, 0, 8, 128, 2, "plain", False),
+    (900_000, 256, 240, 0, 7, 256, 3, "plain", False), (900_000, 256, 1000, 0, 5, 512, 4, "plain", True),
+    (680_000, 64, 1100, 0, 31, 256, 3, "plain", False), (700_011, 256, 250, 0, 4, 1024, 7, "long", False),
+    (700_000, 256, 260, 0, 4, 128, 2, "negative", False), (600_000, 256, 250, 0, 8, 512, 4, "rare", False),
+    (760_000, 64, 200, 4, 7, 128, 2, "plain", False), (800_007, 128, 128, 4, 8, 128, 2, "plain", False),
+    (470_000, 256, 110, 2, 5, 128, 2, "plain", False), (780_001, 128, 420, 1, 3, 128, 2, "plain", False),
+    (860_000, 128, 130, 4, 12, 256, 3, "negative", False), (300_000, 64, 1000, 0, 40, 256, 3, "many", False),
+    (900_000, 128, 400, 0, 8, 512, 4, "rare", False)])
+def test_scan_by_units(n, d, B, T, groups, m, k, kind, units):
     rng = np.random.default_rng(n + d)
     vocab, feats = (40, 4) if kind == "rare" else (40, 30) if kind == "many" else (12, 12)
     w = ragged_workload(n + d, n, d, B, vocab, feats, m, k, T=T)
     pool = [[] if g == 1 and kind != "rare" else [999] if g == 2 else [g % vocab] if g % 3 == 0 or kind == "dense" else
             [g % vocab, *(int(x) for x in rng.choice(vocab, 2 if kind == "long" else 1))] for g in range(groups)]
+    if units:  # (the hashes of ids that differ in the bits of a hash's number alone are the same)
+        w.feat_ids = w.feat_ids * 8
+        pool = [[8 * x for x in f] for f in pool]
     pick = np.concatenate([np.arange(groups), rng.integers(0, groups, B - groups)])
     filters = [pool[g] for g in pick]
     w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
@@ -446,9 +477,9 @@ def test_scan_by_units(n, d, B, T, groups, m, k, kind):
     assert plan["waves"] == 8 and plan["levels"] >= 2, plan
     sigs = oracle_index(w)
     passing = {g: int(np.unpackbits(O.bloom_mask(sigs, m, k, np.array(pool[g], np.uint64)).view(np.uint8)).sum()) for g in range(groups)}
-    # a wavefront's share of what an average query's filter passes decides for this form
-    share = np.mean([passing[g] for g in pick]) / (2048 / plan["q_split"])
-    assert kind in ("rare", "many") or share >= (64 if d <= 128 else 110), share
+    enough, pairs = st.st_search_host_units(n, d, B, max(T, 1), T > 0, K, m, k, w.filt_ids, w.filt_offsets)
+    counted = pairs * np.mean([passing[g] for g in pick]) / n  # (but for the sample's chance: well below a tenth)
+    assert (enough >= 0 and counted >= 1.1 * enough) if units else (enough < 0 or counted <= 0.9 * enough), (enough, pairs, counted)
     fast = [b for b in range(B) if passing[pick[b]] >= 40 * K] if kind not in ("ties", "scales") else []
     assert kind in ("ties", "scales") or len(fast) > B // 2
     check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, B - 1, *range(0, B, max(1, B // 14))}), slow_path=([], fast),

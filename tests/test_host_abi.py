@@ -165,6 +165,25 @@ def test_host_plan_routes_groups_by_size_and_shape():
     assert 0 < large["table_bytes"] < 64 * 1024 and 0 < dense["table_bytes"] < 64 * 1024
 
 
+def test_host_units_names_the_searches_that_may_be_scanned_by_units():
+    def units(n, d, batch, tasks, weighted, filters):
+        ids = np.array([8 * (b % filters) for b in range(batch)], dtype=np.uint64)
+        return st.st_search_host_units(n, d, batch, tasks, weighted, 100, 256, 2, ids, np.arange(batch + 1, dtype=np.int64))
+
+    # from how many items of a filter to a wavefront on: 2048 wavefronts share a level without a split
+    for n, d, batch, least in ((4_000_000, 128, 500, 48), (8_000_000, 256, 250, 100)):
+        enough, pairs = units(n, d, batch, 1, False, 4)
+        assert 0 < enough < pairs and abs(enough / pairs * n / 2048 - least) < 2
+    # weighted scores and units of few products need more items
+    assert units(1_000_000, 128, 500, 1, False, 4)[0] >= 0
+    assert units(1_000_000, 128, 130, 4, True, 4) == (-1, 0) and units(4_000_000, 128, 130, 4, True, 4)[0] >= 0
+    assert units(4_000_000, 256, 256, 1, False, 8) == (-1, 0) and units(10_000_000, 256, 256, 1, False, 8)[0] >= 0
+    assert units(4_000_000, 128, 64, 1, False, 8) == (-1, 0)  # (four wavefronts to a workgroup)
+    assert units(4_000_000, 128, 500, 1, False, 40) == (-1, 0) and units(4_000_000, 512, 200, 1, False, 4) == (-1, 0)
+    with pytest.raises(st.StError):
+        units(1_000_000, 128, 8, 2, False, 4)
+
+
 def test_host_plan_rejects_bad_arguments():
     with pytest.raises(ValueError):
         _plan(1_000_000, 128, 2, 1, 100, 256, 3, [(1,)])  # offsets shorter than the batch: the binding refuses
