@@ -1420,7 +1420,7 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     // (One task, no weights; with fewer than 16 queries more than half of the products would be padding.)
     const auto own_scan = g_scoring_path == 0 && n_tasks == 1 && !weighted && set_dot.q_list.size() >= 16 && sp_d.m_bits <= st::kOwnRows &&
                                   set_dot.rows.size() <= (size_t)st::kOwnRowRefs
-                              ? st::own_kernel(d)
+                              ? st::own_kernel(d, set_dot.q_list.size())
                               : nullptr;
     for (int lv = 0; lv < plan.n_levels; ++lv) {
         const st::Level& L_ = plan.level[lv];
@@ -1477,11 +1477,12 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             sp_o.seg_items = st::kOwnSeg;
             sp_o.seg_per_visit = (int32_t)std::max<int64_t>(1, std::min<int64_t>(4, n_own / plan.groups));
             const size_t lds = st::own_lds_bytes((int)set_dot.q_list.size(), d, sp_o.m_bits);
-            static std::atomic<bool> lds_set[9] = {};  // (setting the attribute twice is harmless)
-            if (!lds_set[d / 32].load(std::memory_order_acquire)) {
+            static std::atomic<bool> lds_set[2][9] = {};  // (setting the attribute twice is harmless)
+            auto& set = lds_set[st::own_one_block(d, set_dot.q_list.size())][d / 32];
+            if (!set.load(std::memory_order_acquire)) {
                 ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(own_scan), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            160 * 1024));
-                lds_set[d / 32].store(true, std::memory_order_release);
+                set.store(true, std::memory_order_release);
             }
             TimedLaunch t(0, stream);
             hipLaunchKernelGGL(own_scan, dim3(std::min(plan.groups, st::kComputeUnits), (set_dot.q_list.size() + st::kOwnCols - 1) / st::kOwnCols),

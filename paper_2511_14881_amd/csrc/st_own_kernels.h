@@ -32,7 +32,7 @@
 //    256      909 -> 341   1458 -> 401  1909 -> 620  2127 -> 733  2222 -> 747
 //     16, 64 bytes  99 -> 88   129 -> 95   128 -> 88   131 -> 103   200 -> 130
 // (with two barriers to a segment and the first level gathered; without them and with scan_own_first_kernel, 256 queries,
-// same card: 349 -> 272, 396 -> 300, 621 -> 427, 711 -> 496, 700 -> 485; 16 queries on 0.8 to 3 M items 0.93 to 1.04 of the time)
+// same card: 349 -> 272, 396 -> 300, 621 -> 427, 711 -> 496, 700 -> 485)
 // one filter for 64 queries, 10 M x 192: 447 -> 176 at 0.02 %, 807 -> 339 at 0.5 %, 825 -> 543 at 5 %; behind cluster probing
 // (600 of 4096 clusters, 3 M x 128, 32 queries) 326 -> 243.
 #pragma once
@@ -43,6 +43,7 @@ namespace st {
 constexpr int kOwnThreads = 512;
 constexpr int kOwnSeg = 512;            // items of a segment
 constexpr int kOwnWords = kOwnSeg / 64; // one mask word per wavefront
+constexpr int kOwnBlock = 32;           // queries of one product
 constexpr int kOwnCols = 256;           // queries resident at a time (one row of the grid)
 constexpr int kOwnRows = 512;           // signature rows of the index, at most
 // Items of a level, at least: two segments to each of the workgroups that are resident.  (Whether the candidate
@@ -82,7 +83,8 @@ __device__ inline void own_barrier()
 // d = 32 * KS.  Grid (workgroups, ceil(queries / kOwnCols)); segments start at multiples of 512 items.  One
 // workgroup to a compute unit is resident (registers), so that many are launched and each takes several
 // regions in turn: the queries and tables are brought to LDS once.
-template <int KS>
+// ONE: at most kOwnBlock queries.
+template <int KS, bool ONE>
 __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int n_refs)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char own_lds[];
@@ -370,7 +372,11 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
             }
             qn = 0;
         };
-        const int64_t next0 = p.item_begin + seg * kOwnSeg + wv * 64;  // (the segment advanced above)
+        auto next_rows = [&]() __attribute__((always_inline)) {
+            const int64_t next0 = p.item_begin + seg * kOwnSeg + wv * 64;  // (the segment advanced above)
+            have0 = region < p.groups && next0 + 64 <= p.n_items;
+            if (have0) rows(std::true_type{}, 0, next0);
+        };
 #pragma unroll
         for (int s = 0; s < 2; ++s) {
             // The scales: exact ones for the tests, and fixed-point factors against a power of two above the scales met
@@ -378,6 +384,40 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
             // roundings involved).
             const float sv[16] = {si[s][0].x, si[s][0].y, si[s][0].z, si[s][0].w, si[s][1].x, si[s][1].y, si[s][1].z, si[s][1].w,
                                   si[s][2].x, si[s][2].y, si[s][2].z, si[s][2].w, si[s][3].x, si[s][3].y, si[s][3].z, si[s][3].w};
+            if constexpr (ONE) {
+                // A single block: factors for 16 items cost more than the exact scores of its 16 pairs, and few lanes pass.
+                const int c = lane & 31;
+                own_i16 acc;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) acc[i] = 0;
+                const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)c * DP) + half;
+#pragma unroll
+                for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][k], qr[2 * k], acc, 0, 0, 0);
+                const float sq = s_sq[c];
+                const uint64_t tau = s_tau[c];
+                const float bound = tau ? key_score(tau) : -__builtin_inff();
+                uint32_t over = 0;  // (scores not below the threshold's, also where a NaN is involved: compared as keys)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) over |= !(rescale(acc[i], sq, sv[i]) < bound) ? 1u << (8 * (i >> 2) + (i & 3)) : 0u;
+                over &= (uint32_t)(s_mask[c] >> (32 * s)) >> (4 * half);
+                if (ballot(over != 0) != 0) {
+                    uint32_t it0 = (uint32_t)my0 + 32u * s + 4u * half;
+                    asm volatile("" : "+v"(it0));  // (16 ids to a half, kept in registers all the time otherwise)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        const int bit = 8 * (i >> 2) + (i & 3);
+                        if (over >> bit & 1u) {
+                            const uint64_t key = make_key(rescale(acc[i], sq, sv[i]), it0 + bit);
+                            if (key >= tau) {
+                                const uint32_t slot = atomicAdd(&s_cnt[c], 1u);
+                                if (slot < (uint32_t)p.cap) p.cand[((int64_t)s_query[c] * p.groups + at_region) * p.cap + slot] = key;
+                            }
+                        }
+                    }
+                }
+                if (s == 0) next_rows();
+                continue;
+            }
             if ((lane & 31) == 0) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) *reinterpret_cast<float4*>(s_si + 32 * s + 8 * j + 4 * half) = si[s][j];
@@ -444,10 +484,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int
                     m &= ~ballot(mine);
                 }
             }
-            if (s == 0) {
-                have0 = region < p.groups && next0 + 64 <= p.n_items;
-                if (have0) rows(std::true_type{}, 0, next0);
-            }
+            if (s == 0) next_rows();
         }
         if (qn > 0) drain();
     }
@@ -564,14 +601,20 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_first_kernel(ScanParams 
 
 // The kernel for rows of d bytes, or null.  (One copy of the kernel to a length: the lengths the MFMA scan has, as far as
 // a workgroup's registers hold the rows of 64 items, and 96 and 192 between them; others go to the gathering scan.)
-inline auto own_kernel(int d) -> decltype(&scan_own_kernel<8>)
+// Up to kOwnBlock queries of rows up to 192 bytes take the form of one block.  Calls with integer bounds and the
+// queue -> with it, in us: 2 M x 64, 17 queries 95.8 -> 86.1; 5 M x 64, 24: 184 -> 169; 3.4 M x 96, 16: 144 -> 134;
+// 4 M x 128, 16: 177 -> 169; 1.5 M x 192, 32: 109.7 -> 106.9.  At 256 bytes its scores do not fit the registers
+// (1.5 M, 32 queries: 133 -> 137).
+constexpr bool own_one_block(int d, size_t n_q) { return n_q <= (size_t)kOwnBlock && d <= 192; }
+inline auto own_kernel(int d, size_t n_q) -> decltype(&scan_own_kernel<8, false>)
 {
+    const bool one = own_one_block(d, n_q);
     switch (d) {
-    case 64: return &scan_own_kernel<2>;
-    case 96: return &scan_own_kernel<3>;
-    case 128: return &scan_own_kernel<4>;
-    case 192: return &scan_own_kernel<6>;
-    case 256: return &scan_own_kernel<8>;
+    case 64: return one ? &scan_own_kernel<2, true> : &scan_own_kernel<2, false>;
+    case 96: return one ? &scan_own_kernel<3, true> : &scan_own_kernel<3, false>;
+    case 128: return one ? &scan_own_kernel<4, true> : &scan_own_kernel<4, false>;
+    case 192: return one ? &scan_own_kernel<6, true> : &scan_own_kernel<6, false>;
+    case 256: return &scan_own_kernel<8, false>;
     default: return nullptr;
     }
 }

@@ -207,7 +207,7 @@ def test_freed_index_memory_goes_back_to_the_driver():
 
 
 # Batches whose queries hardly share filters (the products of all pairs, or of the passing ones where a wavefront has
-# few): row lengths of every variant, one query block and several, two rows of the grid, ragged last segment
+# few): row lengths of every variant, one query block (its own form up to rows of 192) and several, two rows of the grid, ragged last segment
 # and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores; a corpus whose
 # filters pass everything in some stretches and nothing in others (wavefronts change between the two forms), and
 # no filter at all (no signature row is named); scales of many sizes (a wavefront's bounds move as it meets larger ones), some
@@ -221,7 +221,10 @@ def test_freed_index_memory_goes_back_to_the_driver():
                                           (300_011, 96, 20, 257, "none"), (380_001, 128, 130, 256, "scales"),
                                           (300_031, 64, 40, 64, "scales"), (350_000, 192, 70, 512, "beyond"),
                                           (400_007, 64, 150, 100, "beyond"), (330_000, 256, 100, 300, "negative"),
-                                          (420_000, 96, 200, 64, "negative")])
+                                          (420_000, 96, 200, 64, "negative"), (300_031, 128, 32, 512, "mixed"),
+                                          (350_001, 192, 31, 100, "stretches"), (400_003, 96, 32, 64, "ties"),
+                                          (330_000, 64, 24, 257, "negative"), (310_017, 128, 17, 128, "beyond"),
+                                          (300_011, 192, 16, 64, "scales"), (320_009, 256, 32, 128, "mixed")])
 def test_own_filters(n, d, B, m, kind):
     w = ragged_workload(n, n, d, B, 40, 8, m, 3)
     filters = []
@@ -282,6 +285,7 @@ def _extreme_scales(w, kind):
 @pytest.mark.parametrize("form,n,d,B,groups,vocab,plan", [
     ("own, seed", 300_000, 64, 128, 128, 40, dict(mfma_groups=0, seed_pass=1)),
     ("own", 400_000, 256, 160, 160, 40, dict(mfma_groups=0, seed_pass=0)),
+    ("own, one block", 300_000, 96, 32, 32, 40, dict(mfma_groups=0, seed_pass=1)),
     ("four", 300_000, 128, 64, 8, 12, dict(dot_groups=0, waves=4)),
     ("rows of 512", 400_000, 512, 140, 4, 12, dict(dot_groups=0, waves=8)),
     ("few", 600_000, 256, 250, 8, 60, dict(dot_groups=0, waves=8)),
