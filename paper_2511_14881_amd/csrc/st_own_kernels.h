@@ -18,8 +18,9 @@
 // queued with their 16 dot products, and the exact score, key and threshold test run where the queue is emptied.
 // The queries stay in LDS, padded by 16 bytes a row (an odd number of 16-byte pieces: no bank conflicts).
 // 10 M x 256 bytes, 256 queries with filters of their own (5 % each), K = 500: the level after the first takes
-// 1.09 ms, where gathering took 4.5 (1.26 with exact tests of all scores and two barriers to a segment); 778 k x 96
-// with 37 filter programs: 35.5 us (38).  Bound by round trips to LDS (operands, masks, queue: 55 % of a wavefront's
+// 1.09 ms in a long series of calls (1.15 to 1.4 in a run's first twelve), where gathering took 4.5 (1.26 with exact
+// tests of all scores and two barriers to a segment); 778 k x 96 with 37 filter programs: 36 us (38).  Bound by round
+// trips to LDS (operands, masks, queue: 55 % of a wavefront's
 // time) with two wavefronts to a SIMD; the products alone keep the matrix units busy a fifth of the time, the
 // rows of all items once are 0.5 ms of memory.
 //
