@@ -958,6 +958,17 @@ int64_t st_search_overflow_flags_offset(int64_t n_items, int32_t d, int32_t batc
     return (int64_t)st::make_layout(p, batch, K, d, n_tasks).ovf;
 }
 
+// Whether a batch may take the scan for filters of their own (one task, no weights; with fewer than 16 queries more
+// than half of the products would be padding), and whether a level may.
+static bool own_takes(int32_t n_tasks, bool weighted, size_t n_queries, int32_t d, int32_t m_bits, size_t n_rows)
+{
+    return n_tasks == 1 && !weighted && n_queries >= 16 && m_bits <= st::kOwnRows && n_rows <= (size_t)st::kOwnRowRefs && st::own_kernel(d) != nullptr;
+}
+static bool own_takes_level(const st::Level& l)
+{
+    return l.end - l.begin >= st::kOwnMinItems && l.begin % st::kOwnSeg == 0 && st::level_takes_segments(l, st::kOwnSeg);
+}
+
 static int32_t plan_groups_per_row(int32_t q_split) { return st::scan_groups() / std::max(q_split, 1); }
 
 // The filter programs of an expression search: one launch evaluates every distinct one into its row of the
@@ -1417,11 +1428,7 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
     bool mfma_started = false;  // the first MFMA launch builds the resident-query image
     // Batches that hardly share filters: from the second level on all pairs are multiplied, see st_own_kernels.h.
-    // (One task, no weights; with fewer than 16 queries more than half of the products would be padding.)
-    const auto own_scan = g_scoring_path == 0 && n_tasks == 1 && !weighted && set_dot.q_list.size() >= 16 && sp_d.m_bits <= st::kOwnRows &&
-                                  set_dot.rows.size() <= (size_t)st::kOwnRowRefs
-                              ? st::own_kernel(d, set_dot.q_list.size())
-                              : nullptr;
+    const auto own_scan = g_scoring_path == 0 && own_takes(n_tasks, weighted, set_dot.q_list.size(), d, sp_d.m_bits, set_dot.rows.size()) ? st::own_kernel(d) : nullptr;
     for (int lv = 0; lv < plan.n_levels; ++lv) {
         const st::Level& L_ = plan.level[lv];
         se.first = lv == 0 || (lv == 1 && plan.level[0].seed);  // no candidate list from before
@@ -1470,23 +1477,23 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
             TimedLaunch t(0, stream);
             ST_HIP(st::launch_scan_mfma(sp_m, mp, gx, stream));
         }
-        if (set_dot.n && own_scan && lv > 0 && L_.end - L_.begin >= st::kOwnMinItems && L_.begin % st::kOwnSeg == 0 &&
-            st::level_takes_segments(L_, st::kOwnSeg)) {
+        if (set_dot.n && own_scan && lv > 0 && own_takes_level(L_)) {
             st::ScanParams sp_o = sp_d;
             const int64_t n_own = (L_.end - L_.begin + st::kOwnSeg - 1) / st::kOwnSeg;
             sp_o.seg_items = st::kOwnSeg;
             sp_o.seg_per_visit = (int32_t)std::max<int64_t>(1, std::min<int64_t>(4, n_own / plan.groups));
+            static_assert(st::kScanGroups <= st::kOwnSlots * st::kComputeUnits, "a workgroup counts for that many regions");
             const size_t lds = st::own_lds_bytes((int)set_dot.q_list.size(), d, sp_o.m_bits);
-            static std::atomic<bool> lds_set[2][9] = {};  // (setting the attribute twice is harmless)
-            auto& set = lds_set[st::own_one_block(d, set_dot.q_list.size())][d / 32];
+            static std::atomic<bool> lds_set[9] = {};  // (setting the attribute twice is harmless)
+            auto& set = lds_set[d / 32];
             if (!set.load(std::memory_order_acquire)) {
                 ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(own_scan), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            160 * 1024));
                 set.store(true, std::memory_order_release);
             }
             TimedLaunch t(0, stream);
-            hipLaunchKernelGGL(own_scan, dim3(std::min(plan.groups, st::kComputeUnits), (set_dot.q_list.size() + st::kOwnCols - 1) / st::kOwnCols),
-                               dim3(st::kOwnThreads), lds, stream, sp_o, (int)set_dot.rows.size());
+            hipLaunchKernelGGL(own_scan, dim3(std::min(plan.groups, st::kComputeUnits), st::own_grid_rows((int)set_dot.q_list.size())),
+                               dim3(st::kOwnThreads), lds, stream, sp_o);
             ST_HIP(hipGetLastError());
         } else if (set_dot.n && own_scan && lv == 0 && L_.end > L_.begin && plan.cap == 64 && plan.groups % (st::kOwnThreads / 64) == 0) {
             // the first level: 64 consecutive items to a region, every passing pair is admitted

@@ -4,38 +4,30 @@
 // filters that pass 5 % each, 2 G 16-byte gathers, 64 cache lines to an instruction.  Here a wavefront holds
 // the rows of 64 items in registers and multiplies them with all queries by MFMA, whether a filter
 // passes them or not; the filters decide which scores count.  That costs the same for every selectivity, so a
-// wavefront whose filters pass few pairs (own_pairs) gathers after all, and one that did so requests the next
-// items' rows only when their masks are known.
+// wavefront whose filters pass few pairs gathers after all.
 //
-// Eight wavefronts take a segment of 512 items, 64 items each; up to the reports of a region they share the queries
-// and the tables in LDS and nothing else, so that one forms masks or waits for rows while another multiplies.  A wavefront's
-// words of the index (the rows that some filter names, m <= kOwnRows) come to LDS with loads requested a segment
-// ahead, and its mask words of all filters are formed there (a filter's rows fetched one by one from memory took
-// longer than the products).  A mask word is what it needs for one query: lane l of the product's result holds query l % 32,
-// and 16 of its items.  The items go in two halves of 32; the first half of the next ones is requested behind the
-// products of the first half, into the same registers.  A pair is tested by one multiply-add (the item's scale in fixed point,
-// the query's bound) whose sign goes to the bit of the pair's item; lanes with a bit left under the mask are
-// queued with their 16 dot products, and the exact score, key and threshold test run where the queue is emptied.
-// The queries stay in LDS, padded by 16 bytes a row (an odd number of 16-byte pieces: no bank conflicts).
-// 10 M x 256 bytes, 256 queries with filters of their own (5 % each), K = 500: the level after the first takes
-// 1.09 ms in a long series of calls (1.15 to 1.4 in a run's first twelve), where gathering took 4.5 (1.26 with exact
-// tests of all scores and two barriers to a segment); 778 k x 96 with 37 filter programs: 36 us (38).  Bound by round
-// trips to LDS (operands, masks, queue: 55 % of a wavefront's
-// time) with two wavefronts to a SIMD; the products alone keep the matrix units busy a fifth of the time, the
-// rows of all items once are 0.5 ms of memory.
+// Eight wavefronts share the queries and the tables in LDS and nothing else between set-up and report: each draws
+// units of 64 items from a counter, so that one forms masks or waits for rows while another multiplies.  A unit's
+// words of the index (the rows that some filter names, m <= kOwnRows) come to LDS with loads requested a unit
+// ahead, and the mask words of all filters are formed there (a filter's rows fetched one by one from memory took
+// longer than the products).  A mask word is what the unit needs for one query: lane l of a product's result holds query l % 32,
+// and 16 items of each of the two halves of 32.  The bound is part of the product (the slices of st_bound.h), so that the
+// signs of the results are the tests: one instruction to a pair takes them to the bits of its item, where the
+// mask word is.  Pairs left are queued with their results; dot product, exact score, key and
+// threshold test follow where the queue is emptied, 64 pairs at a time.  A block's operands are read while the results of the one
+// before are tested, and an operand serves both halves.
+// The queries lie in LDS with 16 bytes of padding a row (an odd number of 16-byte pieces: no bank conflicts).
 //
-// It takes the place of the gathering scan whatever the filters pass, which the host cannot know.  Calls on 3 M
-// items, m = 512, K = 100, every query with a filter of its own, gathering -> this scan, in us (d = 256 unless
-// said; with rows requested and all index rows staged before the masks were known, 16 queries took 280 to 300 throughout):
-//   queries   0.05 % pass   0.2 %        1 %          5 %          the broadest (3 to 16 %)
-//     16      112 -> 107    155 -> 122   161 -> 124   216 -> 186   410 -> 225
-//     64      244 -> 124    353 -> 129   464 -> 182   527 -> 253   734 -> 269
-//    256      909 -> 341   1458 -> 401  1909 -> 620  2127 -> 733  2222 -> 747
-//     16, 64 bytes  99 -> 88   129 -> 95   128 -> 88   131 -> 103   200 -> 130
-// (with two barriers to a segment and the first level gathered; without them and with scan_own_first_kernel, 256 queries,
-// same card: 349 -> 272, 396 -> 300, 621 -> 427, 711 -> 496, 700 -> 485)
-// one filter for 64 queries, 10 M x 192: 447 -> 176 at 0.02 %, 807 -> 339 at 0.5 %, 825 -> 543 at 5 %; behind cluster probing
-// (600 of 4096 clusters, 3 M x 128, 32 queries) 326 -> 243.
+// 10 M x 256 bytes, 213 queries with filters of their own (5 % each), K = 500: the level after the first takes 0.68 ms,
+// 1.04 with a multiply-add for every pair, operands read for each half, an exact test per lane of 16 results and
+// segments of 512 items tied to a workgroup; gathering took 4.5.  A unit then takes a wavefront 21,500 cycles: 13,500 in products
+// and tests of seven blocks (4,200 is what the products alone need, and two wavefronts share the matrix unit), 4,000
+// in masks, 1,200 and 2,000 around the first and the last block.
+//
+// A unit whose filters pass few pairs hands them to a list that goes from unit to unit until 64 are there, and
+// whose rows come several lanes to a row (a lane to a row touches 64 lines with every load: 10,000 cycles to a round at
+// d = 256, 3,500 so).  Calls on 3 M x 256, 64 queries that pass 0.5 %: 125 -> 99 us.  It takes the place of the gathering scan whatever
+// the filters pass, which the host cannot know.
 #pragma once
 #include "st_search_kernels.h"
 
@@ -44,29 +36,31 @@ namespace st {
 constexpr int kOwnThreads = 512;
 constexpr int kOwnSeg = 512;            // items of a segment
 constexpr int kOwnWords = kOwnSeg / 64; // one mask word per wavefront
-constexpr int kOwnBlock = 32;           // queries of one product
-constexpr int kOwnCols = 256;           // queries resident at a time (one row of the grid)
+constexpr int kOwnCols = 256;           // queries resident at a time (one row of the grid), at most
 constexpr int kOwnRows = 512;           // signature rows of the index, at most
 // Items of a level, at least: two segments to each of the workgroups that are resident.  (Whether the candidate
 // regions have room for segments of this size is the plan's to say: level_takes_segments.)
 constexpr int64_t kOwnMinItems = 512 * kOwnSeg;
 constexpr int kOwnAllRows = 64;         // an index of no more rows is staged whole
-constexpr int kOwnQueue = 16;           // lanes of a wavefront that wait for the exact test
+constexpr int kOwnQueue = 64;           // pairs of a wavefront that wait for the exact test
+constexpr int kOwnSlots = 4;            // regions of a workgroup, at most (the host launches that many workgroups)
 constexpr int kOwnRowRefs = 6144;       // rows all filters name together, at most
 static_assert(kOwnWords == kOwnThreads / 64, "a word per wavefront");
 
-constexpr int own_cols(int n_q) { return n_q < kOwnCols ? (n_q + 31) / 32 * 32 : kOwnCols; }
+constexpr int own_row_bytes(int d) { return d + kSliceBytes + 16; }  // of a query in LDS
+constexpr int own_grid_rows(int n_q) { return (n_q + kOwnCols - 1) / kOwnCols; }
+constexpr int own_cols(int n_q) { return ((n_q + own_grid_rows(n_q) - 1) / own_grid_rows(n_q) + 31) / 32 * 32; }  // of each row
 // A wavefront whose filters pass no more pairs than this of its 64 items gathers the pairs' rows instead of
-// multiplying all: 64 gathered rows of d bytes keep the load path busy for 64 * d / 16 cycles, the product with its
-// tests for 64 items x 256 queries about 12,000 cycles of one of four matrix units (d = 256); and 64 pairs or fewer
-// name no more rows than the product would read.
-constexpr int own_pairs(int cols) { return cols < 64 ? 64 : cols; }
+// multiplying all; one that multiplies has the next rows already, and goes on down to fewer pairs.  (Leaving at 64 too: 2.3 M x
+// 192, 41 queries at 2 %, units on either side of the line: 121 us, 129 so, 133 before; but 2 M x 64, 17 at 10 %: 86 and 82.  Entering at 16 or 32
+// with up to 64 queries: 3 M x 256, 64 at 0.5 %: 100 -> 200.)
+constexpr int kOwnFew = 64, kOwnStay = 32;
+// (a filter's rows take whole multiples of four entries: three more to a filter of the resident queries, at most)
 constexpr size_t own_lds_bytes(int n_q, int d, int m_bits)
 {
     const size_t c = own_cols(n_q);
-    return c * (d + 16) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnRowRefs * 2 + c * (8 + 4 * 7) +
-           own_pairs((int)c) * (kOwnThreads / 64) * 2 + kOwnRows * 2 + kOwnRows / 8 +
-           (size_t)kOwnWords * (64 * 4 + kOwnQueue * (16 * 4 + 8));
+    return c * own_row_bytes(d) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnWords * kOwnQueue * 16 + c * 8 +
+           (kOwnRowRefs + c * 3 + 10) / 8 * 16 + 64 + c * (4 * (2 + kOwnSlots) + 2 * 3) + kOwnRows * 2 + kOwnRows / 8;
 }
 static_assert(own_lds_bytes(kOwnCols, 256, kOwnRows) <= 160 * 1024, "LDS of a compute unit");
 
@@ -81,415 +75,482 @@ __device__ inline void own_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// d = 32 * KS.  Grid (workgroups, ceil(queries / kOwnCols)); segments start at multiples of 512 items.  One
+// d = 32 * KS.  Grid (workgroups, own_grid_rows(queries)); segments start at multiples of 512 items.  One
 // workgroup to a compute unit is resident (registers), so that many are launched and each takes several
 // regions in turn: the queries and tables are brought to LDS once.
-// ONE: at most kOwnBlock queries.
-template <int KS, bool ONE>
-__global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p, int n_refs)
+template <int KS>
+__global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char own_lds[];
-    constexpr int D = 32 * KS, DP = D + 16;
-    constexpr int P = KS <= 2 ? 10 : (KS <= 4 ? 9 : 8);   // bits of a scale in fixed point: |dot| <= 2^14 d, the product at most 2^30
-    constexpr int kPass = (1 << 30) - 1, kNever = -(1 << 30) - 1;  // bounds that every pair reaches, and none
+    constexpr int D = 32 * KS, DP = own_row_bytes(D);
     const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6), half = lane >> 5;
     const int n_q = p.grp_q_off[p.n_groups];
-    const int cols = own_cols(n_q), c0 = (int)blockIdx.y * kOwnCols, n_c = min(n_q - c0, cols);
+    const int cols = own_cols(n_q), c0 = (int)blockIdx.y * cols, n_c = min(n_q - c0, cols);
+    const int n_blk = (n_c + 31) & ~31;  // (of these columns the last row of the grid may have fewer)
     unsigned char* at = own_lds;
-    int8_t* s_q = reinterpret_cast<int8_t*>(at);                  at += (size_t)cols * DP;          // [cols][DP]
+    int8_t* s_q = reinterpret_cast<int8_t*>(at);                  at += (size_t)cols * DP;          // [cols][DP] rows and their slices
     uint64_t* s_mask = reinterpret_cast<uint64_t*>(at) + (size_t)wv * cols;      at += (size_t)cols * kOwnWords * 8;
     uint64_t* s_idx = reinterpret_cast<uint64_t*>(at) + (size_t)wv * p.m_bits;   at += (size_t)p.m_bits * kOwnWords * 8;
+    int4* queue = reinterpret_cast<int4*>(at) + (size_t)wv * kOwnQueue;  at += (size_t)kOwnWords * kOwnQueue * 16;
+    uint2* s_pairs = reinterpret_cast<uint2*>(queue);             // of a wavefront that gathers
+    static_assert(2 * kOwnFew * sizeof(uint2) <= kOwnQueue * sizeof(int4), "the pairs lie where the queue does");
     uint64_t* s_tau = reinterpret_cast<uint64_t*>(at);            at += (size_t)cols * 8;
+    uint16_t* s_refs = reinterpret_cast<uint16_t*>(at);           at += (size_t)(kOwnRowRefs + cols * 3 + 10) / 8 * 16;
+    uint32_t* s_max = reinterpret_cast<uint32_t*>(at);            at += 64;  // [8] largest 1 / scale of a wavefront's sample; largest tau / s_q; first filter, last; no bound for some query; next unit
     float* s_sq = reinterpret_cast<float*>(at);                   at += (size_t)cols * 4;
     int32_t* s_query = reinterpret_cast<int32_t*>(at);            at += (size_t)cols * 4;
-    uint32_t* s_cnt = reinterpret_cast<uint32_t*>(at);            at += (size_t)cols * 4;
-    int32_t* s_r0 = reinterpret_cast<int32_t*>(at);               at += (size_t)cols * 4;
-    int32_t* s_rn = reinterpret_cast<int32_t*>(at);               at += (size_t)cols * 4;
-    const int few = own_pairs(cols);
-    uint16_t* s_pairs = reinterpret_cast<uint16_t*>(at) + (size_t)wv * few;  at += (size_t)few * (kOwnThreads / 64) * 2;
-    uint16_t* s_refs = reinterpret_cast<uint16_t*>(at);           at += (size_t)kOwnRowRefs * 2;
+    uint32_t* s_cnt = reinterpret_cast<uint32_t*>(at);            at += (size_t)cols * 4 * kOwnSlots;  // [slots][cols]
+    uint16_t* s_r0 = reinterpret_cast<uint16_t*>(at);             at += (size_t)cols * 2;
+    uint16_t* s_rn = reinterpret_cast<uint16_t*>(at);             at += (size_t)cols * 2;
+    uint16_t* s_u = reinterpret_cast<uint16_t*>(at);              at += (size_t)cols * 2;   // bounds as slices' numbers (kOwnNoBound: none)
     uint16_t* s_named = reinterpret_cast<uint16_t*>(at);          at += (size_t)kOwnRows * 2;
-    uint32_t* s_bits = reinterpret_cast<uint32_t*>(at);           at += kOwnRows / 8;               // [kOwnRows / 32]
-    uint32_t* q_val = reinterpret_cast<uint32_t*>(at) + (size_t)wv * kOwnQueue * 16;  at += (size_t)kOwnWords * kOwnQueue * 64;
-    uint2* q_code = reinterpret_cast<uint2*>(at) + (size_t)wv * kOwnQueue;  at += (size_t)kOwnWords * kOwnQueue * 8;
-    float* s_si = reinterpret_cast<float*>(at) + (size_t)wv * 64; at += (size_t)kOwnWords * 64 * 4;  // scales of the wavefront's items
-    int32_t* s_neg = reinterpret_cast<int32_t*>(at);              at += (size_t)cols * 4;  // bounds, for the largest exponent so far
-    float* s_tq = reinterpret_cast<float*>(at);                   // [cols] tau / s_q (see bound_quotient)
+    uint32_t* s_bits = reinterpret_cast<uint32_t*>(at);           // [kOwnRows / 32]
+    constexpr int kNoBound = 0xFFFF;
+    static_assert(kSliceTop < kNoBound, "a query's number in 16 bits");
 
+    // ---- set-up: the queries, their thresholds, the filters' rows; and a sample of the scales, spread over the level.
+    // All chains of loads are begun before the first one is waited for (0.36 M x 96, 16 queries: the call 41.2 -> 40.3 us).
     if (tid < kOwnRows / 32) s_bits[tid] = 0;
-    for (int c = tid; c < cols; c += kOwnThreads) {
-        const int q = c < n_c ? p.grp_q[c0 + c] : -1;
-        uint64_t t = ~0ULL;
-        if (q >= 0)
-            for (int pp = 0; pp < p.tau_parts; ++pp) t = min(t, p.tau[(int64_t)q * kTauParts + pp]);
-        s_query[c] = q;
-        s_tau[c] = t;
-        const float sq = q >= 0 ? p.qscale[q] : 0.0f;
-        s_sq[c] = sq;
-        s_tq[c] = t ? bound_quotient(key_score(t), sq) : -__builtin_inff();
-        s_cnt[c] = 0;
-        s_neg[c] = kNever;
+    if (tid < 4) s_refs[tid] = 0;  // (columns without rows read these)
+    if (tid == 0) {
+        s_max[8] = 0;
+        s_max[9] = (uint32_t)p.n_groups;
+        s_max[10] = s_max[11] = 0;
+        s_max[12] = kOwnWords;
     }
-    for (int g = tid; g < p.n_groups; g += kOwnThreads) {
-        const int r0 = p.grp_row_off[g], rn = p.grp_row_off[g + 1] - r0;
+    own_barrier();  // (s_max, s_bits)
+    // Units of 64 items: the words of the segments of this workgroup's regions, drawn by the wavefronts from a counter in
+    // LDS (tied to a segment, or to a region at a time, they waited a sixth to a half of the time for the slowest of them).
+    const int spv = p.seg_per_visit;
+    const int n_seg = (int)((p.item_end - p.item_begin + kOwnSeg - 1) / kOwnSeg), n_visit = (n_seg + spv - 1) / spv;
+    const int slots = (p.groups - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
+    const int n_units = (n_visit + p.groups - 1) / p.groups * slots * spv * kOwnWords;
+    const int64_t item_lim = p.item_end < p.n_items ? p.item_end : p.n_items;
+    // (first item and region slot of a unit; the last round of visits does not reach all regions, nor the last segment all words: negative)
+    const uint32_t per_spv = 0xFFFFFFFFu / (uint32_t)spv + 1u, per_slots = 0xFFFFFFFFu / (uint32_t)slots + 1u;  // (0 for 1)
+    auto unit_at = [&](int unit, int& slot) -> int64_t {
+        const int t = unit / kOwnWords, i = spv == 1 ? t : (int)__umulhi((uint32_t)t, per_spv);  // (divisors up to four, below 2^29)
+        const int round = slots == 1 ? i : (int)__umulhi((uint32_t)i, per_slots);
+        slot = i - round * slots;
+        const int visit = (int)blockIdx.x + slot * (int)gridDim.x + round * p.groups, seg = visit * spv + (t - i * spv);
+        const int64_t first = p.item_begin + (int64_t)seg * kOwnSeg + (unit & (kOwnWords - 1)) * 64;
+        return first < item_lim ? first : -1;
+    };
+    const bool short_unit = cols <= 64;  // (a unit takes hardly longer than its index words: they are requested as early as can be)
+    int unit = wv, slot = 0, next_slot = 0;
+    int64_t my0 = -1, next0 = -1;
+    auto draw = [&]() __attribute__((always_inline)) {
+        uint32_t drawn = 0;
+        if (lane == 0) drawn = atomicAdd(&s_max[12], 1u);
+        unit = __builtin_amdgcn_readfirstlane((int)drawn);
+    };
+    auto settle = [&]() __attribute__((always_inline)) {  // the next unit that has items
+        next0 = -1;
+        while (unit < n_units) {
+            next0 = unit_at(unit, next_slot);
+            if (next0 >= 0) break;
+            draw();
+        }
+    };
+    // This wavefront's item rows, 32 items to a half (past the end the last row is repeated: no mask names it), and the
+    // scale of item `lane`.  If the wavefront multiplied its last items, the next ones are requested behind the
+    // products of the last block of queries, into the same registers, before the masks are known.  Otherwise they are requested behind
+    // the masks: where the filters pass little they are never read.
+    own_i4 a[2][KS];
+    float si = 0.0f;
+    auto rows = [&](int64_t my0) __attribute__((always_inline)) {
+        si = p.iscale[my0 + (uint32_t)min(lane, (int)min(p.n_items - 1 - my0, (int64_t)63))];
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            // (offsets within the 64 rows: the base is the same for all lanes)
+            const int it = min(s * 32 + (lane & 31), (int)min(p.n_items - 1 - my0, (int64_t)63));
+            const own_i4* row = reinterpret_cast<const own_i4*>(p.items + my0 * D + (uint32_t)(it * D + half * 16));
+#pragma unroll
+            for (int k = 0; k < KS; ++k) a[s][k] = row[2 * k];
+        }
+    };
+    settle();
+    my0 = next0;
+    slot = next_slot;
+    const int64_t span = min(p.item_end, p.n_items) - p.item_begin;
+    const float sample = p.iscale[p.item_begin + span * tid / kOwnThreads];
+    constexpr int kPieces = kOwnCols * (D / 16) / kOwnThreads;  // of 16 bytes to a thread
+    static_assert(kOwnCols * (D / 16) % kOwnThreads == 0, "the same number to every thread");
+    int4 piece[kPieces];
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+        const int i = tid + u * kOwnThreads, c = i / (D / 16), x = i - c * (D / 16);
+        piece[u] = make_int4(0, 0, 0, 0);
+        if (c < n_c) piece[u] = reinterpret_cast<const int4*>(p.queries + (int64_t)p.grp_q[c0 + c] * D)[x];
+    }
+    float tq = -__builtin_inff();  // tau / s_q of column tid (kOwnCols columns, at most)
+    int own_q = -1;
+    static_assert(kOwnCols <= kOwnThreads, "a column per thread");
+    if (tid < cols) {
+        own_q = tid < n_c ? p.grp_q[c0 + tid] : -1;
+        uint64_t t = ~0ULL;
+        if (own_q >= 0)
+            for (int pp = 0; pp < p.tau_parts; ++pp) t = min(t, p.tau[(int64_t)own_q * kTauParts + pp]);
+        s_query[tid] = own_q;
+        s_tau[tid] = t;
+        const float sq = own_q >= 0 ? p.qscale[own_q] : 0.0f;
+        s_sq[tid] = sq;
+#pragma unroll
+        for (int k = 0; k < kOwnSlots; ++k) s_cnt[k * cols + tid] = 0;
+        if (own_q >= 0 && t) tq = bound_quotient(key_score(t), sq);
+        if (tq > 0.0f) atomicMax(&s_max[8], __float_as_uint(tq));
+    }
+    // The filters of these queries: their rows lie one filter behind the other, each from a multiple of four on and
+    // filled up to one with its last row.  (A filter to a thread, from the last thread on: the first ones have the columns.)
+    int g0 = 0, g1 = p.n_groups;
+    if (n_q > kOwnCols) {  // (filters in front and behind have no query here)
+        for (int g = tid; g < p.n_groups; g += kOwnThreads)
+            if (p.grp_q_off[g + 1] > c0 && p.grp_q_off[g] < c0 + n_c) {
+                atomicMin(&s_max[9], (uint32_t)g);
+                atomicMax(&s_max[10], (uint32_t)g + 1u);
+            }
+        own_barrier();
+        g0 = (int)s_max[9];
+        g1 = (int)s_max[10];
+    }
+    const int ref0 = p.grp_row_off[g0];
+    auto refs_at = [&](int g) { return (p.grp_row_off[g] - ref0 + 3 * (g - g0) + 3) & ~3; };
+    const bool all_rows = p.m_bits <= kOwnAllRows;
+    for (int g = g0 + kOwnThreads - 1 - tid; g < g1; g += kOwnThreads) {
+        const int r0 = p.grp_row_off[g], rn = p.grp_row_off[g + 1] - r0, to = refs_at(g);
+        for (int r = 0; r < rn; r += 8) {
+            int row[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) row[u] = p.grp_rows[r0 + min(r + u, rn - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (r + u < ((rn + 3) & ~3)) {
+                    s_refs[to + r + u] = (uint16_t)row[u];
+                    if (!all_rows) atomicOr(&s_bits[row[u] >> 5], 1u << (row[u] & 31));
+                }
+        }
         for (int i = p.grp_q_off[g]; i < p.grp_q_off[g + 1]; ++i)
             if (i >= c0 && i < c0 + n_c) {
-                s_r0[i - c0] = r0;
-                s_rn[i - c0] = rn;
+                s_r0[i - c0] = (uint16_t)to;
+                s_rn[i - c0] = (uint16_t)rn;
             }
     }
-    for (int i = tid; i < cols * (D / 16); i += kOwnThreads) {
-        const int c = i / (D / 16), x = i - c * (D / 16);
-        int4 v = make_int4(0, 0, 0, 0);
-        if (c < n_c) v = reinterpret_cast<const int4*>(p.queries + (int64_t)p.grp_q[c0 + c] * D)[x];
-        *reinterpret_cast<int4*>(s_q + (size_t)c * DP + x * 16) = v;
+#pragma unroll
+    for (int u = 0; u < kPieces; ++u) {
+        const int i = tid + u * kOwnThreads, c = i / (D / 16), x = i - c * (D / 16);
+        if (c < cols) *reinterpret_cast<int4*>(s_q + (size_t)c * DP + x * 16) = piece[u];
     }
-
+    // (1 / scale of what is positive and of ordinary size, as a bit pattern: these order as the numbers do)
+    const float inv_sample = sample > 0x1p-90f && sample < 0x1p90f ? __builtin_amdgcn_rcpf(sample) : 0.0f;
+    const uint32_t top = wave_max_u32(__float_as_uint(inv_sample));
+    if (lane == 63) s_max[wv] = top;
+    // The bounds, and the slices behind the queries' rows.
+    own_barrier();
+    uint32_t inv_top = 0xFFFFFFFFu;  // the smallest of the wavefronts' largest ones: a few odd scales do not count
+#pragma unroll
+    for (int w = 0; w < 8; ++w) inv_top = min(inv_top, s_max[w] ? s_max[w] : 0xFFFFFFFFu);
+    const float ref = slice_ref(inv_top != 0xFFFFFFFFu ? __uint_as_float(inv_top) : 0.0f, __uint_as_float(s_max[8]));
+    const float factor = slice_factor(ref);
+    if (tid < cols) {
+        const int u = tq > 0.0f ? slice_query(tq, ref) : 0;
+        const bool none = own_q >= 0 && !(tq > 0.0f);
+        s_u[tid] = (uint16_t)(none ? kNoBound : u);
+        if (none) s_max[11] = 1;
+#pragma unroll
+        for (int w = 0; w < kSliceBytes / 16; ++w)
+            *reinterpret_cast<int4*>(s_q + (size_t)tid * DP + D + 16 * w) =
+                make_int4(slice_query_word(u, 4 * w), slice_query_word(u, 4 * w + 1), slice_query_word(u, 4 * w + 2), slice_query_word(u, 4 * w + 3));
+    }
     // The signature rows that some filter names, numbered in order: only these are staged.  (A small index is staged
     // whole: reading the names first holds up the first segment, 2.5 us of 39 with 8 rows.)
     static_assert(kOwnRows == kOwnThreads, "a row per thread");
     int n_named = p.m_bits;
-    if (p.m_bits <= kOwnAllRows) {
-        for (int i = tid; i < n_refs; i += kOwnThreads) s_refs[i] = (uint16_t)p.grp_rows[i];
-    } else {
-        own_barrier();
-        for (int i = tid; i < n_refs; i += kOwnThreads) {
-            const int r = p.grp_rows[i];
-            s_refs[i] = (uint16_t)r;
-            atomicOr(&s_bits[r >> 5], 1u << (r & 31));
+    if (!all_rows) {
+        // (lane w: named rows in front of the 32 of word w)
+        const uint32_t of_word = lane < kOwnRows / 32 ? (uint32_t)__popc(s_bits[lane]) : 0u, upto = wave_scan_add(of_word), front = upto - of_word;
+        auto named_before = [&](int r) { return (int)__shfl(front, r >> 5) + __popc(s_bits[r >> 5] & ((1u << (r & 31)) - 1u)); };
+        const int of_mine = named_before(tid);
+        if (s_bits[tid >> 5] >> (tid & 31) & 1) s_named[of_mine] = (uint16_t)tid;
+        const int refs = g1 > g0 ? refs_at(g1 - 1) + ((p.grp_row_off[g1] - p.grp_row_off[g1 - 1] + 3) & ~3) : 0;
+        for (int i0 = 0; i0 < refs; i0 += kOwnThreads) {  // (all lanes take part in the exchange)
+            const int i = min(i0 + tid, refs - 1), no = named_before(s_refs[i] & (kOwnRows - 1));
+            if (i0 + tid < refs) s_refs[i] = (uint16_t)no;
         }
-        own_barrier();
-        uint32_t bits[kOwnRows / 32];
-#pragma unroll
-        for (int w = 0; w < kOwnRows / 32; ++w) bits[w] = s_bits[w];
-        auto named_before = [&](int r) {
-            int n = 0;
-#pragma unroll
-            for (int w = 0; w < kOwnRows / 32; ++w) {
-                const int below = min(max(r - 32 * w, 0), 32);
-                n += __popc(bits[w] & (uint32_t)((1ull << below) - 1ull));
-            }
-            return n;
-        };
-        if (s_bits[tid >> 5] >> (tid & 31) & 1) s_named[named_before(tid)] = (uint16_t)tid;
-        for (int i = tid; i < n_refs; i += kOwnThreads) s_refs[i] = (uint16_t)named_before(s_refs[i]);
-        n_named = named_before(kOwnRows);
+        n_named = (int)lane_value(upto, 63);
     }
-    own_barrier();  // the last one: from here on every wavefront works by itself, up to the reports
+    own_barrier();  // the last one: from here on every wavefront works by itself, up to the report
+    const bool open = __builtin_amdgcn_readfirstlane((int)s_max[11]) != 0;
 
-    const int64_t n_seg = (p.item_end - p.item_begin + kOwnSeg - 1) / kOwnSeg;
-    const int64_t n_visit = (n_seg + p.seg_per_visit - 1) / p.seg_per_visit;
-    const int64_t item_lim = p.item_end < p.n_items ? p.item_end : p.n_items;
-    // the segments of this workgroup: the visits of its regions, one region after the other
-    int region = blockIdx.x;
-    int64_t vs = region, seg = vs * p.seg_per_visit;
-    auto settle = [&]() __attribute__((always_inline)) {  // past the region's last visit: on to the next one that has some
-        while (vs >= n_visit && region < p.groups) {
-            region += gridDim.x;
-            vs = region;
-        }
-    };
-    auto advance = [&]() __attribute__((always_inline)) {
-        ++seg;
-        if (seg >= (vs + 1) * p.seg_per_visit || seg >= n_seg) {
-            vs += p.groups;
-            settle();
-            seg = vs * p.seg_per_visit;
-        }
-    };
-    // fill counts of a finished region (and of the ones without a visit behind it)
-    auto report = [&](int from, int to) {
-        __syncthreads();
-        for (int c = tid; c < n_c; c += kOwnThreads) {
-            const int q = s_query[c];
-            const uint32_t n = s_cnt[c];
-            p.cnt[(int64_t)q * p.groups + from] = n < (uint32_t)p.cap ? n : (uint32_t)p.cap;
-            if (n > (uint32_t)p.cap) p.ovf[q] = 1u;
-            s_cnt[c] = 0;
-            for (int r = from + (int)gridDim.x; r < to && r < p.groups; r += (int)gridDim.x) p.cnt[(int64_t)q * p.groups + r] = 0;
-        }
-        __syncthreads();
-    };
     // index words of the wavefront's 64 items: one to a named row
-    constexpr int kIdx = kOwnRows / 64;
+    constexpr int kIdx = KS < 8 ? kOwnRows / 64 : 4;  // (those of rows beyond are read when they are needed: registers)
     uint64_t idx[kIdx];
-    int idx_at[kIdx];
+    uint32_t idx_at[kIdx];  // bytes
 #pragma unroll
     for (int u = 0; u < kIdx; ++u) {
         const int x = max(min(lane + u * 64, n_named - 1), 0);  // (the last row again: an unconditional load)
-        idx_at[u] = (p.m_bits <= kOwnAllRows ? min(x, p.m_bits - 1) : n_named > 0 ? (int)s_named[x] : 0) * kTileWords;
+        idx_at[u] = (uint32_t)(all_rows ? min(x, p.m_bits - 1) : n_named > 0 ? (int)s_named[x] : 0) * (kTileWords * 8);
     }
-    auto fetch = [&](int64_t sg) __attribute__((always_inline)) {
-        const int64_t w0 = ((p.item_begin + sg * kOwnSeg) >> 6) + wv;
-        const uint64_t* src = p.bloom + (w0 >> 4) * (int64_t)p.m_bits * kTileWords + (w0 & 15);
+    auto fetch = [&](int64_t first) __attribute__((always_inline)) {
+        const int64_t w0 = first >> 6;
+        const char* src = reinterpret_cast<const char*>(p.bloom + (w0 >> 4) * (int64_t)p.m_bits * kTileWords + (w0 & 15));
+#pragma unroll
+        for (int u = 0; u < kIdx; ++u) idx[u] = u * 64 < n_named ? *reinterpret_cast<const uint64_t*>(src + idx_at[u]) : 0;
+    };
+    // the rows of this lane's columns: place of the first one, and of the last four from there
+    constexpr uint32_t kNoRows = 0x80000000u;  // an empty filter: all items pass
+    uint32_t my_refs[kOwnCols / 64];
+    int rn_max = 0;
+#pragma unroll
+    for (int u = 0; u < kOwnCols / 64; ++u) {
+        const int c = lane + u * 64, rn = c < n_c ? (s_rn[c] + 3) & ~3 : 0;
+        my_refs[u] = rn ? (uint32_t)s_r0[c] | (uint32_t)(rn - 4) << 16 : c < n_c ? kNoRows : 0u;
+        rn_max = max(rn_max, rn);
+    }
+    rn_max = (int)lane_value(wave_max_u32((uint32_t)rn_max), 63);
+    if (my0 >= 0) fetch(my0);
+    // Pairs that may be admissible: dot product less its bound, item, and column with region slot.  The exact test
+    // runs where the queue is emptied.
+    int qn = 0;
+    auto admit = [&](uint64_t key, int c, int sl_no) __attribute__((always_inline)) {
+        const uint32_t n = atomicAdd(&s_cnt[sl_no * cols + c], 1u);
+        if (n < (uint32_t)p.cap)
+            p.cand[((int64_t)s_query[c] * p.groups + (int)blockIdx.x + sl_no * (int)gridDim.x) * p.cap + n] = key;
+    };
+    auto drain = [&]() __attribute__((always_inline)) {
+        if (lane < qn) {
+            const int4 e = queue[lane];
+            const int c = e.z & 255, u16 = s_u[c];
+            const float s_i = p.iscale[(uint32_t)e.y];
+            const int dot = e.x + slice_bound(u16 == kNoBound ? 0 : u16, slice_item(__builtin_amdgcn_rcpf(s_i), factor));
+            const uint64_t key = make_key(rescale(dot, s_sq[c], s_i), (uint32_t)e.y);
+            if (key >= s_tau[c]) admit(key, c, e.z >> 8);
+        }
+        qn = 0;
+    };
+    // Pairs of a wavefront that gathers, from one unit after the other until there are enough: their rows, kGl lanes to a
+    // row, so that a load takes whole lines (a lane to a row takes four times as many), and the exact test.
+    int pn = 0;
+    auto gather = [&](int total) __attribute__((always_inline)) {
+        constexpr int kPer = D % 96 == 0 ? 3 : 1, kGl = D / 16 / kPer, kGp = 64 / kGl;  // (pieces of a row to a lane, lanes to a row, rows to a load)
+        const int piece = lane & (kGl - 1), in_load = lane / kGl;
+        for (int k0 = 0; k0 < total; k0 += 64) {
+            const int n = min(total - k0, 64);
+            // (the pair whose result this lane keeps)
+            const int my_pair = piece * kGp + in_load;
+            const uint2 mine = s_pairs[k0 + min(my_pair, n - 1)];
+            const float my_si = p.iscale[mine.x];
+            int4 v[kGl][kPer];
+#pragma unroll
+            for (int j = 0; j < kGl; ++j) {
+                const int4* row = reinterpret_cast<const int4*>(p.items + (int64_t)s_pairs[k0 + min(j * kGp + in_load, n - 1)].x * D) + piece;
+#pragma unroll
+                for (int t = 0; t < kPer; ++t) v[j][t] = row[t * kGl];
+            }
+            int my_dot = 0;
+#pragma unroll
+            for (int j = 0; j < kGl; ++j) {
+                const int c = (int)(s_pairs[k0 + min(j * kGp + in_load, n - 1)].y & 255u);
+                const int4* qr = reinterpret_cast<const int4*>(s_q + c * DP) + piece;
+                int dot = 0;
+#pragma unroll
+                for (int t = 0; t < kPer; ++t) dot = dot16(v[j][t], qr[t * kGl], dot);
+                dot += __builtin_amdgcn_update_dpp(0, dot, 0xB1, 0xF, 0xF, false);                // lanes 1, 0, 3, 2 of four
+                if (kGl > 2) dot += __builtin_amdgcn_update_dpp(0, dot, 0x4E, 0xF, 0xF, false);   // lanes 2, 3, 0, 1
+                if (kGl > 4) dot += __builtin_amdgcn_update_dpp(0, dot, 0x141, 0xF, 0xF, false);  // eight lanes mirrored
+                if (kGl > 8) dot += __builtin_amdgcn_update_dpp(0, dot, 0x140, 0xF, 0xF, false);  // sixteen
+                if (piece == j) my_dot = dot;
+            }
+            if (my_pair < n) {
+                const int c = (int)(mine.y & 255u);
+                const uint64_t key = make_key(rescale(my_dot, s_sq[c], my_si), mine.x);
+                if (key >= s_tau[c]) admit(key, c, (int)(mine.y >> 8));
+            }
+        }
+    };
+    // A unit's masks, of all filters: the words of four columns to a lane, so that a step's reads do not wait for each other.
+    // Also draws the next unit, and brings this one's index words to LDS.
+    uint64_t m[kOwnCols / 64];
+    uint32_t n_pass = 0, before = 0, total = 0;  // pairs that pass: this lane's, the lower lanes', all
+    auto masks = [&]() __attribute__((always_inline)) {
+        draw();
 #pragma unroll
         for (int u = 0; u < kIdx; ++u)
-            if (u * 64 < n_named) idx[u] = src[idx_at[u]];
-    };
-    // This wavefront's item rows (past the end the last row is repeated: no mask names it), 32 items to a half, and the
-    // scales of the items this lane holds results of.  If the wavefront multiplied its last items, the first half of the
-    // next ones is requested behind the products of the first half, into the same registers, and the second half
-    // at the top of the segment; both before the masks are known.  Otherwise they are requested behind the masks: where
-    // the filters pass little they are never read.
-    own_i4 a[2][KS];
-    float4 si[2][4];
-    bool have0 = false;
-    // (In two forms: whole words of items with vector loads of the scales, and any, for the words that are late.)
-    auto rows = [&](auto whole, int s, int64_t my0) __attribute__((always_inline)) {
-        constexpr bool kWhole = decltype(whole)::value;
-        int64_t it = my0 + s * 32 + (lane & 31);
-        if (!kWhole) it = min(it, p.n_items - 1);
-        const own_i4* row = reinterpret_cast<const own_i4*>(p.items + it * D) + half;
-#pragma unroll
-        for (int k = 0; k < KS; ++k) a[s][k] = row[2 * k];
-        int64_t it0 = my0 + 4 * half + s * 32;
-        if (!kWhole) asm volatile("" : "+v"(it0));  // (16 offsets, kept in registers all the time otherwise)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            if (kWhole) {
-                si[s][j] = *reinterpret_cast<const float4*>(p.iscale + it0 + j * 8);
-            } else {
-                float v[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = p.iscale[min(it0 + j * 8 + i, p.n_items - 1)];
-                si[s][j] = make_float4(v[0], v[1], v[2], v[3]);
-            }
+            if (lane + u * 64 < n_named) s_idx[lane + u * 64] = idx[u];
+        if (kIdx * 64 < kOwnRows && n_named > kIdx * 64) {
+            const uint64_t* src = p.bloom + (my0 >> 10) * (int64_t)p.m_bits * kTileWords + ((my0 >> 6) & 15);
+            for (int x = lane + kIdx * 64; x < n_named; x += 64) s_idx[x] = src[(int)s_named[x] * kTileWords];
         }
-    };
-    int cur_E = -1000;        // every scale that this wavefront's factors cover is below 2^cur_E (none yet)
-    float fix_scale = 0.0f;   // 2^(P - cur_E)
-    const int first_region = region;
-    settle();
-    seg = vs * p.seg_per_visit;
-    if (region < p.groups) {
-        fetch(seg);
-        const int64_t my0 = p.item_begin + seg * kOwnSeg + wv * 64;
-        have0 = my0 + 64 <= p.n_items;
-        if (have0) rows(std::true_type{}, 0, my0);
-    }
-    int filling = first_region;  // the region that the counters belong to
-    while (region < p.groups) {
-        if (region != filling) {
-            report(filling, region);
-            filling = region;
-        }
-        const int at_region = region;
-        const int64_t item0 = p.item_begin + seg * kOwnSeg, my0 = item0 + wv * 64;
-        auto stage = [&]() __attribute__((always_inline)) {
-#pragma unroll
-            for (int u = 0; u < kIdx; ++u)
-                if (lane + u * 64 < n_named) s_idx[lane + u * 64] = idx[u];
-        };
-        // (the index block is stored in either branch: behind one where the rows may or may not have been
-        // requested, the wait for the block is one for the rows as well)
-        const bool early = have0;  // this wavefront multiplied its last items, and the first half of these rows is requested
-        if (early) {
-            stage();
-            rows(std::true_type{}, 1, my0);
-        } else {
-            stage();
-        }
-        have0 = false;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        advance();
-        if (region < p.groups) fetch(seg);
+        settle();
+        if (next0 >= 0 && short_unit) fetch(next0);
         const int64_t left = item_lim - my0;
         const uint64_t all = left >= 64 ? ~0ULL : left > 0 ? ((1ULL << left) - 1ULL) : 0ULL;
-        uint32_t n_pass = 0;  // pairs that pass, over all queries
-        for (int c = lane; c < cols; c += 64) {
-            uint64_t m = 0;
-            if (c < n_c) {
-                m = all;
-                const uint16_t* refs = s_refs + s_r0[c];
-                const int rn = s_rn[c];
-                int r = 0;
-                for (; r + 4 <= rn; r += 4) {
-                    const uint64_t m0 = s_idx[refs[r]], m1 = s_idx[refs[r + 1]], m2 = s_idx[refs[r + 2]], m3 = s_idx[refs[r + 3]];
-                    m &= (m0 & m1) & (m2 & m3);
-                }
-                for (; r < rn; ++r) m &= s_idx[refs[r]];
-            }
-            s_mask[c] = m;
-            n_pass += (uint32_t)__popcll(m);
+#pragma unroll
+        for (int u = 0; u < kOwnCols / 64; ++u) m[u] = lane + u * 64 < n_c ? all : 0;
+        for (int r = 0; r < rn_max; r += 4) {
+            ushort4 f[kOwnCols / 64];
+#pragma unroll
+            for (int u = 0; u < kOwnCols / 64; ++u)
+                if (u * 64 < cols) f[u] = *reinterpret_cast<const ushort4*>(s_refs + (my_refs[u] & 0xFFFFu) + min(r, (int)(my_refs[u] >> 16 & 0x7FFFu)));
+#pragma unroll
+            for (int u = 0; u < kOwnCols / 64; ++u)
+                if (u * 64 < cols) m[u] &= (s_idx[f[u].x] & s_idx[f[u].y]) & (s_idx[f[u].z] & s_idx[f[u].w]);
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        n_pass = 0;
+#pragma unroll
+        for (int u = 0; u < kOwnCols / 64; ++u)
+            if (u * 64 < cols) {
+                if (my_refs[u] & kNoRows) m[u] = all;
+                n_pass += (uint32_t)__popcll(m[u]);
+            }
         const uint32_t incl = wave_scan_add(n_pass);
-        const uint32_t total = lane_value(incl, 63);
-        if (total <= (uint32_t)few) {
-            uint32_t pos = incl - n_pass;
-            for (int c = lane; c < cols; c += 64) {
-                uint64_t m = s_mask[c];
-                while (m) {
-                    const int bit = __ffsll((long long)m) - 1;
-                    m &= m - 1;
-                    s_pairs[pos++] = (uint16_t)((c << 6) | bit);
+        before = incl - n_pass;
+        total = lane_value(incl, 63);
+    };
+    // The loop has two parts, so that the rows in registers are none while a wavefront gathers.
+    if (my0 >= 0) masks();
+    while (my0 >= 0) {
+        if (total <= (uint32_t)kOwnFew) {
+            if (next0 >= 0 && !short_unit) fetch(next0);
+            if (qn > 0) drain();
+            uint32_t pos = (uint32_t)pn + before;
+#pragma unroll
+            for (int u = 0; u < kOwnCols / 64; ++u)
+                while (m[u]) {
+                    const int bit = __ffsll((long long)m[u]) - 1;
+                    m[u] &= m[u] - 1;
+                    s_pairs[pos++] = make_uint2((uint32_t)my0 + (uint32_t)bit, (uint32_t)(lane + u * 64) | (uint32_t)slot << 8);
                 }
-            }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-            for (uint32_t k = lane; k < total; k += 64) {
-                const int pr = s_pairs[k], c = pr >> 6;
-                const int64_t item = my0 + (pr & 63);
-                const int4* row = reinterpret_cast<const int4*>(p.items + item * D);
-                int4 v[D / 16];
-#pragma unroll
-                for (int x = 0; x < D / 16; ++x) v[x] = row[x];
-                const float s_i = p.iscale[item];
-                int acc = 0;
-#pragma unroll
-                for (int x = 0; x < D / 16; ++x) acc = dot16(v[x], *reinterpret_cast<const int4*>(s_q + (size_t)c * DP + x * 16), acc);
-                const uint64_t key = make_key(rescale(acc, s_sq[c], s_i), (uint32_t)item);
-                if (key >= s_tau[c]) {
-                    const uint32_t slot = atomicAdd(&s_cnt[c], 1u);
-                    if (slot < (uint32_t)p.cap) p.cand[((int64_t)s_query[c] * p.groups + at_region) * p.cap + slot] = key;
-                }
+            pn = __builtin_amdgcn_readfirstlane(pn + (int)total);
+            if (pn >= kOwnFew) {
+                gather(kOwnFew);
+                const uint2 rest = s_pairs[kOwnFew + lane];
+                pn -= kOwnFew;
+                if (lane < pn) s_pairs[lane] = rest;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
             }
+            my0 = next0;
+            slot = next_slot;
+            if (my0 >= 0) masks();
             continue;
         }
-        if (!early) {
-            rows(std::false_type{}, 0, my0);
-            rows(std::false_type{}, 1, my0);
+        if (pn > 0) {
+            gather(pn);
+            pn = 0;
         }
-        // Lanes in which an admission is possible, emptied four lanes to an entry: the exact test of their pairs.
-        int qn = 0;
-        auto drain = [&]() __attribute__((always_inline)) {
-            const int e = lane >> 2, h = lane & 3;
-            if (e < qn) {
-                const uint2 code = q_code[e];  // (admissible results, where the lane was: column, half, set)
-                const int4 v4 = reinterpret_cast<const int4*>(q_val + e * 16)[h];
-                const int c = (int)(code.y & 255u), bit0 = (int)(code.y >> 9) * 32 + 8 * h + 4 * (int)((code.y >> 8) & 1u);
-                const float4 si4 = *reinterpret_cast<const float4*>(s_si + bit0);
-                const float sq = s_sq[c];
-                const uint64_t tau = s_tau[c];
-                const int v[4] = {v4.x, v4.y, v4.z, v4.w};
-                const float sv[4] = {si4.x, si4.y, si4.z, si4.w};
+        rows(my0);
+        for (;;) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint64_t key = make_key(rescale(v[i], sq, sv[i]), (uint32_t)my0 + (uint32_t)(bit0 + i));
-                    if ((code.x >> (8 * h + i) & 1u) && key >= tau) {
-                        const uint32_t slot = atomicAdd(&s_cnt[c], 1u);
-                        if (slot < (uint32_t)p.cap) p.cand[((int64_t)s_query[c] * p.groups + at_region) * p.cap + slot] = key;
-                    }
-                }
+            for (int u = 0; u < kOwnCols / 64; ++u)
+                if (lane + u * 64 < cols) s_mask[lane + u * 64] = m[u];
+            // The scales, and the items' slices: half a slice to a lane, as the operand has it.
+            const bool odd = ballot(!(si >= 0.0f && si < 0x1p90f)) != 0;  // (outside the range that has bounds: all pairs of these items are tested exactly)
+            const int g = slice_item(__builtin_amdgcn_rcpf(si), factor);
+            own_i4 sl[2];
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                const int gs = __shfl(g, 32 * s + (lane & 31));
+                const int same = slice_item_word(gs, 0);
+                sl[s] = own_i4{same, same, same, half ? slice_item_word(gs, 7) : same};
             }
-            qn = 0;
-        };
-        auto next_rows = [&]() __attribute__((always_inline)) {
-            const int64_t next0 = p.item_begin + seg * kOwnSeg + wv * 64;  // (the segment advanced above)
-            have0 = region < p.groups && next0 + 64 <= p.n_items;
-            if (have0) rows(std::true_type{}, 0, next0);
-        };
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+            own_i4 q[KS + 1];  // a block's operands: the rows and slices of 32 queries
+            auto operands = [&](int b) __attribute__((always_inline)) {
+                const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)(b + (lane & 31)) * DP) + half;
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            // The scales: exact ones for the tests, and fixed-point factors against a power of two above the scales met
-            // so far.  A pair can only be admitted if dot * factor reaches its query's bound (rounded down by more than all
-            // roundings involved).
-            const float sv[16] = {si[s][0].x, si[s][0].y, si[s][0].z, si[s][0].w, si[s][1].x, si[s][1].y, si[s][1].z, si[s][1].w,
-                                  si[s][2].x, si[s][2].y, si[s][2].z, si[s][2].w, si[s][3].x, si[s][3].y, si[s][3].z, si[s][3].w};
-            if constexpr (ONE) {
-                // A single block: factors for 16 items cost more than the exact scores of its 16 pairs, and few lanes pass.
-                const int c = lane & 31;
-                own_i16 acc;
+                for (int k = 0; k <= KS; ++k) q[k] = qr[2 * k];
+            };
+            own_i16 acc[2];
+            auto products = [&]() __attribute__((always_inline)) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = 0;
-                const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)c * DP) + half;
+                for (int s = 0; s < 2; ++s)
 #pragma unroll
-                for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][k], qr[2 * k], acc, 0, 0, 0);
-                const float sq = s_sq[c];
-                const uint64_t tau = s_tau[c];
-                const float bound = tau ? key_score(tau) : -__builtin_inff();
-                uint32_t over = 0;  // (scores not below the threshold's, also where a NaN is involved: compared as keys)
+                    for (int i = 0; i < 16; ++i) acc[s][i] = 0;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) over |= !(rescale(acc[i], sq, sv[i]) < bound) ? 1u << (8 * (i >> 2) + (i & 3)) : 0u;
-                over &= (uint32_t)(s_mask[c] >> (32 * s)) >> (4 * half);
-                if (ballot(over != 0) != 0) {
-                    uint32_t it0 = (uint32_t)my0 + 32u * s + 4u * half;
-                    asm volatile("" : "+v"(it0));  // (16 ids to a half, kept in registers all the time otherwise)
+                for (int k = 0; k <= KS; ++k)
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) {
-                        const int bit = 8 * (i >> 2) + (i & 3);
-                        if (over >> bit & 1u) {
-                            const uint64_t key = make_key(rescale(acc[i], sq, sv[i]), it0 + bit);
-                            if (key >= tau) {
-                                const uint32_t slot = atomicAdd(&s_cnt[c], 1u);
-                                if (slot < (uint32_t)p.cap) p.cand[((int64_t)s_query[c] * p.groups + at_region) * p.cap + slot] = key;
-                            }
-                        }
-                    }
-                }
-                if (s == 0) next_rows();
-                continue;
-            }
-            if ((lane & 31) == 0) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) *reinterpret_cast<float4*>(s_si + 32 * s + 8 * j + 4 * half) = si[s][j];
-            }
-            uint32_t top = 0;  // (scales are positive, so their bit patterns order as they do; others switch the bound off)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) top = max(top, __float_as_uint(sv[i]));
-            const float smax = __uint_as_float(max(lane_value(top, 0), lane_value(top, 32)));
-            const bool cull = smax > 0x1p-90f && smax < 0x1p90f;
-            const int E = (int)(__float_as_uint(smax) >> 23) - 126;  // 2^E > smax
-            if (cull && E > cur_E) {  // (a handful of times to a launch; a bound for a larger exponent lets more pairs through)
-                cur_E = E;
-                fix_scale = __uint_as_float((uint32_t)(P - E + 127) << 23);
-                for (int c = lane; c < cols; c += 64) {
-                    const float tq = s_tq[c];
-                    int neg = kPass;
-                    if (tq > 0.0f)
-                        neg = -min(__float2int_rd(fminf(tq * (fix_scale * 0.99999618530273f), 1.2e9f)), (1 << 30) + 1);  // (1 - 2^-18)
-                    atomicMax(&s_neg[c], neg);
-                }
-            }
-            int fix[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) fix[i] = cull ? max(__float2int_ru(sv[i] * fix_scale), 1) : 0;
-            for (int b = 0; b < cols; b += 32) {
+                    for (int s = 0; s < 2; ++s) acc[s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(k < KS ? a[s][k < KS ? k : 0] : sl[s], q[k], acc[s], 0, 0, 0);
+            };
+            auto test = [&](int b, uint64_t word) __attribute__((always_inline)) {
                 const int c = b + (lane & 31);
-                const uint32_t word = (uint32_t)(s_mask[c] >> (32 * s)) >> (4 * half);
-                own_i16 acc;
+                uint32_t keep = ~0u;
+                if (open || odd) keep = odd || s_u[c] == kNoBound ? 0u : ~0u;
+                // result i is item 32 s + 8 (i / 4) + 4 half + i % 4; the signs go to the bits of the mask word
+                uint32_t below[2];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[i] = 0;
-                const own_i4* qr = reinterpret_cast<const own_i4*>(s_q + (size_t)c * DP) + half;
+                for (int s = 0; s < 2; ++s) {
+                    uint32_t part[4];
 #pragma unroll
-                for (int k = 0; k < KS; ++k) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][k], qr[2 * k], acc, 0, 0, 0);
-                const int neg = cull ? s_neg[c] : kPass;
-                // result i is item 32 s + 8 (i / 4) + 4 half + i % 4; the signs of the tests go to the bits of the mask word
-                uint32_t below = 0;
+                    for (int j = 0; j < 4; ++j) {
+                        part[j] = (uint32_t)acc[s][4 * j + 3] >> 31;
 #pragma unroll
-                for (int j = 3; j >= 0; --j) {
-                    if (j < 3) below <<= 4;
-#pragma unroll
-                    for (int i = 4 * j + 3; i >= 4 * j; --i)
-                        below = __builtin_amdgcn_alignbit(below, (uint32_t)(__mul24(acc[i], fix[i]) + neg), 31);
-                }
-                const uint32_t over = word & ~below & 0x0F0F0F0Fu;
-                const uint64_t hits = ballot(over != 0);
-                if (hits == 0) continue;
-                uint64_t m = hits;
-                for (;;) {  // (more lanes than the queue holds go in rounds)
-                    const int n = __popcll(m);
-                    if (qn > 0 && qn + n > kOwnQueue) drain();
-                    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-                    const bool mine = ((m >> lane) & 1ULL) && rank < kOwnQueue;
-                    if (mine) {
-                        int4* dst = reinterpret_cast<int4*>(q_val + (qn + rank) * 16);
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) dst[j] = make_int4(acc[4 * j], acc[4 * j + 1], acc[4 * j + 2], acc[4 * j + 3]);
-                        q_code[qn + rank] = make_uint2(over, (uint32_t)(c | (half << 8) | (s << 9)));
+                        for (int i = 2; i >= 0; --i) part[j] = __builtin_amdgcn_alignbit(part[j], (uint32_t)acc[s][4 * j + i], 31);
                     }
-                    if (n <= kOwnQueue) {
-                        qn = __builtin_amdgcn_readfirstlane(qn + n);
-                        break;
-                    }
-                    qn = kOwnQueue;
-                    m &= ~ballot(mine);
+                    below[s] = (part[3] << 24 | part[2] << 16) | (part[1] << 8 | part[0]);
                 }
+                // (the second half's bits in the gaps of the first one's)
+                const uint32_t pass = ((uint32_t)word >> (4 * half) & 0x0F0F0F0Fu) | ((uint32_t)(word >> 32) >> (4 * half) & 0x0F0F0F0Fu) << 4;
+                uint32_t over = pass & ~((below[0] | below[1] << 4) & keep);
+                uint64_t hits;
+                while ((hits = ballot(over != 0)) != 0) {  // (as a rule one pair to a lane)
+                    const int n = __popcll(hits);
+                    if (qn + n > kOwnQueue) drain();
+                    if (over != 0) {
+                        const int bit = __ffs((int)over) - 1;
+                        over &= over - 1;
+                        // (by masks: choices by a condition become an access indexed by the lane, in private memory)
+                        const int b0 = -(bit & 1), b1 = -(bit >> 1 & 1), b2 = -(bit >> 2 & 1), b3 = -(bit >> 3 & 1), b4 = -(bit >> 4 & 1);
+                        auto pick = [](int m, int x, int y) { return (x & m) | (y & ~m); };
+                        int v[16];
+#pragma unroll
+                        for (int i = 0; i < 16; ++i) v[i] = pick(b2, acc[1][i], acc[0][i]);
+#pragma unroll
+                        for (int i = 0; i < 8; ++i) v[i] = pick(b0, v[2 * i + 1], v[2 * i]);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) v[i] = pick(b1, v[2 * i + 1], v[2 * i]);
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) v[i] = pick(b3, v[2 * i + 1], v[2 * i]);
+                        const int at_item = (bit & 27) + 8 * (bit & 4) + 4 * half;
+                        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+                        queue[qn + rank] = make_int4(pick(b4, v[1], v[0]), (int)((uint32_t)my0 + (uint32_t)at_item), c | slot << 8, 0);
+                    }
+                    qn = __builtin_amdgcn_readfirstlane(qn + n);
+                }
+            };
+            // A block's operands are read behind the products of the one before, and tested while they come.  The next segment's
+            // index words are requested once the rows are there, and its rows behind the last block's products: a wait for
+            // what is older is none for them.
+            operands(0);
+            uint64_t word = s_mask[lane & 31];
+            products();
+            if (next0 >= 0 && !short_unit) fetch(next0);
+            for (int b = 32; b < n_blk; b += 32) {
+                operands(b);
+                const uint64_t next_word = s_mask[b + (lane & 31)];
+                test(b - 32, word);
+                word = next_word;
+                products();
             }
-            if (s == 0) next_rows();
+            rows(next0 >= 0 ? next0 : my0);  // (without a condition: one would turn the wait for the index words into one for the rows)
+            test(n_blk - 32, word);
+            my0 = next0;
+            slot = next_slot;
+            if (my0 < 0) break;
+            masks();
+            if (total <= (uint32_t)kOwnStay) break;
         }
-        if (qn > 0) drain();
     }
-    report(filling, p.groups);
+    if (qn > 0) drain();
+    if (pn > 0) gather(pn);
+    __syncthreads();
+    // fill counts of the workgroup's regions
+    for (int i = tid; i < n_c * slots; i += kOwnThreads) {
+        const int k = i / n_c, c = i - k * n_c, q = s_query[c];
+        const uint32_t n = s_cnt[k * cols + c];
+        p.cnt[(int64_t)q * p.groups + (int)blockIdx.x + k * (int)gridDim.x] = n < (uint32_t)p.cap ? n : (uint32_t)p.cap;
+        if (n > (uint32_t)p.cap) p.ovf[q] = 1u;
+    }
 }
 
 // The first level of such a search, which admits every passing pair: the same products, 64 items (a region) to a
@@ -602,20 +663,14 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_first_kernel(ScanParams 
 
 // The kernel for rows of d bytes, or null.  (One copy of the kernel to a length: the lengths the MFMA scan has, as far as
 // a workgroup's registers hold the rows of 64 items, and 96 and 192 between them; others go to the gathering scan.)
-// Up to kOwnBlock queries of rows up to 192 bytes take the form of one block.  Calls with integer bounds and the
-// queue -> with it, in us: 2 M x 64, 17 queries 95.8 -> 86.1; 5 M x 64, 24: 184 -> 169; 3.4 M x 96, 16: 144 -> 134;
-// 4 M x 128, 16: 177 -> 169; 1.5 M x 192, 32: 109.7 -> 106.9.  At 256 bytes its scores do not fit the registers
-// (1.5 M, 32 queries: 133 -> 137).
-constexpr bool own_one_block(int d, size_t n_q) { return n_q <= (size_t)kOwnBlock && d <= 192; }
-inline auto own_kernel(int d, size_t n_q) -> decltype(&scan_own_kernel<8, false>)
+inline auto own_kernel(int d) -> decltype(&scan_own_kernel<8>)
 {
-    const bool one = own_one_block(d, n_q);
     switch (d) {
-    case 64: return one ? &scan_own_kernel<2, true> : &scan_own_kernel<2, false>;
-    case 96: return one ? &scan_own_kernel<3, true> : &scan_own_kernel<3, false>;
-    case 128: return one ? &scan_own_kernel<4, true> : &scan_own_kernel<4, false>;
-    case 192: return one ? &scan_own_kernel<6, true> : &scan_own_kernel<6, false>;
-    case 256: return &scan_own_kernel<8, false>;
+    case 64: return &scan_own_kernel<2>;
+    case 96: return &scan_own_kernel<3>;
+    case 128: return &scan_own_kernel<4>;
+    case 192: return &scan_own_kernel<6>;
+    case 256: return &scan_own_kernel<8>;
     default: return nullptr;
     }
 }

@@ -23,7 +23,7 @@ static float score(int dot, float sq, float si)
     volatile float b = a * si;
     return b;
 }
-// dot * factor against the threshold's bound, the factor of P bits (scan_own, scan_tile, scan_mfma2)
+// dot * factor against the threshold's bound, the factor of P bits (scan_tile, scan_mfma2)
 static bool passes(int dot, float tq, float si, int E, int P)
 {
     const float fix = std::ldexp(1.0f, P - E);
@@ -94,3 +94,58 @@ def test_integer_bounds_never_cut_a_pair_that_reaches_the_threshold(tmp_path):
     ok, tested, bounded, cut = run.stdout.split()
     # ordinary scales keep their bound, and the bound does cut
     assert ok == "ok" and int(bounded) > 0.3 * int(tested) and int(cut) > 0.03 * int(tested), run.stdout
+
+
+_SLICES = r"""
+#include <cmath>
+#include <cstdint>
+#include <cstdio>
+#include <random>
+#include "st_bound.h"
+
+int main()
+{
+    std::mt19937_64 rng(7);
+    auto uni = [&](double a, double b) { return a + (b - a) * (double)(rng() >> 11) * 0x1p-53; };
+    // the words are the digits, and their products add up to the bound: 32 int8 products, as the matrix unit sums them
+    for (int it = 0; it < 200000; ++it) {
+        const int u = it < 3 ? (it == 0 ? 0 : it == 1 ? st::kSliceTop : 15) : (int)(rng() % (st::kSliceTop + 1)), g = it % 5 ? (int)(rng() % 16384) : 16383;
+        int sum = 0;
+        for (int w = 0; w < st::kSliceBytes / 4; ++w)
+            for (int j = 0; j < 4; ++j) sum += (int)(int8_t)(st::slice_query_word(u, w) >> (8 * j)) * (int)(int8_t)(st::slice_item_word(g, w) >> (8 * j));
+        if (sum != -st::slice_bound(u, g)) return std::printf("words: u=%d g=%d sum=%d bound=%d\n", u, g, sum, st::slice_bound(u, g)), 1;
+    }
+    // never above tau / s_q / s_i, whatever the reference; and within 2 % of it where both numbers are large enough
+    double worst = 0;
+    long close = 0;
+    for (int it = 0; it < 2000000; ++it) {
+        const float si = (float)std::exp2(uni(-100, 89)), T = (float)std::exp2(uni(0, 22)), tq = T * si;
+        if (!(tq > 0x1p-126f) || std::isinf(tq)) continue;
+        const float h_max = it % 3 ? (float)(uni(0.2, 4) / si) : (float)std::exp2(uni(-100, 100));
+        const float ref = st::slice_ref(h_max, tq * (float)uni(1, 3));
+        const int u = st::slice_query(tq, ref), g = st::slice_item(1.0f / si, st::slice_factor(ref));
+        if (u < 0 || u > st::kSliceTop || g < 0 || g > 16383) return std::printf("range: u=%d g=%d\n", u, g), 1;
+        const double exact = (double)tq / si, bound = st::slice_bound(u, g);
+        if (bound > exact * (1 - 0x1p-18)) return std::printf("above: si=%a tq=%a ref=%a bound=%g exact=%g\n", si, tq, ref, bound, exact), 1;
+        if (u >= 128 * 16 && u < st::kSliceTop && g >= 32 * 128 && g < 16383) {
+            ++close;
+            worst = std::fmax(worst, 1 - bound / exact);
+        }
+    }
+    std::printf("ok %ld %.5f\n", close, worst);
+    return worst < 0.02 ? 0 : 1;
+}
+"""
+
+
+def test_the_products_bound_lies_just_below_the_threshold(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    src, exe = tmp_path / "slices.cpp", str(tmp_path / "slices")
+    src.write_text(_SLICES)
+    built = subprocess.run([cxx, "-std=c++17", "-O1", "-ffp-contract=off", "-I", CSRC, str(src), "-o", exe], capture_output=True, text=True)
+    assert built.returncode == 0, built.stderr
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=240)
+    assert run.returncode == 0, run.stdout + run.stderr
+    assert int(run.stdout.split()[1]) > 50_000, run.stdout  # most of what is tested has both numbers in their good range

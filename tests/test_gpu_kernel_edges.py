@@ -207,7 +207,7 @@ def test_freed_index_memory_goes_back_to_the_driver():
 
 
 # Batches whose queries hardly share filters (the products of all pairs, or of the passing ones where a wavefront has
-# few): row lengths of every variant, one query block (its own form up to rows of 192) and several, two rows of the grid, ragged last segment
+# few): row lengths of every variant, one query block and several, two and three rows of the grid (of equal and other widths), ragged last segment
 # and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores; a corpus whose
 # filters pass everything in some stretches and nothing in others (wavefronts change between the two forms), and
 # no filter at all (no signature row is named); scales of many sizes (a wavefront's bounds move as it meets larger ones), some
@@ -224,7 +224,9 @@ def test_freed_index_memory_goes_back_to_the_driver():
                                           (420_000, 96, 200, 64, "negative"), (300_031, 128, 32, 512, "mixed"),
                                           (350_001, 192, 31, 100, "stretches"), (400_003, 96, 32, 64, "ties"),
                                           (330_000, 64, 24, 257, "negative"), (310_017, 128, 17, 128, "beyond"),
-                                          (300_011, 192, 16, 64, "scales"), (320_009, 256, 32, 128, "mixed")])
+                                          (300_011, 192, 16, 64, "scales"), (320_009, 256, 32, 128, "mixed"),
+                                          (300_000, 128, 257, 128, "stretches"), (310_001, 64, 641, 300, "mixed"),
+                                          (400_009, 256, 225, 512, "rare"), (300_007, 192, 65, 64, "outliers")])
 def test_own_filters(n, d, B, m, kind):
     w = ragged_workload(n, n, d, B, 40, 8, m, 3)
     filters = []
@@ -251,6 +253,8 @@ def test_own_filters(n, d, B, m, kind):
         rng = np.random.default_rng(n)
         lo, hi = np.array([(-110, 110), (-3, 3), (-110, -95)])[rng.integers(0, 3, n // 64 + 1).repeat(64)[:n]].T
         w.item_scale = torch.from_numpy(np.exp2(rng.uniform(lo, hi)).astype(np.float32))
+    elif kind == "outliers":  # a twentieth of the items far below the others' scales: the bounds' reference is not theirs
+        w.item_scale = torch.from_numpy(np.where(np.random.default_rng(n).random(n) < 0.05, 1e-6, 1.0).astype(np.float32)) * w.item_scale
     elif kind == "negative":
         w.items = w.items.abs().clamp(1, 127).to(torch.int8)
         w.queries = (-w.queries.abs().clamp(1, 127).to(torch.int16)).to(torch.int8)
