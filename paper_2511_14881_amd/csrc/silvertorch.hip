@@ -1082,6 +1082,21 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
         if (blocks_big > 0 && groups.n_groups <= st::kMfmaMaxGroups && blocks_all * 16 * d <= 4 * (int64_t)st::kMfmaQueryLds)
             min_rows = 1;
     }
+    // ... and all of them to the scan for filters of their own where that takes every level behind the first one: its cost
+    // goes by the queries alone, that of the other by the filters (a pass over the index each, and rows padded to 16).
+    // 200 calls on 0.3 to 10 M items, 16 to 600 queries under 1 to 300 filters, by the MFMA scan -> here, in us:
+    //   8.4 M x 128, 219 queries, 94 filters  4752 -> 512;  2.5 M x 256, 128, 55  756 -> 227;  1.0 M x 64, 98, 62  145 -> 72
+    //   2.7 M x 64, 88, 22  260 -> 134;  1.2 M x 256, 91, 22  302 -> 233, but 3.9 M x 256, 88, 22  230 -> 289
+    // and where the line is: few filters (2.5 M x 64, 35 queries, 5 filters  62 -> 94;  3.6 M x 256, 39, 17  214 -> 280), or many queries
+    // to one (4.5 M x 128, 565, 35  491 -> 746;  4.7 M x 64, 357, 44  328 -> 407).
+    if (shape_ok && g_scoring_path == 0 && own_takes(n_tasks, weighted, batch, d, expr_groups ? expr_row_count : bloom->m_bits, groups.rows.size()) &&
+        groups.n_groups >= (d <= 128 ? 16 : 24) && batch < 8 * groups.n_groups) {
+        st::Plan own_plan;
+        bool own_all = cached_plan(n_items, K, 1, st::kMaxSegItems, allow_seed ? batch * n_tasks : st::kSeedMaxRows + 1, &own_plan, st::scan_groups(),
+                                   min_cap, allow_seed, false) == 0 && own_plan.n_levels > 1;
+        for (int lv = 1; own_all && lv < own_plan.n_levels; ++lv) own_all = own_takes_level(own_plan.level[lv]);
+        if (own_all) min_rows = INT32_MAX;
+    }
     GroupSet &set_mfma = hs.set_mfma, &set_dot = hs.set_dot;
     set_mfma.reset();
     set_dot.reset();

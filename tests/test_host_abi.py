@@ -126,6 +126,20 @@ def _plan(n, d, batch, tasks, K, m, k, filters):
                                   np.array(off, dtype=np.int64))
 
 
+@pytest.mark.parametrize("n,d,batch,tasks,groups,m,own", [
+    (1_000_000, 128, 64, 1, 16, 256, True), (1_000_000, 128, 64, 1, 15, 256, False),  # filters, up to rows of 128
+    (1_000_000, 256, 100, 1, 24, 256, True), (1_000_000, 256, 100, 1, 23, 256, False),  # ... of 256
+    (1_000_000, 64, 159, 1, 20, 256, True), (1_000_000, 64, 160, 1, 20, 256, False),  # queries to a filter
+    (200_000, 64, 100, 1, 40, 256, False), (1_000_000, 128, 64, 2, 32, 256, False),  # short levels, several tasks
+    (1_000_000, 128, 64, 1, 32, 513, False), (1_000_000, 512, 64, 1, 32, 256, False)])  # rows of the index, row length
+def test_host_plan_takes_batches_of_many_filters_to_the_scan_for_filters_of_their_own(n, d, batch, tasks, groups, m, own):
+    # (one filter has four queries at least: a group dense enough for the other scan, which then takes the small ones along)
+    filters = [(7 * (q if q < groups else 0) + 1,) for q in range(batch)]
+    got = _plan(n, d, batch, tasks, 50, m, 3, filters)
+    assert got["distinct_filters"] == groups
+    assert (got["mfma_groups"] == 0) == own and (not own or got["dot_groups"] == groups)
+
+
 def test_host_plan_groups_queries_by_their_filter_as_a_set():
     # Sec. 4.2: a filter is the conjunction of its terms, so the order of the terms, and a term
     # given twice, make no new filter; queries of one filter share one group
