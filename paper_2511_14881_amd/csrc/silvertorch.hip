@@ -2006,7 +2006,6 @@ int st_value_model(const float* dev_task_scores, int64_t n, int32_t n_tasks, con
     if (n_ops < 1 || n_ops > ST_MAX_VM_OPS) return fail(ST_EINVAL, "formula has %d entries (1 to %d)", n_ops, ST_MAX_VM_OPS);
     st::VmProgram prog;
     memset(&prog, 0, sizeof(prog));
-    prog.n_ops = n_ops;
     int depth = 0, deepest = 0;
     for (int32_t i = 0; i < n_ops; ++i) {
         const int32_t code = host_ops[i] & 255;
@@ -2033,10 +2032,9 @@ int st_value_model(const float* dev_task_scores, int64_t n, int32_t n_tasks, con
         }
         if (depth > ST_MAX_VM_DEPTH) return fail(ST_EINVAL, "formula needs a stack deeper than %d", ST_MAX_VM_DEPTH);
         deepest = std::max(deepest, depth);
-        prog.ops[i] = host_ops[i];
-        prog.consts[i] = host_consts[i];
     }
     if (depth != 1) return fail(ST_EINVAL, "formula leaves %d results", depth);
+    st::vm_fold(host_ops, host_consts, n_ops, &prog);
     if (n == 0) return ST_OK;
     const int64_t sets = (n + st::kVmItems - 1) / st::kVmItems;  // items of one thread
     const unsigned grid = (unsigned)std::min<int64_t>((sets + st::kVmThreads - 1) / st::kVmThreads, st::kComputeUnits * 16);

@@ -43,6 +43,17 @@ def test_random_formulas_match_oracle(n, n_tasks):
     check(scores, [T(0)] * 16 + [O.VM_ADD, O.VM_MAX, O.VM_MUL] * 5, "depth 16")
 
 
+# Leaves that are folded into the operation they feed, on either side, and those that are not.
+@pytest.mark.parametrize("n_tasks", [2, 9])
+def test_formulas_whose_leaves_are_folded_match_oracle(n_tasks):
+    scores = np.random.default_rng(n_tasks).uniform(-2, 2, (5003, n_tasks)).astype(np.float32)
+    last, half = T(n_tasks - 1), (C, 0.5)
+    for prog in ([half], [T(0), half, O.VM_SUB], [half, last, O.VM_SUB], [half, (C, 2.0), O.VM_GT], [T(0), last, O.VM_MAX, half, O.VM_SUB],
+                 [T(0), T(1), last, O.VM_SUB, O.VM_SUB], [T(0), half, last, O.VM_SELECT], [T(0), half, O.VM_GT, T(1), last, O.VM_MUL, half, O.VM_SELECT],
+                 [T(0), T(1), O.VM_ADD, last, T(0), O.VM_SUB, O.VM_MIN, half, O.VM_MUL], [half, T(0), T(1), T(0), last, O.VM_SELECT, O.VM_SUB, O.VM_SUB]):
+        check(scores, prog, "folded")
+
+
 def test_ill_formed_formulas_are_rejected():
     s = torch.zeros((4, 2), dtype=torch.float32, device="cuda")
     for bad in ([O.VM_ADD], [T(0), O.VM_ADD], [T(0), T(1)], [T(2)], [99], [T(0), T(1), O.VM_SELECT],
