@@ -786,14 +786,10 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
             ids = d_ids;
         }
         const size_t lds = (size_t)std::min<int32_t>(m_bits, st::kBuildSlabRows) * st::kTileWords * 8;
-        const bool pow2 = (m_bits & (m_bits - 1)) == 0;
-        const auto kernel = pow2 ? &st::bloom_build_kernel<true> : &st::bloom_build_kernel<false>;
-        static std::atomic<bool> lds_set[2] = {{false}, {false}};  // (setting the attribute twice is harmless)
-        if (!lds_set[pow2].load(std::memory_order_acquire)) {
-            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       st::kBuildSlabRows * st::kTileWords * 8));
-            lds_set[pow2].store(true, std::memory_order_release);
-        }
+        const auto kernel = st::build_kernel(m_bits, k_hashes, nnz, n_items, b->n_tiles);
+        // (the attribute is asked for where the default does not do; setting it twice is harmless)
+        if (lds > 64 * 1024)
+            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         {
             TimedLaunch t(0, stream);
             hipLaunchKernelGGL(kernel, dim3((unsigned)b->n_tiles), dim3(st::kBuildThreads), lds, stream, off, ids, n_items,

@@ -59,13 +59,24 @@ __device__ inline uint32_t build_pos(uint64_t x, const BuildMod& b)
 // lists once and the index once.
 constexpr int kBuildThreads = kTileItems;
 constexpr int kBuildSlabRows = 1024;  // 128 KB of LDS
-constexpr int kBuildIds = 8;          // ids of a list in flight per thread
+
+// Two neighbouring ids (a list may start at any multiple of 8 bytes).
+struct __attribute__((packed, aligned(8))) BuildPair {
+    uint64_t a, b;
+};
 
 // Word w32 (32 items) of LDS row r lies at w32 ^ (r & 31): the 64 lanes of a wavefront hold two words'
 // worth of items, and without the swizzle their updates of any rows would meet in two to four banks.
 __device__ inline int build_word(int r, int w32) { return r * 32 + (w32 ^ (r & 31)); }
 
-template <bool POW2>
+// LANES: lanes to an item's list.  A load is paid by the lines that it touches, 64 where every lane reads a list of its own; with
+// four lanes to a list it is 16, but the items come in four passes, and lists of a few ids leave lanes idle.
+// K: hashes of an id (0: as many as k_hashes says), written out so that two of them are in flight and no loop is counted.
+// ONE: the rows fit one slab, and no position is compared with it.  Bound by the instructions of the hashes (some 20 to each,
+// two products among them) beside the LDS updates.  10 M items x 16 ids, 4 hashes, 512 rows: 0.70 ms with a counted loop, a
+// test against the slab and four steps to an address; the whole of a pass with the export 915 us, 820 with
+// two ids to a load, 718 with four lanes to a list.
+template <bool POW2, int K, bool ONE, int LANES>
 __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int64_t* __restrict__ feat_offsets,
                                                                     const uint64_t* __restrict__ feat_ids,
                                                                     int64_t n_items, BuildMod bm,
@@ -74,26 +85,45 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
     extern __shared__ __attribute__((aligned(16))) uint32_t s_bits[];  // [rows][32]: the 16 words of a row as 32-bit halves
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
-    const int64_t item = tile * kTileItems + tid;
     const int m_bits = (int)bm.m;
-    const int64_t f_begin = item < n_items ? feat_offsets[item] : 0;
-    const int64_t f_end = item < n_items ? feat_offsets[item + 1] : 0;
-    const uint32_t bit = 1u << (tid & 31);
+    constexpr int kPairs = LANES == 1 ? 4 : 2;  // pairs of ids in flight per thread
     for (int slab0 = 0; slab0 < m_bits; slab0 += kBuildSlabRows) {
         const int rows = min(kBuildSlabRows, m_bits - slab0);
         for (int i = tid; i < rows * 8; i += kBuildThreads) reinterpret_cast<int4*>(s_bits)[i] = make_int4(0, 0, 0, 0);
         __syncthreads();
-        for (int64_t e = f_begin; e < f_end; e += kBuildIds) {
-            uint64_t f[kBuildIds];
+        for (int pass = 0; pass < LANES; ++pass) {
+            const int it = (tid & ~63) + pass * (64 / LANES) + (tid & 63) / LANES, w32 = it >> 5;  // item of the tile
+            const int64_t item = tile * kTileItems + it;
+            const uint32_t bit = 1u << (it & 31);
+            const int64_t f_begin = item < n_items ? feat_offsets[item] : 0, f_end = item < n_items ? feat_offsets[item + 1] : 0;
+            auto mark = [&](uint64_t id, int j) __attribute__((always_inline)) {
+                const int r = (int)build_pos<POW2>(id ^ (uint64_t)j, bm) - (ONE ? 0 : slab0);
+                if (ONE || (uint32_t)r < (uint32_t)rows) atomicOr(&s_bits[build_word(r, w32)], bit);
+            };
+            for (int64_t e = f_begin + 2 * (tid & (LANES - 1)); e < f_end; e += kPairs * 2 * LANES) {
+                BuildPair f[kPairs];
+                const int left = (int)min(f_end - e, (int64_t)(kPairs * 2 * LANES));
 #pragma unroll
-            for (int u = 0; u < kBuildIds; ++u) f[u] = e + u < f_end ? feat_ids[e + u] : 0;
+                for (int u = 0; u < kPairs; ++u) {
+                    const int at = u * 2 * LANES;
+                    f[u] = {0, 0};
+                    if (at + 1 < left) f[u] = *reinterpret_cast<const BuildPair*>(feat_ids + e + at);
+                    else if (at < left) f[u].a = feat_ids[e + at];
+                }
 #pragma unroll
-            for (int u = 0; u < kBuildIds; ++u)
-                if (e + u < f_end)
-                    for (int j = 0; j < k_hashes; ++j) {
-                        const int r = (int)build_pos<POW2>(f[u] ^ (uint64_t)j, bm) - slab0;
-                        if ((uint32_t)r < (uint32_t)rows) atomicOr(&s_bits[build_word(r, tid >> 5)], bit);
-                    }
+                for (int u = 0; u < kPairs; ++u)
+#pragma unroll
+                    for (int i = 0; i < 2; ++i)
+                        if (u * 2 * LANES + i < left) {
+                            const uint64_t id = i ? f[u].b : f[u].a;
+                            if constexpr (K > 0) {
+#pragma unroll
+                                for (int j = 0; j < K; ++j) mark(id, j);
+                            } else {
+                                for (int j = 0; j < k_hashes; ++j) mark(id, j);
+                            }
+                        }
+            }
         }
         __syncthreads();
         int4* dst = reinterpret_cast<int4*>(bloom + (tile * (int64_t)m_bits + slab0) * kTileWords);
@@ -106,6 +136,29 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
         }
         __syncthreads();
     }
+}
+
+// The kernel for an index: written out for two to five hashes and up to one slab of rows; four lanes to a list from 12 ids to an
+// item on where the tiles fill the chip.  With one lane -> four, a build and an export in us: 1.1 M items x 21 ids 126 -> 101; 4.5 M x 19
+// 391 -> 368; 1.5 M x 13 122.9 -> 120.4; but 2.2 M x 7 88 -> 95, 6.0 M x 3 196 -> 367, 44,000 x 18 75 -> 85.
+constexpr int64_t kBuildLongList = 12, kBuildLongTiles = 512;
+template <bool POW2, int LANES>
+inline auto build_kernel(int k_hashes) -> decltype(&bloom_build_kernel<POW2, 0, false, 1>)
+{
+    switch (k_hashes) {
+    case 2: return &bloom_build_kernel<POW2, 2, true, LANES>;
+    case 3: return &bloom_build_kernel<POW2, 3, true, LANES>;
+    case 4: return &bloom_build_kernel<POW2, 4, true, LANES>;
+    case 5: return &bloom_build_kernel<POW2, 5, true, LANES>;
+    default: return &bloom_build_kernel<POW2, 0, true, LANES>;
+    }
+}
+inline auto build_kernel(int m_bits, int k_hashes, int64_t n_ids, int64_t n_items, int64_t n_tiles) -> decltype(&bloom_build_kernel<true, 0, false, 1>)
+{
+    const bool pow2 = (m_bits & (m_bits - 1)) == 0;
+    if (m_bits > kBuildSlabRows) return pow2 ? &bloom_build_kernel<true, 0, false, 1> : &bloom_build_kernel<false, 0, false, 1>;
+    if (n_ids >= kBuildLongList * n_items && n_tiles >= kBuildLongTiles) return pow2 ? build_kernel<true, 4>(k_hashes) : build_kernel<false, 4>(k_hashes);
+    return pow2 ? build_kernel<true, 1>(k_hashes) : build_kernel<false, 1>(k_hashes);
 }
 
 // In-register transpose of a 32 x 32 bit matrix: bit j of a[i] and bit i of a[j] change places.

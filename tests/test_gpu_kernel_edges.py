@@ -34,6 +34,21 @@ def test_index_build_and_export_at_tile_edges(n, m):
     assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, 3))
 
 
+# Lists of 0 to 40 ids (from 12 to an item on and 512 tiles four lanes share a list; pairs of ids begin at odd places and
+# end with one id), every number of hashes that has a kernel of its own and two that have none, one slab of rows and two.
+@pytest.mark.parametrize("n,m,k,most", [(512 * 1024 + 3, 512, 4, 40), (512 * 1024, 100, 5, 26), (511 * 1024, 64, 2, 40),
+                                        (530_001, 128, 3, 25), (530_001, 256, 3, 20), (525_000, 96, 7, 33), (3_000, 1100, 2, 40),
+                                        (70_001, 1024, 1, 9)])
+def test_index_build_of_long_and_short_lists(n, m, k, most):
+    rng = np.random.default_rng(n + m)
+    off = np.concatenate([[0], np.cumsum(rng.integers(0, most + 1, n))]).astype(np.int64)
+    ids = rng.integers(0, 1 << 62, int(off[-1])).astype(np.int64)
+    bloom = st.st_bloom_build(torch.from_numpy(off).cuda(), torch.from_numpy(ids).cuda(), n, m, k)
+    got = _u64(st.st_bloom_export_signatures(bloom))
+    bloom.free()
+    assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, k))
+
+
 # The tables of a captured call are read again at every replay: eager calls in between (more than there are
 # staging slots) must not get the slot.  Once without a seed pass, once with it.
 @pytest.mark.parametrize("n", [20_000, 300_000])
