@@ -18,15 +18,16 @@
 // before are tested, and an operand serves both halves.
 // The queries lie in LDS with 16 bytes of padding a row (an odd number of 16-byte pieces: no bank conflicts).
 //
-// 10 M x 256 bytes, 213 queries with filters of their own (5 % each), K = 500: the level after the first takes 0.68 ms,
-// 1.04 with a multiply-add for every pair, operands read for each half, an exact test per lane of 16 results and
-// segments of 512 items tied to a workgroup; gathering took 4.5.  A unit then takes a wavefront 21,500 cycles: 13,500 in products
-// and tests of seven blocks (4,200 is what the products alone need, and two wavefronts share the matrix unit), 4,000
+// 10 M x 256 bytes, 256 queries, 161 filters (5 % each), K = 500: the level after the first takes 0.82 ms in a long series of
+// calls (0.82 to 1.1 in a run's first forty).  With 213 of the queries, a call took 1.31 ms with a multiply-add for every pair, operands read for
+// each half, queued lanes of 16 results and segments of 512 items tied to a workgroup, and 1.01 so; gathering took 4.5 in this kernel's place.
+// A unit of seven blocks takes a wavefront 21,500 cycles: 13,500 in products
+// and tests (4,200 is what the products alone need, and two wavefronts share the matrix unit), 4,000
 // in masks, 1,200 and 2,000 around the first and the last block.
 //
 // A unit whose filters pass few pairs hands them to a list that goes from unit to unit until 64 are there, and
 // whose rows come several lanes to a row (a lane to a row touches 64 lines with every load: 10,000 cycles to a round at
-// d = 256, 3,500 so).  Calls on 3 M x 256, 64 queries that pass 0.5 %: 125 -> 99 us.  It takes the place of the gathering scan whatever
+// d = 256).  Calls on 3 M x 256, 64 queries that pass 0.5 %: 125 -> 99 us.  It takes the place of the gathering scan whatever
 // the filters pass, which the host cannot know.
 #pragma once
 #include "st_search_kernels.h"
