@@ -139,7 +139,7 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
 }
 
 // The kernel for an index: written out for two to five hashes and up to one slab of rows; four lanes to a list from 12 ids to an
-// item on where the tiles fill the chip.  With one lane -> four, a build and an export in us: 1.1 M items x 21 ids 126 -> 101; 4.5 M x 19
+// item on where the tiles fill the chip and the positions need no division (100 rows, 2.9 M x 18, 5 hashes: 402 -> 460).  With one lane -> four, a build and an export in us: 1.1 M items x 21 ids 126 -> 101; 4.5 M x 19
 // 391 -> 368; 1.5 M x 13 122.9 -> 120.4; but 2.2 M x 7 88 -> 95, 6.0 M x 3 196 -> 367, 44,000 x 18 75 -> 85.
 constexpr int64_t kBuildLongList = 12, kBuildLongTiles = 512;
 template <bool POW2, int LANES>
@@ -157,7 +157,7 @@ inline auto build_kernel(int m_bits, int k_hashes, int64_t n_ids, int64_t n_item
 {
     const bool pow2 = (m_bits & (m_bits - 1)) == 0;
     if (m_bits > kBuildSlabRows) return pow2 ? &bloom_build_kernel<true, 0, false, 1> : &bloom_build_kernel<false, 0, false, 1>;
-    if (n_ids >= kBuildLongList * n_items && n_tiles >= kBuildLongTiles) return pow2 ? build_kernel<true, 4>(k_hashes) : build_kernel<false, 4>(k_hashes);
+    if (pow2 && n_ids >= kBuildLongList * n_items && n_tiles >= kBuildLongTiles) return build_kernel<true, 4>(k_hashes);
     return pow2 ? build_kernel<true, 1>(k_hashes) : build_kernel<false, 1>(k_hashes);
 }
 
