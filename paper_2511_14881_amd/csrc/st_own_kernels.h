@@ -54,13 +54,16 @@ constexpr int own_cols(int n_q) { return ((n_q + own_grid_rows(n_q) - 1) / own_g
 // A wavefront whose filters pass no more pairs than this of its 64 items gathers the pairs' rows instead of
 // multiplying all; one that multiplies has the next rows already, and goes on down to fewer pairs.  (Leaving at 64 too: 2.3 M x
 // 192, 41 queries at 2 %, units on either side of the line: 121 us, 129 so, 133 before; but 2 M x 64, 17 at 10 %: 86 and 82.  Entering at 16 or 32
-// with up to 64 queries: 3 M x 256, 64 at 0.5 %: 100 -> 200.)
-constexpr int kOwnFew = 64, kOwnStay = 32;
+// with up to 64 queries: 3 M x 256, 64 at 0.5 %: 100 -> 200.  64 with more queries, where all products take longer, -> 112, which is as many as the list
+// has room for: 3.4 M x 256, 117 queries at 1 %: 257 -> 198; 3.5 M x 256, 259 at 1 %: 377 -> 327; 2 M x 128, 250 at 0.5 %: 180 -> 139.)
+constexpr int own_few(int cols) { return cols <= 64 ? 64 : 112; }
+constexpr int own_stay(int cols) { return own_few(cols) / 2; }
+constexpr int kOwnPairs = 64 + own_few(kOwnCols);  // of a list: what is left of a round, and a unit's
 // (a filter's rows take whole multiples of four entries: three more to a filter of the resident queries, at most)
 constexpr size_t own_lds_bytes(int n_q, int d, int m_bits)
 {
     const size_t c = own_cols(n_q);
-    return c * own_row_bytes(d) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnWords * kOwnQueue * 16 + c * 8 +
+    return c * own_row_bytes(d) + c * kOwnWords * 8 + (size_t)m_bits * kOwnWords * 8 + kOwnWords * kOwnPairs * 8 + c * 8 +
            (kOwnRowRefs + c * 3 + 10) / 8 * 16 + 64 + c * (4 * (2 + kOwnSlots) + 2 * 3) + kOwnRows * 2 + kOwnRows / 8;
 }
 static_assert(own_lds_bytes(kOwnCols, 256, kOwnRows) <= 160 * 1024, "LDS of a compute unit");
@@ -92,9 +95,9 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     int8_t* s_q = reinterpret_cast<int8_t*>(at);                  at += (size_t)cols * DP;          // [cols][DP] rows and their slices
     uint64_t* s_mask = reinterpret_cast<uint64_t*>(at) + (size_t)wv * cols;      at += (size_t)cols * kOwnWords * 8;
     uint64_t* s_idx = reinterpret_cast<uint64_t*>(at) + (size_t)wv * p.m_bits;   at += (size_t)p.m_bits * kOwnWords * 8;
-    int4* queue = reinterpret_cast<int4*>(at) + (size_t)wv * kOwnQueue;  at += (size_t)kOwnWords * kOwnQueue * 16;
-    uint2* s_pairs = reinterpret_cast<uint2*>(queue);             // of a wavefront that gathers
-    static_assert(2 * kOwnFew * sizeof(uint2) <= kOwnQueue * sizeof(int4), "the pairs lie where the queue does");
+    uint2* s_pairs = reinterpret_cast<uint2*>(at) + (size_t)wv * kOwnPairs;  at += (size_t)kOwnWords * kOwnPairs * 8;  // of a wavefront that gathers
+    int4* queue = reinterpret_cast<int4*>(s_pairs);               // ... that multiplies
+    static_assert(kOwnQueue * sizeof(int4) <= kOwnPairs * sizeof(uint2) && kOwnPairs * sizeof(uint2) % 16 == 0, "the queue lies where the pairs do");
     uint64_t* s_tau = reinterpret_cast<uint64_t*>(at);            at += (size_t)cols * 8;
     uint16_t* s_refs = reinterpret_cast<uint16_t*>(at);           at += (size_t)(kOwnRowRefs + cols * 3 + 10) / 8 * 16;
     uint32_t* s_max = reinterpret_cast<uint32_t*>(at);            at += 64;  // [8] largest 1 / scale of a wavefront's sample; largest tau / s_q; first filter, last; no bound for some query; next unit
@@ -411,7 +414,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     // The loop has two parts, so that the rows in registers are none while a wavefront gathers.
     if (my0 >= 0) masks();
     while (my0 >= 0) {
-        if (total <= (uint32_t)kOwnFew) {
+        if (total <= (uint32_t)own_few(cols)) {
             if (next0 >= 0 && !short_unit) fetch(next0);
             if (qn > 0) drain();
             uint32_t pos = (uint32_t)pn + before;
@@ -424,10 +427,11 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                 }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
             pn = __builtin_amdgcn_readfirstlane(pn + (int)total);
-            if (pn >= kOwnFew) {
-                gather(kOwnFew);
-                const uint2 rest = s_pairs[kOwnFew + lane];
-                pn -= kOwnFew;
+            if (pn >= 64) {
+                const int whole = pn & ~63;
+                gather(whole);
+                const uint2 rest = s_pairs[min(whole + lane, kOwnPairs - 1)];
+                pn -= whole;
                 if (lane < pn) s_pairs[lane] = rest;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
             }
@@ -539,7 +543,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
             slot = next_slot;
             if (my0 < 0) break;
             masks();
-            if (total <= (uint32_t)kOwnStay) break;
+            if (total <= (uint32_t)own_stay(cols)) break;
         }
     }
     if (qn > 0) drain();
