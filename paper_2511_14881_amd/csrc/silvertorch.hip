@@ -787,9 +787,11 @@ int st_bloom_build(const int64_t* feat_offsets, const uint64_t* feat_ids, int64_
         }
         const size_t lds = (size_t)std::min<int32_t>(m_bits, st::kBuildSlabRows) * st::kTileWords * 8;
         const auto kernel = st::build_kernel(m_bits, k_hashes, nnz, n_items, b->n_tiles);
-        // (the attribute is asked for where the default does not do; setting it twice is harmless)
+        // (asked for where the default does not do, and always the same value: builds of other sizes on other threads share
+        // the kernel, and this call's own size might be less than what one of them is about to launch)
         if (lds > 64 * 1024)
-            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       st::kBuildSlabRows * st::kTileWords * 8));
         {
             TimedLaunch t(0, stream);
             hipLaunchKernelGGL(kernel, dim3((unsigned)b->n_tiles), dim3(st::kBuildThreads), lds, stream, off, ids, n_items,

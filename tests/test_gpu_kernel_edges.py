@@ -1,6 +1,7 @@
 """Kernels at the sizes where their tiling can go wrong, against the CPU oracle: edges of tiles,
 remainders, the smallest and largest shapes of a variant.  Bit-exact like every result of the library."""
 import gc
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 import pytest
@@ -47,6 +48,28 @@ def test_index_build_of_long_and_short_lists(n, m, k, most):
     got = _u64(st.st_bloom_export_signatures(bloom))
     bloom.free()
     assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, k))
+
+
+# Builds of several sizes above the default LDS limit share one kernel, and with it one limit, on any number of threads.
+def test_indexes_of_several_sizes_built_by_threads_at_once():
+    n, k, widths = 40_000, 3, (600, 1000, 700, 900)
+    rng = np.random.default_rng(n)
+    off = np.concatenate([[0], np.cumsum(rng.integers(0, 9, n))]).astype(np.int64)
+    ids = rng.integers(0, 1 << 62, int(off[-1])).astype(np.int64)
+    dev_off, dev_ids = torch.from_numpy(off).cuda(), torch.from_numpy(ids).cuda()
+    torch.cuda.synchronize()
+
+    def build(m):
+        stream = torch.cuda.Stream()
+        for _ in range(100):
+            bloom = st.st_bloom_build(dev_off, dev_ids, n, m, k, stream=stream)
+        got = st.st_bloom_export_signatures(bloom, stream=stream)
+        stream.synchronize()
+        return _u64(got)
+
+    with ThreadPoolExecutor(len(widths)) as pool:
+        for m, got in zip(widths, pool.map(build, widths)):
+            assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, k)), m
 
 
 # The tables of a captured call are read again at every replay: eager calls in between (more than there are
