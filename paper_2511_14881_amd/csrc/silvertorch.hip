@@ -957,7 +957,7 @@ int64_t st_search_overflow_flags_offset(int64_t n_items, int32_t d, int32_t batc
 }
 
 // Whether a batch may take the scan for filters of their own (one task, no weights; with fewer than 16 queries more
-// than half of the products would be padding), and whether a level may.
+// than half of the products would be padding), whether a level may, and whether all levels behind the first one may.
 static bool own_takes(int32_t n_tasks, bool weighted, size_t n_queries, int32_t d, int32_t m_bits, size_t n_rows)
 {
     return n_tasks == 1 && !weighted && n_queries >= 16 && m_bits <= st::kOwnRows && n_rows <= (size_t)st::kOwnRowRefs && st::own_kernel(d) != nullptr;
@@ -965,6 +965,12 @@ static bool own_takes(int32_t n_tasks, bool weighted, size_t n_queries, int32_t 
 static bool own_takes_level(const st::Level& l)
 {
     return l.end - l.begin >= st::kOwnMinItems && l.begin % st::kOwnSeg == 0 && st::level_takes_segments(l, st::kOwnSeg);
+}
+static bool own_takes_levels(const st::Plan& p)
+{
+    for (int lv = 1; lv < p.n_levels; ++lv)
+        if (!own_takes_level(p.level[lv])) return false;
+    return p.n_levels > 1;
 }
 
 static int32_t plan_groups_per_row(int32_t q_split) { return st::scan_groups() / std::max(q_split, 1); }
@@ -1090,10 +1096,9 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     if (shape_ok && g_scoring_path == 0 && own_takes(n_tasks, weighted, batch, d, expr_groups ? expr_row_count : bloom->m_bits, groups.rows.size()) &&
         groups.n_groups >= (d <= 128 ? 16 : 24) && batch < 8 * groups.n_groups) {
         st::Plan own_plan;
-        bool own_all = cached_plan(n_items, K, 1, st::kMaxSegItems, allow_seed ? batch * n_tasks : st::kSeedMaxRows + 1, &own_plan, st::scan_groups(),
-                                   min_cap, allow_seed, false) == 0 && own_plan.n_levels > 1;
-        for (int lv = 1; own_all && lv < own_plan.n_levels; ++lv) own_all = own_takes_level(own_plan.level[lv]);
-        if (own_all) min_rows = INT32_MAX;
+        if (cached_plan(n_items, K, 1, st::kMaxSegItems, allow_seed ? batch * n_tasks : st::kSeedMaxRows + 1, &own_plan, st::scan_groups(),
+                        min_cap, allow_seed, false) == 0 && own_takes_levels(own_plan))
+            min_rows = INT32_MAX;
     }
     GroupSet &set_mfma = hs.set_mfma, &set_dot = hs.set_dot;
     set_mfma.reset();
@@ -1192,14 +1197,17 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
     const size_t at_qprow = blob.add(q_prow);
     if (blob.bytes() > L.meta_bytes) return fail(ST_EINVAL, "group tables exceed their workspace slot");
-    // Sample mode: the first level of a search that the 8-wavefront MFMA scan serves alone scans
-    // its G * cap items as segments spread evenly over the corpus instead of a prefix, and the
-    // second level scans the whole corpus without them.  The threshold the first selection
+    // Sample mode: the first level of a search that the 8-wavefront MFMA scan serves alone, or the scan for
+    // filters of their own behind that level, scans its G * cap items as segments spread evenly over
+    // the corpus instead of a prefix, and the second level scans the whole corpus without them.  The threshold the first selection
     // publishes rests on the assumption that the order of the corpus says nothing about a query's
     // scores; a strided sample keeps that true for corpora ordered along some trend (by age, by
     // popularity, by category), where a prefix would not.
     int64_t samp_stride = 0;
-    if (plan.n_levels >= 2 && !plan.level[0].seed && allow_seed && set_mfma.n && !set_dot.n && mp.waves == 8) {
+    const bool own_alone = !set_mfma.n && g_scoring_path == 0 &&
+                           own_takes(n_tasks, weighted, set_dot.q_list.size(), d, expr_groups ? expr_row_count : bloom->m_bits, set_dot.rows.size()) &&
+                           own_takes_levels(plan);
+    if (plan.n_levels >= 2 && !plan.level[0].seed && allow_seed && ((set_mfma.n && !set_dot.n && mp.waves == 8) || own_alone)) {
         const st::Level& L0 = plan.level[0];
         const int64_t segs = (L0.end - L0.begin) / L0.seg_items;
         if (L0.begin == 0 && segs > 0 && (L0.end - L0.begin) % L0.seg_items == 0 && L0.seg_items % 64 == 0) {
@@ -1441,7 +1449,7 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
     }
     bool mfma_started = false;  // the first MFMA launch builds the resident-query image
     // Batches that hardly share filters: from the second level on all pairs are multiplied, see st_own_kernels.h.
-    const auto own_scan = g_scoring_path == 0 && own_takes(n_tasks, weighted, set_dot.q_list.size(), d, sp_d.m_bits, set_dot.rows.size()) ? st::own_kernel(d) : nullptr;
+    const auto own_scan = g_scoring_path == 0 && own_takes(n_tasks, weighted, set_dot.q_list.size(), d, sp_d.m_bits, set_dot.rows.size()) ? st::own_kernel(d, samp_stride > 0) : nullptr;
     for (int lv = 0; lv < plan.n_levels; ++lv) {
         const st::Level& L_ = plan.level[lv];
         se.first = lv == 0 || (lv == 1 && plan.level[0].seed);  // no candidate list from before
@@ -1492,13 +1500,13 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
         }
         if (set_dot.n && own_scan && lv > 0 && own_takes_level(L_)) {
             st::ScanParams sp_o = sp_d;
-            const int64_t n_own = (L_.end - L_.begin + st::kOwnSeg - 1) / st::kOwnSeg;
+            const int64_t n_own = (L_.end - L_.begin + st::kOwnSeg - 1) / st::kOwnSeg;  // (a sample has as many items as the prefix)
             sp_o.seg_items = st::kOwnSeg;
             sp_o.seg_per_visit = (int32_t)std::max<int64_t>(1, std::min<int64_t>(4, n_own / plan.groups));
             static_assert(st::kScanGroups <= st::kOwnSlots * st::kComputeUnits, "a workgroup counts for that many regions");
             const size_t lds = st::own_lds_bytes((int)set_dot.q_list.size(), d, sp_o.m_bits);
-            static std::atomic<bool> lds_set[9] = {};  // (setting the attribute twice is harmless)
-            auto& set = lds_set[d / 32];
+            static std::atomic<bool> lds_set[2][9] = {};  // (setting the attribute twice is harmless)
+            auto& set = lds_set[samp_stride > 0][d / 32];
             if (!set.load(std::memory_order_acquire)) {
                 ST_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(own_scan), hipFuncAttributeMaxDynamicSharedMemorySize,
                                            160 * 1024));
@@ -1509,7 +1517,7 @@ static int search_impl(const st_bloom* bloom, const int8_t* dev_items, const flo
                                dim3(st::kOwnThreads), lds, stream, sp_o);
             ST_HIP(hipGetLastError());
         } else if (set_dot.n && own_scan && lv == 0 && L_.end > L_.begin && plan.cap == 64 && plan.groups % (st::kOwnThreads / 64) == 0) {
-            // the first level: 64 consecutive items to a region, every passing pair is admitted
+            // the first level: 64 consecutive items to a region (in sample mode a segment), every passing pair is admitted
             static_assert(st::own_first_lds_bytes(256) <= 64 * 1024, "no larger dynamic LDS to be asked for");
             TimedLaunch t(0, stream);
             hipLaunchKernelGGL(st::own_first_kernel(d),

@@ -79,10 +79,35 @@ __device__ inline void own_barrier()
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// d = 32 * KS.  Grid (workgroups, own_grid_rows(queries)); segments start at multiples of 512 items.  One
+// The words of a corpus that the first level's sample left: their numbers and back.
+struct SampleWords {
+    uint32_t stride, taken, rest, segs, per;  // words from one segment of the sample to the next, in it, between them; segments; 2^32 / rest, less up to 2
+    __device__ explicit SampleWords(const ScanParams& p)
+        : stride((uint32_t)(p.samp_stride_items >> 6)), taken((uint32_t)p.samp_seg_items >> 6), rest(max(stride - taken, 1u)), segs((uint32_t)p.samp_segs),
+          per(0xFFFFFFFFu / rest)
+    {
+    }
+    __device__ uint32_t others_before(uint32_t word) const
+    {
+        const uint32_t i = word / stride, in = word - i * stride;
+        return word - (i < segs ? i * taken + min(in, taken) : segs * taken);
+    }
+    __device__ uint32_t other(uint32_t no) const
+    {
+        uint32_t i = __umulhi(no, per);  // (the quotient or one less: below 2^25)
+        if (no - i * rest >= rest) ++i;
+        return no + min(i + 1u, segs) * taken;
+    }
+};
+
+// d = 32 * KS.  Grid (workgroups, own_grid_rows(queries)).  One
 // workgroup to a compute unit is resident (registers), so that many are launched and each takes several
 // regions in turn: the queries and tables are brought to LDS once.
-template <int KS>
+// SAMP: the first level took a sample of the corpus; the other words are numbered, and segments are of these numbers.  (A form of its
+// own: what it keeps in scalar registers cost calls with 16 queries 1 to 3.6 %, whose first level is the seed pass and none of a
+// sample.  Leaving the sample's words out of segments of the corpus gave some workgroups a segment more: 2 M x 128, 250 queries at
+// 0.5 %: 146 -> 156 us.)
+template <int KS, bool SAMP>
 __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char own_lds[];
@@ -126,7 +151,10 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     // Units of 64 items: the words of the segments of this workgroup's regions, drawn by the wavefronts from a counter in
     // LDS (tied to a segment, or to a region at a time, they waited a sixth to a half of the time for the slowest of them).
     const int spv = p.seg_per_visit;
-    const int n_seg = (int)((p.item_end - p.item_begin + kOwnSeg - 1) / kOwnSeg), n_visit = (n_seg + spv - 1) / spv;
+    const SampleWords samp(p);
+    const int first_word = (int)(SAMP ? samp.others_before((uint32_t)(p.item_begin >> 6)) : (uint32_t)(p.item_begin >> 6));
+    const int end_word = (int)(SAMP ? samp.others_before((uint32_t)((p.item_end + 63) >> 6)) : (uint32_t)((p.item_end + 63) >> 6));
+    const int n_seg = (end_word - first_word + kOwnWords - 1) / kOwnWords, n_visit = (n_seg + spv - 1) / spv;
     const int slots = (p.groups - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
     const int n_units = (n_visit + p.groups - 1) / p.groups * slots * spv * kOwnWords;
     const int64_t item_lim = p.item_end < p.n_items ? p.item_end : p.n_items;
@@ -137,8 +165,9 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
         const int round = slots == 1 ? i : (int)__umulhi((uint32_t)i, per_slots);
         slot = i - round * slots;
         const int visit = (int)blockIdx.x + slot * (int)gridDim.x + round * p.groups, seg = visit * spv + (t - i * spv);
-        const int64_t first = p.item_begin + (int64_t)seg * kOwnSeg + (unit & (kOwnWords - 1)) * 64;
-        return first < item_lim ? first : -1;
+        const int word = first_word + seg * kOwnWords + (unit & (kOwnWords - 1));
+        if (word >= end_word) return -1;
+        return (int64_t)(SAMP ? samp.other((uint32_t)word) : (uint32_t)word) << 6;
     };
     const bool short_unit = cols <= 64;  // (a unit takes hardly longer than its index words: they are requested as early as can be)
     int unit = wv, slot = 0, next_slot = 0;
@@ -560,7 +589,8 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
 
 // The first level of such a search, which admits every passing pair: the same products, 64 items (a region) to a
 // wavefront.  An item's place among a filter's passing ones is its place in the region, so there are no counters; the
-// number of bits of the mask word is the region's count.  Masks are formed from the index in memory (a wavefront has one
+// number of bits of the mask word is the region's count.  In sample mode region r takes segment r of the sample, elsewhere the
+// r-th 64 items of the level.  Masks are formed from the index in memory (a wavefront has one
 // segment: staging would not pay).  Grid (regions / 8, ceil(queries / kOwnFirstCols)): half the queries to a workgroup, so that 256 of
 // them fill the chip.  Bound by its round trips and the scattered stores of the keys: 65,536 items, 213 queries with filters
 // of their own (5 %), d = 256: 190 us by gathering a row per pair, now 27 (the call 1.48 -> 1.31 ms; 800,000 x 64, 256 queries: 320 -> 175).
@@ -579,8 +609,8 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_first_kernel(ScanParams 
     float* s_sq = reinterpret_cast<float*>(s_q + (size_t)kOwnFirstCols * (DP + 64));               // [cols]
     int32_t* s_query = reinterpret_cast<int32_t*>(s_sq + kOwnFirstCols);                           // [cols]
     const int region = (int)blockIdx.x * (kOwnThreads / 64) + wv;
-    const int64_t my0 = p.item_begin + (int64_t)region * 64;
-    const int64_t lim = p.item_end < p.n_items ? p.item_end : p.n_items, left = lim - my0;
+    const int64_t my0 = p.samp_role == 1 ? region * p.samp_stride_items : p.item_begin + (int64_t)region * 64;
+    const int64_t lim = p.item_end < p.n_items ? p.item_end : p.n_items, left = p.samp_role == 1 ? (region < p.samp_segs ? 64 : 0) : lim - my0;
     const uint64_t all = left >= 64 ? ~0ULL : left > 0 ? ((1ULL << left) - 1ULL) : 0ULL;
 
     // item rows and scales (past the end the last item is repeated: no mask names it)
@@ -668,17 +698,19 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_first_kernel(ScanParams 
 
 // The kernel for rows of d bytes, or null.  (One copy of the kernel to a length: the lengths the MFMA scan has, as far as
 // a workgroup's registers hold the rows of 64 items, and 96 and 192 between them; others go to the gathering scan.)
-inline auto own_kernel(int d) -> decltype(&scan_own_kernel<8>)
+template <bool SAMP>
+inline auto own_kernel(int d) -> decltype(&scan_own_kernel<8, SAMP>)
 {
     switch (d) {
-    case 64: return &scan_own_kernel<2>;
-    case 96: return &scan_own_kernel<3>;
-    case 128: return &scan_own_kernel<4>;
-    case 192: return &scan_own_kernel<6>;
-    case 256: return &scan_own_kernel<8>;
+    case 64: return &scan_own_kernel<2, SAMP>;
+    case 96: return &scan_own_kernel<3, SAMP>;
+    case 128: return &scan_own_kernel<4, SAMP>;
+    case 192: return &scan_own_kernel<6, SAMP>;
+    case 256: return &scan_own_kernel<8, SAMP>;
     default: return nullptr;
     }
 }
+inline auto own_kernel(int d, bool sample = false) -> decltype(&scan_own_kernel<8, true>) { return sample ? own_kernel<true>(d) : own_kernel<false>(d); }
 inline auto own_first_kernel(int d) -> decltype(&scan_own_first_kernel<8>)
 {
     switch (d) {

@@ -84,10 +84,10 @@ __global__ __launch_bounds__(kScanThreads) void scan_wavedot_kernel(ScanParams p
     const int seg_words = p.seg_items >> 6;
     const int64_t n_seg = (p.item_end - p.item_begin + p.seg_items - 1) / p.seg_items;
     const int64_t n_visit = (n_seg + p.seg_per_visit - 1) / p.seg_per_visit;
-    const int64_t item_lim = p.item_end < p.n_items ? p.item_end : p.n_items;
+    const int64_t item_lim = p.item_end < p.n_items && p.samp_role != 1 ? p.item_end : p.n_items;
     for (int64_t vs = blockIdx.x; vs < n_visit; vs += gridDim.x)
       for (int64_t seg = vs * p.seg_per_visit; seg < (vs + 1) * p.seg_per_visit && seg < n_seg; ++seg) {
-        const int64_t item0 = p.item_begin + seg * p.seg_items;
+        const int64_t item0 = p.samp_role == 1 ? seg * p.samp_stride_items : p.item_begin + seg * p.seg_items;
         const int64_t word0 = item0 >> 6;
         for (int g0 = 0; g0 < p.n_groups; g0 += kFilterBatch) {
             const int nf = min(kFilterBatch, p.n_groups - g0);

@@ -447,6 +447,26 @@ def test_scores_along_a_trend_keep_the_fast_path_where_the_first_level_is_a_samp
     assert np.mean(ids[::16] < prefix) > 2.5 * prefix / n
 
 
+# ... and batches that the scan for filters of their own serves alone: groups of several queries, no two queries of one filter,
+# several rows of the grid, and a K whose first level has regions of 128 items (taken by the dot-product scorer).
+@pytest.mark.parametrize("n,d,B,groups,K", [(400_000, 128, 192, 32, 500), (400_001, 256, 150, 150, 300), (500_003, 64, 440, 64, 200),
+                                            (1_000_000, 96, 20, 20, 33_000)])
+def test_scores_along_a_trend_keep_the_fast_path_with_many_filters(n, d, B, groups, K):
+    w = ragged_workload(n, n, d, B, 40, 30, 256, 1)
+    w.item_scale = (4.0 * torch.exp(-3.0 * torch.arange(n, dtype=torch.float32) / n)).contiguous()
+    pool = [(g % 40, (g * 7 + 1 + g // 40) % 40) for g in range(groups)]
+    filters = [pool[b % groups] for b in range(B)]
+    w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
+    w.filt_offsets = np.arange(0, 2 * B + 1, 2).astype(np.int64)
+    summary = st.st_search_host_plan(n, d, B, 1, K, 256, 1, w.filt_ids, w.filt_offsets)
+    assert summary["mfma_groups"] == 0 and summary["seed_pass"] == 0 and summary["levels"] >= 2
+    some = range(0, B, max(1, B // 10))
+    ids, _, count = check_search(w, K, queries=some, label="scores along a trend, filters of their own", slow_path=([], list(range(B))))
+    assert (count == K).all()
+    prefix = int(st.st_search_plan(n, B, K)[0][0, 1])  # of a first level that is none of a sample
+    assert np.mean(ids[list(some)] < prefix) > 1.8 * prefix / n
+
+
 def test_hot_items_exactly_where_the_seed_pass_looks_defeat_it_and_take_the_exact_slow_path():
     # Small batches take their first threshold from the seed pass over 512 words of 64 items spread
     # evenly over the corpus, and that threshold too is tighter than the K-th best of what the pass
