@@ -20,8 +20,16 @@
 //   u * g >= U * g1 + (U >> 7) * r + ((U & 127) >> 3) * (r >> 4) + f * (g1 >> 4)
 // The first term takes 28 digits (U dealt out evenly over them), each of the others one.  Items with 1 / s_i above H count as if it
 // were H: a lower bound than theirs, which lets more pairs through.  H is the largest 1 / s_i of a sample of the items,
-// less if the largest u would not fit: 28 * 127 * 128 = 455,168 is as large as a bound gets.  Relative
+// less if the largest u would not fit: 28 * 127 * 128 = 455,168 is as large as the digits' product gets.  Relative
 // error of the bound below 2 % for U from 128 on and g from 32 on (tests/test_admission_bound.py).
+//
+// Bounds above that.  Rows with a common mean have dot products, and with them bounds, far beyond 455,168 (rows of 256 bytes
+// that fill the int8 range, with a mean cosine of 0.7 between them: 1 M).  H is lowered for want of room then, all bounds stop at
+// 455,168 or the query's share of it, and most pairs pass them.  So a part of the bound that all items of a unit share comes first: h is
+// 1 / (the unit's largest s_i), the accumulators start at -base with base <= (tau / s_q) * h, a number of the query
+// and the unit, and the items' digits are those of 1 / s_i - h.  An item's bound is then below T only where 1 / s_i
+// exceeds h + H.  Units whose item of the largest scale needs a dot product of no more than 0.909 * 455,168 have no shared part: there a
+// bound that stops at the limit cuts nearly all pairs, too, and the starting values cost some 4 % of a call.
 #pragma once
 #include <stdint.h>
 
@@ -39,6 +47,10 @@ constexpr int kSliceSlots = 28;                             // digits of the fir
 constexpr int kSliceTop = kSliceSlots * 127 * 16 + 15;      // largest u, in sixteenths
 constexpr float kSliceSlack = 0.99951171875f;               // 1 - 2^-11: more than all roundings of either number
 
+// Whether the digits' range does not do for the largest 1 / s_i of the sample and the largest tau / s_q.
+constexpr bool slice_wide(float h_max, float tq_max) { return h_max * (tq_max / 455168.0f) > 1.0f; }
+// Units whose largest scale is below this one have a shared part then.
+constexpr float slice_shared_below(float tq_max) { return tq_max / (455168.0f * 0.909f); }
 // H from the largest 1 / s_i of the sample (0: none is usable) and the largest tau / s_q (0: none).
 constexpr float slice_ref(float h_max, float tq_max)
 {
@@ -58,6 +70,19 @@ constexpr int slice_item(float inv, float factor)
 {
     const float g = inv * factor;
     return g > 0.0f ? g < 16383.0f ? (int)g : 16383 : 0;
+}
+// h from the unit's largest scale (0: no shared part), which is below 2^90.
+constexpr float slice_shared(float inv_top) { return inv_top < 0x1p90f ? inv_top : 0x1p90f; }
+// The part of a unit's bounds that its items share: of a query's u and 8 * h / H, rounded down (2^23 is above any dot product).
+constexpr float slice_base_factor(float h, float factor)
+{
+    const float f = h * (factor * 0x1p-11f);
+    return f < 0x1p24f ? f : 0x1p24f;
+}
+constexpr int slice_base(int u, float base_factor)
+{
+    const float b = (float)u * base_factor;
+    return b < 0x1p23f ? (int)b : 1 << 23;
 }
 // The slices' inner product.
 constexpr int slice_bound(int u, int g)

@@ -13,7 +13,8 @@
 // longer than the products).  A mask word is what the unit needs for one query: lane l of a product's result holds query l % 32,
 // and 16 items of each of the two halves of 32.  The bound is part of the product (the slices of st_bound.h), so that the
 // signs of the results are the tests: one instruction to a pair takes them to the bits of its item, where the
-// mask word is.  Pairs left are queued with their results; dot product, exact score, key and
+// mask word is.  (Where bounds are larger than digits can say, the accumulators start at a part of them: one branch to a block.  3 M x
+// 256, 256 queries, rows with a mean cosine of 0.5: 599 -> 345 us a call; 472 with a multiply-add for every pair.)  Pairs left are queued with their results; dot product, exact score, key and
 // threshold test follow where the queue is emptied, 64 pairs at a time.  A block's operands are read while the results of the one
 // before are tested, and an operand serves both halves.
 // The queries lie in LDS with 16 bytes of padding a row (an odd number of 16-byte pieces: no bank conflicts).
@@ -99,6 +100,15 @@ struct SampleWords {
         return no + min(i + 1u, segs) * taken;
     }
 };
+
+// A value that the compiler takes for a new one: what is formed from it is formed here, and no register holds it from
+// outside a loop on.
+template <class V>
+__device__ inline V fresh(V v)
+{
+    asm volatile("" : "+v"(v));
+    return v;
+}
 
 // d = 32 * KS.  Grid (workgroups, own_grid_rows(queries)).  One
 // workgroup to a compute unit is resident (registers), so that many are launched and each takes several
@@ -282,8 +292,10 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     uint32_t inv_top = 0xFFFFFFFFu;  // the smallest of the wavefronts' largest ones: a few odd scales do not count
 #pragma unroll
     for (int w = 0; w < 8; ++w) inv_top = min(inv_top, s_max[w] ? s_max[w] : 0xFFFFFFFFu);
-    const float ref = slice_ref(inv_top != 0xFFFFFFFFu ? __uint_as_float(inv_top) : 0.0f, __uint_as_float(s_max[8]));
-    const float factor = slice_factor(ref);
+    const float h_max = inv_top != 0xFFFFFFFFu ? __uint_as_float(inv_top) : 0.0f, tq_max = __uint_as_float(s_max[8]);
+    const float ref = slice_ref(h_max, tq_max), factor = slice_factor(ref);
+    const float shared_below = slice_wide(h_max, tq_max) ? slice_shared_below(tq_max) : 0.0f;
+    const bool wide = __builtin_amdgcn_readfirstlane(__float_as_int(shared_below)) != 0;
     if (tid < cols) {
         const int u = tq > 0.0f ? slice_query(tq, ref) : 0;
         const bool none = own_q >= 0 && !(tq > 0.0f);
@@ -349,12 +361,14 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
         if (n < (uint32_t)p.cap)
             p.cand[((int64_t)s_query[c] * p.groups + (int)blockIdx.x + sl_no * (int)gridDim.x) * p.cap + n] = key;
     };
+    // (of a unit's largest scale, as a bit pattern; 0: none)
+    auto shared = [](uint32_t top_scale) { return top_scale ? slice_shared(__builtin_amdgcn_rcpf(__uint_as_float(top_scale))) : 0.0f; };
     auto drain = [&]() __attribute__((always_inline)) {
         if (lane < qn) {
             const int4 e = queue[lane];
-            const int c = e.z & 255, u16 = s_u[c];
-            const float s_i = p.iscale[(uint32_t)e.y];
-            const int dot = e.x + slice_bound(u16 == kNoBound ? 0 : u16, slice_item(__builtin_amdgcn_rcpf(s_i), factor));
+            const int c = e.z & 255, u = s_u[c] == kNoBound ? 0 : s_u[c];
+            const float s_i = p.iscale[(uint32_t)e.y], h = shared((uint32_t)e.w);
+            const int dot = e.x + slice_base(u, slice_base_factor(h, factor)) + slice_bound(u, slice_item(__builtin_amdgcn_rcpf(s_i) - h, factor));
             const uint64_t key = make_key(rescale(dot, s_sq[c], s_i), (uint32_t)e.y);
             if (key >= s_tau[c]) admit(key, c, e.z >> 8);
         }
@@ -461,7 +475,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                 gather(whole);
                 const uint2 rest = s_pairs[min(whole + lane, kOwnPairs - 1)];
                 pn -= whole;
-                if (lane < pn) s_pairs[lane] = rest;
+                if (lane < pn) s_pairs[fresh(lane)] = rest;
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
             }
             my0 = next0;
@@ -480,7 +494,12 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                 if (lane + u * 64 < cols) s_mask[lane + u * 64] = m[u];
             // The scales, and the items' slices: half a slice to a lane, as the operand has it.
             const bool odd = ballot(!(si >= 0.0f && si < 0x1p90f)) != 0;  // (outside the range that has bounds: all pairs of these items are tested exactly)
-            const int g = slice_item(__builtin_amdgcn_rcpf(si), factor);
+            uint32_t top_scale = 0;  // the largest one as a bit pattern, where a part of the bounds is shared
+            if (wide && !odd) {
+                const uint32_t top = lane_value(wave_max_u32(__float_as_uint(si) & 0x7FFFFFFFu), 63);
+                if (__uint_as_float(top) < shared_below) top_scale = top;
+            }
+            const int g = slice_item(__builtin_amdgcn_rcpf(si) - shared(top_scale), factor);
             own_i4 sl[2];
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
@@ -496,13 +515,22 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                 for (int k = 0; k <= KS; ++k) q[k] = qr[2 * k];
             };
             own_i16 acc[2];
-            auto products = [&]() __attribute__((always_inline)) {
+            auto products = [&](int b) __attribute__((always_inline)) {
+                own_i16 from;
+                auto first = [&](int start) __attribute__((always_inline)) {
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
+                    for (int i = 0; i < 16; ++i) from[i] = start;
 #pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[s][i] = 0;
+                    for (int s = 0; s < 2; ++s) acc[s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[s][0], q[0], from, 0, 0, 0);
+                };
+                if (top_scale) {  // (otherwise the instructions start at a constant 0)
+                    const int u = s_u[fresh(b + (lane & 31))];
+                    first(u == kNoBound ? 0 : -slice_base(u, slice_base_factor(shared(top_scale), factor)));
+                } else {
+                    first(0);
+                }
 #pragma unroll
-                for (int k = 0; k <= KS; ++k)
+                for (int k = 1; k <= KS; ++k)
 #pragma unroll
                     for (int s = 0; s < 2; ++s) acc[s] = __builtin_amdgcn_mfma_i32_32x32x32_i8(k < KS ? a[s][k < KS ? k : 0] : sl[s], q[k], acc[s], 0, 0, 0);
             };
@@ -547,7 +575,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                         for (int i = 0; i < 2; ++i) v[i] = pick(b3, v[2 * i + 1], v[2 * i]);
                         const int at_item = (bit & 27) + 8 * (bit & 4) + 4 * half;
                         const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
-                        queue[qn + rank] = make_int4(pick(b4, v[1], v[0]), (int)((uint32_t)my0 + (uint32_t)at_item), c | slot << 8, 0);
+                        queue[qn + rank] = make_int4(pick(b4, v[1], v[0]), (int)((uint32_t)my0 + (uint32_t)at_item), c | slot << 8, (int)top_scale);
                     }
                     qn = __builtin_amdgcn_readfirstlane(qn + n);
                 }
@@ -557,14 +585,14 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
             // what is older is none for them.
             operands(0);
             uint64_t word = s_mask[lane & 31];
-            products();
+            products(0);
             if (next0 >= 0 && !short_unit) fetch(next0);
             for (int b = 32; b < n_blk; b += 32) {
                 operands(b);
                 const uint64_t next_word = s_mask[b + (lane & 31)];
                 test(b - 32, word);
                 word = next_word;
-                products();
+                products(b);
             }
             rows(next0 >= 0 ? next0 : my0);  // (without a condition: one would turn the wait for the index words into one for the rows)
             test(n_blk - 32, word);

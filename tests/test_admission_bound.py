@@ -149,3 +149,90 @@ def test_the_products_bound_lies_just_below_the_threshold(tmp_path):
     run = subprocess.run([exe], capture_output=True, text=True, timeout=240)
     assert run.returncode == 0, run.stdout + run.stderr
     assert int(run.stdout.split()[1]) > 50_000, run.stdout  # most of what is tested has both numbers in their good range
+
+
+_SHARED = r"""
+#include <algorithm>
+#include <cmath>
+#include <cstdint>
+#include <cstdio>
+#include <random>
+#include <vector>
+#include "st_bound.h"
+
+int main()
+{
+    std::mt19937_64 rng(11);
+    auto uni = [&](double a, double b) { return a + (b - a) * (double)(rng() >> 11) * 0x1p-53; };
+    // the two parts together: never above tau / s_q / s_i, for scales up to the unit's largest one, whatever the reference
+    for (int it = 0; it < 2000000; ++it) {
+        const float top = (float)std::exp2(uni(-100, 89)), si = it % 4 ? top * (float)uni(0.01, 1) : top * (float)std::exp2(uni(-40, 0));
+        const float tq = (float)std::exp2(uni(0, 23)) * si;
+        if (!(tq > 0x1p-126f) || std::isinf(tq) || !(si > 0)) continue;
+        const float ref = st::slice_ref(it % 3 ? (float)(uni(0.2, 4) / si) : (float)std::exp2(uni(-100, 100)), tq * (float)uni(1, 30)), factor = st::slice_factor(ref);
+        const int u = st::slice_query(tq, ref);
+        // (a reciprocal within one unit of its last place)
+        const float off[3] = {1.0f - 0x1p-23f, 1.0f, 1.0f + 0x1p-23f};
+        const float h = st::slice_shared(1.0f / top * off[it % 3]), inv = 1.0f / si * off[it / 3 % 3];
+        const int g = st::slice_item(inv - h, factor), base = st::slice_base(u, st::slice_base_factor(h, factor));
+        if (base < 0 || base > 1 << 23 || g < 0 || g > 16383) return std::printf("range: base=%d g=%d\n", base, g), 1;
+        const double exact = (double)tq / si, bound = (double)base + st::slice_bound(u, g);
+        if (bound > exact * (1 - 0x1p-18)) return std::printf("above: top=%a si=%a tq=%a ref=%a bound=%g exact=%g\n", top, si, tq, ref, bound, exact), 1;
+    }
+    // how much is let through: rows with a common mean, units of 64 items, thresholds at the 40th of 6,400 items
+    for (int form = 0; form < 6; ++form) {
+        const int d = form % 2 ? 128 : 256, n = 6400, n_q = 12;
+        const double c = form < 2 ? 0.5 : 0.75;
+        const bool same = form >= 4;  // all scales alike, as of a table that was quantised with one
+        std::vector<int> mu(d), x((size_t)n * d), q((size_t)n_q * d);
+        auto row = [&](int* to) {
+            for (int i = 0; i < d; ++i) to[i] = (int)std::lrint(std::max(-127.0, std::min(127.0, std::sqrt(c) * mu[i] + std::sqrt(1 - c) * uni(-127, 127))));
+        };
+        for (int& v : mu) v = (int)uni(-127, 127);
+        for (int i = 0; i < n; ++i) row(&x[(size_t)i * d]);
+        for (int i = 0; i < n_q; ++i) row(&q[(size_t)i * d]);
+        std::vector<float> si(n);
+        for (float& s : si) s = same ? 0.01f : (float)uni(0.5, 1.5);
+        std::vector<std::vector<int>> dot(n_q, std::vector<int>(n));
+        std::vector<float> tq(n_q);
+        for (int j = 0; j < n_q; ++j) {
+            std::vector<float> sc(n);
+            for (int i = 0; i < n; ++i) {
+                int a = 0;
+                for (int t = 0; t < d; ++t) a += x[(size_t)i * d + t] * q[(size_t)j * d + t];
+                dot[j][i] = a;
+                sc[i] = (float)a * si[i];
+            }
+            std::nth_element(sc.begin(), sc.begin() + 40, sc.end(), std::greater<float>());
+            tq[j] = sc[40];
+        }
+        const float h_max = 1.0f / *std::min_element(si.begin(), si.end()), tq_max = *std::max_element(tq.begin(), tq.end());
+        const float ref = st::slice_ref(h_max, tq_max), factor = st::slice_factor(ref);
+        const float below = st::slice_wide(h_max, tq_max) ? st::slice_shared_below(tq_max) : 0.0f;
+        long through = 0, units = 0;
+        for (int i0 = 0; i0 < n; i0 += 64) {
+            const float top = *std::max_element(si.begin() + i0, si.begin() + i0 + 64), h = top < below ? st::slice_shared(1.0f / top) : 0.0f;
+            units += h > 0;
+            for (int j = 0; j < n_q; ++j) {
+                const int u = st::slice_query(tq[j], ref), base = st::slice_base(u, st::slice_base_factor(h, factor));
+                for (int i = i0; i < i0 + 64; ++i) through += dot[j][i] >= base + st::slice_bound(u, st::slice_item(1.0f / si[i] - h, factor));
+            }
+        }
+        std::printf("d %d mean %.2f: %.4f of the pairs, %ld units with a shared part\n", d, c, (double)through / n / n_q, units);
+        if (through > n / 50 * n_q || (d == 256 && units == 0)) return 1;  // 0.6 % reach the threshold
+    }
+    return 0;
+}
+"""
+
+
+def test_bounds_beyond_the_digits_range_hold_and_cut(tmp_path):
+    cxx = shutil.which("g++")
+    if cxx is None:
+        pytest.skip("no host C++ compiler")
+    src, exe = tmp_path / "shared.cpp", str(tmp_path / "shared")
+    src.write_text(_SHARED)
+    built = subprocess.run([cxx, "-std=c++17", "-O1", "-ffp-contract=off", "-I", CSRC, str(src), "-o", exe], capture_output=True, text=True)
+    assert built.returncode == 0, built.stderr
+    run = subprocess.run([exe], capture_output=True, text=True, timeout=240)
+    assert run.returncode == 0, run.stdout + run.stderr

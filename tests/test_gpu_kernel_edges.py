@@ -249,7 +249,8 @@ def test_freed_index_memory_goes_back_to_the_driver():
 # and word, few and many signature rows, no filter, filters that pass 10 %, 1 % and nothing, tied scores; a corpus whose
 # filters pass everything in some stretches and nothing in others (wavefronts change between the two forms), and
 # no filter at all (no signature row is named); scales of many sizes (a wavefront's bounds move as it meets larger ones), some
-# words of items beyond those that a bound is formed for, scores that are all negative (no bound).  The last selection would make good for lost candidates, so no
+# words of items beyond those that a bound is formed for, scores that are all negative (no bound), rows with a common mean, whose
+# bounds are beyond the digits' range (scales of one size, and some ten times as large).  The last selection would make good for lost candidates, so no
 # query that passes enough items may have needed that.
 @pytest.mark.parametrize("n,d,B,m,kind", [(600_001, 64, 16, 64, "mixed"), (530_049, 96, 33, 100, "mixed"),
                                           (400_003, 128, 130, 512, "mixed"), (524_288 + 31, 192, 40, 257, "mixed"),
@@ -264,7 +265,9 @@ def test_freed_index_memory_goes_back_to_the_driver():
                                           (330_000, 64, 24, 257, "negative"), (310_017, 128, 17, 128, "beyond"),
                                           (300_011, 192, 16, 64, "scales"), (320_009, 256, 32, 128, "mixed"),
                                           (300_000, 128, 257, 128, "stretches"), (310_001, 64, 641, 300, "mixed"),
-                                          (400_009, 256, 225, 512, "rare"), (300_007, 192, 65, 64, "outliers")])
+                                          (400_009, 256, 225, 512, "rare"), (300_007, 192, 65, 64, "outliers"),
+                                          (300_001, 256, 130, 128, "mean"), (330_031, 128, 40, 64, "mean"), (300_007, 64, 20, 300, "mean"),
+                                          (310_003, 192, 200, 64, "mean, large scales"), (340_009, 96, 70, 128, "mean, large scales")])
 def test_own_filters(n, d, B, m, kind):
     w = ragged_workload(n, n, d, B, 40, 8, m, 3)
     filters = []
@@ -293,6 +296,14 @@ def test_own_filters(n, d, B, m, kind):
         w.item_scale = torch.from_numpy(np.exp2(rng.uniform(lo, hi)).astype(np.float32))
     elif kind == "outliers":  # a twentieth of the items far below the others' scales: the bounds' reference is not theirs
         w.item_scale = torch.from_numpy(np.where(np.random.default_rng(n).random(n) < 0.05, 1e-6, 1.0).astype(np.float32)) * w.item_scale
+    elif kind.startswith("mean"):
+        rng = np.random.default_rng(n)
+        mu = rng.uniform(-127, 127, d)
+        def rows(r):
+            return torch.from_numpy((0.85 * mu + 0.5 * rng.uniform(-127, 127, (r, d))).round().clip(-127, 127).astype(np.int8))
+        w.items, w.queries = rows(n), rows(B).view(w.queries.shape)
+        if kind != "mean":
+            w.item_scale = torch.from_numpy(np.where(rng.random(n) < 0.003, 10.0, 1.0).astype(np.float32)) * w.item_scale
     elif kind == "negative":
         w.items = w.items.abs().clamp(1, 127).to(torch.int8)
         w.queries = (-w.queries.abs().clamp(1, 127).to(torch.int16)).to(torch.int8)
