@@ -160,24 +160,26 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
         s_max[12] = kOwnWords;
     }
     own_barrier();  // (s_max, s_bits)
-    // Units of 64 items: the words of the segments of this workgroup's regions, drawn by the wavefronts from a counter in
-    // LDS (tied to a segment, or to a region at a time, they waited a sixth to a half of the time for the slowest of them).
-    const int spv = p.seg_per_visit;
+    // Units of 64 items, drawn by the wavefronts from a counter in LDS (tied to a segment, or to a region at a time, they waited a
+    // sixth to a half of the time for the slowest of them).  The words of the level go to the workgroups in rounds, a visit of
+    // seg_per_visit segments to each, whose candidates go to its regions in turn; the words behind the last whole round are dealt
+    // evenly (as visits they made some workgroups wait for others: 1.65 M x 96, 200 queries: 168.7 -> 151.2 us, 2 M x 64, 16: 79.5 -> 73.7,
+    // 10 M x 256, 256: 944 -> 914).
+    const int spv = p.seg_per_visit, visit = spv * kOwnWords, wgs = (int)gridDim.x;
     const SampleWords samp(p);
     const int first_word = (int)(SAMP ? samp.others_before((uint32_t)(p.item_begin >> 6)) : (uint32_t)(p.item_begin >> 6));
     const int end_word = (int)(SAMP ? samp.others_before((uint32_t)((p.item_end + 63) >> 6)) : (uint32_t)((p.item_end + 63) >> 6));
-    const int n_seg = (end_word - first_word + kOwnWords - 1) / kOwnWords, n_visit = (n_seg + spv - 1) / spv;
-    const int slots = (p.groups - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-    const int n_units = (n_visit + p.groups - 1) / p.groups * slots * spv * kOwnWords;
+    const int slots = (p.groups - (int)blockIdx.x + wgs - 1) / wgs;
+    const int n_rounds = (end_word - first_word) / (wgs * visit), last_word = first_word + n_rounds * wgs * visit, dealt = (end_word - last_word + wgs - 1) / wgs;
+    const int n_units = n_rounds * visit + dealt;
     const int64_t item_lim = p.item_end < p.n_items ? p.item_end : p.n_items;
-    // (first item and region slot of a unit; the last round of visits does not reach all regions, nor the last segment all words: negative)
+    // (first item and region slot of a unit; negative: the workgroups at the end may have fewer)
     const uint32_t per_spv = 0xFFFFFFFFu / (uint32_t)spv + 1u, per_slots = 0xFFFFFFFFu / (uint32_t)slots + 1u;  // (0 for 1)
     auto unit_at = [&](int unit, int& slot) -> int64_t {
-        const int t = unit / kOwnWords, i = spv == 1 ? t : (int)__umulhi((uint32_t)t, per_spv);  // (divisors up to four, below 2^29)
-        const int round = slots == 1 ? i : (int)__umulhi((uint32_t)i, per_slots);
-        slot = i - round * slots;
-        const int visit = (int)blockIdx.x + slot * (int)gridDim.x + round * p.groups, seg = visit * spv + (t - i * spv);
-        const int word = first_word + seg * kOwnWords + (unit & (kOwnWords - 1));
+        const int t = unit / kOwnWords, round = spv == 1 ? t : (int)__umulhi((uint32_t)t, per_spv);  // (divisors up to four, below 2^29)
+        slot = slots == 1 ? 0 : round - (int)__umulhi((uint32_t)round, per_slots) * slots;
+        const int in = unit - round * visit;
+        const int word = round < n_rounds ? first_word + (round * wgs + (int)blockIdx.x) * visit + in : last_word + (int)blockIdx.x * dealt + in;
         if (word >= end_word) return -1;
         return (int64_t)(SAMP ? samp.other((uint32_t)word) : (uint32_t)word) << 6;
     };
