@@ -357,8 +357,12 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     }
     rn_max = (int)lane_value(wave_max_u32((uint32_t)rn_max), 63);
     if (my0 >= 0) fetch(my0);
-    // Pairs that may be admissible: dot product less its bound, item, and column with region slot.  The exact test
-    // runs where the queue is emptied.
+    // Pairs that may be admissible, for the exact test.  LIST: items, and columns with region slots, in one list for a wavefront that
+    // multiplies and one that gathers, and their rows are read again.  Otherwise a wavefront that multiplies has a queue of dot products
+    // less their bounds, items and columns: to pick the result takes some 45 instructions to a pair of each lane, which a product
+    // of rows of 192 or 256 bytes covers (with the list there, 1 M x 192, 100 queries, scales of many sizes: 144 -> 157 us; 10 M x 256,
+    // 256: 918 -> 930) and one of shorter rows does not (1.26 M x 96, 238 queries: 133.5 -> 129.6; 1.65 M x 96, 200: 151.6 -> 146.7; 2 M x 64, 256: 196 -> 185).
+    constexpr bool LIST = KS <= 4;
     int qn = 0;
     auto admit = [&](uint64_t key, int c, int sl_no) __attribute__((always_inline)) {
         const uint32_t n = atomicAdd(&s_cnt[sl_no * cols + c], 1u);
@@ -376,47 +380,56 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
             const uint64_t key = make_key(rescale(dot, s_sq[c], s_i), (uint32_t)e.y);
             if (key >= s_tau[c]) admit(key, c, e.z >> 8);
         }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");  // (what is written here next may be of the list, another type)
         qn = 0;
     };
-    // Pairs of a wavefront that gathers, from one unit after the other until there are enough: their rows, kGl lanes to a
-    // row, so that a load takes whole lines (a lane to a row takes four times as many), and the exact test.
+    // The list goes from one unit to the next until there are 64 pairs.  Their rows come kGl lanes to a row, so that a load takes whole
+    // lines (a lane to a row takes four times as many).
     int pn = 0;
-    auto gather = [&](int total) __attribute__((always_inline)) {
-        constexpr int kPer = D % 96 == 0 ? 3 : 1, kGl = D / 16 / kPer, kGp = 64 / kGl;  // (pieces of a row to a lane, lanes to a row, rows to a load)
+    constexpr int kPer = D % 96 == 0 ? 3 : 1, kGl = D / 16 / kPer, kGp = 64 / kGl;  // (pieces of a row to a lane, lanes to a row, rows to a load)
+    auto gather = [&](int k0, int n) __attribute__((always_inline)) {
         const int piece = lane & (kGl - 1), in_load = lane / kGl;
-        for (int k0 = 0; k0 < total; k0 += 64) {
-            const int n = min(total - k0, 64);
-            // (the pair whose result this lane keeps)
-            const int my_pair = piece * kGp + in_load;
-            const uint2 mine = s_pairs[k0 + min(my_pair, n - 1)];
-            const float my_si = p.iscale[mine.x];
-            int4 v[kGl][kPer];
+        // (the pair whose result this lane keeps)
+        const int my_pair = piece * kGp + in_load;
+        const uint2 mine = s_pairs[k0 + min(my_pair, n - 1)];
+        const float my_si = p.iscale[mine.x];
+        int4 v[kGl][kPer];
 #pragma unroll
-            for (int j = 0; j < kGl; ++j) {
-                const int4* row = reinterpret_cast<const int4*>(p.items + (int64_t)s_pairs[k0 + min(j * kGp + in_load, n - 1)].x * D) + piece;
+        for (int j = 0; j < kGl; ++j) {
+            const int4* row = reinterpret_cast<const int4*>(p.items + (int64_t)s_pairs[k0 + min(j * kGp + in_load, n - 1)].x * D) + piece;
 #pragma unroll
-                for (int t = 0; t < kPer; ++t) v[j][t] = row[t * kGl];
-            }
-            int my_dot = 0;
-#pragma unroll
-            for (int j = 0; j < kGl; ++j) {
-                const int c = (int)(s_pairs[k0 + min(j * kGp + in_load, n - 1)].y & 255u);
-                const int4* qr = reinterpret_cast<const int4*>(s_q + c * DP) + piece;
-                int dot = 0;
-#pragma unroll
-                for (int t = 0; t < kPer; ++t) dot = dot16(v[j][t], qr[t * kGl], dot);
-                dot += __builtin_amdgcn_update_dpp(0, dot, 0xB1, 0xF, 0xF, false);                // lanes 1, 0, 3, 2 of four
-                if (kGl > 2) dot += __builtin_amdgcn_update_dpp(0, dot, 0x4E, 0xF, 0xF, false);   // lanes 2, 3, 0, 1
-                if (kGl > 4) dot += __builtin_amdgcn_update_dpp(0, dot, 0x141, 0xF, 0xF, false);  // eight lanes mirrored
-                if (kGl > 8) dot += __builtin_amdgcn_update_dpp(0, dot, 0x140, 0xF, 0xF, false);  // sixteen
-                if (piece == j) my_dot = dot;
-            }
-            if (my_pair < n) {
-                const int c = (int)(mine.y & 255u);
-                const uint64_t key = make_key(rescale(my_dot, s_sq[c], my_si), mine.x);
-                if (key >= s_tau[c]) admit(key, c, (int)(mine.y >> 8));
-            }
+            for (int t = 0; t < kPer; ++t) v[j][t] = row[t * kGl];
         }
+        int my_dot = 0;
+#pragma unroll
+        for (int j = 0; j < kGl; ++j) {
+            const int c = (int)(s_pairs[k0 + min(j * kGp + in_load, n - 1)].y & 255u);
+            const int4* qr = reinterpret_cast<const int4*>(s_q + c * DP) + piece;
+            int dot = 0;
+#pragma unroll
+            for (int t = 0; t < kPer; ++t) dot = dot16(v[j][t], qr[t * kGl], dot);
+            dot += __builtin_amdgcn_update_dpp(0, dot, 0xB1, 0xF, 0xF, false);                // lanes 1, 0, 3, 2 of four
+            if (kGl > 2) dot += __builtin_amdgcn_update_dpp(0, dot, 0x4E, 0xF, 0xF, false);   // lanes 2, 3, 0, 1
+            if (kGl > 4) dot += __builtin_amdgcn_update_dpp(0, dot, 0x141, 0xF, 0xF, false);  // eight lanes mirrored
+            if (kGl > 8) dot += __builtin_amdgcn_update_dpp(0, dot, 0x140, 0xF, 0xF, false);  // sixteen
+            if (piece == j) my_dot = dot;
+        }
+        if (my_pair < n) {
+            const int c = (int)(mine.y & 255u);
+            const uint64_t key = make_key(rescale(my_dot, s_sq[c], my_si), mine.x);
+            if (key >= s_tau[c]) admit(key, c, (int)(mine.y >> 8));
+        }
+    };
+    // ... all whole rounds of the list, what is left goes to its front
+    auto rounds = [&]() __attribute__((always_inline)) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        if (pn < 64) return;
+        const int whole = pn & ~63;
+        for (int k0 = 0; k0 < whole; k0 += 64) gather(k0, 64);
+        const uint2 rest = s_pairs[min(whole + lane, kOwnPairs - 1)];
+        pn -= whole;
+        if (lane < pn) s_pairs[fresh(lane)] = rest;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
     };
     // A unit's masks, of all filters: the words of four columns to a lane, so that a step's reads do not wait for each other.
     // Also draws the next unit, and brings this one's index words to LDS.
@@ -464,7 +477,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     while (my0 >= 0) {
         if (total <= (uint32_t)own_few(cols)) {
             if (next0 >= 0 && !short_unit) fetch(next0);
-            if (qn > 0) drain();
+            if (!LIST && qn > 0) drain();
             uint32_t pos = (uint32_t)pn + before;
 #pragma unroll
             for (int u = 0; u < kOwnCols / 64; ++u)
@@ -473,23 +486,15 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                     m[u] &= m[u] - 1;
                     s_pairs[pos++] = make_uint2((uint32_t)my0 + (uint32_t)bit, (uint32_t)(lane + u * 64) | (uint32_t)slot << 8);
                 }
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
             pn = __builtin_amdgcn_readfirstlane(pn + (int)total);
-            if (pn >= 64) {
-                const int whole = pn & ~63;
-                gather(whole);
-                const uint2 rest = s_pairs[min(whole + lane, kOwnPairs - 1)];
-                pn -= whole;
-                if (lane < pn) s_pairs[fresh(lane)] = rest;
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-            }
+            rounds();
             my0 = next0;
             slot = next_slot;
             if (my0 >= 0) masks();
             continue;
         }
-        if (pn > 0) {
-            gather(pn);
+        if (!LIST && pn > 0) {  // (the queue lies where the list does)
+            gather(0, pn);
             pn = 0;
         }
         rows(my0);
@@ -561,28 +566,35 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
                 uint32_t over = pass & ~((below[0] | below[1] << 4) & keep);
                 uint64_t hits;
                 while ((hits = ballot(over != 0)) != 0) {  // (as a rule one pair to a lane)
-                    const int n = __popcll(hits);
-                    if (qn + n > kOwnQueue) drain();
+                    const int n = __popcll(hits), rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
+                    if (!LIST && qn + n > kOwnQueue) drain();
                     if (over != 0) {
-                        const int bit = __ffs((int)over) - 1;
+                        const int bit = __ffs((int)over) - 1, at_item = (bit & 27) + 8 * (bit & 4) + 4 * half;
                         over &= over - 1;
-                        // (by masks: choices by a condition become an access indexed by the lane, in private memory)
-                        const int b0 = -(bit & 1), b1 = -(bit >> 1 & 1), b2 = -(bit >> 2 & 1), b3 = -(bit >> 3 & 1), b4 = -(bit >> 4 & 1);
-                        auto pick = [](int m, int x, int y) { return (x & m) | (y & ~m); };
-                        int v[16];
+                        if constexpr (LIST) {
+                            s_pairs[pn + rank] = make_uint2((uint32_t)my0 + (uint32_t)at_item, (uint32_t)(c | slot << 8));
+                        } else {
+                            // (by masks: choices by a condition become an access indexed by the lane, in private memory)
+                            const int b0 = -(bit & 1), b1 = -(bit >> 1 & 1), b2 = -(bit >> 2 & 1), b3 = -(bit >> 3 & 1), b4 = -(bit >> 4 & 1);
+                            auto pick = [](int m, int x, int y) { return (x & m) | (y & ~m); };
+                            int v[16];
 #pragma unroll
-                        for (int i = 0; i < 16; ++i) v[i] = pick(b2, acc[1][i], acc[0][i]);
+                            for (int i = 0; i < 16; ++i) v[i] = pick(b2, acc[1][i], acc[0][i]);
 #pragma unroll
-                        for (int i = 0; i < 8; ++i) v[i] = pick(b0, v[2 * i + 1], v[2 * i]);
+                            for (int i = 0; i < 8; ++i) v[i] = pick(b0, v[2 * i + 1], v[2 * i]);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) v[i] = pick(b1, v[2 * i + 1], v[2 * i]);
+                            for (int i = 0; i < 4; ++i) v[i] = pick(b1, v[2 * i + 1], v[2 * i]);
 #pragma unroll
-                        for (int i = 0; i < 2; ++i) v[i] = pick(b3, v[2 * i + 1], v[2 * i]);
-                        const int at_item = (bit & 27) + 8 * (bit & 4) + 4 * half;
-                        const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0u));
-                        queue[qn + rank] = make_int4(pick(b4, v[1], v[0]), (int)((uint32_t)my0 + (uint32_t)at_item), c | slot << 8, (int)top_scale);
+                            for (int i = 0; i < 2; ++i) v[i] = pick(b3, v[2 * i + 1], v[2 * i]);
+                            queue[qn + rank] = make_int4(pick(b4, v[1], v[0]), (int)((uint32_t)my0 + (uint32_t)at_item), c | slot << 8, (int)top_scale);
+                        }
                     }
-                    qn = __builtin_amdgcn_readfirstlane(qn + n);
+                    if constexpr (LIST) {
+                        pn = __builtin_amdgcn_readfirstlane(pn + n);
+                        if (pn >= 64) rounds();
+                    } else {
+                        qn = __builtin_amdgcn_readfirstlane(qn + n);
+                    }
                 }
             };
             // A block's operands are read behind the products of the one before, and tested while they come.  The next segment's
@@ -608,8 +620,9 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
             if (total <= (uint32_t)own_stay(cols)) break;
         }
     }
-    if (qn > 0) drain();
-    if (pn > 0) gather(pn);
+    if (!LIST && qn > 0) drain();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    if (pn > 0) gather(0, pn);
     __syncthreads();
     // fill counts of the workgroup's regions
     for (int i = tid; i < n_c * slots; i += kOwnThreads) {
