@@ -38,8 +38,12 @@ __device__ inline uint32_t build_pos(uint64_t x, const BuildMod& b)
         // bits 0 .. 15 of w ^ (w >> 31), w = z * (kHi:kLo): the cross products count from bit 32 on, and
         // their low 15 bits depend on the low bits of the factors only (24-bit multiplies)
         const uint64_t lo = (uint64_t)(uint32_t)z * kLo;
-        const uint32_t hi = (uint32_t)(lo >> 32) + __umul24((uint32_t)z & 0xFFFFFFu, kHi & 0xFFFFFFu) +
-                            __umul24((uint32_t)(z >> 32) & 0xFFFFFFu, kLo & 0xFFFFFFu);
+        uint32_t c0 = __umul24((uint32_t)z & 0xFFFFFFu, kHi & 0xFFFFFFu), c1 = __umul24((uint32_t)(z >> 32) & 0xFFFFFFu, kLo & 0xFFFFFFu);
+        // (nobody is to see how few of their bits count: the masks would go, and with them the 24-bit form, for full
+        // products at a quarter of the rate.  3 M items x 6 ids, 8 hashes: 183 -> 170 us; 3 M x 16, 8: 366 -> 350)
+        asm("" : "+v"(c0));
+        asm("" : "+v"(c1));
+        const uint32_t hi = (uint32_t)(lo >> 32) + c0 + c1;
         return ((uint32_t)lo ^ (((uint32_t)lo >> 31) | (hi << 1))) & (b.m - 1u);
     }
     z *= ((uint64_t)kHi << 32) | kLo;
