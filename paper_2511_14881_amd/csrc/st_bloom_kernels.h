@@ -80,7 +80,8 @@ __device__ inline int build_word(int r, int w32) { return r * 32 + (w32 ^ (r & 3
 // two products among them) beside the LDS updates.  10 M items x 16 ids, 4 hashes, 512 rows: 0.70 ms with a counted loop, a
 // test against the slab and four steps to an address; the whole of a pass with the export 915 us, 820 with
 // two ids to a load, 718 with four lanes to a list.
-template <bool POW2, int K, bool ONE, int LANES>
+// PAIRS: two ids to a load, but for short lists, where finding out whether there is a second one costs more than a load.
+template <bool POW2, int K, bool ONE, int LANES, bool PAIRS = true>
 __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int64_t* __restrict__ feat_offsets,
                                                                     const uint64_t* __restrict__ feat_ids,
                                                                     int64_t n_items, BuildMod bm,
@@ -90,7 +91,8 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
     const int tid = threadIdx.x;
     const int64_t tile = blockIdx.x;
     const int m_bits = (int)bm.m;
-    constexpr int kPairs = LANES == 1 ? 4 : 2;  // pairs of ids in flight per thread
+    constexpr int kWide = PAIRS ? 2 : 1, kLoads = LANES == 1 ? 8 / kWide : 2;  // ids to a load, loads in flight per thread
+    constexpr int kStep = kLoads * kWide * LANES;
     for (int slab0 = 0; slab0 < m_bits; slab0 += kBuildSlabRows) {
         const int rows = min(kBuildSlabRows, m_bits - slab0);
         for (int i = tid; i < rows * 8; i += kBuildThreads) reinterpret_cast<int4*>(s_bits)[i] = make_int4(0, 0, 0, 0);
@@ -104,21 +106,21 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
                 const int r = (int)build_pos<POW2>(id ^ (uint64_t)j, bm) - (ONE ? 0 : slab0);
                 if (ONE || (uint32_t)r < (uint32_t)rows) atomicOr(&s_bits[build_word(r, w32)], bit);
             };
-            for (int64_t e = f_begin + 2 * (tid & (LANES - 1)); e < f_end; e += kPairs * 2 * LANES) {
-                BuildPair f[kPairs];
-                const int left = (int)min(f_end - e, (int64_t)(kPairs * 2 * LANES));
+            for (int64_t e = f_begin + kWide * (tid & (LANES - 1)); e < f_end; e += kStep) {
+                BuildPair f[kLoads];
+                const int left = (int)min(f_end - e, (int64_t)kStep);
 #pragma unroll
-                for (int u = 0; u < kPairs; ++u) {
-                    const int at = u * 2 * LANES;
+                for (int u = 0; u < kLoads; ++u) {
+                    const int at = u * kWide * LANES;
                     f[u] = {0, 0};
-                    if (at + 1 < left) f[u] = *reinterpret_cast<const BuildPair*>(feat_ids + e + at);
+                    if (PAIRS && at + 1 < left) f[u] = *reinterpret_cast<const BuildPair*>(feat_ids + e + at);
                     else if (at < left) f[u].a = feat_ids[e + at];
                 }
 #pragma unroll
-                for (int u = 0; u < kPairs; ++u)
+                for (int u = 0; u < kLoads; ++u)
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
-                        if (u * 2 * LANES + i < left) {
+                    for (int i = 0; i < kWide; ++i)
+                        if (u * kWide * LANES + i < left) {
                             const uint64_t id = i ? f[u].b : f[u].a;
                             if constexpr (K > 0) {
 #pragma unroll
@@ -142,10 +144,12 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
     }
 }
 
-// The kernel for an index: written out for two to five hashes and up to one slab of rows; four lanes to a list from 12 ids to an
+// The kernel for an index: written out for two to five hashes and up to one slab of rows; an id to a load where the hashes are counted and
+// an item has fewer than four (5 M items x 3 ids: 1 hash 123.5 -> 115.2 us, 7 154.6 -> 150.8; x 2, 6 hashes: 132.7 -> 128.2; but 4 M x 4, 16:
+// 240 -> 242); four lanes to a list from 12 ids to an
 // item on where the tiles fill the chip and the positions need no division (100 rows, 2.9 M x 18, 5 hashes: 402 -> 460).  With one lane -> four, a build and an export in us: 1.1 M items x 21 ids 126 -> 101; 4.5 M x 19
 // 391 -> 368; 1.5 M x 13 122.9 -> 120.4; but 2.2 M x 7 88 -> 95, 6.0 M x 3 196 -> 367, 44,000 x 18 75 -> 85.
-constexpr int64_t kBuildLongList = 12, kBuildLongTiles = 512;
+constexpr int64_t kBuildLongList = 12, kBuildLongTiles = 512, kBuildShortList = 4;
 template <bool POW2, int LANES>
 inline auto build_kernel(int k_hashes) -> decltype(&bloom_build_kernel<POW2, 0, false, 1>)
 {
@@ -162,6 +166,7 @@ inline auto build_kernel(int m_bits, int k_hashes, int64_t n_ids, int64_t n_item
     const bool pow2 = (m_bits & (m_bits - 1)) == 0;
     if (m_bits > kBuildSlabRows) return pow2 ? &bloom_build_kernel<true, 0, false, 1> : &bloom_build_kernel<false, 0, false, 1>;
     if (pow2 && n_ids >= kBuildLongList * n_items && n_tiles >= kBuildLongTiles) return build_kernel<true, 4>(k_hashes);
+    if (pow2 && (k_hashes < 2 || k_hashes > 5) && n_ids < kBuildShortList * n_items) return &bloom_build_kernel<true, 0, true, 1, false>;
     return pow2 ? build_kernel<true, 1>(k_hashes) : build_kernel<false, 1>(k_hashes);
 }
 

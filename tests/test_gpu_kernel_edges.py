@@ -36,10 +36,11 @@ def test_index_build_and_export_at_tile_edges(n, m):
 
 
 # Lists of 0 to 40 ids (from 12 to an item on and 512 tiles four lanes share a list; pairs of ids begin at odd places and
-# end with one id), every number of hashes that has a kernel of its own and two that have none, one slab of rows and two.
+# end with one id), every number of hashes that has a kernel of its own and two that have none, one slab of rows and two;
+# fewer than four ids to an item with counted hashes (an id to a load).
 @pytest.mark.parametrize("n,m,k,most", [(512 * 1024 + 3, 512, 4, 40), (512 * 1024, 100, 5, 26), (511 * 1024, 64, 2, 40),
                                         (530_001, 128, 3, 25), (530_001, 256, 3, 20), (525_000, 96, 7, 33), (3_000, 1100, 2, 40),
-                                        (70_001, 1024, 1, 9)])
+                                        (70_001, 1024, 1, 9), (70_001, 512, 8, 5), (40_000, 1024, 1, 3), (33_333, 64, 16, 6)])
 def test_index_build_of_long_and_short_lists(n, m, k, most):
     rng = np.random.default_rng(n + m)
     off = np.concatenate([[0], np.cumsum(rng.integers(0, most + 1, n))]).astype(np.int64)
