@@ -254,7 +254,8 @@ def test_freed_index_memory_goes_back_to_the_driver():
 # filters pass everything in some stretches and nothing in others (wavefronts change between the two forms), and
 # no filter at all (no signature row is named); scales of many sizes (a wavefront's bounds move as it meets larger ones), some
 # words of items beyond those that a bound is formed for, scores that are all negative (no bound), rows with a common mean, whose
-# bounds are beyond the digits' range (scales of one size, and some ten times as large).  The last selection would make good for lost candidates, so no
+# bounds are beyond the digits' range (scales of one size, and some ten times as large); whole rounds of 8 words to each of 256
+# workgroups, and one item more, with a sampled first level (of 1024 words) and with a seed pass.  The last selection would make good for lost candidates, so no
 # query that passes enough items may have needed that.
 @pytest.mark.parametrize("n,d,B,m,kind", [(600_001, 64, 16, 64, "mixed"), (530_049, 96, 33, 100, "mixed"),
                                           (400_003, 128, 130, 512, "mixed"), (524_288 + 31, 192, 40, 257, "mixed"),
@@ -271,7 +272,9 @@ def test_freed_index_memory_goes_back_to_the_driver():
                                           (300_000, 128, 257, 128, "stretches"), (310_001, 64, 641, 300, "mixed"),
                                           (400_009, 256, 225, 512, "rare"), (300_007, 192, 65, 64, "outliers"),
                                           (300_001, 256, 130, 128, "mean"), (330_031, 128, 40, 64, "mean"), (300_007, 64, 20, 300, "mean"),
-                                          (310_003, 192, 200, 64, "mean, large scales"), (340_009, 96, 70, 128, "mean, large scales")])
+                                          (310_003, 192, 200, 64, "mean, large scales"), (340_009, 96, 70, 128, "mean, large scales"),
+                                          (458_752, 64, 130, 64, "mixed"), (458_753, 128, 150, 128, "mixed"),
+                                          (393_216, 96, 20, 64, "mixed"), (393_217, 192, 40, 100, "mixed")])
 def test_own_filters(n, d, B, m, kind):
     w = ragged_workload(n, n, d, B, 40, 8, m, 3)
     filters = []
@@ -318,6 +321,38 @@ def test_own_filters(n, d, B, m, kind):
     assert kind in ("ties", "beyond") or len(fast) > B // 2
     check_search(w, K, sigs=sigs, queries=sorted({0, 1, 2, 3, B - 1, *range(0, B, max(1, B // 12))}), slow_path=([], fast),
                  label=f"own filters {kind}")
+
+
+# The list of pairs that such a scan gathers, which goes from unit to unit: units of 64 items with 1 to 64 passing pairs, with up
+# to the 112 that are gathered for more than 64 queries, and with more, which are multiplied, in short stretches, so that wavefronts
+# enter and leave either form with a list that is part full.  Row lengths of every variant (each has its own split of a row over lanes).
+@pytest.mark.parametrize("n,d,B,m", [(400_009, 64, 100, 512), (350_003, 96, 180, 256), (400_001, 128, 140, 512), (350_017, 192, 90, 512),
+                                     (400_003, 256, 225, 512), (350_001, 256, 64, 512), (360_007, 96, 50, 256)])
+def test_own_filters_few_pairs(n, d, B, m):
+    w = ragged_workload(n, n, d, B, 40, 8, m, 3)
+    rng = np.random.default_rng(n + d)
+    # two ids of 40 to a filter: an item with L ids passes about (L / 40)^2 of them (ids 16 apart share no hashes)
+    pairs = rng.choice((15, 40, 60, 75, 100, 115, 200), n // 320 + 1).repeat(320)[:n]
+    want = 40 * np.sqrt(pairs / (64 * B))
+    lens = (np.floor(want) + (rng.random(n) < want % 1)).astype(np.int64)
+    w.feat_offsets = torch.from_numpy(np.concatenate([[0], np.cumsum(lens)]).astype(np.int64))
+    w.feat_ids = torch.from_numpy(16 * rng.integers(0, 40, int(lens.sum())).astype(np.int64))
+    filters = [(b % 40 * 16, (7 * b + b // 40 * 2 + 1) % 40 * 16) for b in range(B)]
+    w.filt_ids = np.array([x for f in filters for x in f], np.uint64)
+    w.filt_offsets = np.arange(0, 2 * B + 1, 2).astype(np.int64)
+    K = 40
+    sigs = oracle_index(w)
+    masks = np.stack([O.bloom_mask(sigs, m, 3, np.array(f, np.uint64)) for f in filters]).view(np.uint64)
+    unit = np.bitwise_count(masks).sum(0, dtype=np.int64)
+    limit = 64 if B <= 64 else 112
+    for lo, hi in ((1, 32), (33, 64), (65, limit), (limit + 1, 1 << 30)):
+        assert lo > hi or np.mean((unit >= lo) & (unit <= hi)) > 0.1, (lo, hi, np.percentile(unit, (5, 25, 50, 75, 95)))
+    got = st.st_search_host_plan(n, d, B, 1, K, m, 3, w.filt_ids, w.filt_offsets)
+    assert got["mfma_groups"] == 0, got
+    passing = np.bitwise_count(masks).sum(1, dtype=np.int64)
+    fast = [b for b in range(B) if passing[b] >= 40 * K]
+    assert len(fast) > B // 2
+    check_search(w, K, sigs=sigs, queries=sorted({0, 1, B - 1, *range(0, B, max(1, B // 16))}), slow_path=([], fast), label="own filters, few pairs")
 
 
 # Scales (finite and > 0) whose scores leave the normal range, in every form of the scans that tests pairs by an
