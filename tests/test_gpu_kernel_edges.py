@@ -35,15 +35,30 @@ def test_index_build_and_export_at_tile_edges(n, m):
     assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, 3))
 
 
-# Lists of 0 to 40 ids (pairs of ids begin at odd places and end with one id).  From 12 to an item on, 512 tiles on and with rows in a
-# power of two, four lanes share a list: every number of hashes that is written out and two that are counted.  One lane, by each of
-# these limits, for the same; lists of fewer than four ids with counted hashes (an id to a load); two slabs of rows.
+# Lists of 0 to 40 ids (pairs of ids begin at odd places and end with one id), hashes that are written out and counted ones, one
+# slab of rows and two.
+@pytest.mark.parametrize("n,m,k,most", [(512 * 1024 + 3, 512, 4, 40), (512 * 1024, 100, 5, 26), (511 * 1024, 64, 2, 40),
+                                        (530_001, 128, 3, 25), (530_001, 256, 3, 20), (525_000, 96, 7, 33), (3_000, 1100, 2, 40),
+                                        (70_001, 1024, 1, 9)])
+def test_index_build_of_long_and_short_lists(n, m, k, most):
+    rng = np.random.default_rng(n + m)
+    off = np.concatenate([[0], np.cumsum(rng.integers(0, most + 1, n))]).astype(np.int64)
+    ids = rng.integers(0, 1 << 62, int(off[-1])).astype(np.int64)
+    bloom = st.st_bloom_build(torch.from_numpy(off).cuda(), torch.from_numpy(ids).cuda(), n, m, k)
+    got = _u64(st.st_bloom_export_signatures(bloom))
+    bloom.close()
+    assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, k))
+
+
+# From 12 ids to an item on, 512 tiles on and with rows in a power of two, four lanes share a list: every number of hashes that is
+# written out and two that are counted.  One lane, by each of these limits, for the same; lists of fewer than four ids with
+# counted hashes (an id to a load); two slabs of rows.
 @pytest.mark.parametrize("n,m,k,most,lanes", [
     (511 * 1024 + 3, 512, 4, 40, 4), (511 * 1024 + 1, 256, 2, 26, 4), (530_001, 128, 3, 25, 4), (512 * 1024, 64, 5, 33, 4), (525_000, 512, 7, 26, 4),
     (524_289, 32, 1, 28, 4), (512 * 1024, 100, 5, 26, 1), (511 * 1024, 64, 2, 40, 1), (530_001, 256, 3, 20, 1), (525_000, 96, 7, 33, 1),
-    (70_001, 256, 4, 9, 1), (50_003, 128, 5, 12, 1), (3_000, 1100, 2, 40, 1), (9_001, 2048, 6, 30, 1), (70_001, 1024, 1, 9, 1),
-    (70_001, 512, 8, 5, 1), (40_000, 1024, 1, 3, 1), (33_333, 64, 16, 6, 1)])
-def test_index_build_of_long_and_short_lists(n, m, k, most, lanes):
+    (70_001, 256, 4, 9, 1), (50_003, 128, 5, 12, 1), (9_001, 2048, 6, 30, 1), (70_001, 512, 8, 5, 1), (40_000, 1024, 1, 3, 1),
+    (33_333, 64, 16, 6, 1)])
+def test_every_form_of_the_index_build(n, m, k, most, lanes):
     rng = np.random.default_rng(n + m)
     off = np.concatenate([[0], np.cumsum(rng.integers(0, most + 1, n))]).astype(np.int64)
     assert (m <= 1024 and m & (m - 1) == 0 and off[-1] >= 12 * n and n > 511 * 1024) == (lanes == 4)
