@@ -46,7 +46,7 @@ def test_index_build_of_long_and_short_lists(n, m, k, most):
     ids = rng.integers(0, 1 << 62, int(off[-1])).astype(np.int64)
     bloom = st.st_bloom_build(torch.from_numpy(off).cuda(), torch.from_numpy(ids).cuda(), n, m, k)
     got = _u64(st.st_bloom_export_signatures(bloom))
-    bloom.close()
+    bloom.free()
     assert np.array_equal(got, O.bloom_build(off, ids.view(np.uint64), m, k))
 
 
