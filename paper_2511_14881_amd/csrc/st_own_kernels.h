@@ -103,12 +103,20 @@ struct SampleWords {
 
 // A value that the compiler takes for a new one: what is formed from it is formed here, and no register holds it from
 // outside a loop on.  (A condition of the lanes is two scalar registers, and some twenty that a unit needs, held over the loop, went to
-// lanes of vector registers and back: without them 2 M x 64, 16 queries: 82.0 -> 79.5 us, 4 M x 128, 16: 149.9 -> 148.2.  At 256 bytes a
-// row the vector registers that this takes are not there: 3.4 M x 256, 117 queries at 1 %: 222 -> 240.)
+// lanes of vector registers and back: without them 2 M x 64, 16 queries: 82.0 -> 79.5 us, 4 M x 128, 16: 149.9 -> 148.2.)
 template <class V>
 __device__ inline V fresh(V v)
 {
     asm volatile("" : "+v"(v));
+    return v;
+}
+// ... the same of a value in a scalar register: lanes are compared with it, and no vector register is taken.  (With a fresh
+// lane number there was none left at 256 bytes a row, and that form kept its 84 spills: with fresh limits 51; 10 M x 256, 256
+// queries: 892 -> 887 us, 2 M x 64, 16: 107.3 -> 105.6, 0.75 M x 96, 211: 136.5 -> 134.9, 4 M x 128, 200: 278 -> 272.)
+__device__ inline int fresh_scalar(int v)
+{
+    v = __builtin_amdgcn_readfirstlane(v);
+    asm volatile("" : "+s"(v));
     return v;
 }
 
@@ -437,10 +445,11 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     uint32_t n_pass = 0, before = 0, total = 0;  // pairs that pass: this lane's, the lower lanes', all
     auto masks = [&]() __attribute__((always_inline)) {
         draw();
-        const int l = KS < 8 ? fresh(lane) : lane;
+        const int named = fresh_scalar(n_named), cl = fresh_scalar(n_c);
+        const uint32_t no_rows = (uint32_t)fresh_scalar((int)kNoRows);
 #pragma unroll
         for (int u = 0; u < kIdx; ++u)
-            if (l + u * 64 < n_named) s_idx[lane + u * 64] = idx[u];
+            if (lane < named - u * 64) s_idx[lane + u * 64] = idx[u];
         if (kIdx * 64 < kOwnRows && n_named > kIdx * 64) {
             const uint64_t* src = p.bloom + (my0 >> 10) * (int64_t)p.m_bits * kTileWords + ((my0 >> 6) & 15);
             for (int x = lane + kIdx * 64; x < n_named; x += 64) s_idx[x] = src[(int)s_named[x] * kTileWords];
@@ -451,7 +460,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
         const int64_t left = item_lim - my0;
         const uint64_t all = left >= 64 ? ~0ULL : left > 0 ? ((1ULL << left) - 1ULL) : 0ULL;
 #pragma unroll
-        for (int u = 0; u < kOwnCols / 64; ++u) m[u] = l + u * 64 < n_c ? all : 0;
+        for (int u = 0; u < kOwnCols / 64; ++u) m[u] = lane < cl - u * 64 ? all : 0;
         for (int r = 0; r < rn_max; r += 4) {
             ushort4 f[kOwnCols / 64];
 #pragma unroll
@@ -465,7 +474,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
 #pragma unroll
         for (int u = 0; u < kOwnCols / 64; ++u)
             if (u * 64 < cols) {
-                if ((KS < 8 ? fresh(my_refs[u]) : my_refs[u]) & kNoRows) m[u] = all;
+                if (my_refs[u] & no_rows) m[u] = all;
                 n_pass += (uint32_t)__popcll(m[u]);
             }
         const uint32_t incl = wave_scan_add(n_pass);
@@ -499,9 +508,10 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
         }
         rows(my0);
         for (;;) {
+            const int cl = fresh_scalar(cols);
 #pragma unroll
             for (int u = 0; u < kOwnCols / 64; ++u)
-                if ((KS < 8 ? fresh(lane) : lane) + u * 64 < cols) s_mask[lane + u * 64] = m[u];
+                if (lane < cl - u * 64) s_mask[lane + u * 64] = m[u];
             // The scales, and the items' slices: half a slice to a lane, as the operand has it.
             const bool odd = ballot(!(si >= 0.0f && si < 0x1p90f)) != 0;  // (outside the range that has bounds: all pairs of these items are tested exactly)
             uint32_t top_scale = 0;  // the largest one as a bit pattern, where a part of the bounds is shared
