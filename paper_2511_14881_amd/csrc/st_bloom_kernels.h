@@ -79,7 +79,7 @@ __device__ inline int build_word(int r, int w32) { return r * 32 + (w32 ^ (r & 3
 // ONE: the rows fit one slab, and no position is compared with it.  Bound by the instructions of the hashes (some 20 to each,
 // two products among them) beside the LDS updates.  10 M items x 16 ids, 4 hashes, 512 rows: 0.70 ms with a counted loop, a
 // test against the slab and four steps to an address; the whole of a pass with the export 915 us, 820 with
-// two ids to a load, 718 with four lanes to a list.
+// two ids to a load, 718 with four lanes to a list, 690 with 24-bit products (the kernel 0.48 ms).
 // PAIRS: two ids to a load, but for short lists, where finding out whether there is a second one costs more than a load.
 template <bool POW2, int K, bool ONE, int LANES, bool PAIRS = true>
 __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int64_t* __restrict__ feat_offsets,
@@ -144,11 +144,13 @@ __global__ __launch_bounds__(kBuildThreads, 8) void bloom_build_kernel(const int
     }
 }
 
-// The kernel for an index: written out for two to five hashes and up to one slab of rows; an id to a load where the hashes are counted and
-// an item has fewer than four (5 M items x 3 ids: 1 hash 123.5 -> 115.2 us, 7 154.6 -> 150.8; x 2, 6 hashes: 132.7 -> 128.2; but 4 M x 4, 16:
-// 240 -> 242); four lanes to a list from 12 ids to an
-// item on where the tiles fill the chip and the positions need no division (100 rows, 2.9 M x 18, 5 hashes: 402 -> 460).  With one lane -> four, a build and an export in us: 1.1 M items x 21 ids 126 -> 101; 4.5 M x 19
-// 391 -> 368; 1.5 M x 13 122.9 -> 120.4; but 2.2 M x 7 88 -> 95, 6.0 M x 3 196 -> 367, 44,000 x 18 75 -> 85.
+// The kernel for an index: written out for two to five hashes and up to one slab of rows.
+// Four lanes to a list from 12 ids to an item on, where the tiles fill the chip and the positions need no division. One lane -> four, a
+// build and an export in us:
+//   1.1 M items x 21 ids 126 -> 101;  4.5 M x 19 391 -> 368;  1.5 M x 13 122.9 -> 120.4
+//   but 2.2 M x 7 88 -> 95;  6.0 M x 3 196 -> 367;  44,000 x 18 75 -> 85;  100 rows, 2.9 M x 18, 5 hashes 402 -> 460
+// An id to a load where the hashes are counted and an item has fewer than four ids. Two ids -> one:
+//   5 M items x 3 ids, 1 hash 123.5 -> 115.2, 7 hashes 154.6 -> 150.8;  x 2, 6 hashes 132.7 -> 128.2;  but 4 M x 4, 16 hashes 240 -> 242
 constexpr int64_t kBuildLongList = 12, kBuildLongTiles = 512, kBuildShortList = 4;
 template <bool POW2, int LANES>
 inline auto build_kernel(int k_hashes) -> decltype(&bloom_build_kernel<POW2, 0, false, 1>)

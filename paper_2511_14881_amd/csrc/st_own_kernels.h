@@ -20,7 +20,7 @@
 // The queries lie in LDS with 16 bytes of padding a row (an odd number of 16-byte pieces: no bank conflicts).
 //
 // 10 M x 256 bytes, 256 queries, 161 filters (5 % each), K = 500: the level after the first takes 0.82 ms in a long series of
-// calls (0.82 to 1.1 in a run's first forty).  With 213 of the queries, a call took 1.31 ms with a multiply-add for every pair, operands read for
+// calls (0.81 to 1.17 in a run's first sixty, 0.87 on average).  With 213 of the queries, a call took 1.31 ms with a multiply-add for every pair, operands read for
 // each half, queued lanes of 16 results and segments of 512 items tied to a workgroup, and 1.01 so; gathering took 4.5 in this kernel's place.
 // A unit of seven blocks takes a wavefront 21,500 cycles: 13,500 in products
 // and tests (4,200 is what the products alone need, and two wavefronts share the matrix unit), 4,000
@@ -52,11 +52,14 @@ static_assert(kOwnWords == kOwnThreads / 64, "a word per wavefront");
 constexpr int own_row_bytes(int d) { return d + kSliceBytes + 16; }  // of a query in LDS
 constexpr int own_grid_rows(int n_q) { return (n_q + kOwnCols - 1) / kOwnCols; }
 constexpr int own_cols(int n_q) { return ((n_q + own_grid_rows(n_q) - 1) / own_grid_rows(n_q) + 31) / 32 * 32; }  // of each row
-// A wavefront whose filters pass no more pairs than this of its 64 items gathers the pairs' rows instead of
-// multiplying all; one that multiplies has the next rows already, and goes on down to fewer pairs.  (Leaving at 64 too: 2.3 M x
-// 192, 41 queries at 2 %, units on either side of the line: 121 us, 129 so, 133 before; but 2 M x 64, 17 at 10 %: 86 and 82.  Entering at 16 or 32
-// with up to 64 queries: 3 M x 256, 64 at 0.5 %: 100 -> 200.  64 with more queries, where all products take longer, -> 112, which is as many as the list
-// has room for: 3.4 M x 256, 117 queries at 1 %: 257 -> 198; 3.5 M x 256, 259 at 1 %: 377 -> 327; 2 M x 128, 250 at 0.5 %: 180 -> 139.)
+// A wavefront whose filters pass no more pairs than own_few of its 64 items gathers the pairs' rows instead of multiplying all;
+// one that multiplies has the next rows already, and goes on down to own_stay.
+// Up to 64 queries the line is 64:
+//   entering at 16 or 32: 3 M x 256, 64 queries at 0.5 %: 100 -> 200 us
+//   leaving at 64 too: 2 M x 64, 17 at 10 %: 82 -> 86, where units lie below the line now and then; but 2.3 M x 192, 41 at 2 %,
+//   units on either side of it: 129 -> 121
+// With more queries all products take longer, and it is 112, as many as the list has room for. 64 -> 112:
+//   3.4 M x 256, 117 at 1 %: 257 -> 198;  3.5 M x 256, 259 at 1 %: 377 -> 327;  2 M x 128, 250 at 0.5 %: 180 -> 139
 constexpr int own_few(int cols) { return cols <= 64 ? 64 : 112; }
 constexpr int own_stay(int cols) { return own_few(cols) / 2; }
 constexpr int kOwnPairs = 64 + own_few(kOwnCols);  // of a list: what is left of a round, and a unit's
@@ -151,7 +154,7 @@ __global__ __launch_bounds__(kOwnThreads) void scan_own_kernel(ScanParams p)
     uint32_t* s_cnt = reinterpret_cast<uint32_t*>(at);            at += (size_t)cols * 4 * kOwnSlots;  // [slots][cols]
     uint16_t* s_r0 = reinterpret_cast<uint16_t*>(at);             at += (size_t)cols * 2;
     uint16_t* s_rn = reinterpret_cast<uint16_t*>(at);             at += (size_t)cols * 2;
-    uint16_t* s_u = reinterpret_cast<uint16_t*>(at);              at += (size_t)cols * 2;   // bounds as slices' numbers (kOwnNoBound: none)
+    uint16_t* s_u = reinterpret_cast<uint16_t*>(at);              at += (size_t)cols * 2;   // bounds as slices' numbers (kNoBound: none)
     uint16_t* s_named = reinterpret_cast<uint16_t*>(at);          at += (size_t)kOwnRows * 2;
     uint32_t* s_bits = reinterpret_cast<uint32_t*>(at);           // [kOwnRows / 32]
     constexpr int kNoBound = 0xFFFF;
